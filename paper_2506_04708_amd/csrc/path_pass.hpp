@@ -103,14 +103,7 @@ __device__ __forceinline__ int commit_row_of(const PathArgs &a, int b, int j)
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave, by data-parallel-primitive moves inside
-// rows of 16 lanes and two row broadcasts (no LDS traffic).  A lane without a source adds 0.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ unsigned long long dpp_fetch_u64(unsigned long long x)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, CTRL, ROW_MASK, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), CTRL, ROW_MASK, 0xF, false);
-    return ((unsigned long long)hi << 32) | lo;
-}
+// rows of 16 lanes and two row broadcasts (no LDS traffic).
 __device__ __forceinline__ unsigned long long wave_inclusive_scan_u64(unsigned long long x)
 {
     x += dpp_fetch_u64<0x111, 0xF>(x);  // row_shr:1

@@ -739,7 +739,7 @@ static int launch_step_fused(stand_handle *h, uint64_t step, const void *d_logit
     const int ud = h->upper_depth < h->D ? h->upper_depth : h->D;
     A.upper_nodes = h->level_start[ud + 1];
     const void *fn = bf16 ? (const void *)stand_step_kernel<kDtBf16> : (const void *)stand_step_kernel<kDtF32>;
-    const size_t smem = step_shared_bytes(h->N, h->D);
+    const size_t smem = step_shared_bytes(h->N);
     if (h->step_slots == 0) {
         // how many of the kernel's workgroups are resident at once: the rows before the tail fill the device once
         int per_cu = 0, cus = 0;

@@ -371,13 +371,13 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
     tail_barrier(sy, 1, (unsigned)a.B, ts);
     if (tid == 0) stamp(sy, b, 6);
     if (tid == 0 && !ts->ok) atomicAdd(&a.stats[kStatWaitExpired], 1ull);
-    draft_trajectory<kStepThreads>(A.draft, b, draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N, A.draft.tree.D));
+    draft_trajectory<kStepThreads>(A.draft, b, draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N));
     if (tid == 0) stamp(sy, b, 7);
 }
 
-__host__ __device__ inline size_t step_shared_bytes(int N, int D)
+__host__ __device__ inline size_t step_shared_bytes(int N)
 {
-    const size_t tail = ((sizeof(TailShared) + 15) & ~(size_t)15) + draft_shared_bytes(N, D);
+    const size_t tail = ((sizeof(TailShared) + 15) & ~(size_t)15) + draft_shared_bytes(N);
     return tail > sizeof(RowShared<kStepWPR>) ? tail : sizeof(RowShared<kStepWPR>);
 }
 

@@ -65,6 +65,20 @@ def test_lockstep_small(gpu, name, over, steps, mode, forced):
 FUSED = 2  # STAND_STEP_FUSED
 
 
+@pytest.mark.parametrize("K,omin,omax,mode", [
+    (8, 1, 8, 0), (4, 1, 3, 0), (9, 1, 4, 0), (16, 2, 6, 0), (16, 1, 4, 2), (17, 1, 5, 0), (32, 1, 8, 0), (32, 3, 3, 2), (7, 4, 8, 1),
+])
+def test_lockstep_draft_payload_layouts(gpu, K, omin, omax, mode):
+    """The draft spreads the payloads of a node's orders over groups of 8, 16 or 32 lanes, in one to four rounds: every
+    group size with both edges, one to eight orders, all drafting modes; a table small enough for displaced keys."""
+    binding, lockstep = gpu
+    over = dict(V=331, B=5, rho=0.8, K=K, order_min=omin, order_max=omax, draft_mode=mode)
+    _say("draft layouts %s" % over)
+    w = synth.Workload("cfg1", run_steps=24, **over)
+    info = lockstep.run_lockstep(w, 24, mode="step", capacity=1 << 11, forced=True, check_rows=False, table_every=6)
+    _say("  -> %s" % info)
+
+
 @pytest.mark.parametrize("name,over,steps,forced", [
     ("cfg1", dict(V=4096, B=2, rho=0.7, step_plan=(FUSED, 2, 0, 0)), 40, True),            # few rows, one launch forced
     ("cfg1", dict(V=2003, B=3, rho=0.7, dtype="bf16", step_plan=(FUSED, 1, 1, 0)), 40, True),   # misaligned rows, one tail workgroup
