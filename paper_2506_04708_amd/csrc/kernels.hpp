@@ -30,6 +30,7 @@
 #include "numeric.hpp"
 #include "wave_ops.hpp"
 #include "row_pass.hpp"
+#include "row_parts.hpp"
 #include "table_merge.hpp"
 #include "path_pass.hpp"
 #include "draft.hpp"

@@ -349,6 +349,8 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
         const unsigned long long edge_f =
             edge_id >= 0 ? fixed_mass(exact_exp2(scaled_offset(load_scalar<DT>(rowp, edge_id), m, a.c)), a.fx_shift) : 0ull;
 
+        NodeTests st;
+        if (stop && nch > 0) st = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
         const unsigned long long S = wave_sum_u64(part);
         const float s = normaliser_from_fixed(S, a.fx_shift);
         if (!stop) {
@@ -368,8 +370,8 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
                 if ((uint32_t)c_id >= (uint32_t)a.V) { c_id = -1; c_mu = 0.0f; }  // never index outside the row
                 else c_l = load_scalar<DT>(rowp, c_id);
                 const float c_e = c_id >= 0 ? exact_exp2(scaled_offset(c_l, m, a.c)) : 0.0f;
-                const NodeResult nr = wave_node_outcome(lane, a.K, c_id, c_mu, c_e / s, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc,
-                                                        false, 0.0f, a.onehot);
+                const NodeTests ct = node_tests_prepare(lane, a.K, c_id, c_mu, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc);
+                const NodeResult nr = wave_node_outcome(lane, a.K, ct, c_e / s, c_n, false, 0.0f, a.onehot);
                 if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row])) atomicAdd(&a.stats[kStatMismatch], 1ull);
             }
             return;
@@ -379,8 +381,7 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
         bool support = nch > 0;
         float my_r = 0.0f, rho = 1.0f;
         if (support) {
-            const NodeResult nr = wave_node_outcome(lane, a.K, my_id, my_mu, my_e / s, nch, ch, a.seed, (uint32_t)b, a.step,
-                                                    fc, false, 0.0f, a.onehot);
+            const NodeResult nr = wave_node_outcome(lane, a.K, st, my_e / s, nch, false, 0.0f, a.onehot);
             my_r = (lane < a.K && my_id >= 0) ? nr.r : 0.0f;
             rho = nr.rho;
             if (lane == 0 && nr.accepted != -1) atomicAdd(&a.stats[kStatMismatch], 1ull);  // the stop node rejects all

@@ -1,0 +1,353 @@
+// row_parts.hpp -- row_parts_kernel: the row pass for few rows (paper Sec. 4.1, 3.2).  Every row is split over
+// workgroups that hold their part in registers.
+#pragma once
+#include "row_pass.hpp"
+
+namespace stand {
+
+// ---------------------------------------------------------------------------------------------
+// With few rows the row pass is bound by latency: by how many compute units pull at a row, and by what a row costs
+// after its last byte has arrived (lists of sixteen waves gathered and pruned one after the other, kept vectors read
+// again).  Here a row is split over P workgroups of kPartThreads threads.  Each holds its part in registers, at most R
+// 16-byte vectors per lane, all requested at once, so that
+//   - the part's maximum is known before its first exponential (no running reference);
+//   - no candidate list is kept while streaming: the K-th largest of the 64 maxima of 8-lane groups is a lower bound
+//     of the part's K-th largest element, and it is tight: 64 ln(64 / (64 - K)) elements reach it on average (11 for
+//     K = 10, 44 for K = 32); those are collected straight from the registers;
+//   - nothing is read twice.
+// The last workgroup of a row to finish (a counter that its last user sets back to zero, so a recorded launch can be
+// replayed) merges the parts: the largest of the parts' bounds cuts the candidates again, one wave ranks them exactly
+// while another runs the node's accept tests.  A part in which more than kPartList elements reach the bound (equal
+// or masked logits) takes the streaming scan of row_pass.hpp instead.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
+constexpr int kPartVectors = 8;                      // most vectors per lane
+constexpr int kPartsMax = 32;                        // most parts of a row
+constexpr int kTicketStride = 32;                    // words between two rows' counters: a cache line each
+constexpr int kPartKeys = 64;                        // candidate keys a part hands over
+constexpr int kPartList = kPartsMax * kPartKeys;     // candidates collected in shared memory
+
+struct PartHead { float m, s, theta; int cnt; };     // maximum, fast sum relative to it, bound, candidates of a part
+
+struct RowPartsArgs {
+    RowPassArgs r;
+    bool streamed;                 // non-temporal loads
+    int P, per;                    // parts per row, vectors per part (<= kPartThreads * R)
+    unsigned *ticket;              // [rows or row slots][kTicketStride] parts that have finished; back at zero after the launch
+    PartHead *head;                // [slots * P]
+    unsigned long long *keys;      // [slots * P][kPartKeys]
+    // update mode: the rows are those of the commits (slot (j, b)) and there are no accept tests
+    bool commit, all_nodes;
+    int W, R;
+    const int32_t *commit_row, *commit_len;
+    float *pr_m;                   // [B*R]
+    int32_t *pr_top_idx;           // [B*R][K]
+    float *pr_top_l;               // [B*R][K]
+};
+
+struct PartShared {
+    float bins[64];                // maxima of groups of 8 lanes
+    int above[64];                 // number of bins above each
+    float wmax[kPartWaves], wsum[kPartWaves];
+    int n, n_row, last;            // candidates of the part, then of the row
+    int rank[kPartList];
+    union {
+        unsigned long long list[kPartList + 8];
+        RowShared<kPartWaves> scan;  // the streaming scan's own memory (ties)
+    };
+    unsigned long long top[kMaxK];
+};
+
+// Adds to rank[i] the number of keys among list[j0..j1) that are larger than key i (n distinct keys; one wave).
+__device__ __forceinline__ void rank_against(const unsigned long long *list, int *rank, int n, int j0, int j1, int lane)
+{
+    for (int base = 0; base < n; base += 64) {
+        const int i = base + lane;
+        const unsigned long long mine = i < n ? list[i] : ~0ull;
+        int c = 0;
+        int jj = j0;
+        for (; jj + 4 <= j1; jj += 4) {
+            const unsigned long long k0 = list[jj], k1 = list[jj + 1], k2 = list[jj + 2], k3 = list[jj + 3];
+            c += (k0 > mine ? 1 : 0) + (k1 > mine ? 1 : 0) + (k2 > mine ? 1 : 0) + (k3 > mine ? 1 : 0);
+        }
+        for (; jj < j1; ++jj) c += list[jj] > mine ? 1 : 0;
+        if (c) atomicAdd(&rank[i], c);   // (c is 0 for lanes without a key)
+    }
+}
+
+template <int AUX, int R>
+__device__ __forceinline__ void load_part(uint4 (&w)[R], __amdgpu_buffer_rsrc_t rsrc, int tid)
+{
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const stream_u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (q * kPartThreads + tid) * 16, 0, AUX);
+        w[q] = make_uint4(t.x, t.y, t.z, t.w);
+    }
+}
+
+// (64 registers leave room for four workgroups per compute unit, so that their phases overlap: 256 rows of 257 KB
+// take 19.6 us; with 116 registers and two workgroups 21.2)
+template <int DT, int R>
+__global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void row_parts_kernel(RowPartsArgs a)
+{
+    constexpr int ES = VecTraits<DT>::ES, EPV = VecTraits<DT>::EPV;
+    __shared__ __align__(16) PartShared sm;
+    const RowPassArgs &r = a.r;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // grid (parts, trajectories, nodes or commit positions): all trajectories' rows of node 0 first
+    const int part = blockIdx.x, b = blockIdx.y, j = blockIdx.z, slot = j * r.B + b;
+    int node = j;
+    if (a.commit) {
+        if (a.all_nodes) node = r.draft_tok[(size_t)b * r.N + j] >= 0 ? j : -1;
+        else {
+            int cl = a.commit_len[b];
+            cl = cl < 0 ? 0 : (cl > a.W ? a.W : cl);
+            node = j < cl ? a.commit_row[(size_t)b * a.W + j] : -1;
+        }
+        if (node < 0 || node >= r.N) return;  // (the same for all parts of the row)
+    }
+    node = __builtin_amdgcn_readfirstlane(node);
+    const int row = b * r.N + node;
+    const char *rowp = (const char *)r.logits + (size_t)row * (size_t)r.V * ES;
+    const RowGeom g = row_geom<DT>(rowp, r.V);
+    const int v0 = part * a.per < g.nvec ? part * a.per : g.nvec;
+    const int v1 = v0 + a.per < g.nvec ? v0 + a.per : g.nvec;
+
+    // ---- the whole part is requested at once (buffer loads: a lane past the part's end gets zeros)
+    uint4 w[R];
+    {
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(g.vp + v0), (short)0, (v1 - v0) * 16, 0x00020000);
+        if (a.streamed) load_part<2>(w, rsrc, tid);
+        else load_part<0>(w, rsrc, tid);
+    }
+    // elements of the row before its first and after its last aligned vector: one per lane of the first wave
+    int edge_id = -1;
+    if (wave == 0) {
+        if (part == 0 && lane < g.head) edge_id = lane;
+        if (part == a.P - 1 && lane >= 32 && lane - 32 < g.ntail) edge_id = g.tail0 + lane - 32;
+    }
+    const float edge_val = edge_id >= 0 ? load_scalar<DT>(rowp, edge_id) : -__builtin_inff();
+    // the node's proposal, for the wave that runs the accept tests if this workgroup is the row's last
+    NodeProposal prop;
+    if (!a.commit && wave == 1) prop.request(r, row, node, lane);
+
+    // ---- maxima
+    float cm[R], lm = edge_val;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        float x[EPV];
+        unpack<DT>(w[q], x);
+        float m1 = x[0];
+#pragma unroll
+        for (int e = 1; e < EPV; ++e) m1 = fmaxf(m1, x[e]);
+        cm[q] = v0 + q * kPartThreads + tid < v1 ? m1 : -__builtin_inff();
+        lm = fmaxf(lm, cm[q]);
+    }
+    float x8 = fmaxf(lm, dpp_fetch_f32<0xB1>(lm));     // quad_perm [1,0,3,2]
+    x8 = fmaxf(x8, dpp_fetch_f32<0x4E>(x8));           // quad_perm [2,3,0,1]
+    x8 = fmaxf(x8, dpp_fetch_f32<0x141>(x8));          // row_half_mirror: groups of 8 lanes
+    const float wm = wave_max_f32(x8);
+
+    // ---- the wave's share of the fast normaliser, relative to its maximum.  The exponent of a term is
+    // fma(l, c, nb); the rounding of nb shifts every exponent by the same dlt, which is taken out at the end
+    // (see wave_row_stream).
+    const bool none = wm == -__builtin_inff();         // (no vector, or masked throughout: adds nothing)
+    const float m_ref = none ? 0.0f : wm;
+    const float nb = -m_ref * r.c, dlt = __builtin_fmaf(-m_ref, r.c, -nb);
+    float s_t = edge_id >= 0 ? fast_exp2(__builtin_fmaf(edge_val, r.c, nb)) : 0.0f;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        float x[EPV];
+        // (unpacked again: kept from the maxima, the elements would take eight registers per vector and half the waves)
+        asm volatile("" : "+v"(w[q].x), "+v"(w[q].y), "+v"(w[q].z), "+v"(w[q].w));
+        unpack<DT>(w[q], x);
+        float e = 0.0f;
+#pragma unroll
+        for (int k = 0; k < EPV; ++k) e += fast_exp2(__builtin_fmaf(x[k], r.c, nb));
+        s_t += v0 + q * kPartThreads + tid < v1 ? e : 0.0f;
+    }
+    s_t = wave_sum_f32(s_t);
+    if ((lane & 7) == 0) sm.bins[wave * 8 + (lane >> 3)] = x8;
+    if (lane == 0) { sm.wmax[wave] = none ? -3.402823466e38f : wm; sm.wsum[wave] = s_t * fast_exp2(dlt); }
+    if (wave == 0) { sm.above[lane] = 0; if (lane == 0) { sm.n = 0; sm.n_row = 0; } }
+    __syncthreads();
+
+    if (wave == 1 && !a.commit) prop.template request_logits<DT>(r, b, rowp, lane);
+
+    // ---- K-th largest of the 64 bins: every wave compares all bins with eight of them
+    const float my_bin = sm.bins[lane];
+    {
+        const float4 o0 = *(const float4 *)&sm.bins[wave * 8], o1 = *(const float4 *)&sm.bins[wave * 8 + 4];
+        const int c = (o0.x > my_bin) + (o0.y > my_bin) + (o0.z > my_bin) + (o0.w > my_bin) +
+                      (o1.x > my_bin) + (o1.y > my_bin) + (o1.z > my_bin) + (o1.w > my_bin);
+        atomicAdd(&sm.above[lane], c);
+    }
+    __syncthreads();
+    const float theta = -wave_max_f32(sm.above[lane] < r.K ? -my_bin : -__builtin_inff());
+
+    float pm, ps;   // the part's maximum and sum (in the waves that use them)
+    if (wave < 2 || a.P == 1) {
+        const float wm_l = lane < kPartWaves ? sm.wmax[lane] : -3.402823466e38f;
+        pm = wave_max_f32(wm_l);
+        ps = wave_sum_f32(lane < kPartWaves ? sm.wsum[lane] * fast_exp2((wm_l - pm) * r.c) : 0.0f);
+    }
+
+    // ---- the elements that reach the bound.  A lane takes its vectors that hold one in turn (nearly always one or
+    // none, so the code for it stands here once and not for every register).
+    unsigned mask = 0u;
+#pragma unroll
+    for (int q = 0; q < R; ++q) mask |= (v0 + q * kPartThreads + tid < v1 && cm[q] >= theta) ? 1u << q : 0u;
+    while (__ballot(mask != 0u)) {
+        uint4 ws = w[0];
+        int q = 0;
+#pragma unroll
+        for (int k = 1; k < R; ++k)
+            if (!(mask & ((1u << k) - 1u))) { ws = w[k]; q = k; }   // the lowest set bit is at least k
+        if (mask) {
+            float x[EPV];
+            unpack<DT>(ws, x);
+            unsigned in = 0u;
+#pragma unroll
+            for (int k = 0; k < EPV; ++k) in |= x[k] >= theta ? 1u << k : 0u;
+            int at = atomicAdd(&sm.n, __popc(in));
+            const int id0 = g.head + (v0 + q * kPartThreads + tid) * EPV;
+            while (in) {
+                const int k = __ffs((int)in) - 1;
+                in &= in - 1u;
+                float xv = x[0];
+#pragma unroll
+                for (int e = 1; e < EPV; ++e) xv = k == e ? x[e] : xv;
+                if (at < kPartList) sm.list[at] = rank_key(xv, (uint32_t)(id0 + k));
+                ++at;
+            }
+            mask &= mask - 1u;
+        }
+    }
+    if (edge_id >= 0 && edge_val >= theta) {
+        const int at = atomicAdd(&sm.n, 1);
+        if (at < kPartList) sm.list[at] = rank_key(edge_val, (uint32_t)edge_id);
+    }
+    __syncthreads();
+    int n = sm.n;
+    if (n > kPartList) {
+        // too many equal elements: the streaming scan over this part (edges included) finds its K best
+        __syncthreads();  // every wave has seen n
+        const int base = part == 0 ? 0 : g.head + v0 * EPV;
+        const int end = part == a.P - 1 ? r.V : g.head + v1 * EPV;
+        const void *sub = rowp + (size_t)base * ES;
+        WaveScan *wsc = &sm.scan.wsh[wave];
+        const WavePartial wp = wave_row_stream<DT>(sub, end - base, r.c, r.K, wsc, lane, wave, kPartWaves);
+        if (lane == 0) sm.scan.part_cnt[wave] = wp.cnt;
+        __syncthreads();
+        if (wave == 0) {
+            const int cnt = gather_wave_records<DT, kPartWaves>(&sm.scan, lane, r.K);
+            wave_row_finish<DT>(sub, end - base, r.K, wsc, sm.scan.ebuf, lane, cnt);
+            const unsigned long long key = lane < r.K ? wsc->top[lane] - (unsigned long long)base : 0ull;  // (the low word counts ids down)
+            __builtin_amdgcn_wave_barrier();
+            if (lane < r.K) sm.list[lane] = key;
+        }
+        n = r.K;   // more than kPartList elements: the part has K
+        __syncthreads();
+    }
+    if (a.P > 1) {
+        if (n > kPartKeys) {
+            // more than a part hands over: its K best
+            for (int i = tid; i < n; i += kPartThreads) sm.rank[i] = 0;
+            __syncthreads();
+            rank_against(sm.list, sm.rank, n, n * wave / kPartWaves, n * (wave + 1) / kPartWaves, lane);
+            __syncthreads();
+            for (int i = tid; i < n; i += kPartThreads)
+                if (sm.rank[i] < r.K) sm.top[sm.rank[i]] = sm.list[i];
+            __syncthreads();
+            if (tid < r.K) sm.list[tid] = sm.top[tid];
+            n = r.K;
+        }
+        // ---- hand over; the row's last workgroup goes on
+        const size_t first = (size_t)slot * a.P, at = first + part;
+        if (wave == 0) {
+            __builtin_amdgcn_wave_barrier();
+            if (lane < n) st_agent(&a.keys[at * kPartKeys + lane], sm.list[lane]);
+            if (lane < 4) {
+                const uint32_t v = lane == 0 ? f2u(pm) : (lane == 1 ? f2u(ps) : (lane == 2 ? f2u(theta) : (uint32_t)n));
+                st_agent((uint32_t *)&a.head[at] + lane, v);
+            }
+            publish_fence();
+            if (lane == 0) {
+                unsigned *tk = &a.ticket[(size_t)slot * kTicketStride];
+                const unsigned before = atomicAdd(tk, 1u);
+                sm.last = before == (unsigned)a.P - 1u;
+                if (sm.last) st_agent(tk, 0u);
+            }
+        }
+        __syncthreads();
+        if (!sm.last) return;
+        consume_fence();
+        // every wave looks at all heads; wave w fetches the keys of parts w, w + 8, ... (whole records: their
+        // lengths arrive with the same round trip)
+        PartHead h;
+        h.m = -3.402823466e38f; h.s = 0.0f; h.theta = -__builtin_inff(); h.cnt = 0;
+        if (lane < a.P) {
+            const uint32_t *p = (const uint32_t *)&a.head[first + lane];
+            h.m = u2f(ld_agent(p)); h.s = u2f(ld_agent(p + 1)); h.theta = u2f(ld_agent(p + 2)); h.cnt = (int)ld_agent(p + 3);
+        }
+        constexpr int kRounds = kPartsMax / kPartWaves;
+        unsigned long long k[kRounds];
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int p = q * kPartWaves + wave;
+            k[q] = p < a.P ? ld_agent(&a.keys[(first + p) * kPartKeys + lane]) : 0ull;
+        }
+        pm = wave_max_f32(h.m);
+        const float bound = wave_max_f32(h.theta);
+        ps = wave_sum_f32(h.s * fast_exp2((h.m - pm) * r.c));
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int p = q * kPartWaves + wave;
+            if (p < a.P) {
+                const int c = __builtin_amdgcn_readlane(h.cnt, p);
+                const bool in = lane < c && rank_key_value(k[q]) >= bound;
+                const unsigned long long bal = __ballot(in);
+                int base = 0;
+                if (lane == 0 && bal) base = atomicAdd(&sm.n_row, __popcll(bal));
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (in) { sm.list[base + lane_prefix_count(bal)] = k[q]; sm.rank[base + lane_prefix_count(bal)] = 0; }
+            }
+        }
+        __syncthreads();
+        n = sm.n_row;
+    } else {
+        for (int i = tid; i < n; i += kPartThreads) sm.rank[i] = 0;
+        __syncthreads();
+    }
+    // ---- one wave runs the accept tests, the others rank the candidates
+    const float m = pm + 0.0f;  // (no negative zero)
+    if (wave == 1) {
+        if (!a.commit) prop.template outcome<DT>(r, b, row, rowp, lane, m, ps);
+    } else {
+        const int who = wave == 0 ? 0 : wave - 1;
+        rank_against(sm.list, sm.rank, n, n * who / (kPartWaves - 1), n * (who + 1) / (kPartWaves - 1), lane);
+    }
+    __syncthreads();
+    const size_t o = (size_t)(a.commit ? b * a.R + j : row) * r.K;
+    for (int i = tid; i < n; i += kPartThreads) {
+        const int at = sm.rank[i];
+        if (at >= r.K) continue;
+        const unsigned long long key = sm.list[i];
+        const float l = rank_key_value(key);
+        if (a.commit) {
+            a.pr_top_idx[o + at] = (int32_t)rank_key_id(key);
+            a.pr_top_l[o + at] = l;
+        } else {
+            r.top_idx[o + at] = (int32_t)rank_key_id(key);
+            r.top_l[o + at] = l;
+            r.top_p[o + at] = exact_exp2(scaled_offset(l, m, r.c)) / ps;
+        }
+    }
+    if (tid == 0) {
+        if (a.commit) a.pr_m[b * a.R + j] = m;
+        else { r.row_m[row] = m; r.row_s[row] = ps; }
+    }
+}
+
+}  // namespace stand

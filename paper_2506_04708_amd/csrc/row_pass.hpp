@@ -64,6 +64,21 @@ __device__ __forceinline__ float wave_max_f32(float x)
     return uniform_f32(fmaxf(fmaxf(r0, r1), fmaxf(r2, r3)));
 }
 
+// sum over the 64 lanes (all active), the same in every lane; data-parallel-primitive steps as above, then the four
+// rows of 16 lanes as (r0 + r1) + (r2 + r3)
+__device__ __forceinline__ float wave_sum_f32(float x)
+{
+    x = x + dpp_fetch_f32<0xB1>(x);
+    x = x + dpp_fetch_f32<0x4E>(x);
+    x = x + dpp_fetch_f32<0x141>(x);
+    x = x + dpp_fetch_f32<0x140>(x);
+    const float r0 = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), 0));
+    const float r1 = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), 16));
+    const float r2 = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), 32));
+    const float r3 = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(x), 48));
+    return uniform_f32((r0 + r1) + (r2 + r3));
+}
+
 // Rank counting over n distinct non-zero keys in list[0..n): the K best are written, best
 // first, to top[0..min(n,K)).  Returns the K-th best key (0 if n < K).  The list must have
 // room for 7 padding entries behind n (they are zeroed here so that the scan can run in
@@ -533,6 +548,59 @@ struct RowPassArgs {
     int fx_shift;               // the exact normaliser counts in units of 2^-(40 - fx_shift) (0 up to V = 2^22)
 };
 
+// The proposal of a node and its accept tests, by one wave.
+struct NodeProposal {
+    int nch = 0, fc = -1;
+    int32_t my_id = -1, ch = -1;
+    float my_mu = 0.0f, my_l = 0.0f;
+    NodeTests tests;
+    // The proposal is requested early, so that its two dependent round trips to memory pass while the row is
+    // being ranked.
+    __device__ __forceinline__ void request(const RowPassArgs &a, int row, int u, int lane)
+    {
+        fc = a.tree.first_child[u];
+        nch = a.draft_has[row];  // children drafted from this node's table entry (0: none)
+        if (lane < a.K) {
+            my_id = a.draft_qid[(size_t)row * a.K + lane];
+            my_mu = a.draft_qmu[(size_t)row * a.K + lane];
+        }
+    }
+    template <int DT>
+    __device__ __forceinline__ void request_logits(const RowPassArgs &a, int b, const void *rowp, int lane)
+    {
+        if (nch == 0) return;  // uniform over the wave
+        if ((uint32_t)my_id >= (uint32_t)a.V) { my_id = -1; my_mu = 0.0f; }  // never index outside the row
+        else my_l = load_scalar<DT>(rowp, my_id);
+        if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
+        tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+    }
+    // accept / reject outcome of the node's children (paper Sec. 3.2, applied recursively)
+    template <int DT>
+    __device__ __forceinline__ int outcome(const RowPassArgs &a, int b, int row, const void *rowp, int lane, float m, float s)
+    {
+        if (nch == 0) {  // uniform over the wave
+            if (lane == 0) a.outcome[row] = -1;
+            return -1;
+        }
+        const float e = (lane < a.K && my_id >= 0) ? exact_exp2(scaled_offset(my_l, m, a.c)) : 0.0f;
+        // Relative error assumed for s: the part that grows with the terms a lane adds (a.eps, from the host);
+        // the offset every exponent shares is corrected in the streaming loop, what is left of it (the
+        // rounding of each term's own argument, relative to that argument, and of the waves' combination)
+        // is covered by a term in |m| c that stays far below a.eps for ordinary inputs.
+        const float eps_row = a.eps + 1e-9f * fabsf(m) * a.c;
+        NodeResult nr = wave_node_outcome(lane, a.K, tests, e / s, nch, true, eps_row, a.onehot);
+        if (nr.near) {
+            // a test fell inside the error bound of the fast normaliser: decide with the exact one
+            const unsigned long long S = wave_row_exact_sum<DT>(rowp, a.V, m, a.c, lane, a.fx_shift);
+            const float sx = normaliser_from_fixed(S, a.fx_shift);
+            nr = wave_node_outcome(lane, a.K, tests, e / sx, nch, false, 0.0f, a.onehot);
+            if (lane == 0) atomicAdd(&a.stats[kStatNear], 1ull);
+        }
+        if (lane == 0) a.outcome[row] = (int32_t)nr.accepted;
+        return nr.accepted;
+    }
+};
+
 // Shared memory of one row's workgroup of WPR waves.
 template <int WPR>
 struct RowShared {
@@ -541,6 +609,30 @@ struct RowShared {
     float part_m[WPR], part_s[WPR];
     int part_cnt[WPR];
 };
+
+// The first wave gathers its partners' records behind its own (each list holds at most K + kPruneSlack ranking
+// keys); with many partners the list is cut down on the way.  Returns the number of records.
+template <int DT, int WPR>
+__device__ __forceinline__ int gather_wave_records(RowShared<WPR> *sm, int lane, int K)
+{
+    WaveScan *ws = &sm->wsh[0];
+    int cnt = sm->part_cnt[0];
+    for (int q = 1; q < WPR; ++q) {
+        const int cq = sm->part_cnt[q];
+        if (cnt + cq > kWavePrune) {
+            WaveScanState gs;
+            gs.cnt = cnt;
+            set_theta(gs, 0ull);
+            __builtin_amdgcn_wave_barrier();
+            wave_prune_fast<false, true, DT == kDtBf16 ? 16 : 0>(ws, gs, lane, K, 0u, ~0u);
+            cnt = gs.cnt;
+        }
+        if (lane < cq) ws->buf[cnt + lane] = sm->wsh[q].buf[lane];
+        cnt += cq;
+    }
+    __builtin_amdgcn_wave_barrier();
+    return cnt;
+}
 
 // One logits row by the WPR waves of the calling workgroup (all of its 64 * WPR threads call this).
 // With pub.row set, the testing wave and the ranking wave also publish what the tail of the same launch
@@ -556,58 +648,14 @@ __device__ __forceinline__ void row_role(const RowPassArgs &a, int row, RowShare
     const int b = row / a.N, u = row % a.N;
     const char *rowp = (const char *)a.logits + (size_t)row * (size_t)a.V * ES;
     float m, s;
-    // The proposal of this node (needed for the accept tests at the end) is requested by the
-    // finishing wave as soon as it has streamed its part, so that its two dependent round trips
-    // to memory pass while the row is being ranked.
-    int nch = 0, fc = -1;
-    int32_t my_id = -1, ch = -1;
-    float my_mu = 0.0f, my_l = 0.0f;
-    auto request_proposal = [&]() {
-        fc = a.tree.first_child[u];
-        nch = a.draft_has[row];  // children drafted from this node's table entry (0: none)
-        if (lane < a.K) {
-            my_id = a.draft_qid[(size_t)row * a.K + lane];
-            my_mu = a.draft_qmu[(size_t)row * a.K + lane];
-        }
-    };
-    auto request_proposal_logits = [&]() {
-        if (nch == 0) return;  // uniform over the wave
-        if ((uint32_t)my_id >= (uint32_t)a.V) { my_id = -1; my_mu = 0.0f; }  // never index outside the row
-        else my_l = load_scalar<DT>(rowp, my_id);
-        if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
-    };
-    // ---- accept / reject outcome of this node's children (paper Sec. 3.2, applied recursively)
-    auto node_tests = [&](float m, float s) -> int {
-        if (nch == 0) {  // uniform over the wave
-            if (lane == 0) a.outcome[row] = -1;
-            return -1;
-        }
-        const float e = (lane < a.K && my_id >= 0) ? exact_exp2(scaled_offset(my_l, m, a.c)) : 0.0f;
-        // Relative error assumed for s: the part that grows with the terms a lane adds (a.eps, from the host);
-        // the offset every exponent shares is corrected in the streaming loop, what is left of it (the
-        // rounding of each term's own argument, relative to that argument, and of the waves' combination)
-        // is covered by a term in |m| c that stays far below a.eps for ordinary inputs.
-        const float eps_row = a.eps + 1e-9f * fabsf(m) * a.c;
-        NodeResult nr = wave_node_outcome(lane, a.K, my_id, my_mu, e / s, nch, ch, a.seed, (uint32_t)b, a.step, fc,
-                                          true, eps_row, a.onehot);
-        if (nr.near) {
-            // a test fell inside the error bound of the fast normaliser: decide with the exact one
-            const unsigned long long S = wave_row_exact_sum<DT>(rowp, a.V, m, a.c, lane, a.fx_shift);
-            const float sx = normaliser_from_fixed(S, a.fx_shift);
-            nr = wave_node_outcome(lane, a.K, my_id, my_mu, e / sx, nch, ch, a.seed, (uint32_t)b, a.step, fc, false,
-                                   0.0f, a.onehot);
-            if (lane == 0) atomicAdd(&a.stats[kStatNear], 1ull);
-        }
-        if (lane == 0) a.outcome[row] = (int32_t)nr.accepted;
-        return nr.accepted;
-    };
+    NodeProposal prop;  // (used by the testing wave)
     // Wave 0 ranks the row at its end, wave 1 runs the accept tests meanwhile.
     static_assert(WPR >= 2, "a row is shared by at least two waves");
     constexpr int kTestWave = 1;
     {
         const WavePartial wp = wave_row_stream<DT>(rowp, a.V, a.c, a.K, ws, lane, wave, WPR);
         if (lane == 0) { sm->part_m[wave] = wp.m_ref; sm->part_s[wave] = wp.s; sm->part_cnt[wave] = wp.cnt; }
-        if (wave == kTestWave) request_proposal();
+        if (wave == kTestWave) prop.request(a, row, u, lane);
     }
     __syncthreads();
     // both finishing waves form the row's maximum and normaliser with the same expressions, so
@@ -619,29 +667,13 @@ __device__ __forceinline__ void row_role(const RowPassArgs &a, int row, RowShare
     for (int q = 0; q < WPR; ++q) s += sm->part_s[q] * fast_exp2((sm->part_m[q] - m) * a.c);
     if (wave == kTestWave) {
         // the accept tests need the row's maximum and normaliser, not its ranking
-        request_proposal_logits();
-        const int oc = node_tests(m, s);
+        prop.request_logits<DT>(a, b, rowp, lane);
+        const int oc = prop.outcome<DT>(a, b, row, rowp, lane, m, s);
         if (pub.row && lane == 0) st_agent(&pub.row[row], pack_row_pub(m, oc, pub.tag));
         return;
     }
     if (wave != 0) return;
-    // gather the partner waves' records behind this wave's own (each list holds at most
-    // K + kPruneSlack ranking keys); with many partners the list is cut down on the way
-    int cnt = sm->part_cnt[0];
-    for (int q = 1; q < WPR; ++q) {
-        const int cq = sm->part_cnt[q];
-        if (cnt + cq > kWavePrune) {
-            WaveScanState gs;
-            gs.cnt = cnt;
-            set_theta(gs, 0ull);
-            __builtin_amdgcn_wave_barrier();
-            wave_prune_fast<false, true, DT == kDtBf16 ? 16 : 0>(ws, gs, lane, a.K, 0u, ~0u);
-            cnt = gs.cnt;
-        }
-        if (lane < cq) ws->buf[cnt + lane] = sm->wsh[q].buf[lane];
-        cnt += cq;
-    }
-    __builtin_amdgcn_wave_barrier();
+    const int cnt = gather_wave_records<DT, WPR>(sm, lane, a.K);
     wave_row_finish<DT>(rowp, a.V, a.K, ws, sm->ebuf, lane, cnt);
 
     if (lane < a.K) {

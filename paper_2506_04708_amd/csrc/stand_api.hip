@@ -73,6 +73,11 @@ struct stand_handle {
     int anc_words;
     float *pr_m, *pr_top_l;
     int32_t *pr_top_idx;
+    // rows split over workgroups (row_parts.hpp): parts per row of a verification and of an update (0: not split)
+    int row_parts, commit_parts;
+    unsigned *part_ticket;           // [rows or commit slots], zero between launches
+    PartHead *part_head;
+    unsigned long long *part_keys;
     unsigned long long *stats;
     unsigned long long *counter;
     bool table_used;
@@ -139,13 +144,30 @@ static void free_all(stand_handle *h)
     if (!h) return;
     void *ptrs[] = {h->d_tree, h->table, h->ctx_tail, h->ctx_len, h->ctx_tail2, h->ctx_len2, h->reorder_map, h->export_buf, h->draft_tok, h->draft_has, h->draft_qid, h->draft_qmu,
                     h->vs.row_m, h->vs.row_s, h->vs.top_l, h->vs.top_p, h->vs.top_idx, h->vs.outcome, h->vs.obs_idx, h->vs.obs_p, h->rec_slot,
-                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->stats, h->counter};
+                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
     for (void *p : ptrs) (void)hipFree(p);
     for (hipEvent_t e : h->ev_begin) (void)hipEventDestroy(e);
     for (hipEvent_t e : h->ev_end) (void)hipEventDestroy(e);
     if (h->probe_ev) (void)hipEventDestroy(h->probe_ev);
     if (h->probe_host) (void)hipHostFree(h->probe_host);
     delete h;
+}
+
+static int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
+
+// Parts of a row for row_parts_kernel, or 0 where it does not fit.  A part must fit the registers of a workgroup;
+// beyond that, few rows are split further until the launch has kPartsTarget workgroups, but not into parts of
+// less than one vector per thread (the maxima of their lane groups would no longer bound the K best well).
+constexpr int kPartsTarget = 256;
+static int choose_parts(const stand_handle *h, int rows)
+{
+    const int64_t nvec = ((int64_t)h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) + 15) / 16;
+    const int64_t least = (nvec + kPartThreads * kPartVectors - 1) / (kPartThreads * kPartVectors);
+    const int64_t most = std::max<int64_t>(least, nvec / kPartThreads);
+    const int64_t want = (kPartsTarget + rows - 1) / rows;
+    const int64_t p = std::min(std::max(want, least), most);
+    if (least > kPartsMax) return 0;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(p, kPartsMax));
 }
 
 extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
@@ -275,6 +297,12 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(dmalloc(&h->vs.stop_i, B * 4)); acc(dmalloc(&h->vs.stop_m, B)); acc(dmalloc(&h->vs.stop_qid, B * kMaxK));
     acc(dmalloc(&h->vs.stop_qmu, B * kMaxK)); acc(dmalloc(&h->vs.stop_ql, B * kMaxK)); acc(dmalloc(&h->vs.stop_child, B * kMaxK));
     acc(dmalloc(&h->pr_m, B * h->R)); acc(dmalloc(&h->pr_top_l, B * h->R * K)); acc(dmalloc(&h->pr_top_idx, B * h->R * K));
+    h->row_parts = rows <= (size_t)kRowsSplit ? choose_parts(h, (int)rows) : 0;
+    h->commit_parts = B * h->R <= (size_t)kCommitSlotsSplit ? choose_parts(h, (int)(B * h->R)) : 0;
+    const size_t part_tickets = std::max(h->row_parts ? rows : 0, h->commit_parts ? B * h->R : 0) * kTicketStride;
+    const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);
+    acc(dmalloc(&h->part_ticket, part_tickets));
+    acc(dmalloc(&h->part_head, part_slots)); acc(dmalloc(&h->part_keys, part_slots * kPartKeys));
     acc(dmalloc(&h->stats, (size_t)kStatCount));
     acc(dmalloc(&h->counter, 1));
     if (e != hipSuccess) { free_all(h); return e == hipErrorOutOfMemory ? STAND_ENOMEM : STAND_EHIP; }
@@ -317,6 +345,7 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(hipMemset(h->vs.row_m, 0, rows * sizeof(float))); acc(hipMemset(h->vs.row_s, 0, rows * sizeof(float)));
     acc(hipMemset(h->vs.top_l, 0, rows * K * sizeof(float))); acc(hipMemset(h->vs.top_p, 0, rows * K * sizeof(float)));
     acc(hipMemset(h->vs.top_idx, 0, rows * K * sizeof(int32_t)));
+    acc(hipMemset(h->part_ticket, 0, part_tickets * sizeof(unsigned)));
     acc(hipMemset(h->stats, 0, kStatCount * sizeof(unsigned long long)));
     acc(hipHostMalloc((void **)&h->probe_host, sizeof(unsigned long long), hipHostMallocDefault));
     if (h->probe_host) *h->probe_host = 0;
@@ -388,6 +417,7 @@ extern "C" int stand_reorder(stand_handle *h, const int32_t *host_src_of, void *
 // exponential and the rescaling of partial sums.  Never below the caller's margin (default 5e-5).
 static float fast_eps(const stand_handle *h, int wpr)
 {
+    // (a row split into parts: wpr = all waves that hold some of it)
     const int epv = h->cfg.logits_dtype == STAND_BF16 ? 8 : 4;
     const double per_lane = std::ceil((double)h->V / epv / (64.0 * wpr)) + epv + 6 + wpr + 16;
     const double bound = 2.0 * per_lane * 5.9604644775390625e-08;
@@ -408,17 +438,49 @@ static RowPassArgs make_row_args(const stand_handle *h, const VerifyScratch &vs,
     return a;
 }
 
-static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, hipStream_t s)
+template <int DT>
+static const void *row_parts_fn(int vectors)
 {
-    const int rows_all = h->B * h->N;
-    RowPassArgs a = make_row_args(h, vs, step, d_logits, rows_all <= kRowsFew ? kRowWPRFewRows : kRowWPR);
+    return vectors <= 1 ? (const void *)row_parts_kernel<DT, 1>
+         : vectors <= 2 ? (const void *)row_parts_kernel<DT, 2>
+         : vectors <= 3 ? (const void *)row_parts_kernel<DT, 3>
+         : vectors <= 4 ? (const void *)row_parts_kernel<DT, 4>
+         : vectors <= 6 ? (const void *)row_parts_kernel<DT, 6>
+                        : (const void *)row_parts_kernel<DT, kPartVectors>;
+}
+// Launch parameters of row_parts_kernel for `parts` parts per row.
+static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r, int parts)
+{
+    RowPartsArgs a;
+    memset(&a, 0, sizeof(a));
+    a.r = r;
+    a.P = parts;
+    // logits beyond what the eight L2 caches hold together (32 MB) are read past them: step of 256 rows of 257 KB 51.1
+    // against 54.6 us; below, the path rows' second read finds them there (16 rows of 128 KB: 29.3 against 30.0 us)
+    a.streamed = (int64_t)h->B * h->N * h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) > ((int64_t)32 << 20);
+    const int64_t nvec = ((int64_t)h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) + 15) / 16;
+    a.per = (int)((nvec + parts - 1) / parts);
+    a.ticket = h->part_ticket; a.head = h->part_head; a.keys = h->part_keys;
+    return a;
+}
+
+// `own`: the scratch is the handle's own (the parts of a split row meet in the handle's memory, which a caller of the
+// entry point with fixed scratch may not expect to be in use).
+static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, bool own, hipStream_t s)
+{
     const int rows = h->B * h->N;
+    const bool split = own && h->row_parts > 0;
     const bool few = rows <= kRowsFew;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
-    const dim3 grid((unsigned)rows), block(64u * (unsigned)(few ? kRowWPRFewRows : kRowWPR));
-    const void *fn = bf16 ? (few ? (const void *)row_pass_kernel<kDtBf16, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtBf16, kRowWPR>)
+    RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * h->row_parts : (few ? kRowWPRFewRows : kRowWPR));
+    RowPartsArgs pa = make_parts_args(h, a, split ? h->row_parts : 1);
+    const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
+    const dim3 grid = split ? dim3((unsigned)h->row_parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
+    const dim3 block(split ? (unsigned)kPartThreads : 64u * (unsigned)(few ? kRowWPRFewRows : kRowWPR));
+    const void *fn = split ? (bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors))
+                   : bf16 ? (few ? (const void *)row_pass_kernel<kDtBf16, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtBf16, kRowWPR>)
                           : (few ? (const void *)row_pass_kernel<kDtF32, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtF32, kRowWPR>);
-    void *args[] = {&a};
+    void *args[] = {split ? (void *)&pa : (void *)&a};
     const bool timed = h->profiling && h->ev_used < h->ev_begin.size();
     if (timed) {
         // the events are attached to the dispatch itself: their difference is the kernel's own
@@ -432,8 +494,6 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
     HIP_TRY(h, hipGetLastError());
     return STAND_OK;
 }
-
-static int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
 static MergeArgs merge_args(stand_handle *h, const int32_t *commit_tok, const int32_t *commit_row, const int32_t *commit_len)
 {
@@ -492,7 +552,17 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
         c.commit_row = commit_row; c.commit_len = commit_len;
         c.pr_m = h->pr_m; c.pr_top_idx = h->pr_top_idx; c.pr_top_l = h->pr_top_l;
         const dim3 grid((unsigned)h->R, (unsigned)h->B);
-        if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
+        if (h->commit_parts > 0) {
+            RowPartsArgs pa = make_parts_args(h, make_row_args(h, vs, step, d_logits, kPartWaves * h->commit_parts), h->commit_parts);
+            pa.streamed = false;  // (every row of an update is read again for its exact sum: 63.6 against 64.9 us, 128 rows of 304 KB)
+            pa.commit = true; pa.all_nodes = c.all_nodes; pa.W = h->W; pa.R = h->R;
+            pa.commit_row = commit_row; pa.commit_len = commit_len;
+            pa.pr_m = h->pr_m; pa.pr_top_idx = h->pr_top_idx; pa.pr_top_l = h->pr_top_l;
+            const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
+            void *args[] = {&pa};
+            HIP_TRY(h, hipLaunchKernel(bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors),
+                                       dim3((unsigned)h->commit_parts, (unsigned)h->B, (unsigned)h->R), dim3(kPartThreads), args, 0, s));
+        } else if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
         else commit_scan_kernel<kDtF32><<<grid, dim3(256), 0, s>>>(c);
     }
     // segments: one round of loads per thread (4 vectors of 16 bytes) where kSegMax allows it;
@@ -590,7 +660,7 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     if (!h || !d_logits || !d_out_tok || !d_out_node || !d_out_len) return STAND_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
-    int rc = launch_row_pass(h, h->vs, step, d_logits, s);
+    int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
     return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
@@ -629,7 +699,7 @@ extern "C" int stand_verify_static(stand_handle *h, uint64_t step, const void *d
     // Nothing in the scratch has to start at zero: every word a kernel of the verification reads was written
     // by an earlier kernel of the same call (row results and outcomes for all rows; partial sums, stop records
     // and observations for exactly the path rows that are read back).
-    int rc = launch_row_pass(h, vs, step, d_logits, s);
+    int rc = launch_row_pass(h, vs, step, d_logits, false, s);
     if (rc) return rc;
     return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
@@ -852,7 +922,7 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     plan_observe(h, s, capturing);
     if (!capturing && step_fused_wanted(h))
         return launch_step_fused(h, step, d_logits, d_out_tok, d_out_node, d_out_len, d_next_draft_tok, commit, s);
-    int rc = launch_row_pass(h, h->vs, step, d_logits, s);
+    int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
     const MergeArgs mg = merge_args(h, commit, nullptr, d_out_len);
     rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, s);

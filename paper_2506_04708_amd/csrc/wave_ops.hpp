@@ -15,6 +15,8 @@ constexpr int kDtBf16 = 0, kDtF32 = 1;
 #endif
 constexpr int kRowWPR = STAND_ROW_WPR, kRowWPRFewRows = 16;
 constexpr int kRowsFew = 768;               // at most this many rows: kRowWPRFewRows waves per row
+constexpr int kRowsSplit = 768;             // at most this many rows: every row is split over workgroups (row_parts.hpp)
+constexpr int kCommitSlotsSplit = 4096;     // the same for the rows of an update (most slots of a call hold no row)
 constexpr int kRowsMany = 8192;             // more rows than this: the step's automatic plan keeps the separate launches
 constexpr int kMaxNodes = 1024;
 constexpr int kMaxDepth = 31;
@@ -194,36 +196,55 @@ __device__ __forceinline__ unsigned long long dpp_fetch_u64(unsigned long long x
 
 struct NodeResult { int accepted; int rounds; bool near; float r; float rho; };
 
+// What the accept tests of a node need besides the row's probabilities: formed while those are on their way.
+// Lane i < K: w, the proposal's weight of stored id i (normalised).  Lane j < nchild: pos, the lane that stores the token of
+// drafted child j (-1: none, the rounds end there), and om, the uniform of its test.
+struct NodeTests { float w, om; int pos; };
+
 // ch: the token of drafted child `lane` (lanes 0..nchild-1), so that the rounds wait on no memory.
+__device__ __forceinline__ NodeTests node_tests_prepare(int lane, int K, int32_t my_id, float my_mu, int nchild, int32_t ch,
+                                                        uint64_t seed, uint32_t b, uint64_t step, int first_child)
+{
+    NodeTests t;
+    const bool act = lane < K;
+    nchild = nchild < kMaxK ? nchild : kMaxK;
+    if (lane >= nchild) ch = -1;
+    t.om = lane < nchild ? uniform(seed, b, step, (uint32_t)(first_child + lane), 0u, kStreamAccept) : 0.0f;
+    t.w = (act && my_mu > 0.0f) ? my_mu : 0.0f;
+    const float zw = wave_tree_sum(t.w);
+    t.w = zw > 0.0f ? t.w / zw : 0.0f;
+    t.pos = -1;
+    for (int j = 0; j < nchild; ++j) {
+        const int32_t x = __builtin_amdgcn_readlane(ch, j);
+        const unsigned long long mask = __ballot(act && x >= 0 && my_id == x);
+        if (!mask) break;
+        const int i = __ffsll((long long)mask) - 1;
+        if (lane == j) t.pos = i;
+    }
+    return t;
+}
+
 // onehot (deterministic drafting, paper Sec. 3.1): the proposal of each round is the one-hot
 // vector on that round's child instead of the renormalised stored means.
-__device__ __forceinline__ NodeResult wave_node_outcome(int lane, int K, int32_t my_id, float my_mu, float my_p, int nchild,
-                                        int32_t ch, uint64_t seed, uint32_t b, uint64_t step, int first_child,
-                                        bool track_err, float eps, bool onehot)
+__device__ __forceinline__ NodeResult wave_node_outcome(int lane, int K, const NodeTests &t, float my_p, int nchild, bool track_err,
+                                                        float eps, bool onehot)
 {
     NodeResult res;
     res.accepted = -1; res.rounds = 0; res.near = false;
     const bool act = lane < K;
     nchild = nchild < kMaxK ? nchild : kMaxK;
-    if (lane >= nchild) ch = -1;
-    const float om_l = lane < nchild ? uniform(seed, b, step, (uint32_t)(first_child + lane), 0u, kStreamAccept) : 0.0f;
-    float w = (act && my_mu > 0.0f) ? my_mu : 0.0f;
-    float zw = wave_tree_sum(w);
-    w = zw > 0.0f ? w / zw : 0.0f;
+    float w = t.w;
     float r = act ? my_p : 0.0f;
     float rho = 1.0f;
     float err = track_err ? eps * r : 0.0f;
     for (int j = 0; j < nchild; ++j) {
-        const int32_t x = __builtin_amdgcn_readlane(ch, j);
-        if (x < 0) break;
-        const unsigned long long mask = __ballot(act && my_id == x);
-        if (!mask) break;
-        const int i = __ffsll((long long)mask) - 1;
+        const int i = __builtin_amdgcn_readlane(t.pos, j);
+        if (i < 0) break;
         if (onehot) w = lane == i ? 1.0f : 0.0f;
         const float wi = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(w), i));
         const float ri = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(r), i));
         const float ei = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(err), i));
-        const float om = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(om_l), j));
+        const float om = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(t.om), j));
         const float lhs = om * wi;
         res.rounds++;
         if (track_err && fabsf(lhs - ri) <= ei + 4e-7f * ri) res.near = true;
@@ -237,11 +258,10 @@ __device__ __forceinline__ NodeResult wave_node_outcome(int lane, int K, int32_t
         if (!(d > 0.0f)) d = 0.0f;
         const float rn = d / Z;
         if (track_err) {
-            float ez = (act && (r - err) < w) ? err : 0.0f;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) ez += __shfl_xor(ez, off);
+            const float ez = wave_tree_sum((act && (r - err) < w) ? err : 0.0f);
             if (ez > 0.25f * Z) res.near = true;
-            err = ((err + rn * ez) / Z) * 1.001f + 4e-7f * rn;
+            // (an upper bound: the reciprocal is good to an ulp, 1.002 covers it and the bound's own roundings)
+            err = (err + rn * ez) * (__builtin_amdgcn_rcpf(Z) * 1.002f) + 4e-7f * rn;
         }
         r = rn;
         rho = rho / Z;

@@ -314,6 +314,39 @@ def test_rows_sizes(gpu, V, K):
     _row_case(gpu, rows, "bf16", K)
 
 
+# Rows split over workgroups: 4096 vectors of 8 (bf16) or 4 (fp32) elements fill the registers of one part
+@pytest.mark.parametrize("dtype,V,K", [
+    ("bf16", 4096 * 8, 10), ("bf16", 4096 * 8 + 1, 32), ("bf16", 3 * 4096 * 8 - 5, 16), ("bf16", 512 * 8 * 16 + 3, 7),
+    ("f32", 4096 * 4, 32), ("f32", 4096 * 4 - 1, 16), ("f32", 5 * 4096 * 4 + 2, 10),
+    ("bf16", 32 * 4096 * 8, 16), ("bf16", 32 * 4096 * 8 + 8, 16),       # the most parts a row has, and one vector too many
+])
+def test_rows_split_over_workgroups(gpu, dtype, V, K):
+    r = np.random.default_rng(V + K)
+    noise = lambda: (r.standard_normal(V) * 1.7).astype(np.float32)  # noqa: E731
+    half, few, tied = noise(), np.full(V, -np.inf, np.float32), noise()
+    half[: V // 2] = -np.inf                                             # whole parts masked
+    few[r.choice(V, size=K - 2, replace=False)] = 1.0                    # fewer tokens left than K: masked ones fill up
+    tied[V // 3: 2 * V // 3] = np.float32(9.0)                           # more equal largest elements than a list holds
+    steps = np.round(noise() * 4) / 4                                    # many ties around the K-th largest
+    edge = noise()
+    edge[[0, 1, V - 2, V - 1]] += 12
+    _say("rows split %s V=%d K=%d" % (dtype, V, K))
+    _row_case(gpu, np.stack([noise(), half, few, tied, steps, edge]), dtype, K)
+
+
+@pytest.mark.parametrize("over,mode", [
+    (dict(V=70001, B=2, rho=0.7), "separate"), (dict(V=70001, B=2, rho=0.7, dtype="bf16"), "separate"),
+    (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"), (dict(V=66000, B=47, rho=0.7, dtype="bf16"), "step"),
+])
+def test_lockstep_rows_split_over_workgroups(gpu, over, mode):
+    """Verification and update on rows of several parts (47 x 16 rows: just below the limit of the split)."""
+    binding, lockstep = gpu
+    _say("lockstep split %s %s" % (over, mode))
+    w = synth.Workload("cfg1", run_steps=6, **over)
+    info = lockstep.run_lockstep(w, 6, mode=mode, capacity=1 << 14, table_every=3, sample_rows=range(0, w.B * w.N, 7))
+    _say("  -> %s" % info)
+
+
 def test_full_shape_rows_sampled(gpu):
     """The headline benchmark configuration's (cfg3) shape (B=32, N=64, V=152064, bf16, K=16) in the launch configuration the
     benchmark times: one verify over all 2048 rows; the oracle checks a sample of them and the
