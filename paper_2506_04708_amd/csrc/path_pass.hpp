@@ -559,47 +559,66 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
     }
 }
 
-// See the comment above PathArgs.  Blocks [0, finish_blocks) finish row slot j of trajectory b with
-// (j, b) = (block / B, block % B); the blocks after them claim merge records, kFinishThreads per block.
+// See the comment above PathArgs.  Verification: blocks [0, B) finish the stop rows (all threads of a block).  The next
+// row_blocks blocks finish the other rows of the paths, or all rows of an update: one wave per row slot (slot-major, as
+// in path_exact_kernel; most slots hold no row, and a workgroup of its own for each kept 1408 workgroups of 1024
+// threads busy with finding that out).  The blocks after them claim merge records, one per thread.
 template <int DT>
-__global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a, MergeArgs mg, int finish_blocks)
+__global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a, MergeArgs mg, int row_blocks)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if ((int)blockIdx.x >= finish_blocks) {
-        merge_claim_record(mg, ((int)blockIdx.x - finish_blocks) * kFinishThreads + tid);
+    const int stop_blocks = a.mode == 0 ? a.B : 0;
+    const int block = (int)blockIdx.x;
+    if (block >= stop_blocks + row_blocks) {
+        count_claims(mg, merge_claim_record(mg, (block - stop_blocks - row_blocks) * kFinishThreads + tid), lane);
         return;
     }
     __shared__ FinishShared sh;
-    const int j = (int)blockIdx.x / a.B, b = (int)blockIdx.x % a.B;  // slot-major, as in path_exact_kernel
-    // Everything whose address depends on (b, j) only is requested at once: the partial sums and,
-    // in verify mode, the stop record of the trajectory (used if this turns out to be its stop row).
-    const unsigned long long part = (wave == 0 && lane < a.nseg) ? ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]) : 0ull;
-    int len = 0, node, nch = 0, fc = -1;
-    bool stop = false;
-    int32_t my_id = -1, ch = -1;
-    float my_mu = 0.0f, my_l = 0.0f, m;
-    if (a.mode == 0) {
-        const int stop_node = a.stop_i[(size_t)b * 4 + 0];
-        len = a.stop_i[(size_t)b * 4 + 1];
-        nch = a.stop_i[(size_t)b * 4 + 2];
-        fc = a.stop_i[(size_t)b * 4 + 3];
-        m = a.stop_m[b];
-        if (wave == 0 && lane < kMaxK) {
+    if (block < stop_blocks) {
+        const int b = block;
+        const bool first = wave == 0;
+        // the partial sums of the first path positions are requested with the stop record, before it says which of
+        // them is the stop row
+        constexpr int kAhead = 4;
+        unsigned long long ahead[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q)
+            ahead[q] = (first && lane < a.nseg && q < a.R) ? ld_agent(&a.seg_part[((size_t)b * a.R + q) * kSegMax + lane]) : 0ull;
+        const int node = a.stop_i[(size_t)b * 4 + 0], len = a.stop_i[(size_t)b * 4 + 1];
+        const int nch = a.stop_i[(size_t)b * 4 + 2], fc = a.stop_i[(size_t)b * 4 + 3];
+        const float m = a.stop_m[b];
+        int32_t my_id = -1, ch = -1;
+        float my_mu = 0.0f, my_l = 0.0f;
+        if (first && lane < kMaxK) {
             my_id = a.stop_qid[(size_t)b * kMaxK + lane]; my_mu = a.stop_qmu[(size_t)b * kMaxK + lane];
             my_l = a.stop_ql[(size_t)b * kMaxK + lane]; ch = a.stop_child[(size_t)b * kMaxK + lane];
         }
-        // all-nodes mode: slot j = node j; an undrafted root (empty context) is still the stop row
-        if (a.all_nodes) node = (a.draft_tok[(size_t)b * a.N + j] >= 0 || j == 0) ? j : -1;
-        else node = j < len ? (j == len - 1 ? stop_node : a.out_node[(size_t)b * a.W + j]) : -1;
-        stop = node >= 0 && node == stop_node;
+        const int j = a.all_nodes ? node : len - 1;  // the stop row's slot
+        unsigned long long part = 0ull;
+        if (first && lane < a.nseg) {
+            if (j < kAhead) {
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) part = q == j ? ahead[q] : part;
+            } else part = ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]);
+        }
+        finish_row<DT, kFinishThreads>(a, sh, b, j, node, true, m, nch, fc, len, my_id, my_mu, my_l, ch, part, tid, wave);
+        return;
+    }
+    const int slot = (block - stop_blocks) * (kFinishThreads / 64) + wave;
+    if (slot >= a.B * a.R) return;
+    const int j = slot / a.B, b = slot % a.B;
+    const unsigned long long part = lane < a.nseg ? ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]) : 0ull;
+    int node;
+    if (a.mode == 0) {
+        const int stop_node = a.stop_i[(size_t)b * 4 + 0], len = a.stop_i[(size_t)b * 4 + 1];
+        if (a.all_nodes) node = (a.draft_tok[(size_t)b * a.N + j] >= 0 && j != stop_node) ? j : -1;
+        else node = j + 1 < len ? a.out_node[(size_t)b * a.W + j] : -1;
     } else {
         node = a.all_nodes ? (a.draft_tok[(size_t)b * a.N + j] >= 0 ? j : -1) : commit_row_of(a, b, j);
-        m = 0.0f;
     }
-    if (node < 0) return;  // block-uniform
-    if (!stop && wave != 0) return;
-    if (!stop) m = a.src_m[a.mode == 0 ? b * a.N + node : b * a.R + j];
-    finish_row<DT, kFinishThreads>(a, sh, b, j, node, stop, m, nch, fc, len, my_id, my_mu, my_l, ch, part, tid, wave);
+    if (node < 0) return;
+    const float m = a.src_m[a.mode == 0 ? b * a.N + node : b * a.R + j];
+    finish_row<DT, kFinishThreads>(a, sh, b, j, node, false, m, 0, -1, 0, -1, 0.0f, 0.0f, -1, part, lane, 0);
 }
 
 }  // namespace stand

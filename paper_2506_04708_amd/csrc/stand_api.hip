@@ -298,7 +298,12 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(dmalloc(&h->vs.stop_qmu, B * kMaxK)); acc(dmalloc(&h->vs.stop_ql, B * kMaxK)); acc(dmalloc(&h->vs.stop_child, B * kMaxK));
     acc(dmalloc(&h->pr_m, B * h->R)); acc(dmalloc(&h->pr_top_l, B * h->R * K)); acc(dmalloc(&h->pr_top_idx, B * h->R * K));
     h->row_parts = rows <= (size_t)kRowsSplit ? choose_parts(h, (int)rows) : 0;
-    h->commit_parts = B * h->R <= (size_t)kCommitSlotsSplit ? choose_parts(h, (int)(B * h->R)) : 0;
+    {
+        // rows an update is likely to hold: every slot where all of them can be on one path or are merged anyway
+        // (chains, all-nodes updates), else a few per trajectory (accepted paths are short)
+        const size_t expect = B * (size_t)((h->W == N || h->R > h->W) ? h->R : std::min(h->W, 4));
+        h->commit_parts = expect <= (size_t)kRowsSplit && B * h->R <= (size_t)kCommitSlotsSplit ? choose_parts(h, (int)expect) : 0;
+    }
     const size_t part_tickets = std::max(h->row_parts ? rows : 0, h->commit_parts ? B * h->R : 0) * kTicketStride;
     const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);
     acc(dmalloc(&h->part_ticket, part_tickets));
@@ -470,7 +475,7 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
 {
     const int rows = h->B * h->N;
     const bool split = own && h->row_parts > 0;
-    const bool few = rows <= kRowsFew;  // one workgroup per row; more waves per row when rows are few
+    const bool few = rows <= kRowsSplit;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * h->row_parts : (few ? kRowWPRFewRows : kRowWPR));
     RowPartsArgs pa = make_parts_args(h, a, split ? h->row_parts : 1);
@@ -572,16 +577,17 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
     // mostly short; the kernel loops over longer ones)
     const int row_slots = (mode == 0 && !a.all_nodes) ? (h->R < 3 ? h->R : 3) : h->R;
     const dim3 g1((unsigned)a.nseg + 1, (unsigned)h->B, (unsigned)row_slots), block(kPathThreads);
-    const int finish_blocks = h->B * h->R;
+    const bool single = mode == 0 && h->R == 1;   // (paths of one node: every row is a stop row)
+    const int row_blocks = single ? 0 : (h->B * h->R + kFinishThreads / 64 - 1) / (kFinishThreads / 64);
     const int claim_blocks = claim ? (h->B * h->R * h->NO + kFinishThreads - 1) / kFinishThreads : 0;
     const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
-    const dim3 g2((unsigned)(finish_blocks + claim_blocks));
+    const dim3 g2((unsigned)((mode == 0 ? h->B : 0) + row_blocks + claim_blocks));
     if (bf16) {
         path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
-        path_finish_kernel<kDtBf16><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, finish_blocks);
+        path_finish_kernel<kDtBf16><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     } else {
         path_exact_kernel<kDtF32><<<g1, block, 0, s>>>(a);
-        path_finish_kernel<kDtF32><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, finish_blocks);
+        path_finish_kernel<kDtF32><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     }
     HIP_TRY(h, hipGetLastError());
     return STAND_OK;
@@ -591,10 +597,10 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
 static int launch_merge_apply(stand_handle *h, const MergeArgs &a, bool append_ctx, hipStream_t s)
 {
     const int nrec = h->B * h->R * h->NO;
-    merge_apply_kernel<<<dim3((unsigned)((nrec + kMergeWaves - 1) / kMergeWaves)), dim3(64 * kMergeWaves), 0, s>>>(a);
-    if (append_ctx)
-        ctx_append_kernel<<<dim3((unsigned)((h->B + 63) / 64)), dim3(64), 0, s>>>(h->B, h->W, h->ctx_tail, h->ctx_len,
-                                                                                a.commit_tok, a.commit_len);
+    const int apply_blocks = (nrec + kMergeWaves - 1) / kMergeWaves;
+    const int append_blocks = append_ctx ? (h->B + 64 * kMergeWaves - 1) / (64 * kMergeWaves) : 0;
+    merge_apply_kernel<<<dim3((unsigned)(apply_blocks + append_blocks)), dim3(64 * kMergeWaves), 0, s>>>(
+        a, apply_blocks, append_ctx ? h->ctx_tail : nullptr, append_ctx ? h->ctx_len : nullptr);
     HIP_TRY(h, hipGetLastError());
     h->table_used = true;
     return STAND_OK;

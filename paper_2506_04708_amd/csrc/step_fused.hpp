@@ -317,7 +317,8 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
         }
         publish_fence();  // out_len and the accepted tokens, written by this wave, are what its claims read
         const int per_traj = A.mg.R * (A.mg.omax - A.mg.omin + 1);
-        for (int i = lane; i < per_traj; i += 64) merge_claim_record(A.mg, b * per_traj + i);
+        for (int i = lane; i < ((per_traj + 63) & ~63); i += 64)
+            count_claims(A.mg, i < per_traj ? merge_claim_record(A.mg, b * per_traj + i) : (int)kClaimNone, lane);
     }
     // ---- the partial sums (of whichever waves summed them), then the rows' observations and the resampled token
     if (tid == 0) stamp(sy, b, 3);

@@ -36,11 +36,14 @@ constexpr uint32_t kTagShift = 8, kTagMax = 0x7FFFFFu, kMultiBit = 0x80000000u;
 
 __device__ __forceinline__ int clamp_len(int len, int W) { return len < 0 ? 0 : (len > W ? W : len); }
 
+enum ClaimOutcome { kClaimNone = 0, kClaimInsert, kClaimMerge, kClaimDrop };
+
 // claims the table slot of merge record rec = (b, position j, order n); run by one thread
-__device__ __forceinline__ void merge_claim_record(const MergeArgs &a, int rec)
+__device__ __forceinline__ int merge_claim_record(const MergeArgs &a, int rec)
 {
     const int NO = a.omax - a.omin + 1;
-    if (rec >= a.B * a.R * NO) return;
+    if (rec >= a.B * a.R * NO) return kClaimNone;
+    int outcome = kClaimNone;
     const int n = a.omin + rec % NO;
     const int j = (rec / NO) % a.R;
     const int b = rec / (NO * a.R);
@@ -77,7 +80,7 @@ __device__ __forceinline__ void merge_claim_record(const MergeArgs &a, int rec)
             SlotHeader *h = slot_header(a.table, slot, a.slot_bytes);
             const unsigned long long old = atomicCAS(&h->fp, 0ull, fp);
             if (old == 0ull || old == fp) {
-                atomicAdd(&a.stats[old == 0ull ? kStatInserts : kStatMerges], 1ull);
+                outcome = old == 0ull ? kClaimInsert : kClaimMerge;
                 // Until the records are applied the order word also carries the smallest record
                 // number that claimed the slot (stored inverted, so that atomicMax keeps it), and
                 // the top bit of the count word says that more than one record did.
@@ -87,9 +90,23 @@ __device__ __forceinline__ void merge_claim_record(const MergeArgs &a, int rec)
                 slot_out = (long long)slot; placed = true; break;
             }
         }
-        if (!placed) atomicAdd(&a.stats[kStatDrops], 1ull);
+        if (!placed) outcome = kClaimDrop;
     }
     st_agent(&a.rec_slot[rec], slot_out);
+    return outcome;
+}
+
+// Adds the outcomes of a wave's claims to the statistics.  (One device-wide addition per record made the claims of an
+// update of 672 rows, 2688 records on one address, take 40 us.)
+__device__ __forceinline__ void count_claims(const MergeArgs &a, int outcome, int lane)
+{
+    const int ins = __popcll(__ballot(outcome == kClaimInsert)), mrg = __popcll(__ballot(outcome == kClaimMerge));
+    const int drp = __popcll(__ballot(outcome == kClaimDrop));
+    if (lane == 0) {
+        if (ins) atomicAdd(&a.stats[kStatInserts], (unsigned long long)ins);
+        if (mrg) atomicAdd(&a.stats[kStatMerges], (unsigned long long)mrg);
+        if (drp) atomicAdd(&a.stats[kStatDrops], (unsigned long long)drp);
+    }
 }
 
 
@@ -100,6 +117,7 @@ __device__ __forceinline__ void merge_claim_record(const MergeArgs &a, int rec)
 // once.  A slot claimed by one record only needs no search for followers.  The waves of a
 // workgroup do not interact.
 constexpr int kMergeWaves = 16;
+constexpr int kFollowGroups = 8;
 
 // Record `rec` by one wave (all 64 lanes call this; l_id / l_val: 2 * kMaxK words of shared memory
 // owned by the wave).  Does nothing unless the record exists and leads its slot.
@@ -178,16 +196,17 @@ __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int la
 
     apply(o_id, o_p);
     if (multi) {
-        // the later records of this slot, in record order (four groups of 64 record slots are read per round)
-        for (int base = rec + 1; base < nrec; base += 256) {
-            long long rs[4];
+        // the later records of this slot, in record order (kFollowGroups groups of 64 record slots are read per
+        // round trip: a step of 128 trajectories has thousands of record slots)
+        for (int base = rec + 1; base < nrec; base += 64 * kFollowGroups) {
+            long long rs[kFollowGroups];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kFollowGroups; ++q) {
                 const int r = base + 64 * q + lane;
                 rs[q] = r < nrec ? ld_agent(&a.rec_slot[r]) : -1;
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < kFollowGroups; ++q) {
                 unsigned long long hits = __ballot(rs[q] == slot);
                 while (hits) {
                     const int bit = __ffsll((long long)hits) - 1;
@@ -205,33 +224,39 @@ __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int la
     if (lane == 0) { st_agent(&h->count, count); st_agent(&h->order, order_word & ((1u << kTagShift) - 1u)); }
 }
 
-__global__ __launch_bounds__(64 * kMergeWaves) void merge_apply_kernel(MergeArgs a)
+// Appends the committed tokens of trajectory b to its context tail (one thread).
+__device__ __forceinline__ void append_context(const MergeArgs &a, int b, int32_t *ctx_tail, long long *ctx_len)
+{
+    const int len = clamp_len(a.commit_len[b], a.W);
+    int32_t t[kMaxOrder];
+#pragma unroll
+    for (int i = 0; i < kMaxOrder; ++i) {
+        // the last kMaxOrder tokens of tail ++ commit
+        const int at = i + len;
+        t[i] = at < kMaxOrder ? ctx_tail[(size_t)b * kMaxOrder + at] : a.commit_tok[(size_t)b * a.W + (at - kMaxOrder)];
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxOrder; ++i) ctx_tail[(size_t)b * kMaxOrder + i] = t[i];
+    ctx_len[b] += len;
+}
+
+// Blocks [0, apply_blocks) apply the records; with ctx_tail set, the blocks after them append the committed tokens to
+// the contexts (stand_update; the claims, which read the contexts as they were, are in an earlier launch).
+__global__ __launch_bounds__(64 * kMergeWaves) void merge_apply_kernel(MergeArgs a, int apply_blocks, int32_t *ctx_tail, long long *ctx_len)
 {
     __shared__ int32_t l_id_all[kMergeWaves][2 * kMaxK];
     __shared__ float l_val_all[kMergeWaves][2 * kMaxK];
+    if ((int)blockIdx.x >= apply_blocks) {
+        const int b = ((int)blockIdx.x - apply_blocks) * 64 * kMergeWaves + (int)threadIdx.x;
+        if (b < a.B) append_context(a, b, ctx_tail, ctx_len);
+        return;
+    }
     const int NO = a.omax - a.omin + 1;
     const int nrec = a.B * a.R * NO;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int rec = (int)blockIdx.x * kMergeWaves + wave;
     if (rec >= nrec) return;
     apply_record(a, rec, lane, l_id_all[wave], l_val_all[wave]);
-}
-
-// append the committed tokens to the context tails
-__global__ void ctx_append_kernel(int B, int W, int32_t *ctx_tail, long long *ctx_len, const int32_t *commit_tok,
-                                  const int32_t *commit_len)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const int len = clamp_len(commit_len[b], W);
-    int32_t t[kMaxOrder];
-    for (int i = 0; i < kMaxOrder; ++i) t[i] = ctx_tail[(size_t)b * kMaxOrder + i];
-    for (int j = 0; j < len; ++j) {
-        for (int i = 0; i + 1 < kMaxOrder; ++i) t[i] = t[i + 1];
-        t[kMaxOrder - 1] = commit_tok[(size_t)b * W + j];
-    }
-    for (int i = 0; i < kMaxOrder; ++i) ctx_tail[(size_t)b * kMaxOrder + i] = t[i];
-    ctx_len[b] += len;
 }
 
 }  // namespace stand
