@@ -60,34 +60,24 @@ __device__ __forceinline__ float uniform(uint64_t seed, uint32_t b, uint64_t ste
     return word_to_uniform(philox_word(p, token & 3u));
 }
 
+// 2^f for |f| <= 1/2, the polynomial part of exact_exp2
+__device__ __forceinline__ float exact_exp2_fraction(float f)
+{
+    float q = 0x1.44138ap-13f;
+    q = __builtin_fmaf(q, f, 0x1.5f0890p-10f);
+    q = __builtin_fmaf(q, f, 0x1.3b2a54p-7f);
+    q = __builtin_fmaf(q, f, 0x1.c6af6cp-5f);
+    q = __builtin_fmaf(q, f, 0x1.ebfbe0p-3f);
+    q = __builtin_fmaf(q, f, 0x1.62e430p-1f);
+    return __builtin_fmaf(q, f, 1.0f);
+}
+
 // ---- 2^y for y <= ~0: 0 below -64, else 2^k * (1 + f Q(f)) with k = rint(y), f = y - k ----------
 __device__ __forceinline__ float exact_exp2(float y)
 {
     if (!(y >= -64.0f)) return 0.0f;
     float k = __builtin_rintf(y);
-    float f = y - k;
-    float q = 0x1.44138ap-13f;
-    q = __builtin_fmaf(q, f, 0x1.5f0890p-10f);
-    q = __builtin_fmaf(q, f, 0x1.3b2a54p-7f);
-    q = __builtin_fmaf(q, f, 0x1.c6af6cp-5f);
-    q = __builtin_fmaf(q, f, 0x1.ebfbe0p-3f);
-    q = __builtin_fmaf(q, f, 0x1.62e430p-1f);
-    float p = __builtin_fmaf(q, f, 1.0f);
-    return __builtin_ldexpf(p, (int)k);
-}
-
-// The same for -64 <= y <= 0 without the test (callers that clamp y themselves).
-__device__ __forceinline__ float exact_exp2_noguard(float y)
-{
-    float k = __builtin_rintf(y);
-    float f = y - k;
-    float q = 0x1.44138ap-13f;
-    q = __builtin_fmaf(q, f, 0x1.5f0890p-10f);
-    q = __builtin_fmaf(q, f, 0x1.3b2a54p-7f);
-    q = __builtin_fmaf(q, f, 0x1.c6af6cp-5f);
-    q = __builtin_fmaf(q, f, 0x1.ebfbe0p-3f);
-    q = __builtin_fmaf(q, f, 0x1.62e430p-1f);
-    float p = __builtin_fmaf(q, f, 1.0f);
+    float p = exact_exp2_fraction(y - k);
     return __builtin_ldexpf(p, (int)k);
 }
 

@@ -118,13 +118,6 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
 {
     return readlane_u64(wave_inclusive_scan_u64(x), 63);
 }
-__device__ __forceinline__ unsigned long long fixed_mass(float e, int shift)
-{
-    uint32_t hi, lo;
-    fixed_split(e, hi, lo);
-    return ((unsigned long long)hi << (20 - shift)) + (lo >> shift);
-}
-
 template <int DT>
 __global__ __launch_bounds__(kPathThreads) void path_exact_kernel(PathArgs a)
 {

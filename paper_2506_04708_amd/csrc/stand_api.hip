@@ -570,12 +570,14 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
         } else if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
         else commit_scan_kernel<kDtF32><<<grid, dim3(256), 0, s>>>(c);
     }
-    // segments: one round of loads per thread (4 vectors of 16 bytes) where kSegMax allows it;
+    // segments: one round of loads per thread where kSegMax allows it, of 4 vectors of 16 bytes, or of 2 for the few
+    // path rows of a small batch (steps with 2 / 4, us: 1 x 32 rows 33.3 / 34.2, 8 x 32 50.4 / 51.2, 32 x 64 158.0 / 156.4);
     // one more block per (row, trajectory) slot for the outputs and the stop record
-    PathArgs a = make_path_args(h, vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, 4 * kPathThreads);
-    // row slots of the grid: every slot in update / all-nodes mode; in verify mode three (paths are
+    const int per_thread = mode == 0 && h->B <= 16 ? 2 : 4;
+    PathArgs a = make_path_args(h, vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, per_thread * kPathThreads);
+    // row slots of the grid: every slot in update / all-nodes mode; in verify mode four (paths are
     // mostly short; the kernel loops over longer ones)
-    const int row_slots = (mode == 0 && !a.all_nodes) ? (h->R < 3 ? h->R : 3) : h->R;
+    const int row_slots = (mode == 0 && !a.all_nodes) ? std::min(h->R, 4) : h->R;
     const dim3 g1((unsigned)a.nseg + 1, (unsigned)h->B, (unsigned)row_slots), block(kPathThreads);
     const bool single = mode == 0 && h->R == 1;   // (paths of one node: every row is a stop row)
     const int row_blocks = single ? 0 : (h->B * h->R + kFinishThreads / 64 - 1) / (kFinishThreads / 64);
