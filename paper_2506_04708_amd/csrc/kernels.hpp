@@ -34,5 +34,6 @@
 #include "table_merge.hpp"
 #include "path_pass.hpp"
 #include "draft.hpp"
+#include "path_tail.hpp"
 #include "step_fused.hpp"
 #include "aux_kernels.hpp"

@@ -552,6 +552,40 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
     }
 }
 
+// The stop record of a trajectory and the partial sums of its stop row, as path_exact_kernel left them.
+struct StopRow {
+    int node, len, nch, fc, j;     // j: the stop row's slot
+    float m;
+    int32_t my_id = -1, ch = -1;
+    float my_mu = 0.0f, my_l = 0.0f;
+    unsigned long long part = 0ull;
+    // `first`: this is the wave that holds the proposal and the partial sums
+    __device__ __forceinline__ void request(const PathArgs &a, int b, int lane, bool first)
+    {
+        // the partial sums of the first path positions are requested with the stop record, before it says which of
+        // them is the stop row
+        constexpr int kAhead = 4;
+        unsigned long long ahead[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q)
+            ahead[q] = (first && lane < a.nseg && q < a.R) ? ld_agent(&a.seg_part[((size_t)b * a.R + q) * kSegMax + lane]) : 0ull;
+        node = a.stop_i[(size_t)b * 4 + 0]; len = a.stop_i[(size_t)b * 4 + 1];
+        nch = a.stop_i[(size_t)b * 4 + 2]; fc = a.stop_i[(size_t)b * 4 + 3];
+        m = a.stop_m[b];
+        if (first && lane < kMaxK) {
+            my_id = a.stop_qid[(size_t)b * kMaxK + lane]; my_mu = a.stop_qmu[(size_t)b * kMaxK + lane];
+            my_l = a.stop_ql[(size_t)b * kMaxK + lane]; ch = a.stop_child[(size_t)b * kMaxK + lane];
+        }
+        j = a.all_nodes ? node : len - 1;
+        if (first && lane < a.nseg) {
+            if (j < kAhead) {
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) part = q == j ? ahead[q] : part;
+            } else part = ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]);
+        }
+    }
+};
+
 // See the comment above PathArgs.  Verification: blocks [0, B) finish the stop rows (all threads of a block).  The next
 // row_blocks blocks finish the other rows of the paths, or all rows of an update: one wave per row slot (slot-major, as
 // in path_exact_kernel; most slots hold no row, and a workgroup of its own for each kept 1408 workgroups of 1024
@@ -568,33 +602,10 @@ __global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a,
     }
     __shared__ FinishShared sh;
     if (block < stop_blocks) {
-        const int b = block;
-        const bool first = wave == 0;
-        // the partial sums of the first path positions are requested with the stop record, before it says which of
-        // them is the stop row
-        constexpr int kAhead = 4;
-        unsigned long long ahead[kAhead];
-#pragma unroll
-        for (int q = 0; q < kAhead; ++q)
-            ahead[q] = (first && lane < a.nseg && q < a.R) ? ld_agent(&a.seg_part[((size_t)b * a.R + q) * kSegMax + lane]) : 0ull;
-        const int node = a.stop_i[(size_t)b * 4 + 0], len = a.stop_i[(size_t)b * 4 + 1];
-        const int nch = a.stop_i[(size_t)b * 4 + 2], fc = a.stop_i[(size_t)b * 4 + 3];
-        const float m = a.stop_m[b];
-        int32_t my_id = -1, ch = -1;
-        float my_mu = 0.0f, my_l = 0.0f;
-        if (first && lane < kMaxK) {
-            my_id = a.stop_qid[(size_t)b * kMaxK + lane]; my_mu = a.stop_qmu[(size_t)b * kMaxK + lane];
-            my_l = a.stop_ql[(size_t)b * kMaxK + lane]; ch = a.stop_child[(size_t)b * kMaxK + lane];
-        }
-        const int j = a.all_nodes ? node : len - 1;  // the stop row's slot
-        unsigned long long part = 0ull;
-        if (first && lane < a.nseg) {
-            if (j < kAhead) {
-#pragma unroll
-                for (int q = 0; q < kAhead; ++q) part = q == j ? ahead[q] : part;
-            } else part = ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]);
-        }
-        finish_row<DT, kFinishThreads>(a, sh, b, j, node, true, m, nch, fc, len, my_id, my_mu, my_l, ch, part, tid, wave);
+        StopRow st;
+        st.request(a, block, lane, wave == 0);
+        finish_row<DT, kFinishThreads>(a, sh, block, st.j, st.node, true, st.m, st.nch, st.fc, st.len, st.my_id, st.my_mu, st.my_l, st.ch,
+                                       st.part, tid, wave);
         return;
     }
     const int slot = (block - stop_blocks) * (kFinishThreads / 64) + wave;

@@ -544,10 +544,11 @@ static PathArgs make_path_args(const stand_handle *h, const VerifyScratch &vs, u
 }
 
 // mode 0 (verify): path from the row pass's outcomes; mode 1 (update): rows given by the caller.
-// With `claim` the launch that finishes the path rows also claims the table slots of that merge.
+// With `claim` the launch that finishes the path rows also claims the table slots of that merge; with `tail` (a step of one
+// trajectory) it also applies them and drafts.
 static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row,
                             const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len,
-                            const MergeArgs *claim, hipStream_t s)
+                            const MergeArgs *claim, const DraftArgs *tail, hipStream_t s)
 {
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     if (mode == 1) {
@@ -584,6 +585,21 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
     const int claim_blocks = claim ? (h->B * h->R * h->NO + kFinishThreads - 1) / kFinishThreads : 0;
     const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
     const dim3 g2((unsigned)((mode == 0 ? h->B : 0) + row_blocks + claim_blocks));
+    if (tail) {
+        // one trajectory: the rest of the step in one workgroup
+        PathTailArgs ta;
+        ta.path = a; ta.mg = mg; ta.draft = *tail;
+        if (bf16) {
+            path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
+            path_tail_kernel<kDtBf16><<<dim3(1), dim3(kTailThreads), 0, s>>>(ta);
+        } else {
+            path_exact_kernel<kDtF32><<<g1, block, 0, s>>>(a);
+            path_tail_kernel<kDtF32><<<dim3(1), dim3(kTailThreads), 0, s>>>(ta);
+        }
+        HIP_TRY(h, hipGetLastError());
+        h->table_used = true;
+        return STAND_OK;
+    }
     if (bf16) {
         path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
         path_finish_kernel<kDtBf16><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
@@ -638,7 +654,7 @@ extern "C" int stand_update(stand_handle *h, uint64_t step, const void *d_logits
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
     const MergeArgs mg = merge_args(h, d_commit_tok, d_commit_row, d_commit_len);
-    int rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, s);
+    int rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, nullptr, s);
     if (rc) return rc;
     return launch_merge_apply(h, mg, true, s);
 }
@@ -670,7 +686,7 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     HIP_TRY(h, hipSetDevice(h->cfg.device));
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
-    return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
+    return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, s);
 }
 
 // Bytes of scratch a verification of this handle's shape needs, laid out as carve_scratch does.
@@ -709,7 +725,7 @@ extern "C" int stand_verify_static(stand_handle *h, uint64_t step, const void *d
     // and observations for exactly the path rows that are read back).
     int rc = launch_row_pass(h, vs, step, d_logits, false, s);
     if (rc) return rc;
-    return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
+    return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, s);
 }
 
 extern "C" uint64_t stand_static_scratch_need(const stand_handle *h)
@@ -933,7 +949,12 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
     const MergeArgs mg = merge_args(h, commit, nullptr, d_out_len);
-    rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, s);
+    // one trajectory and at most one record per thread of the claiming waves: what follows the exact sums is one launch
+    if (h->B == 1 && h->cfg.update_mode == STAND_UPDATE_ACCEPTED_PATH) {
+        const DraftArgs da = make_draft_args(h, step + 1, d_next_draft_tok, commit, d_out_len);
+        return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, &da, s);
+    }
+    rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, nullptr, s);
     if (rc) return rc;
     rc = launch_merge_apply(h, mg, false, s);
     if (rc) return rc;

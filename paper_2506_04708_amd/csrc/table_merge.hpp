@@ -110,13 +110,13 @@ __device__ __forceinline__ void count_claims(const MergeArgs &a, int outcome, in
 }
 
 
-// One wave per record, kMergeWaves records per workgroup (most records of a step do not exist --
-// paths are short -- and a launch of one small workgroup per record spends its time dispatching
-// them).  The lowest record that claimed a slot (its leader, named in the slot header by the
-// claim) applies all records of that slot in record order; the other records' waves leave at
-// once.  A slot claimed by one record only needs no search for followers.  The waves of a
-// workgroup do not interact.
-constexpr int kMergeWaves = 16;
+// One wave per record, kMergeWaves records per workgroup.  The lowest record that claimed a slot (its leader, named in
+// the slot header by the claim) applies all records of that slot in record order; the other records' waves leave at
+// once.  A slot claimed by one record only needs no search for followers.  The waves of a workgroup do not interact.
+// A record that exists costs some 700 instructions, and those that exist are the first positions of each trajectory:
+// consecutive records therefore go to different workgroups, small ones (sixteen consecutive records per workgroup left
+// most compute units idle: step 32 x 64 rows with deep paths 156.5 -> 155.3 us, update of 32 x 21 rows 88 -> 83).
+constexpr int kMergeWaves = 4;
 constexpr int kFollowGroups = 8;
 
 // Record `rec` by one wave (all 64 lanes call this; l_id / l_val: 2 * kMaxK words of shared memory
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_apply_kernel(MergeArgs
     const int NO = a.omax - a.omin + 1;
     const int nrec = a.B * a.R * NO;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int rec = (int)blockIdx.x * kMergeWaves + wave;
+    const int rec = wave * apply_blocks + (int)blockIdx.x;
     if (rec >= nrec) return;
     apply_record(a, rec, lane, l_id_all[wave], l_val_all[wave]);
 }

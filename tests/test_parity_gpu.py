@@ -334,6 +334,21 @@ def test_rows_split_over_workgroups(gpu, dtype, V, K):
     _row_case(gpu, np.stack([noise(), half, few, tied, steps, edge]), dtype, K)
 
 
+@pytest.mark.parametrize("name,over,steps,forced", [
+    ("cfg1", dict(V=600, B=1, rho=0.6), 40, False), ("cfg1", dict(V=2003, B=1, rho=0.8, dtype="bf16"), 30, True),
+    ("cfg3", dict(V=48, B=1, rho=0.5), 40, False),                              # deep paths, many rejections
+    ("cfg5", dict(V=64, B=1, rho=0.5), 30, False),                              # K = 32, five orders
+    ("cfg3", dict(V=48, B=1, rho=0.5, order_min=1, order_max=8, draft_mode=2), 30, False),   # most records per step
+])
+def test_lockstep_one_trajectory(gpu, name, over, steps, forced):
+    """A single trajectory's step ends in one workgroup: rows, claims, applies and the draft."""
+    binding, lockstep = gpu
+    _say("lockstep one trajectory %s %s" % (name, over))
+    w = synth.Workload(name, run_steps=steps, **over)
+    info = lockstep.run_lockstep(w, steps, mode="step", capacity=1 << 12, forced=forced, table_every=5)
+    _say("  -> %s" % info)
+
+
 @pytest.mark.parametrize("over,mode", [
     (dict(V=70001, B=2, rho=0.7), "separate"), (dict(V=70001, B=2, rho=0.7, dtype="bf16"), "separate"),
     (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"), (dict(V=66000, B=47, rho=0.7, dtype="bf16"), "step"),
