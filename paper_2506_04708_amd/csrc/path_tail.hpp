@@ -24,8 +24,7 @@ __global__ __launch_bounds__(kTailThreads) void path_tail_kernel(PathTailArgs A)
 {
     static_assert(kTailThreads == kFinishThreads && kTailThreads == kDraftThreads, "one workgroup runs all parts");
     __shared__ FinishShared fin;
-    __shared__ int32_t l_id[kTailThreads / 64][2 * kMaxK];
-    __shared__ float l_val[kTailThreads / 64][2 * kMaxK];
+    __shared__ __align__(16) unsigned long long scratch[kTailThreads / 64][2 * kMaxK];
     __shared__ __align__(16) char smem[(size_t)kMaxNodes * (kMaxOrder + 3) * 4 + kDraftSharedFixed];
     const PathArgs &a = A.path;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -51,7 +50,7 @@ __global__ __launch_bounds__(kTailThreads) void path_tail_kernel(PathTailArgs A)
     publish_fence();
     __syncthreads();
     consume_fence();
-    for (int i = wave; i < st.len * NO; i += kWaves) apply_record(A.mg, i, lane, l_id[wave], l_val[wave]);
+    for (int i = wave; i < st.len * NO; i += kWaves) apply_record(A.mg, i, lane, scratch[wave]);
     // every record is applied before the first lookup
     publish_fence();
     __syncthreads();

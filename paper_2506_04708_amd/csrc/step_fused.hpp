@@ -120,8 +120,7 @@ struct TailShared {
     float pm[kMaxDepth + 2];   // maximum of each of their rows
     int len, ok;
     FinishShared fin;
-    int32_t l_id[kStepWPR][2 * kMaxK];
-    float l_val[kStepWPR][2 * kMaxK];
+    alignas(16) unsigned long long scratch[kStepWPR][2 * kMaxK];
 };
 
 // All workgroups of one count arrive, then wait for the rest.  Called by the whole workgroup.
@@ -366,7 +365,7 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
     if (tid == 0) stamp(sy, b, 5);
     {
         const int NO = A.mg.omax - A.mg.omin + 1;
-        for (int i = wave; i < len * NO; i += kStepWPR) apply_record(A.mg, b * A.mg.R * NO + i, lane, ts->l_id[wave], ts->l_val[wave]);
+        for (int i = wave; i < len * NO; i += kStepWPR) apply_record(A.mg, b * A.mg.R * NO + i, lane, ts->scratch[wave]);
     }
     // ---- every trajectory's records applied, then the next draft
     tail_barrier(sy, 1, (unsigned)a.B, ts);

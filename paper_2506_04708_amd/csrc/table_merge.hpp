@@ -117,11 +117,13 @@ __device__ __forceinline__ void count_claims(const MergeArgs &a, int outcome, in
 // consecutive records therefore go to different workgroups, small ones (sixteen consecutive records per workgroup left
 // most compute units idle: step 32 x 64 rows with deep paths 156.5 -> 155.3 us, update of 32 x 21 rows 88 -> 83).
 constexpr int kMergeWaves = 4;
-constexpr int kFollowGroups = 8;
+constexpr int kFollowGroups = 16;
 
-// Record `rec` by one wave (all 64 lanes call this; l_id / l_val: 2 * kMaxK words of shared memory
-// owned by the wave).  Does nothing unless the record exists and leads its slot.
-__device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, int32_t *l_id, float *l_val)
+// Record `rec` by one wave (all 64 lanes call this; scratch: 2 * kMaxK words of shared memory, 16-byte aligned, owned by
+// the wave).  Does nothing unless the record exists and leads its slot.
+// Folding one observation into an entry was 2 600 (K = 10) to 6 700 cycles (K = 32) of readlanes; with ids and keys read
+// from shared memory, four and two per access, K compares and 2 K 64-bit compares remain.
+__device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, unsigned long long *scratch)
 {
     const int NO = a.omax - a.omin + 1;
     const int nrec = a.B * a.R * NO;
@@ -158,37 +160,38 @@ __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int la
         } else {
             const float cf = (float)count;
             const float denom = cf + 1.0f;
-            int32_t id = lane < 32 ? e_id : o_id;
-            bool act = lane < 32 ? (lane < K) : (lane < 32 + K);
-            float other = 0.0f;  // for stored lanes: the observation's value for the same id
-            bool dup = false;    // for observation lanes: id already stored
-            for (int q = 0; q < K; ++q) {
-                const int32_t sid = __builtin_amdgcn_readlane(e_id, q);
-                const int32_t oid = __builtin_amdgcn_readlane(o_id, 32 + q);
-                const float op = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(o_p), 32 + q));
-                if (lane < 32 && act && oid == id) other = op;
-                if (lane >= 32 && act && sid == id) dup = true;
+            const int32_t id = lane < 32 ? e_id : o_id;
+            bool act = (lane & 31) < K;
+            // where the other list (stored ids: lanes 0.., observed ids: lanes 32..) holds this id; ids are distinct
+            int32_t *ids_l = (int32_t *)scratch;
+            ids_l[lane] = act ? id : (lane < 32 ? -1 : -2);
+            __builtin_amdgcn_wave_barrier();
+            const int4 *others = (const int4 *)(ids_l + (lane < 32 ? 32 : 0));
+            int at = -1;
+            for (int q = 0; q < K; q += 4) {
+                const int4 v = others[q >> 2];
+                if (v.x == id) at = q;
+                if (v.y == id) at = q + 1;
+                if (v.z == id) at = q + 2;
+                if (v.w == id) at = q + 3;
             }
+            const float o_at = __shfl(o_p, 32 + (at & 31));
             float val;
-            if (lane < 32) { float t = cf * e_mu; t = t + other; val = t / denom; }
-            else { float t = cf * 0.0f; t = t + o_p; val = t / denom; act = act && !dup; }
+            if (lane < 32) { float t = cf * e_mu; t = t + (at >= 0 ? o_at : 0.0f); val = t / denom; }
+            else { float t = cf * 0.0f; t = t + o_p; val = t / denom; act = act && at < 0; }
             const unsigned long long key = act ? rank_key(val, (uint32_t)id) : 0ull;
+            __builtin_amdgcn_wave_barrier();
+            scratch[lane] = key;   // (lanes without an entry hold key 0, which is above no key)
+            __builtin_amdgcn_wave_barrier();
             int rank = 0;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                rank += readlane_u64(key, q) > key ? 1 : 0;
-                rank += readlane_u64(key, 32 + q) > key ? 1 : 0;
+            for (int q = 0; q < K; q += 2) {
+                const ulonglong2 k0 = *(const ulonglong2 *)&scratch[q], k1 = *(const ulonglong2 *)&scratch[32 + q];
+                rank += (k0.x > key ? 1 : 0) + (k0.y > key ? 1 : 0) + (k1.x > key ? 1 : 0) + (k1.y > key ? 1 : 0);
             }
-            if (K > 16) {  // the other lanes are inactive (key 0) for K <= 16
-#pragma unroll
-                for (int q = 16; q < 32; ++q) {
-                    rank += readlane_u64(key, q) > key ? 1 : 0;
-                    rank += readlane_u64(key, 32 + q) > key ? 1 : 0;
-                }
-            }
-            if (act && rank < K) { l_id[rank] = id; l_val[rank] = val; }
+            __builtin_amdgcn_wave_barrier();
+            if (act && rank < K) scratch[rank] = ((unsigned long long)f2u(val) << 32) | (uint32_t)id;
             __builtin_amdgcn_wave_barrier();  // the wave's own part of shared memory: no other wave is involved
-            if (lane < K) { e_id = l_id[lane]; e_mu = l_val[lane]; }
+            if (lane < K) { e_id = (int32_t)(uint32_t)scratch[lane]; e_mu = u2f((uint32_t)(scratch[lane] >> 32)); }
             __builtin_amdgcn_wave_barrier();
         }
         count++;
@@ -244,8 +247,7 @@ __device__ __forceinline__ void append_context(const MergeArgs &a, int b, int32_
 // the contexts (stand_update; the claims, which read the contexts as they were, are in an earlier launch).
 __global__ __launch_bounds__(64 * kMergeWaves) void merge_apply_kernel(MergeArgs a, int apply_blocks, int32_t *ctx_tail, long long *ctx_len)
 {
-    __shared__ int32_t l_id_all[kMergeWaves][2 * kMaxK];
-    __shared__ float l_val_all[kMergeWaves][2 * kMaxK];
+    __shared__ __align__(16) unsigned long long scratch[kMergeWaves][2 * kMaxK];
     if ((int)blockIdx.x >= apply_blocks) {
         const int b = ((int)blockIdx.x - apply_blocks) * 64 * kMergeWaves + (int)threadIdx.x;
         if (b < a.B) append_context(a, b, ctx_tail, ctx_len);
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_apply_kernel(MergeArgs
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int rec = wave * apply_blocks + (int)blockIdx.x;
     if (rec >= nrec) return;
-    apply_record(a, rec, lane, l_id_all[wave], l_val_all[wave]);
+    apply_record(a, rec, lane, scratch[wave]);
 }
 
 }  // namespace stand
