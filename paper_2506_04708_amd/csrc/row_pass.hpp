@@ -560,8 +560,14 @@ struct NodeProposal {
     __device__ __forceinline__ void request_logits(const RowPassArgs &a, int b, const void *rowp, int lane)
     {
         if (nch == 0) return;  // uniform over the wave
-        if ((uint32_t)my_id >= (uint32_t)a.V) { my_id = -1; my_mu = 0.0f; }  // never index outside the row
-        else my_l = load_scalar<DT>(rowp, my_id);
+        // (members are written on one path each: stores to different ones on two paths kept the record in scratch memory
+        // with fp32 logits, and the row pass of 8000 rows took 291 instead of 264 us)
+        const bool inside = (uint32_t)my_id < (uint32_t)a.V;  // never index outside the row
+        float l = 0.0f;
+        if (inside) l = load_scalar<DT>(rowp, my_id);
+        my_l = l;
+        my_id = inside ? my_id : -1;
+        my_mu = inside ? my_mu : 0.0f;
         if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
         tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
     }
