@@ -71,6 +71,7 @@ extern "C" {
 #define STAND_STEP_AUTO 0   /* one launch where it pays (769 .. 8192 rows, accepted-path updates, accepted paths */
                             /* that seldom reach below upper_depth: watched while running), else serial        */
 #define STAND_STEP_SERIAL 1 /* five dependent launches: rows, exact sums, finish + claims, apply, draft           */
+                            /* (three with one trajectory: the last three are one)                               */
 #define STAND_STEP_FUSED 2  /* one launch: the dependent tail runs beside the rows that are still streaming      */
 
 #define STAND_MAX_TOPK 32
@@ -211,7 +212,7 @@ int stand_step(stand_handle *h, uint64_t step, const void *d_logits, int32_t *d_
  *                and takes the serial launches while more than 0.4 paths per step reach below
  *                upper_depth (they would wait for rows that stream late), the one launch again below
  *                0.25; no such copy is made while the stream is being captured, or in the other modes.
- *                While the stream is being captured (HIP graphs) stand_step always issues the five
+ *                While the stream is being captured (HIP graphs) stand_step always issues the serial
  *                launches: the one launch carries its own number as an argument and cannot be replayed.
  *   upper_depth  FUSED: the rows of tree nodes up to this depth take the first places in the launch
  *                (default 2: paths that end above depth 3 never wait for a late row; deeper paths are
@@ -227,7 +228,7 @@ int stand_step(stand_handle *h, uint64_t step, const void *d_logits, int32_t *d_
 int stand_set_step_plan(stand_handle *h, int32_t mode, int32_t upper_depth, int32_t tail_groups, int32_t rows_first,
                         uint32_t shuffle);
 
-/* 1 if stand_step on this handle is currently issued as one launch, 0 if as five (see stand_set_step_plan). */
+/* 1 if stand_step on this handle is currently issued as one launch, 0 if as several (see stand_set_step_plan). */
 int stand_step_is_one_launch(const stand_handle *h);
 
 /* Bound, in microseconds, of every wait inside the one-launch step (default 200 000).  A wait that runs

@@ -4,15 +4,18 @@
 //   row_pass.hpp     row_pass_kernel     softmax statistics + top-K of every logits row in one streaming
 //                                        pass, and the accept/reject outcome of the row's tree node
 //                                                                              (paper Sec. 4.1, 3.2)
+//   row_parts.hpp    row_parts_kernel    the same for few rows, and for the rows of an update: every row split over
+//                                        workgroups that hold their part in registers
 //   path_pass.hpp    path_exact_kernel   exact integer partial sums of the rows on the accepted path;
 //                                        walks the path and gathers the stop node's proposal (Sec. 3.2)
 //                    path_finish_kernel  observation of each path row with the exact normaliser, replay
 //                                        of the stop node, resampled token by inverting the residual's
 //                                        cumulative integer mass; claims the table slots of the merge
 //                                                                              (paper Sec. 3.2, 4.1)
-//                    commit_scan_kernel  top-K of caller-given rows (update without verify)
+//                    commit_scan_kernel  top-K of caller-given rows (update without verify), many rows
 //   table_merge.hpp  merge_apply_kernel  running-mean merge into the open-addressing table (Sec. 4.1)
 //   draft.hpp        draft_kernel        multi-level lookup + Gumbel-Top-K along the static tree (Sec. 4.2)
+//   path_tail.hpp    path_tail_kernel    one trajectory: everything after the exact sums in one workgroup
 //   step_fused.hpp   stand_step_kernel   the whole step in one launch: rows of the tree's upper levels, then
 //                                        the dependent tail beside the remaining rows (bounded waits on
 //                                        device-scope counters)
@@ -23,8 +26,8 @@
 // the 5e-5 bound assumed here); every accept test whose margin is inside that bound, and
 // every probability that is stored in the table or used for resampling, is recomputed with
 // the exact integer normaliser of numeric.hpp, so all decisions are those of exact arithmetic.
-// The kernels after the row pass are chains of dependent memory round trips over little data;
-// their workgroups exchange data only across kernel boundaries.  stand_step_kernel runs the same
+// The kernels after the row pass are chains of dependent instructions and round trips over little data;
+// their workgroups exchange data only across kernel boundaries (row_parts_kernel: through a counter per row).  stand_step_kernel runs the same
 // device functions in one launch and orders them with counters instead.
 #pragma once
 #include "numeric.hpp"

@@ -12,11 +12,10 @@ namespace stand {
 // observation is stored in the table), for the last one also the resampled token.
 //   path_exact_kernel   block (seg, j, b): exact partial sum of a segment of path row j, stored in
 //                       seg_part; the segments spread a handful of rows over all compute units
-//   path_finish_kernel  block (j, b): adds the partial sums, writes the observation of the row;
-//                       at the stop row it replays the node with exact probabilities and draws the
-//                       resampled token by inverting the residual's cumulative integer mass.
-//                       Further blocks of the same launch claim the table slots of the merge,
-//                       which depends on the tokens of the path only.
+//   path_finish_kernel  adds the partial sums of a row and writes its observation: a block per stop row (which also
+//                       replays the node with exact probabilities and draws the resampled token by inverting
+//                       the residual's cumulative integer mass), a wave per other row.  Further blocks of the
+//                       same launch claim the table slots of the merge, which depends on the path's tokens only.
 // Kernel boundaries are the only synchronisation between blocks.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSegMax = 32;  // most segments per path row
