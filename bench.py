@@ -501,7 +501,7 @@ def main():
                    "draft_mode": ["gumbel_topk", "multinomial", "deterministic"][args.draft_mode],
                    "update_mode": ["accepted_path", "all_nodes"][args.update_mode],
                    "merge_policy": ["running_mean", "replace"][args.merge_policy], "peak": args.peak, "max_peaks": args.max_peaks,
-                   "step_issue": "one launch" if m["fused"] else "five launches",
+                   "step_issue": "one launch" if m["fused"] else ("three launches" if w.B == 1 else "five launches"),
                    "acceptance_len": round(m["acc_len"], 3), "table_entries": int(m["entries"]),
                    "table_load_factor": round(m["load"], 4)},
         "hbm_gbps_algorithmic": round(m["step_bytes"] * m["steps_per_s"] / 1e9, 1),
