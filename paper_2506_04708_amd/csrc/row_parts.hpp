@@ -154,7 +154,8 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     // (see wave_row_stream).
     const bool none = wm == -__builtin_inff();         // (no vector, or masked throughout: adds nothing)
     const float m_ref = none ? 0.0f : wm;
-    const float nb = -m_ref * r.c, dlt = __builtin_fmaf(-m_ref, r.c, -nb);
+    float dlt;
+    const float nb = fast_offset(m_ref, r.c, dlt);
     float s_t = edge_id >= 0 ? fast_exp2(__builtin_fmaf(edge_val, r.c, nb)) : 0.0f;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
@@ -329,6 +330,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         rank_against(sm.list, sm.rank, n, n * who / (kPartWaves - 1), n * (who + 1) / (kPartWaves - 1), lane);
     }
     __syncthreads();
+    if (!a.commit && fast_sum_void(m, r.c)) ps = wave_row_plain_sum<DT>(rowp, r.V, m, r.c, lane);
     const size_t o = (size_t)(a.commit ? b * a.R + j : row) * r.K;
     for (int i = tid; i < n; i += kPartThreads) {
         const int at = sm.rank[i];

@@ -233,6 +233,21 @@ __device__ __forceinline__ void wave_offer(WaveScan *ws, WaveScanState &st, int 
         wave_prune_fast<true, false, LOWBIT>(ws, st, lane, K, (uint32_t)(st.theta_key >> 32), order_key(seen_max));
 }
 
+// The exponent of a term of the fast normaliser is fma(l, c, nb), nb = -m c for the reference maximum m.  Logits near the
+// ends of the type's range (vocabularies masked with its lowest value) would make nb infinite and the sum a NaN, so nb is
+// kept within kFastExponentMax: beside an ordinary maximum such a term is 0 all the same.  A row whose own maximum lies out
+// there (fast_sum_void) has no fast normaliser: see wave_row_plain_sum.
+// `dlt` is what the rounding of nb adds to every exponent, see wave_row_stream.
+constexpr float kFastExponentMax = 1e37f;
+__device__ __forceinline__ bool fast_sum_void(float m, float c) { return !(fabsf(m * c) <= kFastExponentMax); }
+__device__ __forceinline__ float fast_offset(float m, float c, float &dlt)
+{
+    const float nb = -m * c;
+    const bool in = fabsf(nb) <= kFastExponentMax;
+    dlt = in ? __builtin_fmaf(-m, c, -nb) : 0.0f;
+    return in ? nb : __builtin_copysignf(kFastExponentMax, nb);
+}
+
 // Leaves the row's K best element keys (value desc, id asc) sorted in ws->top[0..K), returns
 // the row maximum and the fast normaliser sum_v 2^((l_v - m) c).
 //
@@ -274,8 +289,8 @@ __device__ __forceinline__ WavePartial wave_row_stream(const void *rowp, int V, 
     auto raise_reference = [&](float cm) {
         // some lane saw a value above the reference: move the reference to the wave's maximum
         const float nm = uniform_f32(fmaxf(wave_max_f32(cm), m_ref));
-        const float nb_new = -nm * c;
-        const float dlt_new = __builtin_fmaf(-nm, c, -nb_new);
+        float dlt_new;
+        const float nb_new = fast_offset(nm, c, dlt_new);
         s_t *= fast_exp2((m_ref - nm) * c + (dlt - dlt_new));
         m_ref = nm;
         nb = nb_new;
@@ -519,6 +534,19 @@ __device__ unsigned long long wave_row_exact_sum(const void *rowp, int V, float 
     return S;
 }
 
+// Normaliser of a row by one wave, for the results of rows without a fast one (fast_sum_void: logits near the ends of
+// the type's range only).  A loop of few instructions, since it stands in every row kernel and practically never runs.
+template <int DT>
+__device__ __forceinline__ float wave_row_plain_sum(const void *rowp, int V, float m, float c, int lane)
+{
+    double s = 0.0;
+#pragma unroll 2
+    for (int v = lane; v < V; v += 64) s += (double)exact_exp2(scaled_offset(load_scalar<DT>(rowp, v), m, c));
+#pragma unroll 1
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    return (float)s;
+}
+
 struct RowPassArgs {
     const void *logits;
     int B, N, V, K;
@@ -585,6 +613,8 @@ struct NodeProposal {
         // rounding of each term's own argument, relative to that argument, and of the waves' combination)
         // is covered by a term in |m| c that stays far below a.eps for ordinary inputs.
         const float eps_row = a.eps + 1e-9f * fabsf(m) * a.c;
+        // (without a fast normaliser eps_row exceeds every probability: whatever s is, the tests are left to the exact one)
+        if (fast_sum_void(m, a.c)) s = 1.0f;
         NodeResult nr = wave_node_outcome(lane, a.K, tests, e / s, nch, true, eps_row, a.onehot);
         if (nr.near) {
             // a test fell inside the error bound of the fast normaliser: decide with the exact one
@@ -673,6 +703,7 @@ __device__ __forceinline__ void row_role(const RowPassArgs &a, int row, RowShare
     const int cnt = gather_wave_records<DT, WPR>(sm, lane, a.K);
     wave_row_finish<DT>(rowp, a.V, a.K, ws, sm->ebuf, lane, cnt);
 
+    if (fast_sum_void(m, a.c)) s = wave_row_plain_sum<DT>(rowp, a.V, m, a.c, lane);
     if (lane < a.K) {
         const unsigned long long key = ws->top[lane];
         const float l = rank_key_value(key);

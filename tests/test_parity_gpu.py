@@ -259,18 +259,19 @@ def test_lockstep_cfg1_full(gpu):
 
 
 # ---- row pass on crafted rows ----------------------------------------------------------------------
-def _row_case(gpu, rows_f32, dtype, K, T=0.6):
+def _row_case(gpu, rows_f32, dtype, K, T=0.6, parent=None, check=None):
     binding, lockstep = gpu
     R, V = rows_f32.shape
     lg = rows_f32 if dtype == "f32" else synth.f32_to_bf16_bits(rows_f32)
-    parent = np.array([-1] + [0] * (R - 1), np.int32) if R > 1 else np.array([-1], np.int32)
+    if parent is None:
+        parent = np.array([-1] + [0] * (R - 1), np.int32) if R > 1 else np.array([-1], np.int32)
     g = binding.Stand(V, 1, 1, 2, K, parent, T, 1 << 10, 16, 5, binding.STAND_F32 if dtype == "f32" else binding.STAND_BF16)
     out_tok, out_node, out_len, d = g.new_outputs()
     dl = lockstep._logits_to_device(lg.reshape(1, R, V), dtype)
     g.verify(0, dl, out_tok, out_node, out_len)
     torch.cuda.synchronize()
     m, s, idx, p = (t.cpu().numpy() for t in g.row_results())
-    for r in range(R):
+    for r in range(R) if check is None else check:
         oi, op, om, os_ = oracle.row_obs(lg[r], T, K)
         assert np.array_equal(idx[r], oi), (r, idx[r], oi)
         assert m[r] == om
@@ -332,6 +333,63 @@ def test_rows_split_over_workgroups(gpu, dtype, V, K):
     edge[[0, 1, V - 2, V - 1]] += 12
     _say("rows split %s V=%d K=%d" % (dtype, V, K))
     _row_case(gpu, np.stack([noise(), half, few, tied, steps, edge]), dtype, K)
+
+
+def _lowest(dtype):
+    return float(torch.finfo(torch.float32 if dtype == "f32" else torch.bfloat16).min)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("many_rows", [False, True])
+def test_rows_masked_with_the_lowest_value(gpu, dtype, many_rows):
+    """Vocabularies masked with the type's lowest value instead of -inf, and logits near the ends of the type's range:
+    the exponent of such a term leaves binary32 (lowest * log2(e) / T), the row's normaliser must not.  Few rows (split
+    over workgroups) and many (four waves per row)."""
+    low = _lowest(dtype)
+    V, K = 9003, 16
+    r = np.random.default_rng(11)
+    noise = lambda: (r.standard_normal(V) * 1.7).astype(np.float32)  # noqa: E731
+    rows = [noise() for _ in range(6)]
+    rows[0][: V // 2] = low                       # whole waves masked, the row starts with them
+    rows[1][V // 3:] = low
+    rows[2][:] = low                              # everything masked: all tokens alike
+    rows[3][:] = low
+    rows[3][[5, V - 1]] = 0.5                     # two tokens left
+    rows[4] = np.where(r.random(V) < 0.9, low, rows[4]).astype(np.float32)
+    rows[5] = (rows[5] * 1e37).astype(np.float32)  # finite, far apart
+    rows = np.stack(rows)
+    parent = None
+    if many_rows:                                 # 1 + 16 + 256 + 257 nodes, no node with more than K children
+        parent = np.array([-1] + [(u - 1) // K for u in range(1, 530)], np.int32)
+        rows = np.tile(rows, (89, 1))[:530]
+    _say("rows masked with the lowest value %s, %d rows" % (dtype, len(rows)))
+    _row_case(gpu, rows, dtype, K, parent=parent, check=range(6))
+
+
+@pytest.mark.parametrize("name,over", [
+    ("cfg1", dict(V=3001, B=2, rho=0.6)), ("cfg1", dict(V=3001, B=2, rho=0.6, dtype="bf16")),          # split rows
+    ("cfg3", dict(V=1500, B=13, rho=0.6, step_plan=(1, 2, 0, 0))),                                      # four waves per row
+    ("cfg3", dict(V=1500, B=13, rho=0.6, dtype="f32", step_plan=(FUSED, 2, 0, 0))),                     # one launch
+])
+def test_lockstep_masked_with_the_lowest_value(gpu, name, over):
+    """The same inside whole steps: the accept tests of such rows are those of exact arithmetic."""
+    binding, lockstep = gpu
+    w = synth.Workload(name, run_steps=16, **over)
+    low, plain = _lowest(w.dtype), w.logits
+
+    def masked(step, draft):
+        lg = plain(step, draft)
+        x = lg if w.dtype == "f32" else synth.bf16_bits_to_f32(lg)
+        x = x.reshape(w.B * w.N, w.V).copy()
+        x[::2, w.V // 2:] = low
+        x[3::7] = low
+        x = x.reshape(w.B, w.N, w.V)
+        return x if w.dtype == "f32" else synth.f32_to_bf16_bits(x)
+    w.logits = masked
+    _say("lockstep masked with the lowest value %s %s" % (name, over))
+    info = lockstep.run_lockstep(w, 16, mode="step", capacity=1 << 14, forced=False)
+    _say("  -> %s" % {k: v for k, v in info.items() if k != "node_counts"})
+    assert info["emitted"] > 16 * w.B
 
 
 @pytest.mark.parametrize("name,over,steps,forced", [
