@@ -101,18 +101,6 @@ __device__ __forceinline__ int commit_row_of(const PathArgs &a, int b, int j)
     return (node < 0 || node >= a.N) ? -1 : node;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave, by data-parallel-primitive moves inside
-// rows of 16 lanes and two row broadcasts (no LDS traffic).
-__device__ __forceinline__ unsigned long long wave_inclusive_scan_u64(unsigned long long x)
-{
-    x += dpp_fetch_u64<0x111, 0xF>(x);  // row_shr:1
-    x += dpp_fetch_u64<0x112, 0xF>(x);  // row_shr:2
-    x += dpp_fetch_u64<0x114, 0xF>(x);  // row_shr:4
-    x += dpp_fetch_u64<0x118, 0xF>(x);  // row_shr:8
-    x += dpp_fetch_u64<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
-    x += dpp_fetch_u64<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
-    return x;
-}
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x)
 {
     return readlane_u64(wave_inclusive_scan_u64(x), 63);

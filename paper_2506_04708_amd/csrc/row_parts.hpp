@@ -17,8 +17,12 @@ namespace stand {
 //   - nothing is read twice.
 // The last workgroup of a row to finish (a counter that its last user sets back to zero, so a recorded launch can be
 // replayed) merges the parts: the largest of the parts' bounds cuts the candidates again, one wave ranks them exactly
-// while another runs the node's accept tests.  A part in which more than kPartList elements reach the bound (equal
-// or masked logits) takes the streaming scan of row_pass.hpp instead.
+// while another runs the node's accept tests.
+// Masked vocabularies (-inf, or the type's lowest value) and quantised logits make whole parts equal to their own bound.
+// Where more than kPartTies lanes of a wave are at or above the bound, the part collects all that exceeds it, but of what
+// equals it each wave takes only the lowest ids, as many as can be among the K best (it meets its elements in id order):
+// row pass over 256 rows of 257 KB whose upper half is masked 27 us, without a mask 19; with the streaming scan for
+// all such parts, which orders every tie, 154.  Only more than kPartList elements above the bound are still left to the scan of row_pass.hpp.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
 constexpr int kPartVectors = 8;                      // most vectors per lane
@@ -26,6 +30,8 @@ constexpr int kPartsMax = 32;                        // most parts of a row
 constexpr int kTicketStride = 32;                    // words between two rows' counters: a cache line each
 constexpr int kPartKeys = 64;                        // candidate keys a part hands over
 constexpr int kPartList = kPartsMax * kPartKeys;     // candidates collected in shared memory
+constexpr int kPartTies = 32;                        // more lanes of a wave than this at or above the bound: most elements there equal it
+constexpr int kPartTied = 1 << 20;                   // added to the count of candidates by such a wave
 
 struct PartHead { float m, s, theta; int cnt; };     // maximum, fast sum relative to it, bound, candidates of a part
 
@@ -122,11 +128,15 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         else load_part<0>(w, rsrc, tid);
     }
     // elements of the row before its first and after its last aligned vector: one per lane of the first wave
-    int edge_id = -1;
-    if (wave == 0) {
-        if (part == 0 && lane < g.head) edge_id = lane;
-        if (part == a.P - 1 && lane >= 32 && lane - 32 < g.ntail) edge_id = g.tail0 + lane - 32;
-    }
+    auto edge_of_lane = [&]() {
+        int id = -1;
+        if (wave == 0) {
+            if (part == 0 && lane < g.head) id = lane;
+            if (part == a.P - 1 && lane >= 32 && lane - 32 < g.ntail) id = g.tail0 + lane - 32;
+        }
+        return id;
+    };
+    const int edge_id = edge_of_lane();
     const float edge_val = edge_id >= 0 ? load_scalar<DT>(rowp, edge_id) : -__builtin_inff();
     // the node's proposal, for the wave that runs the accept tests if this workgroup is the row's last
     NodeProposal prop;
@@ -174,8 +184,6 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     if (wave == 0) { sm.above[lane] = 0; if (lane == 0) { sm.n = 0; sm.n_row = 0; } }
     __syncthreads();
 
-    if (wave == 1 && !a.commit) prop.template request_logits<DT>(r, b, rowp, lane);
-
     // ---- K-th largest of the 64 bins: every wave compares all bins with eight of them
     const float my_bin = sm.bins[lane];
     {
@@ -199,6 +207,26 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     unsigned mask = 0u;
 #pragma unroll
     for (int q = 0; q < R; ++q) mask |= (v0 + q * kPartThreads + tid < v1 && cm[q] >= theta) ? 1u << q : 0u;
+    // `which` elements of the lane's vector q, ws, join the list
+    auto collect = [&](const uint4 &ws, int q, unsigned which) {
+        float x[EPV];
+        unpack<DT>(ws, x);
+        int at = atomicAdd(&sm.n, __popc(which));
+        const int id0 = g.head + (v0 + q * kPartThreads + tid) * EPV;
+        while (which) {
+            const int k = __ffs((int)which) - 1;
+            which &= which - 1u;
+            float xv = x[0];
+#pragma unroll
+            for (int e = 1; e < EPV; ++e) xv = k == e ? x[e] : xv;
+            if (at < kPartList) sm.list[at] = rank_key(xv, (uint32_t)(id0 + k));
+            ++at;
+        }
+    };
+    if (__popcll(__ballot(mask != 0u)) > kPartTies) {
+        if (lane == 0) atomicAdd(&sm.n, kPartTied);
+        mask = 0u;
+    }
     while (__ballot(mask != 0u)) {
         uint4 ws = w[0];
         int q = 0;
@@ -211,17 +239,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
             unsigned in = 0u;
 #pragma unroll
             for (int k = 0; k < EPV; ++k) in |= x[k] >= theta ? 1u << k : 0u;
-            int at = atomicAdd(&sm.n, __popc(in));
-            const int id0 = g.head + (v0 + q * kPartThreads + tid) * EPV;
-            while (in) {
-                const int k = __ffs((int)in) - 1;
-                in &= in - 1u;
-                float xv = x[0];
-#pragma unroll
-                for (int e = 1; e < EPV; ++e) xv = k == e ? x[e] : xv;
-                if (at < kPartList) sm.list[at] = rank_key(xv, (uint32_t)(id0 + k));
-                ++at;
-            }
+            collect(ws, q, in);
             mask &= mask - 1u;
         }
     }
@@ -231,8 +249,63 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     }
     __syncthreads();
     int n = sm.n;
-    if (n > kPartList) {
-        // too many equal elements: the streaming scan over this part (edges included) finds its K best
+    if (__builtin_expect(n >= kPartTied, 0)) {
+        // again, without most of what equals the bound (the part is fetched a second time: kept until here it would cost
+        // the registers of a fourth workgroup per compute unit)
+        __syncthreads();  // every wave has seen n
+        if (tid == 0) sm.n = 0;
+        __syncthreads();
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(g.vp + v0), (short)0, (v1 - v0) * 16, 0x00020000);
+        uint4 next[1];
+        load_part<0>(next, rsrc, tid);
+        int left = r.K;   // elements equal to the bound that the wave may still take
+#pragma unroll 1
+        for (int q = 0; q < R; ++q) {
+            const uint4 ws = next[0];
+            load_part<0>(next, rsrc, (q + 1) * kPartThreads + tid);
+            unsigned in = 0u, equal = 0u;
+            if (v0 + q * kPartThreads + tid < v1) {
+                float x[EPV];
+                unpack<DT>(ws, x);
+#pragma unroll
+                for (int k = 0; k < EPV; ++k) {
+                    in |= x[k] > theta ? 1u << k : 0u;
+                    equal |= x[k] == theta ? 1u << k : 0u;
+                }
+            }
+            if (q == 0 || (left > 0 && __ballot(equal != 0u))) {
+                const int c = __popc(equal), upto = (int)wave_inclusive_scan_u64((unsigned long long)c);
+                const int total = __builtin_amdgcn_readlane(upto, 63);
+                int all = total;
+                if (q == 0) {
+                    // the waves' first vectors follow each other in the row, and all others follow them
+                    if (lane == 0) sm.rank[wave] = total;
+                    __syncthreads();
+                    all = 0;
+                    for (int o = 0; o < kPartWaves; ++o) {
+                        left -= o < wave ? sm.rank[o] : 0;
+                        all += sm.rank[o];
+                    }
+                }
+                const int keep = left - (upto - c);   // what the lower lanes leave
+                for (int d = c; d > keep && d > 0; --d) equal &= ~(0x80000000u >> __clz((int)equal));
+                in |= equal;
+                left = (q == 0 ? r.K : left) - all;
+            }
+            if (in) collect(ws, q, in);
+        }
+        const int id = edge_of_lane();   // (again: registers, as above)
+        const float val = id >= 0 ? load_scalar<DT>(rowp, id) : -__builtin_inff();
+        if (id >= 0 && val >= theta) {
+            const int at = atomicAdd(&sm.n, 1);
+            if (at < kPartList) sm.list[at] = rank_key(val, (uint32_t)id);
+        }
+        __syncthreads();
+        n = sm.n;
+    }
+    if (__builtin_expect(n > kPartList, 0)) {
+        // too many above the bound: the streaming scan over this part (edges included) finds its K best
         __syncthreads();  // every wave has seen n
         const int base = part == 0 ? 0 : g.head + v0 * EPV;
         const int end = part == a.P - 1 ? r.V : g.head + v1 * EPV;
@@ -250,6 +323,11 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         }
         n = r.K;   // more than kPartList elements: the part has K
         __syncthreads();
+    }
+    // (here and not where their data arrive: the part's registers are free, and the other waves are handing over)
+    if (wave == 1 && !a.commit) {
+        prop.template request_logits<DT>(r, b, rowp, lane);
+        prop.prepare(r, b, lane);
     }
     if (a.P > 1) {
         if (n > kPartKeys) {

@@ -597,7 +597,11 @@ struct NodeProposal {
         my_id = inside ? my_id : -1;
         my_mu = inside ? my_mu : 0.0f;
         if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
-        tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+    }
+    // what the tests need besides the row's maximum and normaliser
+    __device__ __forceinline__ void prepare(const RowPassArgs &a, int b, int lane)
+    {
+        if (nch > 0) tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
     }
     // accept / reject outcome of the node's children (paper Sec. 3.2, applied recursively)
     template <int DT>
@@ -695,6 +699,7 @@ __device__ __forceinline__ void row_role(const RowPassArgs &a, int row, RowShare
     if (wave == kTestWave) {
         // the accept tests need the row's maximum and normaliser, not its ranking
         prop.request_logits<DT>(a, b, rowp, lane);
+        prop.prepare(a, b, lane);
         const int oc = prop.outcome<DT>(a, b, row, rowp, lane, m, s);
         if (pub.row && lane == 0) st_agent(&pub.row[row], pack_row_pub(m, oc, pub.tag));
         return;

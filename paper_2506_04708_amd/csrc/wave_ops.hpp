@@ -196,6 +196,19 @@ __device__ __forceinline__ unsigned long long dpp_fetch_u64(unsigned long long x
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave, by data-parallel-primitive moves inside
+// rows of 16 lanes and two row broadcasts (no LDS traffic).
+__device__ __forceinline__ unsigned long long wave_inclusive_scan_u64(unsigned long long x)
+{
+    x += dpp_fetch_u64<0x111, 0xF>(x);  // row_shr:1
+    x += dpp_fetch_u64<0x112, 0xF>(x);  // row_shr:2
+    x += dpp_fetch_u64<0x114, 0xF>(x);  // row_shr:4
+    x += dpp_fetch_u64<0x118, 0xF>(x);  // row_shr:8
+    x += dpp_fetch_u64<0x142, 0xA>(x);  // row_bcast:15 into rows 1 and 3
+    x += dpp_fetch_u64<0x143, 0xC>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
 struct NodeResult { int accepted; int rounds; bool near; float r; float rho; };
 
 // What the accept tests of a node need besides the row's probabilities: formed while those are on their way.

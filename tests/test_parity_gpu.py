@@ -392,6 +392,54 @@ def test_lockstep_masked_with_the_lowest_value(gpu, name, over):
     assert info["emitted"] > 16 * w.B
 
 
+# 256 rows: parts as large as the registers hold (vectors per lane in brackets)
+@pytest.mark.parametrize("dtype,V,K", [
+    ("bf16", 32768, 16), ("bf16", 40001, 32), ("bf16", 16000, 10), ("bf16", 131071, 7), ("bf16", 4099, 32),    # 8, 6, 4, 8, 2
+    ("f32", 16384, 32), ("f32", 12001, 10), ("f32", 50003, 16),                                                # 8, 6, 8
+])
+def test_rows_of_equal_logits_split_over_workgroups(gpu, dtype, V, K):
+    """Parts in which hundreds of elements equal the part's own bound: of those each wave hands over its lowest ids only."""
+    r = np.random.default_rng(V)
+    f32 = np.float32
+    rows = [np.zeros(V, f32), np.full(V, -np.inf, f32), r.integers(0, 2, V).astype(f32), np.round(r.standard_normal(V)).astype(f32),
+            np.full(V, _lowest(dtype), f32), (np.arange(V) // (V // 5)).astype(f32), np.repeat(r.standard_normal(V // 64 + 1), 64)[:V].astype(f32),
+            np.where(np.arange(V) % 1000 < 997, -np.inf, r.standard_normal(V)).astype(f32)]
+    rows[1][V - K // 2:] = 1.0                                    # masked, but for fewer tokens than K at the end
+    rows[4][r.choice(V, size=K + 3, replace=False)] = r.standard_normal(K + 3).astype(f32)
+    rows = np.tile(np.stack(rows), (32, 1))
+    parent = np.array([-1] + [(u - 1) // 6 for u in range(1, 256)], np.int32)
+    _say("rows of equal logits %s V=%d K=%d" % (dtype, V, K))
+    _row_case(gpu, rows, dtype, K, parent=parent, check=range(8))
+
+
+@pytest.mark.parametrize("mask", ["half", "few", "lowest"])
+def test_masked_rows_cost_what_others_cost(gpu, mask):
+    """The row pass over masked vocabularies takes about the time of the unmasked one (with every tie ordered by the
+    streaming scan it took five times as long)."""
+    binding, lockstep = gpu
+    B, N, V = 8, 32, 128256
+    parent = synth.make_tree(N, 6, [4, 2, 2, 1])
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    lg = (torch.randn((B, N, V), generator=gen, device="cuda") * 1.7).to(torch.bfloat16)
+    masked = lg.clone()
+    if mask == "few":
+        keep = torch.zeros_like(lg, dtype=torch.bool).scatter_(2, torch.randint(0, V, (B, N, 64), generator=gen, device="cuda"), True)
+        masked[~keep] = float("-inf")
+    else:
+        masked[:, :, V // 2:] = float("-inf") if mask == "half" else _lowest("bf16")
+    g = binding.Stand(V, B, 1, 4, 10, parent, 0.6, 1 << 12, 64, 5, binding.STAND_BF16)
+    outs = g.new_outputs()[:3]
+    ms = {}
+    for name, x in (("warm", lg), ("plain", lg), (mask, masked)):
+        g.profile_begin(20)
+        for step in range(20):
+            g.verify(step, x, *outs)
+        ms[name] = g.profile_end()[0] / 20
+    g.close()
+    _say("row pass, us: %s" % {k: round(1e3 * v, 1) for k, v in ms.items()})
+    assert ms[mask] < 2.5 * ms["plain"]
+
+
 @pytest.mark.parametrize("name,over,steps,forced", [
     ("cfg1", dict(V=600, B=1, rho=0.6), 40, False), ("cfg1", dict(V=2003, B=1, rho=0.8, dtype="bf16"), 30, True),
     ("cfg3", dict(V=48, B=1, rho=0.5), 40, False),                              # deep paths, many rejections
