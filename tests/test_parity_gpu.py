@@ -440,6 +440,44 @@ def test_masked_rows_cost_what_others_cost(gpu, mask):
     assert ms[mask] < 2.5 * ms["plain"]
 
 
+@pytest.mark.parametrize("dtype,V", [("f32", 31 * 16384 - 3), ("bf16", 32 * 32768 - 9)])
+def test_many_parts_with_large_k(gpu, dtype, V):
+    """Rows of 31 and 32 parts, K = 32: more candidates meet than are ranked at once, with and without ties among them."""
+    r = np.random.default_rng(V)
+    rows = [(r.standard_normal(V) * 1.7).astype(np.float32) for _ in range(3)]
+    rows[1] = np.round(rows[1] * 8) / 8
+    rows[2][r.choice(V, size=900, replace=False)] = 30.0
+    _say("many parts, K = 32, %s V=%d" % (dtype, V))
+    _row_case(gpu, np.stack(rows), dtype, 32)
+
+
+def test_update_of_long_rows_does_not_grow_with_k(gpu):
+    """An update on rows of 31 parts with K = 32 takes at most twice the time of the same with K = 8 (ranking all
+    candidates against all made it more than three times)."""
+    binding, lockstep = gpu
+    B, V = 16, 500000
+    parent = np.arange(-1, 8, dtype=np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    lg = torch.randn((B, 9, V), generator=gen, device="cuda") * 1.7
+    tok = torch.randint(0, V, (B, 9), generator=gen, device="cuda", dtype=torch.int32)
+    row = torch.arange(9, device="cuda", dtype=torch.int32).repeat(B, 1).contiguous()
+    ln = torch.full((B,), 9, device="cuda", dtype=torch.int32)
+    ms = {}
+    for K in (8, 8, 32):                          # (the first: warm-up)
+        g = binding.Stand(V, B, 1, 4, K, parent, 0.6, 1 << 14, 64, 5, binding.STAND_F32)
+        g.update(0, lg, tok, row, ln)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[0].record()
+        for step in range(10):
+            g.update(step, lg, tok, row, ln)
+        ev[1].record()
+        torch.cuda.synchronize()
+        ms[K] = ev[0].elapsed_time(ev[1]) / 10
+        g.close()
+    _say("update of %d rows of %d logits, us: %s" % (B * 9, V, {k: round(1e3 * v, 1) for k, v in ms.items()}))
+    assert ms[32] < 2.0 * ms[8]
+
+
 @pytest.mark.parametrize("name,over,steps,forced", [
     ("cfg1", dict(V=600, B=1, rho=0.6), 40, False), ("cfg1", dict(V=2003, B=1, rho=0.8, dtype="bf16"), 30, True),
     ("cfg3", dict(V=48, B=1, rho=0.5), 40, False),                              # deep paths, many rejections
