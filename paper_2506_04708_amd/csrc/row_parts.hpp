@@ -25,9 +25,6 @@ namespace stand {
 // all such parts, which orders every tie, 154.  Only more than kPartList elements above the bound are still left to the
 // scan of row_pass.hpp.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
-constexpr int kPartVectors = 8;                      // most vectors per lane
-constexpr int kPartsMax = 32;                        // most parts of a row
 constexpr int kTicketStride = 32;                    // words between two rows' counters: a cache line each
 constexpr int kPartKeys = 64;                        // candidate keys a part hands over
 constexpr int kPartList = kPartsMax * kPartKeys;     // candidates collected in shared memory

@@ -1,0 +1,83 @@
+// row_plan.hpp -- which launch form the rows of a verification or an update take: a function of their number, their
+// length, K and the type only.  Plain host code.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace stand {
+
+// Row pass.  Thousands of rows: one row per workgroup of four waves.  Few rows: every row is split over workgroups
+// (row_parts.hpp), or, where that does not pay (plan_row_parts) or does not apply (the entry point with fixed scratch),
+// spread over the sixteen waves of one as long as each compute unit has at most one of them: verifications, sixteen / four
+// waves, us: 256 rows of 522 KB (bf16) 49.2 / 54.3, 288 rows 63.7 / 59.6.
+#ifndef STAND_ROW_WPR
+#define STAND_ROW_WPR 4
+#endif
+constexpr int kRowWPR = STAND_ROW_WPR, kRowWPRFewRows = 16;
+constexpr int kRowsSixteenWaves = 256;
+constexpr int unsplit_waves(int64_t rows) { return rows <= kRowsSixteenWaves ? kRowWPRFewRows : kRowWPR; }
+
+constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
+constexpr int kPartVectors = 8;                      // most vectors per lane
+constexpr int kPartsMax = 32;                        // most parts of a row
+constexpr int kPartsTarget = 256;                    // workgroups that few rows are split into
+constexpr int kRowsSplit = 512;                      // more rows are never split
+constexpr int kCommitSlotsSplit = 4096;              // row slots of an update that may be split (most hold no row)
+
+constexpr int64_t row_vectors(int64_t V, int element_bytes) { return (V * element_bytes + 15) / 16; }
+
+// Parts of a row for row_parts_kernel, or 0 where it does not fit.  A part must fit the registers of a workgroup;
+// beyond that, few rows are split further until the launch has kPartsTarget workgroups, but not into parts of
+// less than one vector per thread (the maxima of their lane groups would no longer bound the K best well).
+inline int choose_parts(int64_t vectors, int64_t rows)
+{
+    const int64_t least = (vectors + kPartThreads * kPartVectors - 1) / (kPartThreads * kPartVectors);
+    const int64_t most = std::max<int64_t>(least, vectors / kPartThreads);
+    const int64_t want = (kPartsTarget + rows - 1) / rows;
+    const int64_t p = std::min(std::max(want, least), most);
+    if (least > kPartsMax) return 0;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(p, kPartsMax));
+}
+
+// Most workgroups (rows x parts) that a split launch of so many rows should have.  A workgroup holds its part in
+// registers from its first load to its last candidate, so beyond a few device-fulls (1024 are resident) the streaming
+// kernels, which overlap one row's end with the next one's loads, are faster.  Verifications, split / the other form, us:
+//   <= 256 rows, sixteen waves: 128 x 20 parts 55.5 / 63.2, 192 x 13 57.5 / 57.4, 256 x 10 49.7 / 50.0, 256 x 16 (fp32) 71.3 / 67.8,
+//               256 x 20 (bf16) 103 / 87, 160 x 31 (bf16) 110 / 100
+//   more rows, four waves: 288 x 16 89.1 / 92.1, x 20 113 / 110; 384 x 8 58.3 / 61.8, x 10 71.5 / 68.7; 448 x 4 40.7 / 40.7, x 6 52.9 / 50.0;
+//               512 x 2 30.8 / 32.5, x 4 44.7 / 41.6, x 10 (fp32) 81.9 / 72.6
+// The crossing falls with the number of rows along 16 (576 - rows).
+constexpr int64_t split_limit(int64_t rows)
+{
+    return rows <= kRowsSixteenWaves ? 2560 : (rows <= kRowsSplit ? 16 * (576 - rows) : 0);
+}
+
+// A part's bound needs at least K of its 64 lane groups (8 vectors each) to hold elements, and some more to be a good one:
+// K = 32, 256 rows of 32 / 40 lane groups split 23.3 / 18.2 us, sixteen waves 21.4 / 21.5; of 24 31.3 / 21.1 (no bound
+// at all: every element is a candidate).
+constexpr bool bound_holds(int64_t vectors, int K) { return vectors >= 10 * (int64_t)K; }
+
+// Parts per row of a verification, 0: not split.
+inline int plan_row_parts(int64_t V, int element_bytes, int64_t rows, int K)
+{
+    const int64_t vectors = row_vectors(V, element_bytes);
+    const int p = choose_parts(vectors, rows);
+    return bound_holds(vectors, K) && rows * p <= split_limit(rows) ? p : 0;
+}
+
+// Parts per row of an update with R row slots per trajectory, W = longest path, N = nodes; 0: not split.
+// Where all slots can be on one path or are merged anyway (chains, all-nodes updates) every slot counts as a row.  Else
+// accepted paths are short: the parts are chosen for up to four rows per trajectory, the limit is that of two.  Updates,
+// split / unsplit, us: 128 trajectories x 300 KB (5 parts), paths of 1 / 2 / 4 / 8: 52 / 74, 68 / 89, 105 / 118, 172 / 160;
+// x 800 KB (fp32, 13 parts: not split): 96 / 141, 139 / 167, 220 / 215, 426 / 291; 64 x 800 KB (split): 69 / 80, 84 / 89, 127 / 116, 216 / 157.
+inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int N, int R, int K)
+{
+    const int64_t vectors = row_vectors(V, element_bytes);
+    const bool all = W == N || R > W;
+    const int64_t expect = B * (all ? R : std::min(W, 4)), usual = B * (all ? R : std::min(W, 2));
+    if (expect > kRowsSplit || B * R > kCommitSlotsSplit || !bound_holds(vectors, K)) return 0;
+    const int p = choose_parts(vectors, expect);
+    return usual * p <= split_limit(usual) ? p : 0;
+}
+
+}  // namespace stand

@@ -155,20 +155,7 @@ static void free_all(stand_handle *h)
 
 static int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
-// Parts of a row for row_parts_kernel, or 0 where it does not fit.  A part must fit the registers of a workgroup;
-// beyond that, few rows are split further until the launch has kPartsTarget workgroups, but not into parts of
-// less than one vector per thread (the maxima of their lane groups would no longer bound the K best well).
-constexpr int kPartsTarget = 256;
-static int choose_parts(const stand_handle *h, int rows)
-{
-    const int64_t nvec = ((int64_t)h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) + 15) / 16;
-    const int64_t least = (nvec + kPartThreads * kPartVectors - 1) / (kPartThreads * kPartVectors);
-    const int64_t most = std::max<int64_t>(least, nvec / kPartThreads);
-    const int64_t want = (kPartsTarget + rows - 1) / rows;
-    const int64_t p = std::min(std::max(want, least), most);
-    if (least > kPartsMax) return 0;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(p, kPartsMax));
-}
+static int element_bytes(const stand_config &cfg) { return cfg.logits_dtype == STAND_BF16 ? 2 : 4; }
 
 extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
 {
@@ -297,13 +284,8 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(dmalloc(&h->vs.stop_i, B * 4)); acc(dmalloc(&h->vs.stop_m, B)); acc(dmalloc(&h->vs.stop_qid, B * kMaxK));
     acc(dmalloc(&h->vs.stop_qmu, B * kMaxK)); acc(dmalloc(&h->vs.stop_ql, B * kMaxK)); acc(dmalloc(&h->vs.stop_child, B * kMaxK));
     acc(dmalloc(&h->pr_m, B * h->R)); acc(dmalloc(&h->pr_top_l, B * h->R * K)); acc(dmalloc(&h->pr_top_idx, B * h->R * K));
-    h->row_parts = rows <= (size_t)kRowsSplit ? choose_parts(h, (int)rows) : 0;
-    {
-        // rows an update is likely to hold: every slot where all of them can be on one path or are merged anyway
-        // (chains, all-nodes updates), else a few per trajectory (accepted paths are short)
-        const size_t expect = B * (size_t)((h->W == N || h->R > h->W) ? h->R : std::min(h->W, 4));
-        h->commit_parts = expect <= (size_t)kRowsSplit && B * h->R <= (size_t)kCommitSlotsSplit ? choose_parts(h, (int)expect) : 0;
-    }
+    h->row_parts = plan_row_parts(h->V, element_bytes(*cfg), (int64_t)rows, K);
+    h->commit_parts = plan_commit_parts(h->V, element_bytes(*cfg), h->B, h->W, N, h->R, K);
     const size_t part_tickets = std::max(h->row_parts ? rows : 0, h->commit_parts ? B * h->R : 0) * kTicketStride;
     const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);
     acc(dmalloc(&h->part_ticket, part_tickets));
@@ -462,9 +444,8 @@ static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r,
     a.P = parts;
     // logits beyond what the eight L2 caches hold together (32 MB) are read past them: step of 256 rows of 257 KB 51.1
     // against 54.6 us; below, the path rows' second read finds them there (16 rows of 128 KB: 29.3 against 30.0 us)
-    a.streamed = (int64_t)h->B * h->N * h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) > ((int64_t)32 << 20);
-    const int64_t nvec = ((int64_t)h->V * (h->cfg.logits_dtype == STAND_BF16 ? 2 : 4) + 15) / 16;
-    a.per = (int)((nvec + parts - 1) / parts);
+    a.streamed = (int64_t)h->B * h->N * h->V * element_bytes(h->cfg) > ((int64_t)32 << 20);
+    a.per = (int)((row_vectors(h->V, element_bytes(h->cfg)) + parts - 1) / parts);
     a.ticket = h->part_ticket; a.head = h->part_head; a.keys = h->part_keys;
     return a;
 }
@@ -475,7 +456,7 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
 {
     const int rows = h->B * h->N;
     const bool split = own && h->row_parts > 0;
-    const bool few = rows <= kRowsSplit;  // one workgroup per row; more waves per row when rows are few
+    const bool few = unsplit_waves(rows) == kRowWPRFewRows;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * h->row_parts : (few ? kRowWPRFewRows : kRowWPR));
     RowPartsArgs pa = make_parts_args(h, a, split ? h->row_parts : 1);

@@ -3,21 +3,11 @@
 // of one tree node (paper Sec. 3.2).
 #pragma once
 #include "numeric.hpp"
+#include "row_plan.hpp"
 
 namespace stand {
 
 constexpr int kDtBf16 = 0, kDtF32 = 1;
-// Row pass.  Thousands of rows: one row per workgroup of four waves.  Few rows: every row is split over workgroups
-// (row_parts.hpp), or, where that does not apply (rows of more than kPartsMax parts, the entry point with fixed scratch),
-// spread over the sixteen waves of one.
-#ifndef STAND_ROW_WPR
-#define STAND_ROW_WPR 4
-#endif
-constexpr int kRowWPR = STAND_ROW_WPR, kRowWPRFewRows = 16;
-// At most this many rows are split.  Steps, split / four waves per row, us: 256 rows of 257 KB 51.6 / 54.7, 287 of 287 KB
-// 84.3 / 87.8, 324 of 40 KB 43.6 / 46.5; 576 of 191 KB 80.7 / 79.7, 637 of 75 KB 70.2 / 68.9.
-constexpr int kRowsSplit = 512;
-constexpr int kCommitSlotsSplit = 4096;     // row slots of an update that may be split (most hold no row)
 constexpr int kRowsFew = 768;               // at most this many rows: the step's automatic plan keeps the separate launches
 constexpr int kRowsMany = 8192;             // more rows than this: the step's automatic plan keeps the separate launches
 constexpr int kMaxNodes = 1024;

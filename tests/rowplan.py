@@ -1,0 +1,57 @@
+"""The library's rule for splitting rows (csrc/row_plan.hpp, plain host code), compiled with the host compiler: tests
+state through it which launch form a shape takes."""
+import ctypes
+import os
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+_SRC = """
+#include "row_plan.hpp"
+using namespace stand;
+extern "C" {
+int row_parts(int64_t V, int es, int64_t rows, int K) { return plan_row_parts(V, es, rows, K); }
+int commit_parts(int64_t V, int es, int64_t B, int W, int N, int R, int K) { return plan_commit_parts(V, es, B, W, N, R, K); }
+int waves(int64_t rows) { return unsplit_waves(rows); }
+int64_t limit(int64_t rows) { return split_limit(rows); }
+int64_t vectors(int64_t V, int es) { return row_vectors(V, es); }
+int threads() { return kPartThreads; }
+int most_vectors() { return kPartVectors; }
+int parts_max() { return kPartsMax; }
+}
+"""
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        with tempfile.TemporaryDirectory() as d:
+            src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
+            open(src, "w").write(_SRC)
+            subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
+                            os.path.join(ROOT, "paper_2506_04708_amd", "csrc"), "-o", so, src], check=True)
+            _lib = ctypes.CDLL(so)
+        i, l = ctypes.c_int, ctypes.c_int64
+        _lib.row_parts.argtypes = [l, i, l, i]
+        _lib.commit_parts.argtypes = [l, i, l, i, i, i, i]
+        _lib.waves.argtypes = [l]
+        _lib.limit.argtypes, _lib.limit.restype = [l], l
+        _lib.vectors.argtypes, _lib.vectors.restype = [l, i], l
+    return _lib
+
+
+def element_bytes(dtype):
+    return 2 if dtype == "bf16" else 4
+
+
+def row_parts(V, dtype, rows, K):
+    """Parts per row of a verification; 0: not split."""
+    return lib().row_parts(V, element_bytes(dtype), rows, K)
+
+
+def part_registers(V, dtype, rows, K):
+    """Vectors per lane of a part."""
+    p = row_parts(V, dtype, rows, K)
+    per = -(-lib().vectors(V, element_bytes(dtype)) // p)
+    return -(-per // lib().threads())

@@ -1,0 +1,64 @@
+"""CPU tests of the rule that splits few rows over workgroups (csrc/row_plan.hpp)."""
+import random
+
+import pytest
+
+from tests import rowplan
+
+
+@pytest.mark.parametrize("V,dtype,rows,K,split", [
+    (152064, "bf16", 32, 10, True), (32000, "f32", 16, 10, True), (128256, "bf16", 256, 10, True), (8000, "bf16", 512, 16, True),
+    # too short for a bound: fewer lane groups hold elements than are asked for, or hardly more
+    (300, "bf16", 16, 10, False), (1000, "bf16", 256, 32, False), (2000, "bf16", 512, 32, False), (1000, "bf16", 256, 10, True),
+    (2600, "bf16", 256, 32, True), (48, "bf16", 64, 16, False),
+    # too many workgroups: the streaming kernels are faster
+    (262144, "f32", 512, 32, False), (152064, "f32", 512, 16, False), (500000, "f32", 256, 16, False), (1000000, "bf16", 384, 16, False),
+    (500000, "f32", 32, 16, True), (262144, "f32", 128, 16, True), (128256, "bf16", 512, 10, False), (63000, "bf16", 512, 10, True),
+    # more parts than a row has; more rows than are split
+    (32 * 32768 + 8, "bf16", 2, 16, False), (32 * 32768, "bf16", 2, 16, True), (32003, "f32", 576, 20, False), (8000, "bf16", 513, 16, False),
+])
+def test_split_of_verified_rows(V, dtype, rows, K, split):
+    assert (rowplan.row_parts(V, dtype, rows, K) > 0) == split
+
+
+@pytest.mark.parametrize("V,dtype,B,W,N,R,K,split", [
+    (152064, "bf16", 4, 32, 32, 32, 16, True),       # transcript: a chain of 32 nodes, every slot a row
+    (50257, "bf16", 6, 7, 40, 7, 10, True),          # accepted paths
+    (152064, "bf16", 128, 11, 128, 11, 32, True),
+    (500000, "f32", 128, 9, 64, 9, 32, False),       # 256 rows of 31 parts
+    (200000, "f32", 16, 32, 32, 32, 32, False),      # 512 rows of 13
+    (1000, "bf16", 64, 9, 64, 9, 32, False),         # no bound
+    (32000, "bf16", 32, 9, 64, 64, 16, False),       # all-nodes update: 2048 rows
+    (32000, "bf16", 4, 9, 64, 64, 16, True),
+    (32000, "bf16", 129, 9, 64, 9, 16, False),
+])
+def test_split_of_updated_rows(V, dtype, B, W, N, R, K, split):
+    assert (rowplan.lib().commit_parts(V, rowplan.element_bytes(dtype), B, W, N, R, K) > 0) == split
+
+
+def test_waves_of_unsplit_rows():
+    assert [rowplan.lib().waves(r) for r in (1, 256, 257, 768, 16384)] == [16, 16, 4, 4, 4]
+
+
+def test_every_plan_fits_the_kernel():
+    """Registers, the most parts, the workgroup limit, parts long enough for a bound, and the memory of the candidates."""
+    L, r = rowplan.lib(), random.Random(5)
+    for _ in range(20000):
+        es = r.choice([2, 4])
+        V = int(2 ** r.uniform(5, 22))
+        K = r.randint(1, min(32, V))
+        rows = r.choice([r.randint(1, 64), r.randint(1, 600)])
+        p, vec = L.row_parts(V, es, rows, K), L.vectors(V, es)
+        if p:
+            per = -(-vec // p)
+            last = vec - (p - 1) * per
+            assert 1 <= p <= L.parts_max() and per <= L.threads() * L.most_vectors() and rows * p <= L.limit(rows)
+            assert last >= 10 * K and (p == 1 or last >= L.threads() - L.parts_max())
+        W, N = r.randint(1, 32), r.randint(1, 1024)
+        N = max(N, W)
+        R = r.choice([W, N])
+        B = r.randint(1, 300)
+        c = L.commit_parts(V, es, B, W, N, R, K)
+        if c:
+            assert c <= L.parts_max() and -(-vec // c) <= L.threads() * L.most_vectors()
+            assert B * R * c * 64 * 8 <= 24 << 20      # 64 candidate keys per part
