@@ -12,6 +12,7 @@ torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
 from paper_2506_04708_amd import synth  # noqa: E402
+from tests import rowplan  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -495,15 +496,46 @@ def test_lockstep_one_trajectory(gpu, name, over, steps, forced):
 
 @pytest.mark.parametrize("over,mode", [
     (dict(V=70001, B=2, rho=0.7), "separate"), (dict(V=70001, B=2, rho=0.7, dtype="bf16"), "separate"),
-    (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"), (dict(V=66000, B=47, rho=0.7, dtype="bf16"), "step"),
+    (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"),
 ])
 def test_lockstep_rows_split_over_workgroups(gpu, over, mode):
-    """Verification and update on rows of several parts (47 x 16 rows: just below the limit of the split)."""
+    """Verification and update on rows of several parts."""
     binding, lockstep = gpu
     _say("lockstep split %s %s" % (over, mode))
     w = synth.Workload("cfg1", run_steps=6, **over)
+    assert rowplan.row_parts(w.V, w.dtype, w.B * w.N, w.K) > 1
     info = lockstep.run_lockstep(w, 6, mode=mode, capacity=1 << 14, table_every=3, sample_rows=range(0, w.B * w.N, 7))
     _say("  -> %s" % info)
+
+
+def test_lockstep_at_the_limit_of_the_split(gpu):
+    """Whole steps on the most trajectories whose rows are split (63 MB of logits: read past the caches) and on one more."""
+    binding, lockstep = gpu
+    V = 66000
+    split = [b for b in range(1, 65) if rowplan.row_parts(V, "bf16", 16 * b, 10) > 0]
+    assert split == list(range(1, len(split) + 1)) and len(split) * 16 * V * 2 > 32 << 20
+    for B in (len(split), len(split) + 1):
+        w = synth.Workload("cfg1", run_steps=6, V=V, B=B, rho=0.7, dtype="bf16")
+        assert (w.N, w.K) == (16, 10) and (rowplan.row_parts(V, w.dtype, B * w.N, w.K) > 0) == (B == len(split))
+        _say("limit of the split: %d rows" % (B * w.N))
+        info = lockstep.run_lockstep(w, 6, mode="step", capacity=1 << 14, table_every=3, sample_rows=range(0, B * w.N, 7))
+        _say("  -> %s" % info)
+
+
+@pytest.mark.parametrize("dtype,V,registers", [
+    ("bf16", 3000, 1), ("bf16", 8003, 2), ("bf16", 12000, 3), ("bf16", 16001, 4), ("bf16", 24000, 6), ("bf16", 32001, 8),
+    ("f32", 8001, 4), ("f32", 12003, 6), ("f32", 16000, 8),
+])
+def test_lockstep_by_registers_of_a_part(gpu, dtype, V, registers):
+    """256 rows with drafts pending, parts of every number of vectors per lane that the kernel is built for."""
+    binding, lockstep = gpu
+    over = dict(V=V, B=16, rho=0.7, dtype=dtype)
+    w = synth.Workload("cfg1", run_steps=4, **over)
+    need = rowplan.part_registers(V, dtype, w.B * w.N, w.K)
+    assert min(r for r in (1, 2, 3, 4, 6, 8) if r >= need) == registers
+    _say("part registers %s %s" % (registers, over))
+    info = lockstep.run_lockstep(w, 4, mode="step", capacity=1 << 14, table_every=3, sample_rows=range(0, w.B * w.N, 5))
+    _say("  -> %s" % {k: v for k, v in info.items() if k != "node_counts"})
 
 
 def test_full_shape_rows_sampled(gpu):
@@ -772,12 +804,18 @@ def test_vocabularies_above_2_22(gpu, over, steps, rows):
     assert info["emitted"] >= steps * w.B and info["worst_rel"] < 1e-5
 
 
-def test_step_recorded_into_a_graph_replays_correctly(gpu):
-    """stand_step recorded into a HIP graph (the five launches are taken while a stream is being captured, whatever the
+@pytest.mark.parametrize("name,over,one_launch", [
+    ("cfg3", dict(V=3000, B=13, rho=0.7), True),
+    ("cfg1", dict(V=70001, B=1, rho=0.7, dtype="bf16"), False),    # split rows, one workgroup for the rest of the step
+    ("cfg1", dict(V=70001, B=3, rho=0.7), False),                  # split rows, separate launches
+])
+def test_step_recorded_into_a_graph_replays_correctly(gpu, name, over, one_launch):
+    """stand_step recorded into a HIP graph (the separate launches are taken while a stream is being captured, whatever the
     plan) and replayed three times, with eager work and synchronisations between the replays: every replay gives what
-    the same call gives eagerly on a twin handle (which runs it as one launch)."""
+    the same call gives eagerly on a twin handle (which runs it as one launch where that is the plan)."""
     binding, lockstep = gpu
-    w = synth.Workload("cfg3", run_steps=12, V=3000, B=13, rho=0.7)
+    w = synth.Workload(name, run_steps=12, **over)
+    assert one_launch or rowplan.row_parts(w.V, w.dtype, w.B * w.N, w.K) > 1
     hs = []
     for _ in range(2):
         o, g = lockstep.make_pair(w, 1 << 14)
@@ -793,7 +831,7 @@ def test_step_recorded_into_a_graph_replays_correctly(gpu):
         ga.step(step, lg, ta, na, la, da)
         gb.step(step, lg, tb, nb, lb, db)
     torch.cuda.synchronize()
-    assert ga.step_is_one_launch() and torch.equal(da, db)
+    assert ga.step_is_one_launch() == one_launch and torch.equal(da, db)
     lg = lockstep._logits_to_device(w.logits(6, da.cpu().numpy()), w.dtype)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
