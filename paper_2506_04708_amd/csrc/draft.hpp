@@ -33,7 +33,7 @@ struct DraftShared {
     int32_t (*recent)[kMaxOrder];    // [N][kMaxOrder] recent[u][i]: the token i positions before the end of the
                                      // sequence that ends at node u (recent[u][0] is the node's own token), so a
                                      // key is read without walking up the tree; 16-byte aligned
-    unsigned long long (*keys)[kMaxK];  // [16 waves][kMaxK] scores of the node a wave is ranking; 16-byte aligned
+    unsigned long long (*keys)[kMaxK];  // [waves][kMaxK] scores of the node a wave is ranking; 16-byte aligned
     long long *clen;
     unsigned *n_hit;                 // [kMaxOrder + 1] lookups answered by order n; [0]: misses
     int32_t *live;                   // [kMaxDepth + 2] a node of this tree level has a token
@@ -41,13 +41,13 @@ struct DraftShared {
     int32_t *info;                   // [N] first child << 8 | number of children
     int32_t *has;                    // [N] children drafted
 };
-constexpr size_t kDraftSharedFixed = (size_t)16 * kMaxK * 8 + 16 + 48 + 144;
-__host__ __device__ inline size_t draft_shared_bytes(int N) { return (size_t)N * (kMaxOrder + 3) * 4 + kDraftSharedFixed; }
-__device__ __forceinline__ DraftShared draft_shared_carve(char *base, int N)
+constexpr size_t draft_shared_fixed(int waves) { return (size_t)waves * kMaxK * 8 + 16 + 48 + 144; }
+constexpr size_t draft_shared_bytes(int N, int waves) { return (size_t)N * (kMaxOrder + 3) * 4 + draft_shared_fixed(waves); }
+__device__ __forceinline__ DraftShared draft_shared_carve(char *base, int N, int waves)
 {
     DraftShared s;
     s.recent = (int32_t(*)[kMaxOrder])base;  base += (size_t)N * kMaxOrder * 4;
-    s.keys = (unsigned long long(*)[kMaxK])base;  base += (size_t)16 * kMaxK * 8;
+    s.keys = (unsigned long long(*)[kMaxK])base;  base += (size_t)waves * kMaxK * 8;
     s.clen = (long long *)base;              base += 16;
     s.n_hit = (unsigned *)base;              base += 48;
     s.live = (int32_t *)base;                base += 144;
@@ -82,7 +82,6 @@ __device__ __forceinline__ unsigned long long fingerprint_multiplier_of_lane(int
 template <int NT>
 __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
 {
-    static_assert(NT / 64 <= 16, "keys: one row per wave");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int32_t *tok = sm.tok;
     int32_t(*recent)[kMaxOrder] = sm.recent;
@@ -305,8 +304,8 @@ __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, cons
 
 __global__ __launch_bounds__(kDraftThreads) void draft_kernel(DraftArgs a)
 {
-    __shared__ __align__(16) char smem[(size_t)kMaxNodes * (kMaxOrder + 3) * 4 + kDraftSharedFixed];
-    draft_trajectory<kDraftThreads>(a, (int)blockIdx.x, draft_shared_carve(smem, a.tree.N));
+    __shared__ __align__(16) char smem[draft_shared_bytes(kMaxNodes, kDraftThreads / 64)];
+    draft_trajectory<kDraftThreads>(a, (int)blockIdx.x, draft_shared_carve(smem, a.tree.N, kDraftThreads / 64));
 }
 
 }  // namespace stand

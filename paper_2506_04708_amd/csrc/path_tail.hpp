@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kTailThreads) void path_tail_kernel(PathTailArgs A)
     static_assert(kTailThreads == kFinishThreads && kTailThreads == kDraftThreads, "one workgroup runs all parts");
     __shared__ FinishShared fin;
     __shared__ __align__(16) unsigned long long scratch[kTailThreads / 64][2 * kMaxK];
-    __shared__ __align__(16) char smem[(size_t)kMaxNodes * (kMaxOrder + 3) * 4 + kDraftSharedFixed];
+    __shared__ __align__(16) char smem[draft_shared_bytes(kMaxNodes, kTailThreads / 64)];
     const PathArgs &a = A.path;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int kWaves = kTailThreads / 64, kClaimWaves = kMaxOrder * (kMaxDepth + 1) / 64;
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kTailThreads) void path_tail_kernel(PathTailArgs A)
     publish_fence();
     __syncthreads();
     consume_fence();
-    draft_trajectory<kTailThreads>(A.draft, 0, draft_shared_carve(smem, A.draft.tree.N));
+    draft_trajectory<kTailThreads>(A.draft, 0, draft_shared_carve(smem, A.draft.tree.N, kTailThreads / 64));
 }
 
 }  // namespace stand

@@ -371,15 +371,18 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
     tail_barrier(sy, 1, (unsigned)a.B, ts);
     if (tid == 0) stamp(sy, b, 6);
     if (tid == 0 && !ts->ok) atomicAdd(&a.stats[kStatWaitExpired], 1ull);
-    draft_trajectory<kStepThreads>(A.draft, b, draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N));
+    draft_trajectory<kStepThreads>(A.draft, b, draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N, kStepWPR));
     if (tid == 0) stamp(sy, b, 7);
 }
 
-__host__ __device__ inline size_t step_shared_bytes(int N)
+constexpr size_t step_shared_bytes(int N)
 {
-    const size_t tail = ((sizeof(TailShared) + 15) & ~(size_t)15) + draft_shared_bytes(N);
+    const size_t tail = ((sizeof(TailShared) + 15) & ~(size_t)15) + draft_shared_bytes(N, kStepWPR);
     return tail > sizeof(RowShared<kStepWPR>) ? tail : sizeof(RowShared<kStepWPR>);
 }
+// The registers leave room for three workgroups per compute unit; so must the shared memory (160 KB, given out in units of
+// 1280 bytes) for every tree: with scores for sixteen waves in it the largest trees had two (step of 4 x 1024 rows 219 us against 201).
+static_assert(3 * ((step_shared_bytes(kMaxNodes) + 1279) / 1280 * 1280) <= 160 * 1024, "three workgroups per compute unit");
 
 template <int DT>
 __global__ __launch_bounds__(kStepThreads) __attribute__((amdgpu_waves_per_eu(STAND_STEP_MINWAVES, 8))) void stand_step_kernel(StepArgs A)
