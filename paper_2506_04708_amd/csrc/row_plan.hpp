@@ -80,4 +80,9 @@ inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int
     return usual * p <= split_limit(usual) ? p : 0;
 }
 
+// 16-byte loads per thread and segment of the exact sums: one round of four, or of two for the few path rows of a small
+// batch (steps with 2 / 4, us: 1 x 32 rows 33.3 / 34.2, 8 x 32 50.4 / 51.2, 32 x 64 158.0 / 156.4).  Not where every drafted
+// row is summed, which fills the vector ALUs at any batch size: all-nodes steps of 16 x 64 rows 357 / 331, 4 x 64 98 / 94.
+constexpr int exact_loads(bool verify, bool all_nodes, int64_t B) { return verify && !all_nodes && B <= 16 ? 2 : 4; }
+
 }  // namespace stand

@@ -552,10 +552,9 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
         } else if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
         else commit_scan_kernel<kDtF32><<<grid, dim3(256), 0, s>>>(c);
     }
-    // segments: one round of loads per thread where kSegMax allows it, of 4 vectors of 16 bytes, or of 2 for the few
-    // path rows of a small batch (steps with 2 / 4, us: 1 x 32 rows 33.3 / 34.2, 8 x 32 50.4 / 51.2, 32 x 64 158.0 / 156.4);
-    // one more block per (row, trajectory) slot for the outputs and the stop record
-    const int per_thread = mode == 0 && h->B <= 16 ? 2 : 4;
+    // segments: one round of loads per thread where kSegMax allows it; one more block per (row, trajectory) slot for the
+    // outputs and the stop record
+    const int per_thread = exact_loads(mode == 0, h->cfg.update_mode == STAND_UPDATE_ALL_NODES, h->B);
     PathArgs a = make_path_args(h, vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, per_thread * kPathThreads);
     // row slots of the grid: every slot in update / all-nodes mode; in verify mode four (paths are
     // mostly short; the kernel loops over longer ones)

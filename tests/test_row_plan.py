@@ -40,6 +40,12 @@ def test_waves_of_unsplit_rows():
     assert [rowplan.lib().waves(r) for r in (1, 256, 257, 768, 16384)] == [16, 16, 4, 4, 4]
 
 
+def test_loads_of_the_exact_sums():
+    """Few path rows are cut finer; all drafted rows of a tree are not few, whatever the batch."""
+    assert [rowplan.lib().loads(1, 0, b) for b in (1, 16, 17, 128)] == [2, 2, 4, 4]
+    assert [rowplan.lib().loads(1, 1, b) for b in (1, 16, 17)] == [4, 4, 4] and rowplan.lib().loads(0, 0, 1) == 4
+
+
 def test_every_plan_fits_the_kernel():
     """Registers, the most parts, the workgroup limit, parts long enough for a bound, and the memory of the candidates."""
     L, r = rowplan.lib(), random.Random(5)
