@@ -71,7 +71,7 @@ extern "C" {
 #define STAND_STEP_AUTO 0   /* one launch where it pays (769 .. 8192 rows, accepted-path updates, accepted paths */
                             /* that seldom reach below upper_depth: watched while running), else serial        */
 #define STAND_STEP_SERIAL 1 /* five dependent launches: rows, exact sums, finish + claims, apply, draft           */
-                            /* (three with one trajectory: the last three are one)                               */
+                            /* (three with one trajectory and accepted-path updates: the last three are one)     */
 #define STAND_STEP_FUSED 2  /* one launch: the dependent tail runs beside the rows that are still streaming      */
 
 #define STAND_MAX_TOPK 32
