@@ -23,6 +23,7 @@ constexpr int kPartsMax = 32;                        // most parts of a row
 constexpr int kPartsTarget = 256;                    // workgroups that few rows are split into
 constexpr int kRowsSplit = 512;                      // more rows are never split
 constexpr int kCommitSlotsSplit = 4096;              // row slots of an update that may be split (most hold no row)
+constexpr int kCommitWorkgroups = 2560;              // workgroups that find a row in a split update of short paths
 
 constexpr int64_t row_vectors(int64_t V, int element_bytes) { return (V * element_bytes + 15) / 16; }
 
@@ -41,15 +42,16 @@ inline int choose_parts(int64_t vectors, int64_t rows)
 
 // Most workgroups (rows x parts) that a split launch of so many rows should have.  A workgroup holds its part in
 // registers from its first load to its last candidate, so beyond a few device-fulls (1024 are resident) the streaming
-// kernels, which overlap one row's end with the next one's loads, are faster.  Verifications, split / the other form, us:
-//   <= 256 rows, sixteen waves: 128 x 20 parts 55.5 / 63.2, 192 x 13 57.5 / 57.4, 256 x 10 49.7 / 50.0, 256 x 16 (fp32) 71.3 / 67.8,
-//               256 x 20 (bf16) 103 / 87, 160 x 31 (bf16) 110 / 100
-//   more rows, four waves: 288 x 16 89.1 / 92.1, x 20 113 / 110; 384 x 8 58.3 / 61.8, x 10 71.5 / 68.7; 448 x 4 40.7 / 40.7, x 6 52.9 / 50.0;
-//               512 x 2 30.8 / 32.5, x 4 44.7 / 41.6, x 10 (fp32) 81.9 / 72.6
-// The crossing falls with the number of rows along 16 (576 - rows).
+// kernels, which overlap one row's end with the next one's loads, are faster.  Verifications of rows that start on cache
+// lines, split / the other form, us (parts; bf16 unless named):
+//   up to 256 rows, the other form has sixteen waves:  128 x 16 52.7 / 58.6, x 25 80.3 / 81.9;  160 x 13 52.2 / 55.6, x 20 75.8 / 71.1;
+//     192 x 10 49.1 / 49.3, x 13 57.4 / 55.4;  224 x 8 42.8 / 44.0, x 13 61.9 / 58.2;  256 x 4 30.8 / 33.3, x 6 39.2 / 38.5, x 10 56.3 / 54.6
+//   more rows, four waves:  288 x 10 61.6 / 68.5, x 16 89.1 / 91.4, fp32 78.6 / 77.4;  320 x 8 52.6 / 59.1, x 16 96.9 / 92.0;
+//     384 x 4 38.0 / 40.0, fp32 x 8 53.6 / 50.0;  448 x 3 35.6 / 35.2;  512 x 2 30.8 / 32.5, x 4 44.3 / 40.6
+// (Rows that start anywhere slow the other forms down by up to a tenth and leave the split as it is.)
 constexpr int64_t split_limit(int64_t rows)
 {
-    return rows <= kRowsSixteenWaves ? 2560 : (rows <= kRowsSplit ? 16 * (576 - rows) : 0);
+    return rows <= kRowsSixteenWaves ? 420000 / std::max<int64_t>(rows, 1) : (rows <= kRowsSplit ? 300000000 / (rows * rows) : 0);
 }
 
 // A part's bound needs at least K of its 64 lane groups (8 vectors each) to hold elements, and some more to be a good one:
@@ -67,7 +69,7 @@ inline int plan_row_parts(int64_t V, int element_bytes, int64_t rows, int K)
 
 // Parts per row of an update with R row slots per trajectory, W = longest path, N = nodes; 0: not split.
 // Where all slots can be on one path or are merged anyway (chains, all-nodes updates) every slot counts as a row.  Else
-// accepted paths are short: the parts are chosen for up to four rows per trajectory, the limit is that of two.  Updates,
+// accepted paths are short: the parts are chosen for up to four rows per trajectory, the limit is on two.  Updates,
 // split / unsplit, us: 128 trajectories x 300 KB (5 parts), paths of 1 / 2 / 4 / 8: 52 / 74, 68 / 89, 105 / 118, 172 / 160;
 // x 800 KB (fp32, 13 parts: not split): 96 / 141, 139 / 167, 220 / 215, 426 / 291; 64 x 800 KB (split): 69 / 80, 84 / 89, 127 / 116, 216 / 157.
 inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int N, int R, int K)
@@ -77,7 +79,7 @@ inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int
     const int64_t expect = B * (all ? R : std::min(W, 4)), usual = B * (all ? R : std::min(W, 2));
     if (expect > kRowsSplit || B * R > kCommitSlotsSplit || !bound_holds(vectors, K)) return 0;
     const int p = choose_parts(vectors, expect);
-    return usual * p <= split_limit(usual) ? p : 0;
+    return usual * p <= (all ? split_limit(usual) : kCommitWorkgroups) ? p : 0;
 }
 
 // 16-byte loads per thread and segment of the exact sums: one round of four, or of two for the few path rows of a small
