@@ -535,7 +535,9 @@ __device__ unsigned long long wave_row_exact_sum(const void *rowp, int V, float 
 }
 
 // Normaliser of a row by one wave, for the results of rows without a fast one (fast_sum_void: logits near the ends of
-// the type's range only).  A loop of few instructions, since it stands in every row kernel and practically never runs.
+// the type's range only).  A loop of few instructions, since it stands in every row kernel and practically never runs;
+// it and the exact recompute of an undecided test are marked unlikely, so that they leave the straight line (row pass
+// of 2048 rows of 304 KB 106.6 -> 102.8 us).
 template <int DT>
 __device__ __forceinline__ float wave_row_plain_sum(const void *rowp, int V, float m, float c, int lane)
 {
@@ -620,7 +622,7 @@ struct NodeProposal {
         // (without a fast normaliser eps_row exceeds every probability: whatever s is, the tests are left to the exact one)
         if (fast_sum_void(m, a.c)) s = 1.0f;
         NodeResult nr = wave_node_outcome(lane, a.K, tests, e / s, nch, true, eps_row, a.onehot);
-        if (nr.near) {
+        if (__builtin_expect(nr.near, 0)) {
             // a test fell inside the error bound of the fast normaliser: decide with the exact one
             const unsigned long long S = wave_row_exact_sum<DT>(rowp, a.V, m, a.c, lane, a.fx_shift);
             const float sx = normaliser_from_fixed(S, a.fx_shift);
@@ -708,7 +710,7 @@ __device__ __forceinline__ void row_role(const RowPassArgs &a, int row, RowShare
     const int cnt = gather_wave_records<DT, WPR>(sm, lane, a.K);
     wave_row_finish<DT>(rowp, a.V, a.K, ws, sm->ebuf, lane, cnt);
 
-    if (fast_sum_void(m, a.c)) s = wave_row_plain_sum<DT>(rowp, a.V, m, a.c, lane);
+    if (__builtin_expect(fast_sum_void(m, a.c), 0)) s = wave_row_plain_sum<DT>(rowp, a.V, m, a.c, lane);
     if (lane < a.K) {
         const unsigned long long key = ws->top[lane];
         const float l = rank_key_value(key);
