@@ -4,6 +4,7 @@
 //   row_pass.hpp     row_pass_kernel     softmax statistics + top-K of every logits row in one streaming
 //                                        pass, and the accept/reject outcome of the row's tree node
 //                                                                              (paper Sec. 4.1, 3.2)
+//   row_plan.hpp     (host) which rows are split, and by how much
 //   row_parts.hpp    row_parts_kernel    the same for few rows, and for the rows of an update: every row split over
 //                                        workgroups that hold their part in registers
 //   path_pass.hpp    path_exact_kernel   exact integer partial sums of the rows on the accepted path;

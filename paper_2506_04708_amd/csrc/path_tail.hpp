@@ -10,7 +10,7 @@ namespace stand {
 // and the records' slots claimed, the records applied and the next tree drafted by the waves of one workgroup, with
 // workgroup barriers where a larger batch has kernel boundaries.  Bound by the chain of dependent instructions and
 // round trips, which the two launches and their first loads only lengthened: steps of 1 x 16 rows 30.1 -> 28.3 us, of
-// 1 x 32 rows 33.3 -> 32.0 us.
+// 1 x 32 rows 33.3 -> 32.0 us when it was taken in (today 28.6 .. 29.6 and 31 .. 33, from box to box).
 constexpr int kTailThreads = 1024;
 
 struct PathTailArgs {

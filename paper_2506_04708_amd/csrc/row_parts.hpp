@@ -121,7 +121,7 @@ __device__ __forceinline__ void load_part(uint4 (&w)[R], __amdgpu_buffer_rsrc_t 
 }
 
 // (64 registers leave room for four workgroups per compute unit, so that their phases overlap: 256 rows of 257 KB
-// take 19.6 us; with 116 registers and two workgroups 21.2)
+// take 19.7 us; with 116 registers and two workgroups 21.2)
 template <int DT, int R>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void row_parts_kernel(RowPartsArgs a)
 {

@@ -723,7 +723,7 @@ static bool step_fused_possible(const stand_handle *h)
     // never hold more than a fraction of the device (256 compute units, three such workgroups each)
     if (h->B * (h->tail_groups > 0 ? h->tail_groups : 1) > 256) return false;
     if (h->step_mode == STAND_STEP_FUSED) return true;
-    // With few rows the pass is latency-bound and sixteen waves per row serve it better.  With very many the
+    // With few rows the pass is latency-bound, and split rows serve it better (see kRowsFew for where).  With very many the
     // dependent launches are a few per cent of the step, which is all one launch could save, and it varied more
     // from run to run than that (B=128 x 128 nodes: 0.84-0.96 ms against 0.85-0.88 ms).
     return h->B * h->N > kRowsFew && h->B * h->N <= kRowsMany;
