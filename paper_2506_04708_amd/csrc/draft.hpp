@@ -1,5 +1,7 @@
 // draft.hpp -- draft_kernel: multi-level lookup and Gumbel-Top-K along the static tree (paper Sec. 4.2).
 #pragma once
+#include <type_traits>
+
 #include "wave_ops.hpp"
 
 namespace stand {
@@ -57,176 +59,215 @@ __device__ __forceinline__ DraftShared draft_shared_carve(char *base, int N, int
     return s;
 }
 
-__device__ __forceinline__ unsigned long long fingerprint_multiplier_of_lane(int lane)
+// How a node's work is spread over the lanes of a wave: in each row of 16 lanes, G groups of 16 / G lanes hold the same
+// 16 / G candidates (all values of a candidate are in one row, so that they move by data-parallel primitives, never
+// through shared memory).  G = 4 for K <= 16, else 2.
+template <int G>
+struct CandLayout {
+    static constexpr int kPerRow = 16 / G, kSlots = 4 * kPerRow;   // candidates per row, and of the wave
+    static __device__ __forceinline__ int candidate(int lane) { return (lane >> 4) * kPerRow + (lane & (kPerRow - 1)); }
+    static __device__ __forceinline__ int group(int lane) { return (lane & 15) / kPerRow; }
+    static __device__ __forceinline__ int lane_of(int cand) { return cand / kPerRow * 16 + cand % kPerRow; }
+    static constexpr int banks(int g) { return G == 4 ? 1 << g : 3 << (2 * g); }   // lanes of group g as banks of 4 lanes
+    // combined over the groups of a row: rotations by 8 and, with four groups, 4 lanes
+    static __device__ __forceinline__ int any_of_groups(int x)
+    {
+        x |= __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);
+        if (G == 4) x |= __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, true);
+        return x;
+    }
+    static __device__ __forceinline__ int sum_of_groups(int x)
+    {
+        x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);
+        if (G == 4) x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, true);
+        return x;
+    }
+};
+
+// The value eight lanes further in the row of 16: the two halves of a row exchange theirs.
+__device__ __forceinline__ uint32_t other_half(uint32_t x)
 {
-    unsigned long long m = 0ull;
-#pragma unroll
-    for (int i = 0; i < kMaxOrder; ++i) m = lane == i ? fingerprint_multiplier(i) : m;
-    return m;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, true);
 }
 
-// The draft of trajectory b by the NT threads of the calling workgroup (all of them call this).
-//
-// Bound by the instructions of ONE wave per tree level, one level after the other: with clock readings between the
-// parts, a level of a warm 64-node tree took 7 700 cycles, of which a wave waited 300 for memory; the rest was the
-// fingerprint (570), one address computation per order and payload half (1 300), the selection of the winning
-// order's payload (750), Philox and three logarithms (1 650), sixteen readlane comparisons (570) and the copies of
-// the recent tokens (680).  So the work of a node is spread over the lanes a K-entry payload leaves idle: each order
-// is one lane up to its slot's address; payloads of 64 / KP orders arrive with one pair of loads (KP = K rounded up to
-// 8, 16 or 32 lanes); ln mu is taken by the upper 32 lanes while the lower ones take ln U; the ranking compares in
-// 64 / KP groups of lanes against scores in shared memory.  Draft and packing of 32 such trees, back to back:
-// 31.3 -> 21.3 us; the one-launch step of 32 x 64 rows, which ends with its draft: 126 -> 117.6 us.
-// (Table entries are read past the XCD's own caches in every launch form: in the one-launch step other workgroups
-// have just written them, and as ordinary loads they made no repeated call faster and the first call after other work
-// 6 us slower.)
-template <int NT>
-__device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
+// `uniform` of a token that lanes l and l ^ 8 both hold: each runs one of the two multiplications of a round (the same
+// integers as philox4x32_10: lane 0..7 of a row holds words 0 and 3 of the state, lane 8..15 words 2 and 1), so that a
+// round is one multiplication and one exchange long instead of two multiplications.
+__device__ __forceinline__ float uniform_by_halves(uint64_t seed, uint32_t b, uint64_t step, uint32_t node, uint32_t token,
+                                                   uint32_t stream, bool upper)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t x = upper ? (uint32_t)step : token >> 2;
+    uint32_t y = upper ? node | (stream << 24) : b | ((uint32_t)(step >> 32) << 20);
+    const uint32_t mul = upper ? 0xCD9E8D57u : 0xD2511F53u;
+    uint32_t key = upper ? (uint32_t)(seed >> 32) : (uint32_t)seed;
+    const uint32_t key_step = upper ? 0xBB67AE85u : 0x9E3779B9u;
+    asm volatile("" : "+v"(key));   // (the ten keys are formed on the way: kept from node to node they would take ten registers)
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t p = (uint64_t)mul * x;
+        uint32_t t = other_half(y) ^ key;
+        asm("" : "+v"(t));   // (formed beside the multiplication: regrouped, the round would be two instructions longer)
+        x = other_half((uint32_t)(p >> 32)) ^ t;
+        y = (uint32_t)p;
+        key += key_step;
+    }
+    // words 0..3 of the result: x of the lower, y of the upper, x of the upper, y of the lower lane
+    const uint32_t mine = (token & 1u) ? y : x, other = other_half(mine);
+    const bool want_upper = ((token ^ (token >> 1)) & 1u) != 0u;
+    return word_to_uniform(want_upper == upper ? mine : other);
+}
+
+// Levels of the draft of trajectory b (see draft_trajectory): tree levels in sequence, one wave per node.
+template <int NT, int G>
+__device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const DraftShared &sm, int level_reg, long long clen)
+{
+    using L = CandLayout<G>;
+    constexpr int kMaxRounds = kMaxOrder / G;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int32_t *tok = sm.tok;
     int32_t(*recent)[kMaxOrder] = sm.recent;
     unsigned long long *keys = sm.keys[wave];
-    const int N = a.tree.N, K = a.K;
-    // lane d of every wave holds the first node of level d (D + 2 <= 33 entries)
-    const int level_reg = lane < a.tree.D + 2 ? a.tree.level_start[lane] : 0;
-    for (int u = tid; u < N; u += NT) {
-        sm.info[u] = (a.tree.first_child[u] << 8) | a.tree.nchild[u];  // (a leaf's first child, -1, is not looked at)
-        if (u > 0) tok[u] = -1;  // the root's token is set with the context below
-        sm.has[u] = 0;
-    }
-    if (tid <= kMaxOrder) sm.n_hit[tid] = 0u;
-    if (tid >= 1 && tid < kMaxDepth + 2) sm.live[tid] = 0;
-    if (wave == 1) {
-        // Context tail of this trajectory, after appending the tokens committed by this step.  Lane i < 8 holds
-        // the stored tail, lane 8 + j the j-th committed token (W <= 32), all requested at once: the new tail is
-        // the last eight of the first 8 + n lanes.
-        int32_t v = 0;
-        if (lane < kMaxOrder) v = a.ctx_tail[(size_t)b * kMaxOrder + lane];
-        else if (a.append_tok && lane < kMaxOrder + a.W) v = a.append_tok[(size_t)b * a.W + (lane - kMaxOrder)];
-        const int n = a.append_tok ? clamp_len(a.append_len[b], a.W) : 0;
-        const long long len = a.ctx_len[b] + n;
-        const int32_t t = __shfl(v, (lane & (kMaxOrder - 1)) + n);
-        if (lane < kMaxOrder) {
-            recent[0][kMaxOrder - 1 - lane] = t;
-            if (a.append_tok) a.ctx_tail[(size_t)b * kMaxOrder + lane] = t;
-            if (lane == kMaxOrder - 1) { tok[0] = len > 0 ? t : -1; sm.live[0] = len > 0 && t >= 0; }
-        }
-        if (lane == 0) {
-            if (a.append_tok) a.ctx_len[b] = len;
-            *sm.clen = len;
-        }
-    }
-    __syncthreads();
-    const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
-    const int NO = a.omax - a.omin + 1;
-    const unsigned long long term_mul = fingerprint_multiplier_of_lane(lane);
-    const int kp_shift = K <= 8 ? 3 : (K <= 16 ? 4 : 5);  // lanes per payload: 8, 16 or 32
-    const int li = lane & ((1 << kp_shift) - 1), grp = lane >> kp_shift;
-    const int per_round = 64 >> kp_shift, per_round_shift = 6 - kp_shift;
-    const int rounds = (NO + per_round - 1) >> per_round_shift;  // <= kMaxRounds
-    constexpr int kMaxRounds = kMaxOrder / 2;
-    const int half = lane & 31;  // candidates are held twice: lanes 0..K-1 and 32..32+K-1
+    const int N = a.tree.N, K = a.K, NO = a.omax - a.omin + 1;
+    const int cand = L::candidate(lane), grp = L::group(lane);
+    const bool upper = (lane & 8) != 0, has_cand = cand < K;
+    // Lane j < omax of every row forms the term of the token omax - 1 - j positions back; the fingerprint of the last
+    // n = omax - j tokens is then the sum over lanes j, j + 1, ... (three data-parallel moves), so that lane 0 holds the
+    // longest order.
+    const int j16 = lane & 15, n = a.omax - j16;
+    unsigned long long term_mul = 0ull;
+#pragma unroll
+    for (int i = 0; i < kMaxOrder; ++i) term_mul = n == i + 1 ? fingerprint_multiplier(i) : term_mul;
+    const unsigned long long order_term = (unsigned long long)(uint32_t)n * 0x2545F4914F6CDD1DULL;
+    const bool order_lane = n >= a.omin && j16 < a.omax;
+    const int rounds = (NO + G - 1) / G;  // <= kMaxRounds
+    const unsigned payload = 16u + 4u * (unsigned)(has_cand ? cand : 0);   // where the lane's candidate stands in a slot
+    unsigned my_hits = 0u;   // lane n <= kMaxOrder: lookups of this wave answered by order n; lane 0: misses
     int32_t *qid_out = a.draft_qid + (size_t)b * N * K;
     float *qmu_out = a.draft_qmu + (size_t)b * N * K;
     for (int d = 0; d < a.tree.D; ++d) {
         // values read from shared memory that are the same in every lane go to scalar registers
         const int lo = __builtin_amdgcn_readlane(level_reg, d), hi = __builtin_amdgcn_readlane(level_reg, d + 1);
-        if (!__builtin_amdgcn_readfirstlane(sm.live[d])) break;  // a level without a drafted node ends the tree (the same in every wave)
-        for (int u = lo + wave; u < hi; u += NT / 64) {
-            const int4 r_lo = *(const int4 *)&recent[u][0], r_hi = *(const int4 *)&recent[u][4];
-            const int32_t my_recent = recent[u][lane & (kMaxOrder - 1)];
-            const int info = __builtin_amdgcn_readfirstlane(sm.info[u]);
+        // the wave's first node of the level is read together with the flag that ends the tree
+        int live = sm.live[d];
+        int u = lo + wave;
+        int4 r_lo, r_hi;
+        int32_t my_recent;
+        int info, my_tok;
+        auto read_node = [&](int at) {
+            r_lo = *(const int4 *)&recent[at][0]; r_hi = *(const int4 *)&recent[at][4];
+            my_recent = recent[at][(n - 1) & (kMaxOrder - 1)];
+            info = sm.info[at]; my_tok = tok[at];
+        };
+        read_node(u < N ? u : 0);
+        asm volatile("" : "+v"(live), "+v"(info), "+v"(my_tok), "+v"(my_recent));  // (one round trip, not one after the branch)
+        if (!__builtin_amdgcn_readfirstlane(live)) break;  // a level without a drafted node ends the tree (the same in every wave)
+        for (; u < hi; u += NT / 64) {
+            if (u != lo + wave) read_node(u);
+            info = __builtin_amdgcn_readfirstlane(info);
             const int nch = info & 0xFF, first = info >> 8;
-            if (nch == 0 || __builtin_amdgcn_readfirstlane(tok[u]) < 0) continue;
-            // ---- multi-level lookup (paper Sec. 4.2): lane n - 1 takes order n.  The home slot of every
-            // order is read together with its payload in one round trip; only a key that was displaced by linear
-            // probing needs further probes.  Lane i < 8 forms the term of the token i positions back; the sum of
-            // the first n terms of the fingerprint is then an inclusive scan over the lanes (three data-parallel
-            // moves inside a row of 16 lanes), so no lane multiplies more than once.
-            unsigned long long fp = 0ull;
+            if (nch == 0 || __builtin_amdgcn_readfirstlane(my_tok) < 0) continue;
+            // ---- multi-level lookup (paper Sec. 4.2).  The home slot of every order is read together with its
+            // payload in one round trip; only a key that was displaced by linear probing needs further probes.
+            unsigned long long fp;
             {
-                const int n = lane + 1;
                 unsigned long long acc = term_mul * ((unsigned long long)(uint32_t)my_recent + 1u);
-                acc += dpp_fetch_u64<0x111, 0xF>(acc);  // row_shr:1
-                acc += dpp_fetch_u64<0x112, 0xF>(acc);  // row_shr:2
-                acc += dpp_fetch_u64<0x114, 0xF>(acc);  // row_shr:4
-                acc += (unsigned long long)(uint32_t)n * 0x2545F4914F6CDD1DULL;
-                const unsigned long long hsh = fmix64(acc);
-                if (n >= a.omin && n <= a.omax && clen + d >= n) fp = hsh ? hsh : 1ull;
+                acc += dpp_fetch_u64<0x101, 0xF>(acc);  // row_shl:1
+                acc += dpp_fetch_u64<0x102, 0xF>(acc);  // row_shl:2
+                acc += dpp_fetch_u64<0x104, 0xF>(acc);  // row_shl:4
+                fp = fmix64(acc + order_term);
+                fp = fp ? fp : 1ull;
             }
-            const char *home = fp ? a.table + (fp & a.mask) * (unsigned long long)(unsigned)a.slot_bytes : nullptr;
-            unsigned long long home_fp = 0ull;
-            uint32_t home_cnt = 0;
-            if (fp) {
-                home_fp = ld_agent(&((const SlotHeader *)home)->fp);
-                home_cnt = ld_agent(&((const SlotHeader *)home)->count);
-            }
-            // lane group g of round r fetches the payload of order omax - (r * per_round + g)
-            int32_t pid[kMaxRounds];
-            float pmu[kMaxRounds];
-#pragma unroll
-            for (int r = 0; r < kMaxRounds; ++r) {
-                pid[r] = -1; pmu[r] = 0.0f;
-                if (r < rounds) {
-                    const int oi = (r << per_round_shift) + grp;
-                    const unsigned long long at = shfl_u64((unsigned long long)home, (a.omax - 1 - oi) & 63);
-                    if (oi < NO && at && li < K) {
-                        pid[r] = ld_agent((const int32_t *)(at + 16) + li);
-                        pmu[r] = ld_agent((const float *)(at + 16) + K + li);
-                    }
+            // (an order that is not looked up reads the table's first slot: no branch around the loads, which would make
+            // them two round trips)
+            const bool looked_up = order_lane && clen + d >= n;
+            const unsigned long long home = looked_up ? (fp & a.mask) * (unsigned long long)(unsigned)a.slot_bytes : 0ull;
+            const unsigned long long home_fp = ld_agent((const unsigned long long *)(a.table + home));
+            const uint32_t home_cnt = ld_agent((const uint32_t *)(a.table + home + 8));
+            // lane group g of round r fetches the payload of order omax - (r * G + g)
+            int32_t pid[kMaxRounds] = {};
+            uint32_t pmu[kMaxRounds] = {};
+            const int home_lo = (int)(uint32_t)home, home_hi = (int)(uint32_t)(home >> 32);
+            auto fetch = [&](auto round) {
+                constexpr int r = decltype(round)::value;
+                int at_lo = 0, at_hi = 0;
+                auto take = [&](auto group) {   // (row_newbcast: lane r * G + g of the row, to the lanes of group g)
+                    constexpr int g = decltype(group)::value;
+                    at_lo = __builtin_amdgcn_update_dpp(at_lo, home_lo, 0x150 + r * G + g, 0xF, L::banks(g), false);
+                    at_hi = __builtin_amdgcn_update_dpp(at_hi, home_hi, 0x150 + r * G + g, 0xF, L::banks(g), false);
+                };
+                take(std::integral_constant<int, 0>{});
+                take(std::integral_constant<int, 1>{});
+                if constexpr (G == 4) {
+                    take(std::integral_constant<int, 2>{});
+                    take(std::integral_constant<int, 3>{});
                 }
+                const char *at = a.table + (((unsigned long long)(uint32_t)at_hi << 32) | (uint32_t)at_lo) + payload;
+                pid[r] = ld_agent((const int32_t *)at);
+                pmu[r] = ld_agent((const uint32_t *)(at + 4 * K));
+            };
+            fetch(std::integral_constant<int, 0>{});
+            if (rounds > 1) fetch(std::integral_constant<int, 1>{});
+            if constexpr (kMaxRounds > 2) {
+                if (rounds > 2) fetch(std::integral_constant<int, 2>{});
+                if (rounds > 3) fetch(std::integral_constant<int, 3>{});
             }
-            long long hit_slot = -1;
-            if (fp) {
-                if (home_fp == fp) { if (home_cnt > 0) hit_slot = (long long)(fp & a.mask); }
-                else if (home_fp != 0ull) {
+            asm volatile("" :: "v"(home_fp), "v"(home_cnt));   // (all have arrived here, whichever are used below)
+#pragma unroll
+            for (int r = 0; r < kMaxRounds; ++r) asm volatile("" :: "v"(pid[r]), "v"(pmu[r]));
+            bool hit = looked_up && home_fp == fp && home_cnt > 0;
+            unsigned long long slot = fp & a.mask;
+            const bool displaced = looked_up && lane < 16 && home_fp != fp && home_fp != 0ull;
+            if (__builtin_expect(__ballot(displaced) != 0ull, 0)) {
+                if (displaced) {
                     for (int i = 1; i < a.max_probe; ++i) {  // displaced key: keep probing
-                        const uint64_t slot = (fp + (uint64_t)i) & a.mask;
-                        const SlotHeader *h = slot_header(a.table, slot, a.slot_bytes);
+                        const uint64_t s = (fp + (uint64_t)i) & a.mask;
+                        const SlotHeader *h = slot_header(a.table, s, a.slot_bytes);
                         const unsigned long long cur = ld_agent(&h->fp);
-                        if (cur == fp) { if (ld_agent(&h->count) > 0) hit_slot = (long long)slot; break; }
+                        if (cur == fp) { if (ld_agent(&h->count) > 0) { hit = true; slot = s; } break; }
                         if (cur == 0ull) break;
                     }
                 }
             }
-            const unsigned long long hits = __ballot(hit_slot >= 0);
+            const unsigned long long hits = __ballot(hit) & 0xFFFFull;   // (the rows hold the same)
             if (!hits) {
-                if (lane == 0) atomicAdd(&sm.n_hit[0], 1u);
+                my_hits += lane == 0 ? 1u : 0u;
                 continue;
             }
-            const int win = 63 - __builtin_clzll(hits);  // highest lane = longest order
-            const long long slot = (long long)readlane_u64((unsigned long long)hit_slot, win);
-            const unsigned long long win_fp = readlane_u64(fp, win);
-            if (lane == 0) atomicAdd(&sm.n_hit[win + 1], 1u);
-            int32_t id = -1;
-            float mu = 0.0f;
-            if ((unsigned long long)slot == (win_fp & a.mask)) {
-                // the payload fetched with the home slot is the entry's
-                const int oi = a.omax - 1 - win, r_win = oi >> per_round_shift;
-                const int src = ((oi & (per_round - 1)) << kp_shift) + half;
+            const int win = __ffsll((long long)hits) - 1;  // lowest lane = longest order
+            my_hits += lane == a.omax - win ? 1u : 0u;
+            int32_t id;
+            float mu;
+            if (__builtin_expect((__ballot(slot == (fp & a.mask)) >> win) & 1ull, 1)) {
+                // the payload fetched with the home slot is the entry's: from the winning order's group to all groups
+                const int r_win = win / G;
                 int32_t t_id = pid[0];
-                float t_mu = pmu[0];
+                uint32_t t_mu = pmu[0];
 #pragma unroll
                 for (int r = 1; r < kMaxRounds; ++r) if (r == r_win) { t_id = pid[r]; t_mu = pmu[r]; }
-                t_id = __shfl(t_id, src & 63);
-                t_mu = __shfl(t_mu, src & 63);
-                if (half < K) { id = t_id; mu = t_mu; }
-            } else if (half < K) {
-                id = ld_agent(&slot_ids(a.table, (uint64_t)slot, a.slot_bytes)[half]);
-                mu = ld_agent(&slot_mu(a.table, (uint64_t)slot, a.slot_bytes, K)[half]);
+                const bool from = grp == win % G;
+                id = L::any_of_groups(from ? t_id : 0);
+                mu = u2f((uint32_t)L::any_of_groups(from ? (int)t_mu : 0));
+            } else {
+                const char *at = a.table + readlane_u64(slot, win) * (unsigned long long)(unsigned)a.slot_bytes + payload;
+                id = ld_agent((const int32_t *)at);
+                mu = u2f(ld_agent((const uint32_t *)(at + 4 * K)));
+                asm volatile("" : "+v"(id), "+v"(mu));
             }
-            const bool cand = lane < K && mu > 0.0f;
+            // (stored here, so that the acknowledgements have the ranking to arrive before the next level's loads are waited for)
+            if (has_cand && grp == 0) { qid_out[u * K + cand] = id; qmu_out[u * K + cand] = mu; }
+            const bool usable = has_cand && mu > 0.0f;
+            const int ncand = __popcll(__ballot(usable && grp == 0));
             int rank = kMaxK;  // child rank of this lane's candidate (>= nch: not drafted)
             if (a.mode == 1) {
                 // ---- sequential sampling without replacement (the ablation's plain stochastic
                 // drafting): draw j takes the first remaining candidate, in stored order, whose
-                // running sum of mu exceeds U_j * (sum of the remaining mu)
+                // running sum of mu exceeds U_j * (sum of the remaining mu).  Lane i holds candidate i here.
                 const float u_l = lane < nch ? uniform(a.seed, (uint32_t)b, a.step, (uint32_t)u, (uint32_t)lane, kStreamDraft) : 0.0f;
-                bool left = cand;
-                const int ncand_all = __popcll(__ballot(cand));
-                const int draws = nch < ncand_all ? nch : ncand_all;
+                const float mu_l = __shfl(mu, L::lane_of(lane & (L::kSlots - 1)));
+                bool left = lane < K && mu_l > 0.0f;
+                const int draws = nch < ncand ? nch : ncand;
                 for (int j = 0; j < draws; ++j) {
-                    const float mleft = left ? mu : 0.0f;
+                    const float mleft = left ? mu_l : 0.0f;
                     const float z = wave_tree_sum(mleft);
                     const float t = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(u_l), j)) * z;
                     float acc = 0.0f;
@@ -242,52 +283,109 @@ __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, cons
                     if (pick < 0) pick = last;
                     if (lane == pick) { rank = j; left = false; }
                 }
+                rank = __shfl(rank, cand);
             } else {
                 // ---- Gumbel-Top-K (paper Sec. 4.2): score = ln mu - ln(-ln U), the largest scores in
                 // order; deterministic drafting (Sec. 3.1): the largest means themselves
                 unsigned long long key;
                 if (a.mode == 2) key = rank_key(mu, (uint32_t)id);
                 else {
-                    const float U = uniform(a.seed, (uint32_t)b, a.step, (uint32_t)u, (uint32_t)id, kStreamDraft);
-                    const float lnx = exact_log(lane < 32 ? U : (mu > 0.0f ? mu : 1.0f));
-                    const float ln_mu = __shfl_xor(lnx, 32);
-                    const float g = exact_log(lane < 32 ? -lnx : 1.0f);
-                    key = rank_key(ln_mu - g, (uint32_t)id);
+                    // ln mu in the upper half of a row while the lower one takes ln U
+                    const float U = uniform_by_halves(a.seed, (uint32_t)b, a.step, (uint32_t)u, (uint32_t)id, kStreamDraft, upper);
+                    const float lnx = exact_log(upper ? (mu > 0.0f ? mu : 1.0f) : U);
+                    const float ln_mu = u2f(other_half(f2u(lnx)));
+                    const float g = exact_log(upper ? 1.0f : -lnx);
+                    key = rank_key(ln_mu - g, (uint32_t)id);   // (in the lower half)
                 }
-                // lane group g counts, for candidate li, the larger ones among every group's share of the scores;
-                // lanes without a candidate hold key 0, which is above no key
-                if (lane < kMaxK) keys[lane] = cand ? key : 0ull;
+                // each group compares the candidate with its share of the scores; an empty place holds key 0, which is
+                // above no key
+                if (grp == 0) keys[cand] = usable ? key : 0ull;
                 __builtin_amdgcn_wave_barrier();
-                const unsigned long long mine = keys[li];
-                rank = 0;
-                const int share = 1 << (2 * kp_shift - 6);  // KP * KP / 64: 1, 4 or 16 scores per group
+                const unsigned long long mine = keys[cand];
+                constexpr int share = L::kSlots / G;   // 4 or 16
                 const unsigned long long *ks = keys + grp * share;
-                if (kp_shift == 3) rank += ks[0] > mine ? 1 : 0;
-                else {
-                    for (int q = 0; q < share; q += 4) {
-                        const unsigned long long k0 = ks[q], k1 = ks[q + 1], k2 = ks[q + 2], k3 = ks[q + 3];
-                        rank += (k0 > mine ? 1 : 0) + (k1 > mine ? 1 : 0) + (k2 > mine ? 1 : 0) + (k3 > mine ? 1 : 0);
-                    }
-                }
-                rank += __shfl_xor(rank, 32);
-                if (kp_shift <= 4) rank += __shfl_xor(rank, 16);
-                if (kp_shift == 3) rank += __shfl_xor(rank, 8);
+                rank = 0;
+#pragma unroll
+                for (int q = 0; q < share; ++q) rank += ks[q] > mine ? 1 : 0;
+                rank = L::sum_of_groups(rank);
                 __builtin_amdgcn_wave_barrier();
             }
-            if (cand && rank < nch) {
+            if (usable && grp == 0 && rank < nch) {
                 const int child = first + rank;
                 tok[child] = id;
                 *(int4 *)&recent[child][0] = make_int4(id, r_lo.x, r_lo.y, r_lo.z);
                 *(int4 *)&recent[child][4] = make_int4(r_lo.w, r_hi.x, r_hi.y, r_hi.z);
                 sm.live[d + 1] = 1;
             }
-            const int ncand = __popcll(__ballot(cand));
             if (lane == 0) sm.has[u] = ncand < nch ? ncand : nch;
-            if (lane < K) { qid_out[u * K + lane] = id; qmu_out[u * K + lane] = mu; }
         }
         __syncthreads();
     }
     // (counted per workgroup: hundreds of lookups of a launch would add to the same line one after the other)
+    if (my_hits) atomicAdd(&sm.n_hit[lane], my_hits);
+    __syncthreads();
+}
+
+// The draft of trajectory b by the NT threads of the calling workgroup (all of them call this).
+//
+// Bound by the instructions of ONE wave per tree level, one level after the other, and one round trip to the table per
+// level.  So a node's dependent chain is kept short: its values never leave the rows of 16 lanes that hold them
+// (CandLayout: exchanges by data-parallel primitives, not through shared memory), the two multiplications of a Philox
+// round run side by side (53 cycles a round instead of 107), ln mu is taken beside ln U, header and payload of every
+// order are requested without a branch between them (which had made two round trips of them), a node's outputs are stored
+// before its ranking, and nothing in the level loop waits for a store.  With clock readings between the parts a level of a
+// warm 64-node tree went from about 4 700 to 2 900 cycles; draft of 32 such trees 19.7 -> 15.0 us, steps of 32 x 64 rows
+// x 152 064 154.3 -> 149.9 us (separate launches) and 116.9 -> 114.3 us (one launch), of 8 x 32 49.3 -> 47.1 us.
+// (Table entries are read past the XCD's own caches in every launch form: in the one-launch step other workgroups
+// have just written them, and as ordinary loads they made no repeated call faster and the first call after other work
+// 6 us slower.)
+template <int NT>
+__device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t *tok = sm.tok;
+    int32_t(*recent)[kMaxOrder] = sm.recent;
+    const int N = a.tree.N;
+    // ---- everything that is read from memory is requested at once.  Lane d of every wave holds the first node of level d
+    // (D + 2 <= 33 entries).  Context tail of this trajectory, after appending the tokens committed by this step: lane
+    // i < 8 of the second wave holds the stored tail, lane 8 + j the j-th committed token (W <= 32); the new tail is the
+    // last eight of the first 8 + n lanes.
+    const bool appends = a.append_tok != nullptr;
+    int32_t ctx = 0, n = 0;
+    long long len = 0;
+    if (wave == 1) {
+        if (lane < kMaxOrder) ctx = a.ctx_tail[(size_t)b * kMaxOrder + lane];
+        else if (appends && lane < kMaxOrder + a.W) ctx = a.append_tok[(size_t)b * a.W + (lane - kMaxOrder)];
+        if (appends) n = a.append_len[b];
+        len = a.ctx_len[b];
+    }
+    int level_reg = lane < a.tree.D + 2 ? a.tree.level_start[lane] : 0;
+    for (int u = tid; u < N; u += NT) {
+        sm.info[u] = (a.tree.first_child[u] << 8) | a.tree.nchild[u];  // (a leaf's first child, -1, is not looked at)
+        if (u > 0) tok[u] = -1;  // the root's token is set with the context below
+        sm.has[u] = 0;
+    }
+    if (tid <= kMaxOrder) sm.n_hit[tid] = 0u;
+    if (tid >= 1 && tid < kMaxDepth + 2) sm.live[tid] = 0;
+    if (wave == 1) {
+        n = clamp_len(n, a.W);
+        len += n;
+        const int32_t t = __shfl(ctx, (lane & (kMaxOrder - 1)) + n);
+        if (lane < kMaxOrder) {
+            recent[0][kMaxOrder - 1 - lane] = t;
+            if (appends) a.ctx_tail[(size_t)b * kMaxOrder + lane] = t;
+            if (lane == kMaxOrder - 1) { tok[0] = len > 0 ? t : -1; sm.live[0] = len > 0 && t >= 0; }
+        }
+        if (lane == 0) {
+            if (appends) a.ctx_len[b] = len;
+            *sm.clen = len;
+        }
+    }
+    asm volatile("" : "+v"(level_reg));   // (here: waited for inside the loop, it would wait for the stores of every level)
+    __syncthreads();
+    const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
+    if (a.K <= 16) draft_levels<NT, 4>(a, b, sm, level_reg, clen);
+    else draft_levels<NT, 2>(a, b, sm, level_reg, clen);
     if (tid <= a.omax) {
         const unsigned c = sm.n_hit[tid];
         if (c) atomicAdd(&a.stats[tid == 0 ? (int)kStatMisses : (int)kStatHits + tid], (unsigned long long)c);

@@ -80,6 +80,18 @@ def test_lockstep_draft_payload_layouts(gpu, K, omin, omax, mode):
     _say("  -> %s" % info)
 
 
+@pytest.mark.parametrize("K,omin,omax,mode", [(1, 1, 4, 0), (15, 2, 5, 1), (16, 1, 8, 1), (17, 1, 2, 1), (31, 1, 5, 0), (32, 2, 8, 1), (20, 1, 4, 2)])
+def test_lockstep_draft_candidates_in_rows_of_lanes(gpu, K, omin, omax, mode):
+    """The draft holds a node's candidates four (K <= 16) or eight to a row of 16 lanes: both edges with every drafting mode,
+    as one launch (the other form is in the test above)."""
+    binding, lockstep = gpu
+    over = dict(V=271, B=3, rho=0.8, K=K, order_min=omin, order_max=omax, draft_mode=mode, step_plan=(FUSED, 2, 0, 0))
+    _say("draft candidates %s" % over)
+    w = synth.Workload("cfg1", run_steps=20, **over)
+    info = lockstep.run_lockstep(w, 20, mode="step", capacity=1 << 11, forced=True, check_rows=False, table_every=5)
+    _say("  -> %s" % info)
+
+
 @pytest.mark.parametrize("name,over,steps,forced", [
     ("cfg1", dict(V=4096, B=2, rho=0.7, step_plan=(FUSED, 2, 0, 0)), 40, True),            # few rows, one launch forced
     ("cfg1", dict(V=2003, B=3, rho=0.7, dtype="bf16", step_plan=(FUSED, 1, 1, 0)), 40, True),   # misaligned rows, one tail workgroup
