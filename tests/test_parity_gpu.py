@@ -80,7 +80,7 @@ def test_lockstep_draft_payload_layouts(gpu, K, omin, omax, mode):
     _say("  -> %s" % info)
 
 
-@pytest.mark.parametrize("K,omin,omax,mode", [(1, 1, 4, 0), (15, 2, 5, 1), (16, 1, 8, 1), (17, 1, 2, 1), (31, 1, 5, 0), (32, 2, 8, 1), (20, 1, 4, 2)])
+@pytest.mark.parametrize("K,omin,omax,mode", [(5, 1, 4, 0), (15, 2, 5, 1), (16, 1, 8, 1), (17, 1, 2, 1), (31, 1, 5, 0), (32, 2, 8, 1), (20, 1, 4, 2)])
 def test_lockstep_draft_candidates_in_rows_of_lanes(gpu, K, omin, omax, mode):
     """The draft holds a node's candidates four (K <= 16) or eight to a row of 16 lanes: both edges with every drafting mode,
     as one launch (the other form is in the test above)."""
