@@ -88,11 +88,13 @@ def host_description():
         return "%d CPUs usable by this process" % len(os.sched_getaffinity(0))
 
 
-def launch_names(fused, B, rows, update_mode):
+def launch_names(fused, B, rows, update_mode, small_batch=False):
     """(kernel that reads the logits, how the step is issued).  The one workload here of at most 512 rows has its rows
-    split over workgroups; one trajectory's accepted-path step ends in one launch."""
+    split over workgroups; what follows the rows of a small batch (up to 64 trajectories, accepted-path updates) is one launch."""
     if fused:
         return "stand_step_kernel", "one launch"
+    if small_batch:
+        return "row_parts_kernel" if rows <= 512 else "row_pass_kernel", "two launches"
     return ("row_parts_kernel" if rows <= 512 else "row_pass_kernel",
             "three launches" if B == 1 and update_mode == 0 else "five launches")
 
@@ -380,7 +382,7 @@ def measure(args, np, torch, binding, synth, peak, max_peaks, K_steps, W_steps, 
     step_bytes = logits_bytes + w.B * w.V * 2 + rows * (8 + 12 * w.K) + 1_200_000 + 500_000
     row_bytes = logits_bytes + rows * (8 + 12 * w.K)
     fused = h2.step_is_one_launch()
-    kernel, issue = launch_names(fused, w.B, rows, args.update_mode)
+    kernel, issue = launch_names(fused, w.B, rows, args.update_mode, w.B <= 64 and args.update_mode == 0)
     kbytes = step_bytes if fused else row_bytes
     # HBM bytes per launch of that kernel from profiler counters, if the committed summary holds them
     traffic = traffic_commit = None

@@ -339,8 +339,10 @@ __device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const Dr
 // (Table entries are read past the XCD's own caches in every launch form: in the one-launch step other workgroups
 // have just written them, and as ordinary loads they made no repeated call faster and the first call after other work
 // 6 us slower.)
+// draft_prepare brings the tree and the context (after appending the committed tokens) into shared memory: it needs none
+// of the table, so a caller that waits for other workgroups' updates calls it meanwhile.  Returns what draft_run takes.
 template <int NT>
-__device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
+__device__ __forceinline__ int draft_prepare(const DraftArgs &a, int b, const DraftShared &sm)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int32_t *tok = sm.tok;
@@ -382,6 +384,15 @@ __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, cons
         }
     }
     asm volatile("" : "+v"(level_reg));   // (here: waited for inside the loop, it would wait for the stores of every level)
+    return level_reg;
+}
+
+template <int NT>
+__device__ __forceinline__ void draft_run(const DraftArgs &a, int b, const DraftShared &sm, int level_reg)
+{
+    const int tid = threadIdx.x, N = a.tree.N;
+    const int32_t *tok = sm.tok;
+    const int32_t(*recent)[kMaxOrder] = sm.recent;
     __syncthreads();
     const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
     if (a.K <= 16) draft_levels<NT, 4>(a, b, sm, level_reg, clen);
@@ -398,6 +409,12 @@ __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, cons
     if (a.recent_out)
         for (int i = tid; i < N * kMaxOrder; i += NT)
             if (tok[i / kMaxOrder] >= 0) a.recent_out[(size_t)b * N * kMaxOrder + i] = recent[i / kMaxOrder][i % kMaxOrder];
+}
+
+template <int NT>
+__device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
+{
+    draft_run<NT>(a, b, sm, draft_prepare<NT>(a, b, sm));
 }
 
 __global__ __launch_bounds__(kDraftThreads) void draft_kernel(DraftArgs a)

@@ -16,7 +16,7 @@
 //                    commit_scan_kernel  top-K of caller-given rows (update without verify), many rows
 //   table_merge.hpp  merge_apply_kernel  running-mean merge into the open-addressing table (Sec. 4.1)
 //   draft.hpp        draft_kernel        multi-level lookup + Gumbel-Top-K along the static tree (Sec. 4.2)
-//   path_tail.hpp    path_tail_kernel    one trajectory: everything after the exact sums in one workgroup
+//   step_tail.hpp    step_tail_kernel    small batches: everything after the row kernel in one launch
 //   step_fused.hpp   stand_step_kernel   the whole step in one launch: rows of the tree's upper levels, then
 //                                        the dependent tail beside the remaining rows (bounded waits on
 //                                        device-scope counters)
@@ -38,6 +38,6 @@
 #include "table_merge.hpp"
 #include "path_pass.hpp"
 #include "draft.hpp"
-#include "path_tail.hpp"
+#include "step_tail.hpp"
 #include "step_fused.hpp"
 #include "aux_kernels.hpp"

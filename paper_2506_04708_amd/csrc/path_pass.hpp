@@ -212,21 +212,27 @@ struct FinishShared {
     int32_t top0;                       // the row's best token
 };
 
-// masked integer masses of the EPV elements of vector idx (elements e0 .. e0 + EPV - 1 of the row)
+// integer masses of the EPV elements of a vector; those in `without` count nothing
 template <int DT>
-__device__ __forceinline__ void vector_masses(const uint4 &w, int e0, float m, float c, int shift, const FinishShared &sh,
-                                              unsigned long long *f)
+__device__ __forceinline__ void vector_masses(const uint4 &w, uint32_t without, float m, float c, int shift, unsigned long long *f)
 {
     constexpr int EPV = VecTraits<DT>::EPV;
     float x[EPV];
     unpack<DT>(w, x);
+#pragma unroll
+    for (int q = 0; q < EPV; ++q) f[q] = ((without >> q) & 1u) ? 0ull : fixed_mass(exact_exp2(scaled_offset(x[q], m, c)), shift);
+}
+// the same for elements e0 .. e0 + EPV - 1 of the row without the stored ids
+template <int DT>
+__device__ __forceinline__ void vector_masses(const uint4 &w, int e0, float m, float c, int shift, const FinishShared &sh,
+                                              unsigned long long *f)
+{
     uint32_t bits = 0u;
     for (int q = 0; q < sh.nsup; ++q) {
         const uint32_t d = (uint32_t)(sh.sup_id[q] - e0);
-        if (d < (uint32_t)EPV) bits |= 1u << d;
+        if (d < (uint32_t)VecTraits<DT>::EPV) bits |= 1u << d;
     }
-#pragma unroll
-    for (int q = 0; q < EPV; ++q) f[q] = ((bits >> q) & 1u) ? 0ull : fixed_mass(exact_exp2(scaled_offset(x[q], m, c)), shift);
+    vector_masses<DT>(w, bits, m, c, shift, f);
 }
 // Update mode: maximum and top-K of the given commit rows (one workgroup of 4 waves per row).
 struct CommitScanArgs {
@@ -239,6 +245,7 @@ struct CommitScanArgs {
     float *pr_m;          // [B*W]
     int32_t *pr_top_idx;  // [B*W][K]
     float *pr_top_l;      // [B*W][K]
+    SumClear clear;
 };
 
 template <int DT>
@@ -250,6 +257,7 @@ __global__ __launch_bounds__(256) void commit_scan_kernel(CommitScanArgs a)
     __shared__ int part_cnt[4];
     const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int node;
+    a.clear.row(b, j);
     if (a.all_nodes) {
         if (a.draft_tok[(size_t)b * a.N + j] < 0) return;
         node = j;
@@ -283,25 +291,78 @@ __global__ __launch_bounds__(256) void commit_scan_kernel(CommitScanArgs a)
 }
 
 
-// Finishes row slot j of trajectory b, whose row is tree node `node`: its observation (paper Sec. 4.1:
-// top-k ids and probabilities with the exact normaliser) and, at the stop row of a verification, the
-// replay of the node's accept tests with exact probabilities and the resampled token.  A row that is
-// not a stop row is finished by ONE wave (wave = 0, tid = lane); the stop row by all NT threads of the
-// workgroup, which all call this with their wave and thread numbers.  m: the row's maximum.  Wave 0's
-// lanes hold the stop node's proposal (my_id, my_mu), the row's logits at those ids (my_l) and the
-// tokens of the drafted children (ch); nch / fc / len as in the stop record.  `walked`: the node's outcome as
-// the caller followed it (a path node that is not the stop node is replayed against it), or -2: read it from
-// the row pass's results.
+// The row's top-K: lane i < K its i-th best.
+__device__ __forceinline__ void load_top(const PathArgs &a, int src, int lane, int32_t &id, float &l)
+{
+    if (lane >= a.K) return;
+    if (a.top_pub) {
+        // (the caller has seen these words carry this launch's mark)
+        const unsigned long long tw = ld_agent(&a.top_pub[(size_t)src * a.K + lane]);
+        id = top_pub_id(tw); l = top_pub_logit(tw);
+    } else {
+        id = a.src_top_idx[(size_t)src * a.K + lane]; l = a.src_top_l[(size_t)src * a.K + lane];
+    }
+}
+
+// Observation of row slot j of trajectory b (paper Sec. 4.1: top-k ids and probabilities), lane i < K its i-th best.
+__device__ __forceinline__ void write_observation(const PathArgs &a, int b, int j, int32_t id, float l, float m, float s, int lane)
+{
+    if (lane < a.K) {
+        st_agent(&a.obs_idx[((size_t)b * a.R + j) * a.K + lane], id);
+        st_agent(&a.obs_p[((size_t)b * a.R + j) * a.K + lane], exact_exp2(scaled_offset(l, m, a.c)) / s);
+    }
+}
+
+// Finishes row slot j of trajectory b, whose row is tree node `node` and not the stop row of a verification, by ONE wave:
+// its observation and, on the path of a verification, a replay of the row pass's decision.  m: the row's maximum.
+// get_part() gives the lane its share of the row's exact sum; it is called where the sum is needed (a caller may wait for
+// it there).  `walked`: the node's outcome as the caller followed it, or -2: read it from the row pass's results.
+template <int DT, typename GetPart>
+__device__ __forceinline__ void finish_upper_row(const PathArgs &a, int b, int j, int node, float m, const GetPart &get_part, int lane,
+                                                 int walked = -2)
+{
+    const int row = b * a.N + node;
+    const int src = a.mode == 0 ? row : b * a.R + j;
+    const char *rowp = (const char *)a.logits + (size_t)row * (size_t)a.V * VecTraits<DT>::ES;
+    int32_t o_idx = 0;
+    float o_l = 0.0f;
+    load_top(a, src, lane, o_idx, o_l);
+    // the self-check's inputs: the accept tests again with exact probabilities must name the child the row pass (with the
+    // fast normaliser and its error bound) has named
+    int c_n = 0, c_fc = -1;
+    int32_t c_id = -1, c_ch = -1;
+    float c_mu = 0.0f, c_l = 0.0f;
+    if (a.mode == 0) { c_n = a.draft_has[row]; c_fc = a.tree.first_child[node]; }
+    if (c_n > 0) {
+        if (lane < a.K) { c_id = a.draft_qid[(size_t)row * a.K + lane]; c_mu = a.draft_qmu[(size_t)row * a.K + lane]; }
+        if (lane < c_n && lane < kMaxK && c_fc >= 0 && c_fc + lane < a.N) c_ch = a.draft_tok[(size_t)b * a.N + c_fc + lane];
+        if ((uint32_t)c_id >= (uint32_t)a.V) { c_id = -1; c_mu = 0.0f; }  // never index outside the row
+        else c_l = load_scalar<DT>(rowp, c_id);
+    }
+    const float s = normaliser_from_fixed(wave_sum_u64(get_part()), a.fx_shift);
+    write_observation(a, b, j, o_idx, o_l, m, s, lane);
+    if (c_n > 0) {
+        const float c_e = c_id >= 0 ? exact_exp2(scaled_offset(c_l, m, a.c)) : 0.0f;
+        const NodeTests ct = node_tests_prepare(lane, a.K, c_id, c_mu, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc);
+        const NodeResult nr = wave_node_outcome(lane, a.K, ct, c_e / s, c_n, false, 0.0f, a.onehot);
+        if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row])) atomicAdd(&a.stats[kStatMismatch], 1ull);
+    }
+}
+
+// Finishes the stop row of a verification, row slot j of trajectory b and tree node `node`: its observation, the replay of
+// the node's accept tests with exact probabilities and the resampled token.  All NT threads of the workgroup call this with
+// their wave and thread numbers.  m: the row's maximum.  Wave 0's lanes hold the stop node's proposal (my_id, my_mu), the
+// row's logits at those ids (my_l), the tokens of the drafted children (ch) and, lane q < nseg, the partial sum of segment
+// q (part); nch / fc / len as in the stop record.
 template <int DT, int NT>
-__device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, int b, int j, int node, bool stop, float m,
-                                           int nch, int fc, int len, int32_t my_id, float my_mu, float my_l, int32_t ch,
-                                           unsigned long long part, int tid, int wave, int walked = -2)
+__device__ __forceinline__ void finish_stop_row(const PathArgs &a, FinishShared &sh, int b, int j, int node, float m, int nch, int fc,
+                                                int len, int32_t my_id, float my_mu, float my_l, int32_t ch, unsigned long long part,
+                                                int tid, int wave)
 {
     constexpr int ES = VecTraits<DT>::ES, EPV = VecTraits<DT>::EPV;
     const int lane = tid & 63;
     const int nseg = a.nseg;
     const int row = b * a.N + node;
-    const int src = a.mode == 0 ? row : b * a.R + j;
     const char *rowp = (const char *)a.logits + (size_t)row * (size_t)a.V * ES;
     const RowGeom g = row_geom<DT>(rowp, a.V);
     const int per = (g.nvec + nseg - 1) / nseg;
@@ -309,53 +370,20 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
     if (wave == 0) {
         int32_t o_idx = 0;
         float o_l = 0.0f;
-        if (lane < a.K) {
-            if (a.top_pub) {
-                // (the caller has seen these words carry this launch's mark)
-                const unsigned long long tw = ld_agent(&a.top_pub[(size_t)src * a.K + lane]);
-                o_idx = top_pub_id(tw); o_l = top_pub_logit(tw);
-            } else {
-                o_idx = a.src_top_idx[(size_t)src * a.K + lane]; o_l = a.src_top_l[(size_t)src * a.K + lane];
-            }
-        }
-        if (stop && lane == 0) sh.top0 = o_idx;
-        if (!stop || nch <= 0 || lane >= a.K) { my_id = -1; my_mu = 0.0f; }
+        load_top(a, row, lane, o_idx, o_l);
+        if (lane == 0) sh.top0 = o_idx;
+        if (nch <= 0 || lane >= a.K) { my_id = -1; my_mu = 0.0f; }
         const float my_e = my_id >= 0 ? exact_exp2(scaled_offset(my_l, m, a.c)) : 0.0f;
         int edge_id = -1;
-        if (stop) {
-            if (lane < g.head) edge_id = lane;
-            else if (lane < g.head + g.ntail) edge_id = g.tail0 + (lane - g.head);
-        }
+        if (lane < g.head) edge_id = lane;
+        else if (lane < g.head + g.ntail) edge_id = g.tail0 + (lane - g.head);
         const unsigned long long edge_f =
             edge_id >= 0 ? fixed_mass(exact_exp2(scaled_offset(load_scalar<DT>(rowp, edge_id), m, a.c)), a.fx_shift) : 0ull;
 
         NodeTests st;
-        if (stop && nch > 0) st = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+        if (nch > 0) st = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
         const unsigned long long S = wave_sum_u64(part);
         const float s = normaliser_from_fixed(S, a.fx_shift);
-        if (!stop) {
-            // observation of this row (paper Sec. 4.1: top-k ids and probabilities)
-            if (lane < a.K) {
-                st_agent(&a.obs_idx[((size_t)b * a.R + j) * a.K + lane], o_idx);
-                st_agent(&a.obs_p[((size_t)b * a.R + j) * a.K + lane], exact_exp2(scaled_offset(o_l, m, a.c)) / s);
-            }
-            if (a.mode == 0 && a.draft_has[row] > 0) {
-                // self-check of the row pass's decision at this node (taken with the fast normaliser and its
-                // error bound): the accept tests again with exact probabilities must name the same child
-                const int c_n = a.draft_has[row], c_fc = a.tree.first_child[node];
-                int32_t c_id = -1, c_ch = -1;
-                float c_mu = 0.0f, c_l = 0.0f;
-                if (lane < a.K) { c_id = a.draft_qid[(size_t)row * a.K + lane]; c_mu = a.draft_qmu[(size_t)row * a.K + lane]; }
-                if (lane < c_n && lane < kMaxK && c_fc >= 0 && c_fc + lane < a.N) c_ch = a.draft_tok[(size_t)b * a.N + c_fc + lane];
-                if ((uint32_t)c_id >= (uint32_t)a.V) { c_id = -1; c_mu = 0.0f; }  // never index outside the row
-                else c_l = load_scalar<DT>(rowp, c_id);
-                const float c_e = c_id >= 0 ? exact_exp2(scaled_offset(c_l, m, a.c)) : 0.0f;
-                const NodeTests ct = node_tests_prepare(lane, a.K, c_id, c_mu, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc);
-                const NodeResult nr = wave_node_outcome(lane, a.K, ct, c_e / s, c_n, false, 0.0f, a.onehot);
-                if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row])) atomicAdd(&a.stats[kStatMismatch], 1ull);
-            }
-            return;
-        }
 
         // ---- residual at the stop node: replay its accept sequence with exact probabilities
         bool support = nch > 0;
@@ -371,10 +399,7 @@ __device__ __forceinline__ void finish_row(const PathArgs &a, FinishShared &sh, 
             if (!(rs <= 2.0f) || !(rho < __builtin_inff())) support = false;
         }
         // the stop row's observation (its loads have had the replay to arrive)
-        if (lane < a.K) {
-            st_agent(&a.obs_idx[((size_t)b * a.R + j) * a.K + lane], o_idx);
-            st_agent(&a.obs_p[((size_t)b * a.R + j) * a.K + lane], exact_exp2(scaled_offset(o_l, m, a.c)) / s);
-        }
+        write_observation(a, b, j, o_idx, o_l, m, s, lane);
         // ---- integer masses (unit 2^-(40 - fx_shift) / s * rho): support token i weighs floor(r_i * (S / rho)),
         // a token outside the support the term it contributes to S
         const bool has_edge = g.head + g.ntail > 0;  // rows that start on a 16-byte boundary have none
@@ -591,8 +616,8 @@ __global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a,
     if (block < stop_blocks) {
         StopRow st;
         st.request(a, block, lane, wave == 0);
-        finish_row<DT, kFinishThreads>(a, sh, block, st.j, st.node, true, st.m, st.nch, st.fc, st.len, st.my_id, st.my_mu, st.my_l, st.ch,
-                                       st.part, tid, wave);
+        finish_stop_row<DT, kFinishThreads>(a, sh, block, st.j, st.node, st.m, st.nch, st.fc, st.len, st.my_id, st.my_mu, st.my_l, st.ch,
+                                            st.part, tid, wave);
         return;
     }
     const int slot = (block - stop_blocks) * (kFinishThreads / 64) + wave;
@@ -609,7 +634,7 @@ __global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a,
     }
     if (node < 0) return;
     const float m = a.src_m[a.mode == 0 ? b * a.N + node : b * a.R + j];
-    finish_row<DT, kFinishThreads>(a, sh, b, j, node, false, m, 0, -1, 0, -1, 0.0f, 0.0f, -1, part, lane, 0);
+    finish_upper_row<DT>(a, b, j, node, m, [&] { return part; }, lane);
 }
 
 }  // namespace stand

@@ -132,6 +132,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     // grid (parts, trajectories, nodes or commit positions): all trajectories' rows of node 0 first
     const int part = blockIdx.x, b = blockIdx.y, j = blockIdx.z, slot = j * r.B + b;
     int node = j;
+    if (part == 0) r.clear.row(b, j);
     if (a.commit) {
         if (a.all_nodes) node = r.draft_tok[(size_t)b * r.N + j] >= 0 ? j : -1;
         else {

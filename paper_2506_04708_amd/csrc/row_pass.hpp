@@ -466,14 +466,35 @@ __device__ __forceinline__ unsigned long long fixed_mass(float e, int shift)
     return ((unsigned long long)hi << (20 - shift)) + (lo >> shift);
 }
 
-// Exact fixed-point sum over the vectors [v0, v1) of a row (plus the edge elements if with_edge),
-// strided over `nthreads` threads; returns this thread's partial sum_v floor(E((l_v - m) c) * 2^(40 - shift)).
+// Adds the terms floor(E((l_v - m) c) * 2^40) / 2^shift of a vector's elements to acc, down = shift << 23; those in `without`
+// add nothing.
 // Bound by the vector ALUs (a handful of rows read from the caches), so a term is formed in few instructions, with
 // the operations of exact_exp2: y + (1.5 2^23 + 40) leaves rint(y) + 40 in the low mantissa bits (an even constant, so
 // ties go as in rint), and that sum shifted to the exponent turns 2^f into the scaled term in one integer addition.
 // Truncated, the term is an integer of at most 2^40 held exactly in binary64; a lane adds at most 64 of them before they
 // go to the integer sum.  (Split into two 20-bit integers, as before, large terms cost nine instructions instead of
 // three: path_exact_kernel over 128 rows of 304 KB 15.2 -> 13.4 us, 672 rows of 100 KB at T = 1 27 -> 23.7.)
+template <int DT>
+__device__ __forceinline__ void add_exact_terms(const uint4 &w, uint32_t without, float m, float c, uint32_t down, double &acc)
+{
+    constexpr int EPV = VecTraits<DT>::EPV;
+    constexpr float kRound = 12582912.0f + 40.0f;
+    float x[EPV];
+    unpack<DT>(w, x);
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) {
+        // y is clamped at -64 instead of tested: E(-64) = 2^-64 contributes 0 like the E = 0 of smaller y, and a NaN is
+        // clamped as well
+        const float y = fmaxf(scaled_offset(x[j], m, c), -64.0f);
+        const float k = y + kRound;
+        const float p = exact_exp2_fraction(y - (k - kRound));
+        const float term = __builtin_truncf(u2f((f2u(k) << 23) + (f2u(p) - down)));
+        acc += (double)(((without >> j) & 1u) ? 0.0f : term);
+    }
+}
+
+// Exact fixed-point sum over the vectors [v0, v1) of a row (plus the edge elements if with_edge),
+// strided over `nthreads` threads; returns this thread's partial sum_v floor(E((l_v - m) c) * 2^(40 - shift)).
 template <int DT, int INFLIGHT = 4>
 __device__ __forceinline__ unsigned long long thread_exact_partial(const void *rowp, const RowGeom &g, int v0, int v1,
                                                                    bool with_edge, float m, float c, int t, int nthreads,
@@ -491,23 +512,7 @@ __device__ __forceinline__ unsigned long long thread_exact_partial(const void *r
     // INFLIGHT independent loads are issued before any of them is used (indices clamped, so the
     // number of loads in flight does not depend on the position in the row)
     const int vlast = v1 > v0 ? v1 - 1 : v0;
-    constexpr float kRound = 12582912.0f + 40.0f;
     const uint32_t down = (uint32_t)shift << 23;  // (units of 2^-(40 - shift))
-    // y is clamped at -64 instead of tested: E(-64) = 2^-64 contributes 0 like the E = 0 of smaller y, and a NaN is
-    // clamped as well
-    auto add_vec = [&](const uint4 &w, int idx, double &acc) {
-        if (idx < v1) {
-            float x[EPV];
-            unpack<DT>(w, x);
-#pragma unroll
-            for (int j = 0; j < EPV; ++j) {
-                const float y = fmaxf(scaled_offset(x[j], m, c), -64.0f);
-                const float k = y + kRound;
-                const float p = exact_exp2_fraction(y - (k - kRound));
-                acc += (double)__builtin_truncf(u2f((f2u(k) << 23) + (f2u(p) - down)));
-            }
-        }
-    };
     for (int base = v0 + t; base < v1; base += INFLIGHT * nthreads) {
         uint4 w[INFLIGHT];
 #pragma unroll
@@ -517,7 +522,8 @@ __device__ __forceinline__ unsigned long long thread_exact_partial(const void *r
         }
         double acc = 0.0;
 #pragma unroll
-        for (int q = 0; q < INFLIGHT; ++q) add_vec(w[q], base + q * nthreads, acc);
+        for (int q = 0; q < INFLIGHT; ++q)
+            if (base + q * nthreads < v1) add_exact_terms<DT>(w[q], 0u, m, c, down, acc);
         S += (unsigned long long)acc;
     }
     return S;
@@ -549,6 +555,22 @@ __device__ __forceinline__ float wave_row_plain_sum(const void *rowp, int V, flo
     return (float)s;
 }
 
+// The words in which a step_tail_kernel meets (partial sums of the path rows, two counters), set to zero by the row kernel
+// that is launched before it.
+struct SumClear {
+    unsigned long long *part;   // [B][R][words], or NULL: nothing to clear
+    unsigned *bar;              // [2]
+    int R, words;
+    // called by all threads of the workgroup that holds (the first part of) row slot j of trajectory b
+    __device__ __forceinline__ void row(int b, int j) const
+    {
+        if (!part) return;
+        if (j < R)
+            for (int i = threadIdx.x; i < words; i += blockDim.x) part[((size_t)b * R + j) * words + i] = 0ull;
+        if (b == 0 && j == 0 && threadIdx.x < 2) bar[threadIdx.x] = 0u;
+    }
+};
+
 struct RowPassArgs {
     const void *logits;
     int B, N, V, K;
@@ -567,6 +589,7 @@ struct RowPassArgs {
     bool onehot;                // deterministic drafting: one-hot proposals in the accept tests
     float eps;                  // relative error assumed for the fast normaliser from its additions (>= kFastEps)
     int fx_shift;               // the exact normaliser counts in units of 2^-(40 - fx_shift) (0 up to V = 2^22)
+    SumClear clear;             // what the step_tail_kernel that follows needs at zero
 };
 
 // The proposal of a node and its accept tests, by one wave.
@@ -732,6 +755,7 @@ __global__ __launch_bounds__(64 * WPR) void row_pass_kernel(RowPassArgs a)
     // rows that finish the kernel are leaves.
     const int slot = blockIdx.x;
     if (slot >= a.B * a.N) return;
+    a.clear.row(slot % a.B, slot / a.B);
     row_role<DT, WPR>(a, (slot % a.B) * a.N + slot / a.B, &sm, RowPub{nullptr, nullptr, 0u});
 }
 

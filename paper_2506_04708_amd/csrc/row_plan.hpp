@@ -87,4 +87,20 @@ inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int
 // row is summed, which fills the vector ALUs at any batch size: all-nodes steps of 16 x 64 rows 357 / 331, 4 x 64 98 / 94.
 constexpr int exact_loads(bool verify, bool all_nodes, int64_t B) { return verify && !all_nodes && B <= 16 ? 2 : 4; }
 
+// Ranges of vectors of a path row in step_tail_kernel, each summed by one wave; workgroups hold `waves` of them.  One vector
+// per lane for a few trajectories, where the latency of a sum counts; four where so many workgroups would wait to be
+// started.  Steps with 1 / 2 vectors per lane, us: 1 x 32 rows x 152 064 25.6 / 27.6, 8 x 32 x 128 256 41.4 / 42.0; with
+// 1 / 2 / 4 / 8: 32 x 64 x 152 064, long paths 158.6 / 152.0 / 148.3 / 149.6.
+inline int plan_tail_ranges(int64_t V, int element_bytes, int64_t B, int waves, int most)
+{
+    const int64_t per_wave = 64 * (B <= 16 ? 1 : 4);
+    const int64_t n = (row_vectors(V, element_bytes) + per_wave - 1) / per_wave;
+    return (int)std::min<int64_t>((n + waves - 1) / waves * waves, most);
+}
+
+// Whether an update with W row slots and NO orders takes step_tail_kernel, where one workgroup finishes a trajectory's rows
+// and applies its records: separate launches / one, us: update and draft of 6 x 14 rows x 4 orders 35.7 / 37.4, of
+// 4 x 32 x 4 50.9 / 66.7 (all slots hold a row); verify, update and draft with 7 x 4 62.3 / 55.0 (paths of one or two rows).
+constexpr bool plan_tail_update(int W, int NO) { return W * NO <= 40; }
+
 }  // namespace stand

@@ -75,6 +75,11 @@ struct stand_handle {
     int32_t *pr_top_idx;
     // rows split over workgroups (row_parts.hpp): parts per row of a verification and of an update (0: not split)
     int row_parts, commit_parts;
+    // small batches: what follows the row kernel is one launch (step_tail.hpp)
+    bool tail_launch, tail_update;   // of a step or verification; of an update
+    int tail_nsub;                   // ranges of a path row that are summed by a wave each
+    unsigned long long *tail_part;   // [B][W][tail_nsub]
+    unsigned *tail_bar;              // [2]
     unsigned *part_ticket;           // [rows or commit slots], zero between launches
     PartHead *part_head;
     unsigned long long *part_keys;
@@ -144,7 +149,7 @@ static void free_all(stand_handle *h)
     if (!h) return;
     void *ptrs[] = {h->d_tree, h->table, h->ctx_tail, h->ctx_len, h->ctx_tail2, h->ctx_len2, h->reorder_map, h->export_buf, h->draft_tok, h->draft_has, h->draft_qid, h->draft_qmu,
                     h->vs.row_m, h->vs.row_s, h->vs.top_l, h->vs.top_p, h->vs.top_idx, h->vs.outcome, h->vs.obs_idx, h->vs.obs_p, h->rec_slot,
-                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
+                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->tail_part, h->tail_bar, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
     for (void *p : ptrs) (void)hipFree(p);
     for (hipEvent_t e : h->ev_begin) (void)hipEventDestroy(e);
     for (hipEvent_t e : h->ev_end) (void)hipEventDestroy(e);
@@ -290,6 +295,10 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);
     acc(dmalloc(&h->part_ticket, part_tickets));
     acc(dmalloc(&h->part_head, part_slots)); acc(dmalloc(&h->part_keys, part_slots * kPartKeys));
+    h->tail_launch = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch;
+    h->tail_update = h->tail_launch && plan_tail_update(h->W, h->NO);
+    h->tail_nsub = plan_tail_ranges(h->V, element_bytes(*cfg), h->B, kTailWaves, kSubMax);
+    acc(dmalloc(&h->tail_part, h->tail_launch ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, 2));
     acc(dmalloc(&h->stats, (size_t)kStatCount));
     acc(dmalloc(&h->counter, 1));
     if (e != hipSuccess) { free_all(h); return e == hipErrorOutOfMemory ? STAND_ENOMEM : STAND_EHIP; }
@@ -422,8 +431,12 @@ static RowPassArgs make_row_args(const stand_handle *h, const VerifyScratch &vs,
     a.onehot = h->cfg.draft_mode == STAND_DRAFT_DETERMINISTIC;
     a.eps = fast_eps(h, wpr);
     a.fx_shift = h->fx_shift;
+    a.clear = SumClear{nullptr, nullptr, 0, 0};
     return a;
 }
+
+// what the row kernel before a step_tail_kernel clears
+static SumClear tail_clear(const stand_handle *h) { return SumClear{h->tail_part, h->tail_bar, h->W, h->tail_nsub}; }
 
 template <int DT>
 static const void *row_parts_fn(int vectors)
@@ -459,6 +472,7 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
     const bool few = unsplit_waves(rows) == kRowWPRFewRows;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * h->row_parts : (few ? kRowWPRFewRows : kRowWPR));
+    if (own && h->tail_launch) a.clear = tail_clear(h);
     RowPartsArgs pa = make_parts_args(h, a, split ? h->row_parts : 1);
     const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
     const dim3 grid = split ? dim3((unsigned)h->row_parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
@@ -524,34 +538,46 @@ static PathArgs make_path_args(const stand_handle *h, const VerifyScratch &vs, u
     return a;
 }
 
-// mode 0 (verify): path from the row pass's outcomes; mode 1 (update): rows given by the caller.
-// With `claim` the launch that finishes the path rows also claims the table slots of that merge; with `tail` (a step of one
-// trajectory) it also applies them and drafts.
-static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row,
-                            const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len,
-                            const MergeArgs *claim, const DraftArgs *tail, hipStream_t s)
+// maximum and top-K of the rows given to an update
+static int launch_commit_rows(stand_handle *h, uint64_t step, const void *d_logits, const int32_t *commit_row, const int32_t *commit_len,
+                              bool tail, hipStream_t s)
 {
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
-    if (mode == 1) {
-        CommitScanArgs c;
-        c.logits = d_logits; c.B = h->B; c.N = h->N; c.V = h->V; c.K = h->K; c.W = h->W; c.c = h->c;
-        c.R = h->R; c.all_nodes = h->cfg.update_mode == STAND_UPDATE_ALL_NODES; c.draft_tok = h->draft_tok;
-        c.commit_row = commit_row; c.commit_len = commit_len;
-        c.pr_m = h->pr_m; c.pr_top_idx = h->pr_top_idx; c.pr_top_l = h->pr_top_l;
-        const dim3 grid((unsigned)h->R, (unsigned)h->B);
-        if (h->commit_parts > 0) {
-            RowPartsArgs pa = make_parts_args(h, make_row_args(h, vs, step, d_logits, kPartWaves * h->commit_parts), h->commit_parts);
-            pa.streamed = false;  // (every row of an update is read again for its exact sum: 63.6 against 64.9 us, 128 rows of 304 KB)
-            pa.commit = true; pa.all_nodes = c.all_nodes; pa.W = h->W; pa.R = h->R;
-            pa.commit_row = commit_row; pa.commit_len = commit_len;
-            pa.pr_m = h->pr_m; pa.pr_top_idx = h->pr_top_idx; pa.pr_top_l = h->pr_top_l;
-            const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
-            void *args[] = {&pa};
-            HIP_TRY(h, hipLaunchKernel(bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors),
-                                       dim3((unsigned)h->commit_parts, (unsigned)h->B, (unsigned)h->R), dim3(kPartThreads), args, 0, s));
-        } else if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
-        else commit_scan_kernel<kDtF32><<<grid, dim3(256), 0, s>>>(c);
+    const SumClear clear = tail ? tail_clear(h) : SumClear{nullptr, nullptr, 0, 0};
+    if (h->commit_parts > 0) {
+        RowPartsArgs pa = make_parts_args(h, make_row_args(h, h->vs, step, d_logits, kPartWaves * h->commit_parts), h->commit_parts);
+        pa.r.clear = clear;
+        pa.streamed = false;  // (every row of an update is read again for its exact sum: 63.6 against 64.9 us, 128 rows of 304 KB)
+        pa.commit = true; pa.all_nodes = h->cfg.update_mode == STAND_UPDATE_ALL_NODES; pa.W = h->W; pa.R = h->R;
+        pa.commit_row = commit_row; pa.commit_len = commit_len;
+        pa.pr_m = h->pr_m; pa.pr_top_idx = h->pr_top_idx; pa.pr_top_l = h->pr_top_l;
+        const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
+        void *args[] = {&pa};
+        HIP_TRY(h, hipLaunchKernel(bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors),
+                                   dim3((unsigned)h->commit_parts, (unsigned)h->B, (unsigned)h->R), dim3(kPartThreads), args, 0, s));
+        return STAND_OK;
     }
+    CommitScanArgs c;
+    c.logits = d_logits; c.B = h->B; c.N = h->N; c.V = h->V; c.K = h->K; c.W = h->W; c.c = h->c;
+    c.R = h->R; c.all_nodes = h->cfg.update_mode == STAND_UPDATE_ALL_NODES; c.draft_tok = h->draft_tok;
+    c.commit_row = commit_row; c.commit_len = commit_len;
+    c.pr_m = h->pr_m; c.pr_top_idx = h->pr_top_idx; c.pr_top_l = h->pr_top_l;
+    c.clear = clear;
+    const dim3 grid((unsigned)h->R, (unsigned)h->B);
+    if (bf16) commit_scan_kernel<kDtBf16><<<grid, dim3(256), 0, s>>>(c);
+    else commit_scan_kernel<kDtF32><<<grid, dim3(256), 0, s>>>(c);
+    HIP_TRY(h, hipGetLastError());
+    return STAND_OK;
+}
+
+// What follows the row kernel, in separate launches: exact sums, then the rows' ends.  mode 0 (verify): path from the row
+// pass's outcomes; mode 1 (update): rows given by the caller.  With `claim` the launch that finishes the path rows also
+// claims the table slots of that merge.
+static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row,
+                            const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len,
+                            const MergeArgs *claim, hipStream_t s)
+{
+    const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     // segments: one round of loads per thread where kSegMax allows it; one more block per (row, trajectory) slot for the
     // outputs and the stop record
     const int per_thread = exact_loads(mode == 0, h->cfg.update_mode == STAND_UPDATE_ALL_NODES, h->B);
@@ -565,21 +591,6 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
     const int claim_blocks = claim ? (h->B * h->R * h->NO + kFinishThreads - 1) / kFinishThreads : 0;
     const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
     const dim3 g2((unsigned)((mode == 0 ? h->B : 0) + row_blocks + claim_blocks));
-    if (tail) {
-        // one trajectory: the rest of the step in one workgroup
-        PathTailArgs ta;
-        ta.path = a; ta.mg = mg; ta.draft = *tail;
-        if (bf16) {
-            path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
-            path_tail_kernel<kDtBf16><<<dim3(1), dim3(kTailThreads), 0, s>>>(ta);
-        } else {
-            path_exact_kernel<kDtF32><<<g1, block, 0, s>>>(a);
-            path_tail_kernel<kDtF32><<<dim3(1), dim3(kTailThreads), 0, s>>>(ta);
-        }
-        HIP_TRY(h, hipGetLastError());
-        h->table_used = true;
-        return STAND_OK;
-    }
     if (bf16) {
         path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
         path_finish_kernel<kDtBf16><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
@@ -588,6 +599,32 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
         path_finish_kernel<kDtF32><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     }
     HIP_TRY(h, hipGetLastError());
+    return STAND_OK;
+}
+
+// The same in one launch (step_tail.hpp): `merge` as well for an update, `draft` too for a step.
+static int launch_step_tail(stand_handle *h, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row, const int32_t *commit_len,
+                            int32_t *out_tok, int32_t *out_node, int32_t *out_len, const int32_t *given_tok, const MergeArgs *merge,
+                            const DraftArgs *draft, hipStream_t s)
+{
+    const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
+    StepTailArgs A;
+    memset(&A, 0, sizeof(A));
+    A.path = make_path_args(h, h->vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, kPathThreads);
+    A.mg = merge ? *merge : merge_args(h, nullptr, nullptr, nullptr);
+    if (draft) A.draft = *draft;
+    else A.draft.tree = A.path.tree;
+    A.part = h->tail_part; A.bar = h->tail_bar; A.nsub = h->tail_nsub;
+    A.merge = merge != nullptr; A.drafts = draft != nullptr;
+    A.given_tok = given_tok; A.ctx_tail = h->ctx_tail; A.ctx_len = h->ctx_len;
+    // path rows with workgroups of their own: 2 / 3 / 4 / all, steps of 32 x 64 rows with long paths 151.4 / 147.9 / 148.4 / 149.2 us
+    A.row_slots = mode == 0 ? std::min(h->W, 3) : h->W;
+    const dim3 grid((unsigned)(h->B + A.row_slots * h->B * (A.nsub / kTailWaves))), block(kTailThreads);
+    const size_t smem = tail_shared_bytes(h->N);
+    if (bf16) step_tail_kernel<kDtBf16><<<grid, block, smem, s>>>(A);
+    else step_tail_kernel<kDtF32><<<grid, block, smem, s>>>(A);
+    HIP_TRY(h, hipGetLastError());
+    if (merge) h->table_used = true;
     return STAND_OK;
 }
 
@@ -634,7 +671,11 @@ extern "C" int stand_update(stand_handle *h, uint64_t step, const void *d_logits
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
     const MergeArgs mg = merge_args(h, d_commit_tok, d_commit_row, d_commit_len);
-    int rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, nullptr, s);
+    int rc = launch_commit_rows(h, step, d_logits, d_commit_row, d_commit_len, h->tail_update, s);
+    if (rc) return rc;
+    if (h->tail_update)
+        return launch_step_tail(h, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, d_commit_tok, &mg, nullptr, s);
+    rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, s);
     if (rc) return rc;
     return launch_merge_apply(h, mg, true, s);
 }
@@ -666,7 +707,9 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     HIP_TRY(h, hipSetDevice(h->cfg.device));
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
-    return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, s);
+    if (h->tail_launch)
+        return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, nullptr, s);
+    return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
 
 // Bytes of scratch a verification of this handle's shape needs, laid out as carve_scratch does.
@@ -705,7 +748,7 @@ extern "C" int stand_verify_static(stand_handle *h, uint64_t step, const void *d
     // and observations for exactly the path rows that are read back).
     int rc = launch_row_pass(h, vs, step, d_logits, false, s);
     if (rc) return rc;
-    return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, s);
+    return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
 
 extern "C" uint64_t stand_static_scratch_need(const stand_handle *h)
@@ -929,12 +972,11 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
     if (rc) return rc;
     const MergeArgs mg = merge_args(h, commit, nullptr, d_out_len);
-    // one trajectory and at most one record per thread of the claiming waves: what follows the exact sums is one launch
-    if (h->B == 1 && h->cfg.update_mode == STAND_UPDATE_ACCEPTED_PATH) {
+    if (h->tail_launch) {
         const DraftArgs da = make_draft_args(h, step + 1, d_next_draft_tok, commit, d_out_len);
-        return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, &da, s);
+        return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, d_force_tok, &mg, &da, s);
     }
-    rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, nullptr, s);
+    rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, s);
     if (rc) return rc;
     rc = launch_merge_apply(h, mg, false, s);
     if (rc) return rc;

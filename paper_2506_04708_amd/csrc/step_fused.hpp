@@ -123,13 +123,15 @@ struct TailShared {
     alignas(16) unsigned long long scratch[kStepWPR][2 * kMaxK];
 };
 
-// All workgroups of one count arrive, then wait for the rest.  Called by the whole workgroup.
-__device__ __forceinline__ void tail_barrier(const StepSync &sy, int which, unsigned arrivals, TailShared *ts)
+// All workgroups of one count arrive, then wait for the rest (`meanwhile` runs in between).  Called by the whole workgroup.
+template <typename Meanwhile>
+__device__ __forceinline__ void tail_barrier(const StepSync &sy, int which, unsigned arrivals, TailShared *ts, const Meanwhile &meanwhile)
 {
     publish_fence();  // this workgroup's stores (table, records, observations) are complete before its arrival
     __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&sy.bar[which], 1u);
+    meanwhile();
     if (threadIdx.x == 0) {
-        atomicAdd(&sy.bar[which], 1u);
         if (!wait_reached(&sy.bar[which], arrivals * sy.epoch, sy.wait_ticks)) ts->ok = 0;
     }
     __syncthreads();
@@ -297,7 +299,7 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
         if (lane < W) {  // W <= 32
             a.out_node[(size_t)b * W + lane] = lane < len ? ts->path[lane] : -1;
             // accepted tokens are the tokens of the path nodes after the root; the last emitted token
-            // (position len - 1) is written by finish_row
+            // (position len - 1) is written by finish_stop_row
             if (lane + 1 < len) a.out_tok[(size_t)b * W + lane] = a.draft_tok[(size_t)b * N + ts->path[lane + 1]];
             else if (lane >= len - 1) a.out_tok[(size_t)b * W + lane] = -1;
         }
@@ -347,12 +349,12 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
         for (int j = wave; j + 1 < len; j += kStepWPR) {  // rows above the stop row: one wave each
             const int node = ts->path[j];
             const unsigned long long part = wait_parts(j);
-            finish_row<DT, kStepThreads>(a, ts->fin, b, j, node, false, ts->pm[j], 0, -1, len, -1, 0.0f, 0.0f, -1, part, lane, 0, ts->acc[j]);
+            finish_upper_row<DT>(a, b, j, node, ts->pm[j], [&] { return part; }, lane, ts->acc[j]);
         }
         __syncthreads();
         if (ts->ok) {
-            finish_row<DT, kStepThreads>(a, ts->fin, b, len - 1, stop_node, true, stop_m, nch, fc, len, my_id, my_mu, my_l, ch, part_stop,
-                                         tid, wave);
+            finish_stop_row<DT, kStepThreads>(a, ts->fin, b, len - 1, stop_node, stop_m, nch, fc, len, my_id, my_mu, my_l, ch, part_stop,
+                                              tid, wave);
         } else if (tid == 0) {
             a.out_tok[(size_t)b * W + (len - 1)] = -1;
             atomicAdd(&a.stats[kStatWaitExpired], 1ull);
@@ -361,17 +363,19 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
 
     // ---- every trajectory's claims and observations, then this trajectory's records
     if (tid == 0) stamp(sy, b, 4);
-    tail_barrier(sy, 0, (unsigned)a.B, ts);
+    tail_barrier(sy, 0, (unsigned)a.B, ts, [] {});
     if (tid == 0) stamp(sy, b, 5);
     {
         const int NO = A.mg.omax - A.mg.omin + 1;
         for (int i = wave; i < len * NO; i += kStepWPR) apply_record(A.mg, b * A.mg.R * NO + i, lane, ts->scratch[wave]);
     }
     // ---- every trajectory's records applied, then the next draft
-    tail_barrier(sy, 1, (unsigned)a.B, ts);
+    const DraftShared dsm = draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N, kStepWPR);
+    int level_reg = 0;
+    tail_barrier(sy, 1, (unsigned)a.B, ts, [&] { level_reg = draft_prepare<kStepThreads>(A.draft, b, dsm); });
     if (tid == 0) stamp(sy, b, 6);
     if (tid == 0 && !ts->ok) atomicAdd(&a.stats[kStatWaitExpired], 1ull);
-    draft_trajectory<kStepThreads>(A.draft, b, draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N, kStepWPR));
+    draft_run<kStepThreads>(A.draft, b, dsm, level_reg);
     if (tid == 0) stamp(sy, b, 7);
 }
 

@@ -38,6 +38,27 @@ __device__ __forceinline__ int clamp_len(int len, int W) { return len < 0 ? 0 : 
 
 enum ClaimOutcome { kClaimNone = 0, kClaimInsert, kClaimMerge, kClaimDrop };
 
+// claims a table slot for merge record rec, whose key of order n has fingerprint fp; run by one thread
+__device__ __forceinline__ int claim_slot(const MergeArgs &a, int rec, int n, unsigned long long fp, long long &slot_out)
+{
+    for (int i = 0; i < a.max_probe; ++i) {
+        const uint64_t slot = (fp + (uint64_t)i) & a.mask;
+        SlotHeader *h = slot_header(a.table, slot, a.slot_bytes);
+        const unsigned long long old = atomicCAS(&h->fp, 0ull, fp);
+        if (old == 0ull || old == fp) {
+            // Until the records are applied the order word also carries the smallest record
+            // number that claimed the slot (stored inverted, so that atomicMax keeps it), and
+            // the top bit of the count word says that more than one record did.
+            const uint32_t tag = ((kTagMax - (uint32_t)rec) << kTagShift) | (uint32_t)n;
+            const uint32_t before = atomicMax(&h->order, tag);
+            if (before >> kTagShift) atomicOr(&h->count, kMultiBit);
+            slot_out = (long long)slot;
+            return old == 0ull ? kClaimInsert : kClaimMerge;
+        }
+    }
+    return kClaimDrop;
+}
+
 // claims the table slot of merge record rec = (b, position j, order n); run by one thread
 __device__ __forceinline__ int merge_claim_record(const MergeArgs &a, int rec)
 {
@@ -73,24 +94,7 @@ __device__ __forceinline__ int merge_claim_record(const MergeArgs &a, int rec)
             key[i] = (back <= j) ? a.commit_tok[(size_t)b * a.W + (j - back)]
                                  : a.ctx_tail[(size_t)b * kMaxOrder + (kMaxOrder - (back - j))];
         }
-        const unsigned long long fp = fingerprint(n, key);
-        bool placed = false;
-        for (int i = 0; i < a.max_probe; ++i) {
-            const uint64_t slot = (fp + (uint64_t)i) & a.mask;
-            SlotHeader *h = slot_header(a.table, slot, a.slot_bytes);
-            const unsigned long long old = atomicCAS(&h->fp, 0ull, fp);
-            if (old == 0ull || old == fp) {
-                outcome = old == 0ull ? kClaimInsert : kClaimMerge;
-                // Until the records are applied the order word also carries the smallest record
-                // number that claimed the slot (stored inverted, so that atomicMax keeps it), and
-                // the top bit of the count word says that more than one record did.
-                const uint32_t tag = ((kTagMax - (uint32_t)rec) << kTagShift) | (uint32_t)n;
-                const uint32_t before = atomicMax(&h->order, tag);
-                if (before >> kTagShift) atomicOr(&h->count, kMultiBit);
-                slot_out = (long long)slot; placed = true; break;
-            }
-        }
-        if (!placed) outcome = kClaimDrop;
+        outcome = claim_slot(a, rec, n, fingerprint(n, key), slot_out);
     }
     st_agent(&a.rec_slot[rec], slot_out);
     return outcome;
@@ -119,26 +123,37 @@ __device__ __forceinline__ void count_claims(const MergeArgs &a, int outcome, in
 constexpr int kMergeWaves = 4;
 constexpr int kFollowGroups = 16;
 
-// Record `rec` by one wave (all 64 lanes call this; scratch: 2 * kMaxK words of shared memory, 16-byte aligned, owned by
-// the wave).  Does nothing unless the record exists and leads its slot.
+// The entry stored in a slot, lane i < K its i-th place.  Only the slot's leader writes it, so it may be requested as soon as
+// the slot is known.
+struct StoredEntry { int32_t id; float mu; };
+__device__ __forceinline__ StoredEntry request_entry(const MergeArgs &a, long long slot, int lane)
+{
+    StoredEntry e{-1, 0.0f};
+    if (lane < a.K) {
+        e.id = ld_agent(&slot_ids(a.table, (uint64_t)slot, a.slot_bytes)[lane]);
+        e.mu = ld_agent(&slot_mu(a.table, (uint64_t)slot, a.slot_bytes, a.K)[lane]);
+    }
+    return e;
+}
+
+// Record `rec`, which claimed `slot`, by one wave (all 64 lanes call this; scratch: 2 * kMaxK words of shared memory, 16-byte aligned, owned by
+// the wave); `stored`: the slot's entry.  Does nothing unless the record leads its slot.
 // Folding one observation into an entry was 2 600 (K = 10) to 6 700 cycles (K = 32) of readlanes; with ids and keys read
 // from shared memory, four and two per access, K compares and 2 K 64-bit compares remain.
-__device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, unsigned long long *scratch)
+__device__ __forceinline__ void apply_claimed(const MergeArgs &a, int rec, long long slot, const StoredEntry &stored, int lane,
+                                              unsigned long long *scratch)
 {
     const int NO = a.omax - a.omin + 1;
     const int nrec = a.B * a.R * NO;
     const int K = a.K;
-    const long long slot = ld_agent(&a.rec_slot[rec]);
-    if (slot < 0) return;
     SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
     int32_t *ids = slot_ids(a.table, (uint64_t)slot, a.slot_bytes);
     float *mus = slot_mu(a.table, (uint64_t)slot, a.slot_bytes, K);
     // header, stored entry and this record's observation are requested together
     const uint32_t order_word = ld_agent(&h->order);
     uint32_t count = ld_agent(&h->count);
-    int32_t e_id = -1;
-    float e_mu = 0.0f;
-    if (lane < K) { e_id = ld_agent(&ids[lane]); e_mu = ld_agent(&mus[lane]); }
+    int32_t e_id = stored.id;
+    float e_mu = stored.mu;
     // lanes 0..K-1: stored entry; lanes 32..32+K-1: observation
     int32_t o_id = -1;
     float o_p = 0.0f;
@@ -202,15 +217,16 @@ __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int la
         // the later records of this slot, in record order (kFollowGroups groups of 64 record slots are read per
         // round trip: a step of 128 trajectories has thousands of record slots)
         for (int base = rec + 1; base < nrec; base += 64 * kFollowGroups) {
-            long long rs[kFollowGroups];
+            unsigned found = 0u;   // bit q: the lane's record slot of group q is such a record
 #pragma unroll
             for (int q = 0; q < kFollowGroups; ++q) {
                 const int r = base + 64 * q + lane;
-                rs[q] = r < nrec ? ld_agent(&a.rec_slot[r]) : -1;
+                found |= (r < nrec ? ld_agent(&a.rec_slot[r]) : -1ll) == slot ? 1u << q : 0u;
             }
-#pragma unroll
+            if (!__ballot(found != 0u)) continue;
+#pragma unroll 1
             for (int q = 0; q < kFollowGroups; ++q) {
-                unsigned long long hits = __ballot(rs[q] == slot);
+                unsigned long long hits = __ballot((found >> q) & 1u);
                 while (hits) {
                     const int bit = __ffsll((long long)hits) - 1;
                     hits &= hits - 1;
@@ -225,6 +241,14 @@ __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int la
     }
     if (lane < K) { st_agent(&ids[lane], e_id); st_agent(&mus[lane], e_mu); }
     if (lane == 0) { st_agent(&h->count, count); st_agent(&h->order, order_word & ((1u << kTagShift) - 1u)); }
+}
+
+// The same for a record whose slot is still to be looked up; does nothing unless it exists.
+__device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, unsigned long long *scratch)
+{
+    const long long slot = ld_agent(&a.rec_slot[rec]);
+    if (slot < 0) return;
+    apply_claimed(a, rec, slot, request_entry(a, slot, lane), lane, scratch);
 }
 
 // Appends the committed tokens of trajectory b to its context tail (one thread).

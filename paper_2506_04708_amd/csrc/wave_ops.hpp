@@ -26,6 +26,17 @@ enum StatSlot {
     kStatCount
 };
 
+// A kernel's arguments (one structure by value), read again from where the launch put them.  A kernel of many phases would
+// otherwise hold the arguments of all of them in scalar registers from its start, and spill them: each phase takes its own
+// `fresh` reference, whose loads cannot be moved above it.
+template <typename T>
+__device__ __forceinline__ const T &fresh_args()
+{
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const T *)p;
+}
+
 struct TreeDev {
     const int32_t *parent, *depth, *nchild, *first_child, *level_start;  // level_start[D+2]
     int N, D;

@@ -506,6 +506,25 @@ def test_lockstep_one_trajectory(gpu, name, over, steps, forced):
     _say("  -> %s" % info)
 
 
+@pytest.mark.parametrize("name,over,steps,mode,forced", [
+    ("cfg1", dict(V=13, B=2, rho=0.5, K=10, dtype="bf16"), 40, "step", False),        # one vector or none, the rest are edges
+    ("cfg1", dict(V=600_011, B=1, rho=0.7), 8, "step", False),                        # the most ranges, several vectors per lane
+    ("cfg1", dict(V=70_001, B=17, rho=0.7, dtype="bf16"), 6, "step", False),          # four vectors per lane
+    ("cfg1", dict(V=300, B=64, rho=0.7), 12, "step", False),                          # the largest batch of one launch ...
+    ("cfg1", dict(V=300, B=65, rho=0.7), 12, "step", False),                          # ... and one more
+    ("cfg3", dict(V=48, B=9, rho=0.5, order_min=1, order_max=4), 24, "separate", False),   # updates of 9 rows x 4 orders: one launch
+    ("cfg3", dict(V=48, B=9, rho=0.5, order_min=1, order_max=5), 24, "separate", False),   # x 5 orders: separate launches
+])
+def test_lockstep_rest_of_the_step_in_one_launch(gpu, name, over, steps, mode, forced):
+    """What follows the row kernel of a small batch is one launch: ranges of a row from none to the most, batches and updates
+    at the limit and beyond it."""
+    binding, lockstep = gpu
+    _say("lockstep rest of the step %s %s %s" % (name, over, mode))
+    w = synth.Workload(name, run_steps=steps, **over)
+    info = lockstep.run_lockstep(w, steps, mode=mode, capacity=1 << 14, forced=forced, check_rows=w.V < 1000, table_every=4)
+    _say("  -> %s" % info)
+
+
 @pytest.mark.parametrize("over,mode", [
     (dict(V=70001, B=2, rho=0.7), "separate"), (dict(V=70001, B=2, rho=0.7, dtype="bf16"), "separate"),
     (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"), (dict(V=66000, B=47, rho=0.7, dtype="bf16"), "step"),
