@@ -8,7 +8,7 @@ namespace stand {
 
 // Row pass.  Thousands of rows: one row per workgroup of four waves.  Few rows: every row is split over workgroups
 // (row_parts.hpp), or, where that does not pay (plan_row_parts) or does not apply (the entry point with fixed scratch),
-// spread over the sixteen waves of one as long as each compute unit has at most one of them: verifications, sixteen / four
+// held whole by one (plan_row_whole), or spread over the sixteen waves of one as long as each compute unit has at most one of them: verifications, sixteen / four
 // waves, us: 256 rows of 522 KB (bf16) 49.2 / 54.3, 288 rows 63.7 / 59.6.
 #ifndef STAND_ROW_WPR
 #define STAND_ROW_WPR 4
@@ -21,7 +21,7 @@ constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
 constexpr int kPartVectors = 8;                      // most vectors per lane
 constexpr int kPartsMax = 32;                        // most parts of a row
 constexpr int kPartsTarget = 256;                    // workgroups that few rows are split into
-constexpr int kRowsSplit = 512;                      // more rows are never split
+constexpr int kRowsSplit = 512;                      // more rows are never split (but may be held whole, plan_row_whole)
 constexpr int kCommitSlotsSplit = 4096;              // row slots of an update that may be split (most hold no row)
 constexpr int kCommitWorkgroups = 2560;              // workgroups that find a row in a split update of short paths
 
@@ -65,6 +65,17 @@ inline int plan_row_parts(int64_t V, int element_bytes, int64_t rows, int K)
     const int64_t vectors = row_vectors(V, element_bytes);
     const int p = choose_parts(vectors, rows);
     return bound_holds(vectors, K) && rows * p <= split_limit(rows) ? p : 0;
+}
+
+// Whether a row that is not split is held whole in the registers of one workgroup of row_parts_kernel, however many rows
+// there are: nothing is read twice, no list is kept while streaming, and a workgroup's end is shorter than the streaming
+// pass's.  (Rows of one part use none of the memory in which parts meet.)  Streaming with four waves / whole, us:
+//   verify 1036 x 2096 vectors (bf16) 32.2 / 29.9, 1440 x 3804 44.3 / 41.4, 2784 x 3800 55.7 / 54.6, 882 x 2064 (fp32) 28.4 / 25.8,
+//   16384 x 4000 193.1 / 192.7, fp32 199.9 / 185.2, 16384 x 500 101.0 / 99.5;  step 540 x 1079 37.3 / 34.6, 720 x 1024 33.3 / 29.2
+// (Two parts of rows that do not fit: 553 x 4288 41.3 / 42.2, 759 x 5280 43.3 / 47.1.)
+constexpr bool plan_row_whole(int64_t V, int element_bytes, int K)
+{
+    return row_vectors(V, element_bytes) <= kPartThreads * kPartVectors && bound_holds(row_vectors(V, element_bytes), K);
 }
 
 // Parts per row of an update with R row slots per trajectory, W = longest path, N = nodes; 0: not split.

@@ -468,14 +468,17 @@ static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r,
 static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, bool own, hipStream_t s)
 {
     const int rows = h->B * h->N;
-    const bool split = own && h->row_parts > 0;
+    // (few rows of the entry point with fixed scratch keep sixteen waves each; a grid has at most 65535 trajectories)
+    const bool whole = plan_row_whole(h->V, element_bytes(h->cfg), h->K) && (own || rows > kRowsSixteenWaves) && h->B <= 65535;
+    const int parts = own && h->row_parts > 0 ? h->row_parts : (whole ? 1 : 0);
+    const bool split = parts > 0;
     const bool few = unsplit_waves(rows) == kRowWPRFewRows;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
-    RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * h->row_parts : (few ? kRowWPRFewRows : kRowWPR));
+    RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * parts : (few ? kRowWPRFewRows : kRowWPR));
     if (own && h->tail_launch) a.clear = tail_clear(h);
-    RowPartsArgs pa = make_parts_args(h, a, split ? h->row_parts : 1);
+    RowPartsArgs pa = make_parts_args(h, a, split ? parts : 1);
     const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
-    const dim3 grid = split ? dim3((unsigned)h->row_parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
+    const dim3 grid = split ? dim3((unsigned)parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
     const dim3 block(split ? (unsigned)kPartThreads : 64u * (unsigned)(few ? kRowWPRFewRows : kRowWPR));
     const void *fn = split ? (bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors))
                    : bf16 ? (few ? (const void *)row_pass_kernel<kDtBf16, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtBf16, kRowWPR>)

@@ -506,6 +506,24 @@ def test_lockstep_one_trajectory(gpu, name, over, steps, forced):
     _say("  -> %s" % info)
 
 
+@pytest.mark.parametrize("name,over,mode", [
+    ("cfg1", dict(V=8000, B=33, rho=0.7, dtype="bf16"), "separate"),        # 528 rows of 1000 vectors: two vectors per lane
+    ("cfg1", dict(V=16384, B=33, rho=0.7), "step"),                         # fp32, a workgroup's registers full
+    ("cfg1", dict(V=16389, B=33, rho=0.7), "step"),                         # one vector more: streamed
+    ("cfg1", dict(V=803, B=34, rho=0.7, dtype="bf16"), "separate"),         # 100 vectors, the fewest for K = 10; misaligned rows
+    ("cfg1", dict(V=797, B=34, rho=0.7, dtype="bf16"), "separate"),         # one vector fewer: streamed
+])
+def test_lockstep_rows_held_whole(gpu, name, over, mode):
+    """Rows too many to be split, each held in the registers of one workgroup."""
+    binding, lockstep = gpu
+    w = synth.Workload(name, run_steps=4, **over)
+    assert w.K == 10 and w.B * w.N > 512
+    _say("lockstep rows held whole %s %s" % (over, mode))
+    info = lockstep.run_lockstep(w, 4, mode=mode, capacity=1 << 13, table_every=4, sample_rows=range(0, w.B * w.N, 7))
+    _say("  -> %s" % info)
+    assert info["worst_rel"] < 1e-5
+
+
 @pytest.mark.parametrize("name,over,steps,mode,forced", [
     ("cfg1", dict(V=13, B=2, rho=0.5, K=10, dtype="bf16"), 40, "step", False),        # one vector or none, the rest are edges
     ("cfg1", dict(V=600_011, B=1, rho=0.7), 8, "step", False),                        # the most ranges, several vectors per lane

@@ -71,3 +71,17 @@ def test_every_plan_fits_the_kernel():
         if c:
             assert c <= L.parts_max() and -(-vec // c) <= L.threads() * L.most_vectors()
             assert B * R * c * 64 * 8 <= 28 << 20      # 64 candidate keys per part
+
+
+def test_rows_held_whole():
+    """As many vectors as a workgroup's registers hold, and enough of them for a bound."""
+    L = rowplan.lib()
+    assert [L.whole(V, 2, 10) for V in (792, 800, 32768, 32769)] == [0, 1, 1, 0]
+    assert [L.whole(V, 4, 32) for V in (1276, 1280, 16384, 16385)] == [0, 1, 1, 0]
+
+
+def test_ranges_of_a_path_row():
+    """Whole workgroups of sixteen waves, at most 512 ranges; one vector per lane for few trajectories, four for many."""
+    L = rowplan.lib()
+    assert [L.ranges(V, 2, 1) for V in (13, 8192, 8200, 152064, 10 ** 7)] == [16, 16, 32, 304, 512]
+    assert [L.ranges(152064, 2, B) for B in (16, 17, 64)] == [304, 80, 80]
