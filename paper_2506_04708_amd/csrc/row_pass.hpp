@@ -466,14 +466,28 @@ __device__ __forceinline__ unsigned long long fixed_mass(float e, int shift)
     return ((unsigned long long)hi << (20 - shift)) + (lo >> shift);
 }
 
-// Adds the terms floor(E((l_v - m) c) * 2^40) / 2^shift of a vector's elements to acc, down = shift << 23; those in `without`
-// add nothing.
+// Whole parts of terms are summed by binary64 additions whose sum stands at 2^52 or above, where binary64 holds whole
+// numbers only, rounded toward zero: the fraction of a term falls away in the addition and needs no truncation of its own.
+// (asm: the addition must stand between the two changes of the rounding mode, which the compiler does not know of)
+__device__ __forceinline__ double add_whole(double acc, double x)
+{
+    asm volatile("v_add_f64 %0, %0, %1" : "+v"(acc) : "v"(x));
+    return acc;
+}
+constexpr double kWhole = 4503599627370496.0;   // 2^52; what is above it, the low 52 bits, is the sum
+__device__ __forceinline__ void whole_begin() { __builtin_amdgcn_s_setreg((1 << 11) | (2 << 6) | 1, 3); }   // MODE[3:2], binary64 rounding: toward zero
+__device__ __forceinline__ void whole_end() { __builtin_amdgcn_s_setreg((1 << 11) | (2 << 6) | 1, 0); }     // to nearest even again
+
+
+// Adds the terms floor(E((l_v - m) c) * 2^(40 - shift)) of a vector's elements to acc (from kWhole, between whole_begin and
+// whole_end), down = shift << 23; those in `without` add nothing.
 // Bound by the vector ALUs (a handful of rows read from the caches), so a term is formed in few instructions, with
 // the operations of exact_exp2: y + (1.5 2^23 + 40) leaves rint(y) + 40 in the low mantissa bits (an even constant, so
 // ties go as in rint), and that sum shifted to the exponent turns 2^f into the scaled term in one integer addition.
-// Truncated, the term is an integer of at most 2^40 held exactly in binary64; a lane adds at most 64 of them before they
-// go to the integer sum.  (Split into two 20-bit integers, as before, large terms cost nine instructions instead of
-// three: path_exact_kernel over 128 rows of 304 KB 15.2 -> 13.4 us, 672 rows of 100 KB at T = 1 27 -> 23.7.)
+// Its whole part is at most 2^40; a lane adds at most 64 of them before they go to the integer sum.  (Split into two 20-bit
+// integers, large terms cost nine instructions instead of three; path_exact_kernel over 128 rows of 304 KB then took 15.2
+// instead of 13.4 us.  With a truncation per term: update and draft of 4 x 32 rows of 304 KB 49.0 instead of 47.9 us, of
+// 32 x 23 rows of 133 KB 108.7 instead of 105.8.)
 template <int DT>
 __device__ __forceinline__ void add_exact_terms(const uint4 &w, uint32_t without, float m, float c, uint32_t down, double &acc)
 {
@@ -488,8 +502,8 @@ __device__ __forceinline__ void add_exact_terms(const uint4 &w, uint32_t without
         const float y = fmaxf(scaled_offset(x[j], m, c), -64.0f);
         const float k = y + kRound;
         const float p = exact_exp2_fraction(y - (k - kRound));
-        const float term = __builtin_truncf(u2f((f2u(k) << 23) + (f2u(p) - down)));
-        acc += (double)(((without >> j) & 1u) ? 0.0f : term);
+        const float term = u2f((f2u(k) << 23) + (f2u(p) - down));
+        acc = add_whole(acc, (double)(((without >> j) & 1u) ? 0.0f : term));
     }
 }
 
@@ -520,11 +534,13 @@ __device__ __forceinline__ unsigned long long thread_exact_partial(const void *r
             const int i = base + q * nthreads;
             w[q] = load_streamed(&g.vp[i < vlast ? i : vlast]);  // (read once more, then never: 0.5 % of a step against plain loads)
         }
-        double acc = 0.0;
+        double acc = kWhole;
+        whole_begin();
 #pragma unroll
         for (int q = 0; q < INFLIGHT; ++q)
             if (base + q * nthreads < v1) add_exact_terms<DT>(w[q], 0u, m, c, down, acc);
-        S += (unsigned long long)acc;
+        whole_end();
+        S += (unsigned long long)__double_as_longlong(acc) & 0xFFFFFFFFFFFFFull;
     }
     return S;
 }

@@ -336,7 +336,8 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
 #pragma unroll
         for (int k = 0; k < kBatch; ++k)
             if (k0 + k < cpt) w[k] = g.vp[r0 + k0 + k < last ? r0 + k0 + k : last];
-        double acc = 0.0;
+        double acc = kWhole;
+        whole_begin();
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
             if (k0 + k >= cpt) continue;   // uniform
@@ -348,7 +349,8 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
             }
             add_exact_terms<DT>(w[k], r0 + k0 + k < r1 ? without : ~0u, m, a.c, (uint32_t)a.fx_shift << 23, acc);
         }
-        sum += (unsigned long long)acc;
+        whole_end();
+        sum += (unsigned long long)__double_as_longlong(acc) & 0xFFFFFFFFFFFFFull;
     }
     const unsigned long long finc = wave_inclusive_scan_u64(sum);
     const int who = __ffsll((long long)__ballot(rem < finc)) - 1;
