@@ -149,7 +149,7 @@ class StandError(RuntimeError):
 
 
 def _check(rc, handle=None):
-    if rc != 0:
+    if rc:
         msg = lib().stand_strerror(rc).decode()
         if handle is not None and rc == -3:
             msg += " [hip error %d]" % lib().stand_last_hip_error(handle)
@@ -157,16 +157,28 @@ def _check(rc, handle=None):
 
 
 def _dptr(t, dtype=None):
+    # (a plain integer: the functions' argtypes make the pointer)
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous()
     if dtype is not None:
-        assert t.dtype == dtype, (t.dtype, dtype)
-    return C.c_void_p(t.data_ptr())
+        assert t.dtype is dtype, (t.dtype, dtype)
+    return t.data_ptr()
 
 
 def _stream_ptr():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch.cuda.current_stream().cuda_stream
+
+
+# The same for calls that have just been given tensors of the GPU (torch's runtime is up): without the stream object, which
+# costs more than the rest of such a call's arguments together.
+try:
+    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+    def _stream_ptr_up():
+        return _raw_stream(_device())
+except AttributeError:   # (a torch without them)
+    _stream_ptr_up = _stream_ptr
 
 
 class Stand:
@@ -181,6 +193,7 @@ class Stand:
         self.h = C.c_void_p()
         _check(lib().stand_create(C.byref(cfg), C.byref(self.h)))
         self.B, self.N, self.K, self.V = max_batch, par.shape[0], topk, vocab
+        self._lib, self._logits = lib(), max_batch * par.shape[0] * vocab
         self.D = lib().stand_depth(self.h)
         self.W = self.D + 1
         self.logits_dtype = logits_dtype
@@ -198,12 +211,12 @@ class Stand:
             pass
 
     def _logits_ptr(self, logits):
-        assert logits.is_cuda and logits.is_contiguous() and logits.numel() == self.B * self.N * self.V
+        assert logits.is_cuda and logits.is_contiguous() and logits.numel() == self._logits
         if self.logits_dtype == STAND_BF16:
             assert logits.dtype in (torch.bfloat16, torch.uint16, torch.int16)
         else:
             assert logits.dtype == torch.float32
-        return C.c_void_p(logits.data_ptr())
+        return logits.data_ptr()
 
     def new_outputs(self):
         i32 = dict(dtype=torch.int32, device=self.device)
@@ -221,28 +234,28 @@ class Stand:
 
     def update(self, step, logits, commit_tok, commit_row, commit_len):
         assert commit_tok.shape == (self.B, self.W) and commit_row.shape == (self.B, self.W) and commit_len.shape == (self.B,)
-        _check(lib().stand_update(self.h, step, self._logits_ptr(logits), _dptr(commit_tok, torch.int32),
-                                  _dptr(commit_row, torch.int32), _dptr(commit_len, torch.int32), _stream_ptr()), self.h)
+        _check(self._lib.stand_update(self.h, step, self._logits_ptr(logits), _dptr(commit_tok, torch.int32),
+                                  _dptr(commit_row, torch.int32), _dptr(commit_len, torch.int32), _stream_ptr_up()), self.h)
 
     def draft(self, step, draft_tok):
         assert draft_tok.shape == (self.B, self.N)
-        _check(lib().stand_draft(self.h, step, _dptr(draft_tok, torch.int32), _stream_ptr()), self.h)
+        _check(self._lib.stand_draft(self.h, step, _dptr(draft_tok, torch.int32), _stream_ptr_up()), self.h)
 
     def verify(self, step, logits, out_tok, out_node, out_len):
-        _check(lib().stand_verify(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
-                                  _dptr(out_node, torch.int32), _dptr(out_len, torch.int32), _stream_ptr()), self.h)
+        _check(self._lib.stand_verify(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
+                                  _dptr(out_node, torch.int32), _dptr(out_len, torch.int32), _stream_ptr_up()), self.h)
 
     def verify_static(self, step, logits, out_tok, out_node, out_len):
-        _check(lib().stand_verify_static(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
-                                         _dptr(out_node, torch.int32), _dptr(out_len, torch.int32), _stream_ptr()), self.h)
+        _check(self._lib.stand_verify_static(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
+                                         _dptr(out_node, torch.int32), _dptr(out_len, torch.int32), _stream_ptr_up()), self.h)
 
     def static_scratch_need(self):
         return int(lib().stand_static_scratch_need(self.h))
 
     def step(self, step, logits, out_tok, out_node, out_len, next_draft_tok, force_tok=None):
-        _check(lib().stand_step(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
+        _check(self._lib.stand_step(self.h, step, self._logits_ptr(logits), _dptr(out_tok, torch.int32),
                                 _dptr(out_node, torch.int32), _dptr(out_len, torch.int32),
-                                _dptr(next_draft_tok, torch.int32), _dptr(force_tok, torch.int32), _stream_ptr()), self.h)
+                                _dptr(next_draft_tok, torch.int32), _dptr(force_tok, torch.int32), _stream_ptr_up()), self.h)
 
     def row_results(self):
         rows = self.B * self.N
@@ -250,7 +263,7 @@ class Stand:
         s = torch.empty(rows, dtype=torch.float32, device=self.device)
         idx = torch.empty((rows, self.K), dtype=torch.int32, device=self.device)
         p = torch.empty((rows, self.K), dtype=torch.float32, device=self.device)
-        _check(lib().stand_row_results(self.h, _dptr(m), _dptr(s), _dptr(idx), _dptr(p), _stream_ptr()), self.h)
+        _check(self._lib.stand_row_results(self.h, _dptr(m), _dptr(s), _dptr(idx), _dptr(p), _stream_ptr_up()), self.h)
         return m, s, idx, p
 
     def table_export(self):
@@ -312,7 +325,7 @@ class Stand:
         """(mask [B, N, N] uint8, positions [B, N] int64) of the pending drafts, on the GPU."""
         mask = torch.empty((self.B, self.N, self.N), dtype=torch.uint8, device=self.device)
         pos = torch.empty((self.B, self.N), dtype=torch.int64, device=self.device)
-        _check(lib().stand_tree_packing(self.h, _dptr(mask), _dptr(pos), _stream_ptr()), self.h)
+        _check(self._lib.stand_tree_packing(self.h, _dptr(mask), _dptr(pos), _stream_ptr_up()), self.h)
         return mask, pos
 
     def record_slots(self, rows_per_trajectory, orders):
