@@ -114,4 +114,21 @@ inline int plan_tail_ranges(int64_t V, int element_bytes, int64_t B, int waves, 
 // 4 x 32 x 4 50.9 / 66.7 (all slots hold a row); verify, update and draft with 7 x 4 62.3 / 55.0 (paths of one or two rows).
 constexpr bool plan_tail_update(int W, int NO) { return W * NO <= 40; }
 
+// Whether a step of a small batch (row kernel and step_tail_kernel) keeps these two launches where its rows alone would
+// allow the one launch (more than kRowsFew).  One launch / two launches, bf16, us:
+//   up to 1024 rows: 8 x 100 x 32 000 45.0 / 38.5, 16 x 64 x 64 000 57.0 / 53.6, x 152 064 87.0 / 84.1, 32 x 32 x 152 064 89.7 / 84.7;
+//     not of long rows: 13 x 64 x 128 256 fp32 94.8 / 104.8
+//   rows held whole, up to 1600: 16 x 81 x 32 000 48.0 / 45.3, 32 x 50 53.5 / 53.4;  2048: 16 x 128 52.7 / 54.7, 32 x 64 54.9 / 57.5
+//     others beyond 1024: 16 x 81 x 64 000 58.5 / 63.3, 32 x 50 x 64 000 68.2 / 71.7
+//   more than 32 trajectories (one or two tail workgroups each in the one launch): 64 x 32 x 32 000 68.9 / 62.4,
+//     x 64 000 85.9 / 82.4;  x 152 064 124.3 / 142.5, 64 x 48 x 128 256 148.5 / 164.4
+inline bool plan_two_launches(int64_t B, int64_t rows, int64_t V, int element_bytes, int K)
+{
+    // (rows of less than one vector per thread, vocabularies of a few thousand tokens, keep the plain rule on rows)
+    if (row_vectors(V, element_bytes) < kPartThreads) return false;
+    const int64_t bytes = rows * V * element_bytes;
+    return (rows <= 1024 && bytes <= 320000000) || (rows <= 1600 && plan_row_whole(V, element_bytes, K)) ||
+           (B > 32 && rows <= 2048 && bytes <= 265000000);
+}
+
 }  // namespace stand

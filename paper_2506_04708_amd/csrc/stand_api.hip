@@ -772,6 +772,7 @@ static bool step_fused_possible(const stand_handle *h)
     // With few rows the pass is latency-bound, and split rows serve it better (see kRowsFew for where).  With very many the
     // dependent launches are a few per cent of the step, which is all one launch could save, and it varied more
     // from run to run than that (B=128 x 128 nodes: 0.84-0.96 ms against 0.85-0.88 ms).
+    if (h->tail_launch && plan_two_launches(h->B, (int64_t)h->B * h->N, h->V, element_bytes(h->cfg), h->K)) return false;
     return h->B * h->N > kRowsFew && h->B * h->N <= kRowsMany;
 }
 static bool step_fused_wanted(const stand_handle *h)

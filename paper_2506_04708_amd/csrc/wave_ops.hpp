@@ -8,9 +8,8 @@
 namespace stand {
 
 constexpr int kDtBf16 = 0, kDtF32 = 1;
-// At most this many rows: the step's automatic plan keeps the separate launches.  (Part of the interface.  The line was drawn
-// against sixteen waves per row; against the present launches the one launch takes, 528 / 768 rows, us: 50 257 bf16 41.9 for
-// 47.5 / 44.0 for 48.0, 152 064 bf16 62.9 for 62.8 / 71.0 for 69.9.)
+// At most this many rows: the step's automatic plan keeps the separate launches (part of the interface; a small batch keeps
+// its two launches for more rows than that, plan_two_launches).
 constexpr int kRowsFew = 768;
 constexpr int kRowsMany = 8192;             // more rows than this: the step's automatic plan keeps the separate launches
 constexpr int kMaxNodes = 1024;

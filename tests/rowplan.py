@@ -17,6 +17,7 @@ int64_t limit(int64_t rows) { return split_limit(rows); }
 int64_t vectors(int64_t V, int es) { return row_vectors(V, es); }
 int whole(int64_t V, int es, int K) { return plan_row_whole(V, es, K); }
 int ranges(int64_t V, int es, int64_t B) { return plan_tail_ranges(V, es, B, 16, 512); }
+int two_launches(int64_t B, int64_t rows, int64_t V, int es, int K) { return plan_two_launches(B, rows, V, es, K); }
 int loads(int verify, int all_nodes, int64_t B) { return exact_loads(verify, all_nodes, B); }
 int threads() { return kPartThreads; }
 int most_vectors() { return kPartVectors; }
@@ -39,6 +40,7 @@ def lib():
         _lib.row_parts.argtypes = [l, i, l, i]
         _lib.commit_parts.argtypes = [l, i, l, i, i, i, i]
         _lib.waves.argtypes = [l]
+        _lib.two_launches.argtypes = [l, l, l, i, i]
         _lib.whole.argtypes, _lib.ranges.argtypes = [l, i, i], [l, i, l]
         _lib.limit.argtypes, _lib.limit.restype = [l], l
         _lib.loads.argtypes = [i, i, l]

@@ -85,3 +85,12 @@ def test_ranges_of_a_path_row():
     L = rowplan.lib()
     assert [L.ranges(V, 2, 1) for V in (13, 8192, 8200, 152064, 10 ** 7)] == [16, 16, 32, 304, 512]
     assert [L.ranges(152064, 2, B) for B in (16, 17, 64)] == [304, 80, 80]
+
+
+@pytest.mark.parametrize("B,N,V,dtype,two", [
+    (16, 64, 152064, "bf16", True), (16, 65, 152064, "bf16", False), (13, 64, 128256, "f32", False),
+    (32, 50, 32000, "bf16", True), (32, 51, 32000, "bf16", False), (32, 64, 152064, "bf16", False), (32, 64, 96, "bf16", False),
+    (64, 32, 64000, "bf16", True), (64, 33, 32000, "bf16", False), (64, 48, 128256, "bf16", False),
+])
+def test_two_launches_of_a_small_batch(B, N, V, dtype, two):
+    assert bool(rowplan.lib().two_launches(B, B * N, V, rowplan.element_bytes(dtype), 16)) == two
