@@ -5,8 +5,8 @@
 //                                        pass, and the accept/reject outcome of the row's tree node
 //                                                                              (paper Sec. 4.1, 3.2)
 //   row_plan.hpp     (host) which rows are split, and by how much
-//   row_parts.hpp    row_parts_kernel    the same for few rows, and for the rows of an update: every row split over
-//                                        workgroups that hold their part in registers
+//   row_parts.hpp    row_parts_kernel    the same for few rows, for short rows and for the rows of an update: every row split
+//                                        over workgroups that hold their part (or all of it) in registers
 //   path_pass.hpp    path_exact_kernel   exact integer partial sums of the rows on the accepted path;
 //                                        walks the path and gathers the stop node's proposal (Sec. 3.2)
 //                    path_finish_kernel  observation of each path row with the exact normaliser, replay
@@ -28,7 +28,8 @@
 // every probability that is stored in the table or used for resampling, is recomputed with
 // the exact integer normaliser of numeric.hpp, so all decisions are those of exact arithmetic.
 // The kernels after the row pass are chains of dependent instructions and round trips over little data;
-// their workgroups exchange data only across kernel boundaries (row_parts_kernel: through a counter per row).  stand_step_kernel runs the same
+// their workgroups exchange data only across kernel boundaries (row_parts_kernel: through a counter per row).  step_tail_kernel
+// runs them as one launch for small batches, stand_step_kernel the same
 // device functions in one launch and orders them with counters instead.
 #pragma once
 #include "numeric.hpp"
