@@ -116,8 +116,8 @@ typedef struct {
     uint64_t accept_tests;
     uint64_t filter_mismatch;           /* path nodes whose outcome changed under exact arithmetic     */
                                         /* (must stay 0; a self-check of the error bound)              */
-    uint64_t wait_expired;              /* one-launch step: bounded waits that ran out (must stay 0;   */
-                                        /* the outputs of that step are void, see stand_set_wait_limit) */
+    uint64_t wait_expired;              /* waits inside a launch that ran out (must stay 0; outputs of  */
+                                        /* that call are void, see stand_set_wait_limit)                */
     uint64_t late_paths;                /* accepted paths that reached below tree depth upper_depth    */
                                         /* (stand_set_step_plan): what STAND_STEP_AUTO watches          */
 } stand_stats;
@@ -232,11 +232,13 @@ int stand_set_step_plan(stand_handle *h, int32_t mode, int32_t upper_depth, int3
 /* 1 if stand_step on this handle is currently issued as one launch, 0 if as several (see stand_set_step_plan). */
 int stand_step_is_one_launch(const stand_handle *h);
 
-/* Bound, in microseconds, of every wait inside the one-launch step (default 200 000).  A wait that runs
- * out is counted in stand_stats.wait_expired; every kernel still ends normally, but the step's outputs
- * for the affected trajectories are void (out_len 0, tokens -1) and the table must be considered invalid.
- * With a healthy device no wait comes near the default.  0 makes every wait that is not satisfied at once
- * expire (for tests of this path). */
+/* Bound, in microseconds, of every wait inside a launch (default 200 000): in the one-launch step, and in the
+ * launch that follows the rows of a small batch (stand_step in two launches, stand_verify, stand_update).  A
+ * wait that runs out is counted in stand_stats.wait_expired; every kernel still ends normally, but the call's
+ * outputs for the affected trajectories are void (out_len 0, tokens -1) and the table must be considered invalid.
+ * In the launch after the rows of a small batch the context of such a trajectory does not move on, none of its
+ * records is merged and nothing is drafted for it.  With a healthy device no wait comes near the default.
+ * 0 makes every wait that is not satisfied at once expire (for tests of this path). */
 int stand_set_wait_limit(stand_handle *h, uint64_t microseconds);
 
 /* Measurement aid: where the time of the one-launch step goes.  enable != 0 makes later one-launch steps

@@ -387,13 +387,13 @@ __device__ __forceinline__ int draft_prepare(const DraftArgs &a, int b, const Dr
     return level_reg;
 }
 
+// (called after a barrier that follows draft_prepare, or whatever else has filled `sm`)
 template <int NT>
 __device__ __forceinline__ void draft_run(const DraftArgs &a, int b, const DraftShared &sm, int level_reg)
 {
     const int tid = threadIdx.x, N = a.tree.N;
     const int32_t *tok = sm.tok;
     const int32_t(*recent)[kMaxOrder] = sm.recent;
-    __syncthreads();
     const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
     if (a.K <= 16) draft_levels<NT, 4>(a, b, sm, level_reg, clen);
     else draft_levels<NT, 2>(a, b, sm, level_reg, clen);
@@ -414,7 +414,9 @@ __device__ __forceinline__ void draft_run(const DraftArgs &a, int b, const Draft
 template <int NT>
 __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
 {
-    draft_run<NT>(a, b, sm, draft_prepare<NT>(a, b, sm));
+    const int level_reg = draft_prepare<NT>(a, b, sm);
+    __syncthreads();
+    draft_run<NT>(a, b, sm, level_reg);
 }
 
 __global__ __launch_bounds__(kDraftThreads) void draft_kernel(DraftArgs a)

@@ -317,9 +317,11 @@ __device__ __forceinline__ void write_observation(const PathArgs &a, int b, int 
 // its observation and, on the path of a verification, a replay of the row pass's decision.  m: the row's maximum.
 // get_part() gives the lane its share of the row's exact sum; it is called where the sum is needed (a caller may wait for
 // it there).  `walked`: the node's outcome as the caller followed it, or -2: read it from the row pass's results.
-template <int DT, typename GetPart>
+// sum_valid(), asked where the replay differs: whether that share was the whole one (a wait for it may have run out).
+struct AlwaysValid { __device__ __forceinline__ bool operator()() const { return true; } };
+template <int DT, typename GetPart, typename SumValid = AlwaysValid>
 __device__ __forceinline__ void finish_upper_row(const PathArgs &a, int b, int j, int node, float m, const GetPart &get_part, int lane,
-                                                 int walked = -2)
+                                                 int walked = -2, const SumValid &sum_valid = SumValid())
 {
     const int row = b * a.N + node;
     const int src = a.mode == 0 ? row : b * a.R + j;
@@ -345,7 +347,7 @@ __device__ __forceinline__ void finish_upper_row(const PathArgs &a, int b, int j
         const float c_e = c_id >= 0 ? exact_exp2(scaled_offset(c_l, m, a.c)) : 0.0f;
         const NodeTests ct = node_tests_prepare(lane, a.K, c_id, c_mu, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc);
         const NodeResult nr = wave_node_outcome(lane, a.K, ct, c_e / s, c_n, false, 0.0f, a.onehot);
-        if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row])) atomicAdd(&a.stats[kStatMismatch], 1ull);
+        if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row]) && sum_valid()) atomicAdd(&a.stats[kStatMismatch], 1ull);
     }
 }
 

@@ -435,6 +435,9 @@ static RowPassArgs make_row_args(const stand_handle *h, const VerifyScratch &vs,
     return a;
 }
 
+// the handle's wait limit in ticks of the device's constant clock
+static unsigned long long wait_ticks(const stand_handle *h) { return h->wait_limit_us * (uint64_t)h->wall_khz / 1000ull; }
+
 // what the row kernel before a step_tail_kernel clears
 static SumClear tail_clear(const stand_handle *h) { return SumClear{h->tail_part, h->tail_bar, h->W, h->tail_nsub}; }
 
@@ -620,6 +623,7 @@ static int launch_step_tail(stand_handle *h, uint64_t step, const void *d_logits
     A.part = h->tail_part; A.bar = h->tail_bar; A.nsub = h->tail_nsub;
     A.merge = merge != nullptr; A.drafts = draft != nullptr;
     A.given_tok = given_tok; A.ctx_tail = h->ctx_tail; A.ctx_len = h->ctx_len;
+    A.wait_units = (unsigned)((wait_ticks(h) + (1u << kWaitShift) - 1) >> kWaitShift);   // (at most a minute)
     // path rows with workgroups of their own: 2 / 3 / 4 / all, steps of 32 x 64 rows with long paths 151.4 / 147.9 / 148.4 / 149.2 us
     A.row_slots = mode == 0 ? std::min(h->W, 3) : h->W;
     const dim3 grid((unsigned)(h->B + A.row_slots * h->B * (A.nsub / kTailWaves))), block(kTailThreads);
@@ -850,7 +854,7 @@ static int launch_step_fused(stand_handle *h, uint64_t step, const void *d_logit
                                         // consecutive numbers, see RowPub)
     A.sync.pub = RowPub{h->row_pub, h->top_pub, A.sync.epoch};
     A.path.top_pub = h->top_pub;
-    A.sync.wait_ticks = h->wait_limit_us * (uint64_t)h->wall_khz / 1000ull;
+    A.sync.wait_ticks = wait_ticks(h);
     A.sync.stamps = h->stamps;
     if (h->stamps) {
         // earliest start: all ones, latest end: zero (set by a fill kernel; the launch stays capturable)

@@ -45,7 +45,6 @@ constexpr int kStepThreads = 64 * kStepWPR;
 constexpr int kTailInflight = STAND_TAIL_INFLIGHT;  // 16-byte loads a lane of the tail keeps in flight while it sums a row segment
 constexpr int kPathPub = 2 * (kMaxDepth + 2) + 2;  // words per trajectory of the published path
 constexpr unsigned long long kPartThere = 1ull << 63;  // set in a stored partial sum of this launch
-constexpr unsigned kWaitMaxPolls = 1u << 24;  // a wait ends after this many polls whatever the clock says
 
 struct StepSync {
     RowPub pub;                     // what a row hands to the tail: self-validating words, tag = epoch

@@ -27,6 +27,8 @@ namespace stand {
 //   - Between claims and applies, and between applies and the draft's lookups, the trajectories meet at a counter
 //     (cleared by the row kernel as well, so that a recorded launch can be replayed).
 //   - Inside a workgroup the waves meet at counters in shared memory until all of them join for the draft.
+//   - Waits are bounded by the handle's wait limit (TailWait).  When all waves of a trajectory have joined, its waits are over:
+//     one of them that ran out is counted there, the trajectory's outputs are void, its context stays and nothing is drafted.
 // The first B workgroups are resident from the start, and two fit a compute unit: even with launches of other handles
 // beside it (four hardware queues) the summing workgroups, which wait for nothing, have room.
 //
@@ -44,7 +46,6 @@ constexpr int kTailThreads = 1024, kTailWaves = kTailThreads / 64;
 constexpr int kTailBatch = 64;
 constexpr int kSubMax = 512, kSubPerLane = kSubMax / 64;   // most ranges of a row
 constexpr unsigned long long kSumThere = 1ull << 63;   // set in a partial sum (a row's sum is below 2^63)
-constexpr unsigned kTailMaxPolls = 1u << 24;           // a wait ends after this many polls, whatever happens
 
 struct StepTailArgs {
     PathArgs path;
@@ -54,7 +55,9 @@ struct StepTailArgs {
     unsigned *bar;              // [2]
     int nsub;                   // ranges of a row: a multiple of kTailWaves
     int row_slots;              // path rows that have summing workgroups of their own (longer paths loop)
-    bool merge, drafts;         // a verification: neither; an update: merge; a step: both
+    unsigned wait_units;        // bound of every wait in units of wait_clock
+    int merge, drafts;          // a verification: neither; an update: merge; a step: both  (words: as bytes they would be vector
+                                // loads, whose wait is one for every store before them as well)
     const int32_t *given_tok;   // [B][W] tokens committed instead of the emitted ones, or NULL (an update: its tokens)
     int32_t *ctx_tail;
     long long *ctx_len;
@@ -62,9 +65,10 @@ struct StepTailArgs {
 
 struct SmallTail {
     int path[kMaxDepth + 2];
-    int len, ok;
+    int len, ok;                // ok: 0 once a wait of the trajectory has run out (TailWait)
     int arrived[2], met;        // waves that are done with their part before a meeting; the first meeting is over
     int32_t seq[kMaxOrder + kMaxDepth + 2];   // context tail (oldest first), then the committed tokens
+    long long had;                            // length of the context before
     long long slot[kMaxOrder * (kMaxDepth + 1)];   // table slot of each record of the trajectory
     unsigned long long P[kSubMax];
     alignas(16) unsigned long long scratch[kTailWaves][2 * kMaxK];
@@ -156,6 +160,30 @@ __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
     }
 }
 
+__device__ __forceinline__ bool still_ok(const SmallTail *ts)
+{
+    return __hip_atomic_load(&ts->ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
+}
+// The device's constant clock in units of 64 ticks (32 bits of them are 45 minutes at 100 MHz).
+constexpr int kWaitShift = 6;
+__device__ __forceinline__ unsigned wait_clock() { return (unsigned)(wall_clock64() >> kWaitShift); }
+// A wait: whether it, not satisfied yet, goes on for another poll.  It ends after `units` of that clock or kWaitMaxPolls polls,
+// and as soon as another wait of the trajectory has run out.
+struct TailWait {
+    unsigned since = wait_clock(), now = since;
+    unsigned polls = 0u;
+    __device__ __forceinline__ bool goes_on(SmallTail *ts, unsigned units)
+    {
+        // (the clock is far away: its reading is looked at after the next poll)
+        if (now - since < units && ++polls < kWaitMaxPolls && __builtin_amdgcn_readfirstlane(still_ok(ts) ? 1 : 0)) {
+            now = wait_clock();
+            return true;
+        }
+        __hip_atomic_store(&ts->ok, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return false;
+    }
+};
+
 // Lane l waits for the partial sums of ranges [l * q, l * q + q), q = ranges per lane, of path row j.
 // request() asks for them once, wait() asks again until they are there.
 struct SubSums {
@@ -178,19 +206,19 @@ struct SubSums {
         for (int k = 0; k < kSubPerLane; ++k) v[k] = kSumThere;
         ask();
     }
-    __device__ __forceinline__ void wait(SmallTail *ts, int lane)
+    __device__ __forceinline__ void wait(SmallTail *ts, unsigned units)
     {
-        unsigned polls = 0;
+        TailWait w;
+#pragma clang loop unroll(disable)
         for (;;) {
             bool all = true;
 #pragma unroll
             for (int k = 0; k < kSubPerLane; ++k)
                 if (k < q) all &= (v[k] & kSumThere) != 0ull;
-            if (__all(all) || ++polls >= kTailMaxPolls) break;
+            if (__all(all) || !w.goes_on(ts, units)) break;
             __builtin_amdgcn_s_sleep(1);
             ask();
         }
-        if (polls >= kTailMaxPolls && lane == 0) ts->ok = 0;
 #pragma unroll
         for (int k = 0; k < kSubPerLane; ++k) v[k] = k < q && k < here ? v[k] & ~kSumThere : 0ull;
     }
@@ -245,7 +273,7 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     const bool in_sub = my_id >= g.head && my_id < g.tail0;
     const int my_sub = in_sub ? ((my_id - g.head) / EPV) / per : -1;
 
-    part.wait(ts, lane);
+    part.wait(ts, A.wait_units);
     const unsigned long long S = wave_sum_u64(lane_total(part));
     const float s = normaliser_from_fixed(S, a.fx_shift);
     // ---- residual at the stop node
@@ -255,7 +283,7 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
         const NodeResult nr = wave_node_outcome(lane, a.K, tests, my_e / s, nch, false, 0.0f, a.onehot);
         my_r = (lane < a.K && my_id >= 0) ? nr.r : 0.0f;
         rho = nr.rho;
-        if (lane == 0 && nr.accepted != -1) atomicAdd(&a.stats[kStatMismatch], 1ull);  // the stop node rejects all
+        if (lane == 0 && nr.accepted != -1 && still_ok(ts)) atomicAdd(&a.stats[kStatMismatch], 1ull);  // the stop node rejects all
         // a residual that is not a distribution any more (the normalising mass underflowed) is not used
         const float rs = wave_tree_sum(my_r);
         if (!(rs <= 2.0f) || !(rho < __builtin_inff())) support = false;
@@ -370,7 +398,7 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
         }
     }
     // not reachable while the partial sums describe this row; keep the output a valid token
-    if (lane == 0) atomicAdd(&a.stats[kStatMismatch], 1ull);
+    if (lane == 0 && still_ok(ts)) atomicAdd(&a.stats[kStatMismatch], 1ull);
     return top0;
 }
 
@@ -393,9 +421,8 @@ __device__ __forceinline__ void tail_meet(const StepTailArgs &A, int which, Smal
     if (B == 1) return;
     if (lane == 0) {
         atomicAdd(&A.bar[which], 1u);
-        unsigned polls = 0;
-        while (ld_agent(&A.bar[which]) < B && ++polls < kTailMaxPolls) __builtin_amdgcn_s_sleep(1);
-        if (polls >= kTailMaxPolls) ts->ok = 0;
+        TailWait w;
+        while (ld_agent(&A.bar[which]) < B && w.goes_on(ts, A.wait_units)) __builtin_amdgcn_s_sleep(1);
     }
     consume_fence();
 }
@@ -469,6 +496,7 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
             const int jt = lane - kMaxOrder;
             if (!A.given_tok && jt >= 0) v = jt + 1 < len ? stage.tok[ts->path[jt + 1]] : 0;
             if (lane < kMaxOrder + W) ts->seq[lane] = v;
+            if (lane == 0) ts->had = ctx_len;
             __builtin_amdgcn_wave_barrier();
             for (int i = lane; i < ((per_traj + 63) & ~63); i += 64) {
                 int outcome = kClaimNone;
@@ -527,7 +555,7 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
                 if (lane < a.K) { id = a.src_top_idx[row * a.K + lane]; l = a.src_top_l[row * a.K + lane]; }
                 SubSums part;
                 part.request(A, b, j, q, lane);
-                part.wait(ts, lane);
+                part.wait(ts, A.wait_units);
                 const unsigned long long S = wave_sum_u64(lane_total(part));
                 write_observation(a, b, j, id, l, stage.m[node], normaliser_from_fixed(S, a.fx_shift), lane);
                 continue;
@@ -536,9 +564,9 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
             finish_upper_row<DT>(a, b, j, node, m, [&] {
                 SubSums part;
                 part.request(A, b, j, q, lane);
-                part.wait(ts, lane);
+                part.wait(ts, A.wait_units);
                 return lane_total(part);
-            }, lane);
+            }, lane, -2, [&] { return still_ok(ts); });
         }
     }
     if (fresh_args<StepTailArgs>().merge && wave >= first) {
@@ -558,12 +586,17 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
             if (lane == 0) __hip_atomic_store(&ts->met, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         wave_await(&ts->met, 1);
-        if (ts->ok) {
+        if (still_ok(ts)) {
             while (i < n_rec) {
                 if (slot >= 0) apply_claimed(mg, rec0 + i, slot, e, lane, ts->scratch[wave]);
                 i += kTailWaves - first;
                 slot = i < n_rec ? ts->slot[i] : -1;
                 if (slot >= 0) e = request_entry(mg, slot, lane);
+            }
+        } else {
+            for (; i < n_rec; i += kTailWaves - first) {
+                slot = ts->slot[i];
+                if (slot >= 0 && lane == 0) release_claimed(mg, slot);
             }
         }
         if (A.drafts) {
@@ -578,14 +611,7 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
         const StepTailArgs &A = fresh_args<StepTailArgs>();
         const PathArgs &a = A.path;
         const int32_t token = tail_token<DT>(A, ts, stage, b, len, q, lane);
-        if (lane == 0) {
-            a.out_tok[(size_t)b * a.W + (len - 1)] = token;
-            if (!ts->ok) {
-                // (not reachable while the summing workgroups run: the trajectory's outputs are void)
-                atomicAdd(&a.stats[kStatWaitExpired], 1ull);
-                a.out_len[b] = 0;
-            }
-        }
+        if (lane == 0) a.out_tok[(size_t)b * a.W + (len - 1)] = token;
         if (A.drafts) {
             // the new context: the last tokens of tail and commit
             const int jt = lane - kMaxOrder;
@@ -601,8 +627,29 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
             if (lane == 0) { *dsm.clen = now; A.ctx_len[b] = now; }
         }
     }
-    if (!fresh_args<StepTailArgs>().drafts) return;
-    draft_run<kTailThreads>(fresh_args<StepTailArgs>().draft, b, dsm, level_reg);
+    const bool drafts = fresh_args<StepTailArgs>().drafts != 0;
+    __syncthreads();   // (every wave has joined: no wait of this trajectory is left)
+    if (drafts) draft_run<kTailThreads>(fresh_args<StepTailArgs>().draft, b, dsm, level_reg);
+    if (__builtin_expect(!still_ok(ts), 0)) {
+        // (not reachable while the other workgroups run)
+        const StepTailArgs &A = fresh_args<StepTailArgs>();
+        if (tid == 0) atomicAdd(&A.path.stats[kStatWaitExpired], 1ull);
+        if (A.path.mode == 0) {
+            const size_t at = (size_t)b * A.path.W;
+            if (tid < A.path.W) { A.path.out_tok[at + tid] = -1; A.path.out_node[at + tid] = -1; }
+            if (tid == 0) A.path.out_len[b] = 0;
+        }
+        if (A.merge) {   // (the context as it was)
+            if (tid < kMaxOrder) A.ctx_tail[(size_t)b * kMaxOrder + tid] = ts->seq[tid];
+            if (tid == 0) A.ctx_len[b] = ts->had;
+        }
+        if (!drafts) return;
+        for (int u = tid; u < N; u += kTailThreads) {
+            A.draft.draft_tok[(size_t)b * N + u] = -1;
+            A.draft.draft_has[(size_t)b * N + u] = 0;
+            if (A.draft.out_tok) A.draft.out_tok[(size_t)b * N + u] = -1;
+        }
+    }
 }
 
 // (64 registers: two workgroups per compute unit)

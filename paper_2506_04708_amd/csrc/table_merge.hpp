@@ -243,7 +243,16 @@ __device__ __forceinline__ void apply_claimed(const MergeArgs &a, int rec, long 
     if (lane == 0) { st_agent(&h->count, count); st_agent(&h->order, order_word & ((1u << kTagShift) - 1u)); }
 }
 
-// The same for a record whose slot is still to be looked up; does nothing unless it exists.
+// Takes back what the claim of a record that will not be applied left in its slot's header (one lane): no later merge or
+// lookup sees it.
+__device__ __forceinline__ void release_claimed(const MergeArgs &a, long long slot)
+{
+    SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
+    atomicAnd(&h->order, (1u << kTagShift) - 1u);
+    atomicAnd(&h->count, ~kMultiBit);
+}
+
+// apply_claimed for a record whose slot is still to be looked up; does nothing unless it exists.
 __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, unsigned long long *scratch)
 {
     const long long slot = ld_agent(&a.rec_slot[rec]);

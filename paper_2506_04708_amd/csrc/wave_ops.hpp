@@ -12,6 +12,7 @@ constexpr int kDtBf16 = 0, kDtF32 = 1;
 // its two launches for more rows than that, plan_two_launches).
 constexpr int kRowsFew = 768;
 constexpr int kRowsMany = 8192;             // more rows than this: the step's automatic plan keeps the separate launches
+constexpr unsigned kWaitMaxPolls = 1u << 24;  // a wait inside a launch ends after this many polls whatever the clock says
 constexpr int kMaxNodes = 1024;
 constexpr int kMaxDepth = 31;
 constexpr int kPathThreads = 256;

@@ -207,6 +207,75 @@ def test_one_launch_step_waits_are_bounded(gpu):
     ga.close()
 
 
+@pytest.mark.parametrize("call", ["step", "verify", "update"])
+def test_small_batch_waits_are_bounded(gpu, call):
+    """The launch that follows the rows of a small batch keeps the same limit: at zero its waits run out, every call
+    still ends, the expiry is counted, void trajectories have length 0, tokens and nodes -1, no draft and the context they
+    had, and no claim stays behind in the table: with the default limit again, every record of the handle is merged."""
+    binding, lockstep = gpu
+    _say("wait limit 0, %s" % call)
+    w = synth.Workload("cfg3", run_steps=4, V=20000, B=8, rho=0.7)
+    assert w.W * 4 <= 40      # (an update of this tree is one launch after its rows)
+    g = binding.Stand(w.V, w.B, 1, 4, w.K, w.parent, w.T, 1 << 14, 64, 5, binding.STAND_BF16)
+    g.set_step_plan(1, 2, 0, 0)
+    for b in range(w.B):
+        g.set_context(b, w.prompt(b))
+    out_tok, out_node, out_len, d = g.new_outputs()
+    g.draft(0, d)
+    lg = lockstep._logits_to_device(w.logits(0, d.cpu().numpy()), w.dtype)
+    tok = torch.arange(w.B * w.W, dtype=torch.int32, device="cuda").reshape(w.B, w.W) + 100
+    row = torch.zeros((w.B, w.W), dtype=torch.int32, device="cuda")
+    length = torch.full((w.B,), 2, dtype=torch.int32, device="cuda")
+
+    def run(step):
+        if call == "step":
+            g.step(step, lg, out_tok, out_node, out_len, d, tok)
+        elif call == "verify":
+            g.verify(step, lg, out_tok, out_node, out_len)
+        else:
+            g.update(step, lg, tok, row, length)
+        torch.cuda.synchronize()
+
+    def merged():
+        rec = oracle.parse_table_export(g.table_export(), w.K)
+        assert len(rec) == 0 or (int(rec["count"].max()) < 1000 and int(rec["order"].max()) <= 4), "a claim is left in a header"
+        return int(rec["count"].sum()) if len(rec) else 0
+
+    for step in range(3):
+        before = [g.get_context(b, 1)[1] for b in range(w.B)]
+        expired = g.stats().wait_expired
+        g.set_wait_limit(0)
+        run(step)
+        void = g.stats().wait_expired - expired
+        _say("  -> %d waits expired" % void)
+        assert void > 0
+        moved = [g.get_context(b, 1)[1] - before[b] for b in range(w.B)]
+        if call == "verify":
+            assert moved == [0] * w.B
+        elif call == "update":
+            assert all(m in (0, 2) for m in moved) and moved.count(0) == void
+        if call != "update":
+            gl, gt, gn = out_len.cpu().numpy(), out_tok.cpu().numpy(), out_node.cpu().numpy()
+            assert int((gl == 0).sum()) == void
+            for b in range(w.B):
+                assert (gl[b] == 0) == bool((gt[b] == -1).all()) == bool((gn[b] == -1).all())
+                if call == "step":
+                    assert moved[b] == gl[b] and (gl[b] > 0 or (d[b] == -1).all())
+        merged()
+        # the same keys with the default limit: every record counts
+        g.set_wait_limit(200000)
+        g.draft(step, d)
+        expired, counts, stats = g.stats().wait_expired, merged(), g.stats()
+        run(step + 10)
+        now = g.stats()
+        assert now.wait_expired == expired
+        assert merged() - counts == now.inserts + now.merges - stats.inserts - stats.merges
+        assert call == "verify" or now.inserts + now.merges > stats.inserts + stats.merges
+        assert call == "update" or (out_len.cpu().numpy() >= 1).all()
+    assert g.stats().filter_mismatch == 0
+    g.close()
+
+
 @pytest.mark.parametrize("name,over,steps,mode", [
     ("cfg3", dict(V=48, B=4, rho=0.5, filter_margin=1.0), 40, "step"),                      # practically every test decided exactly
     ("cfg3", dict(V=51, B=4, rho=0.5, filter_margin=0.05), 40, "step"),                     # a mix, misaligned rows
