@@ -200,7 +200,8 @@ uint64_t stand_static_scratch_need(const stand_handle *h);
  * rows -> stand_draft(step + 1) into d_next_draft_tok [B][N].
  * If d_force_tok ([B][D+1], may be NULL) is given, the tokens committed to the contexts and
  * used as table keys are d_force_tok[b][0 .. out_len[b]) instead of the emitted ones (replay
- * of a recorded trajectory); the emitted tokens are still returned in d_out_tok. */
+ * of a recorded trajectory); the emitted tokens are still returned in d_out_tok.  d_force_tok == d_out_tok
+ * commits the emitted tokens. */
 int stand_step(stand_handle *h, uint64_t step, const void *d_logits, int32_t *d_out_tok,
                int32_t *d_out_node, int32_t *d_out_len, int32_t *d_next_draft_tok,
                const int32_t *d_force_tok, void *stream);

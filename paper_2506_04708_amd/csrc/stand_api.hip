@@ -967,6 +967,8 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     if (!h || !d_logits || !d_out_tok || !d_out_node || !d_out_len) return STAND_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
+    // (given tokens in the array of the outputs are the emitted ones: that array is written before it is read)
+    if (d_force_tok == d_out_tok) d_force_tok = nullptr;
     const int32_t *commit = d_force_tok ? d_force_tok : d_out_tok;
     // The one launch numbers itself (its waits and the words its rows publish carry the launch's number, given as
     // a kernel argument): recorded into a graph it would be replayed with a number that has passed.  While the

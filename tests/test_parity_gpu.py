@@ -971,6 +971,38 @@ def test_step_recorded_into_a_graph_replays_correctly(gpu, name, over, one_launc
     gb.close()
 
 
+@pytest.mark.parametrize("plan,B", [(0, 1), (1, 3), (FUSED, 3), (1, 65)])
+def test_given_tokens_in_the_output_array_are_the_emitted_ones(gpu, plan, B):
+    """stand_step with d_force_tok == d_out_tok commits what it emits, in every launch form."""
+    binding, lockstep = gpu
+    _say("given tokens in the output array: plan %d, %d trajectories" % (plan, B))
+    w = synth.Workload("cfg1", run_steps=8, V=300, B=B, rho=0.7)
+    hs = []
+    for _ in range(2):
+        o, g = lockstep.make_pair(w, 1 << 12)
+        o.close()
+        g.set_step_plan(plan, 2, 0, 0)
+        for b in range(w.B):
+            g.set_context(b, w.prompt(b))
+        hs.append((g,) + tuple(g.new_outputs()))
+    (ga, ta, na, la, da), (gb, tb, nb, lb, db) = hs
+    ga.draft(0, da)
+    gb.draft(0, db)
+    for step in range(8):
+        lg = lockstep._logits_to_device(w.logits(step, da.cpu().numpy()), w.dtype)
+        ga.step(step, lg, ta, na, la, da)
+        gb.step(step, lg, tb, nb, lb, db, tb)
+        torch.cuda.synchronize()
+        for x, y in ((ta, tb), (na, nb), (la, lb), (da, db)):
+            assert torch.equal(x, y), "step %d" % step
+        for b in range(w.B):
+            (xa, na_), (xb, nb_) = ga.get_context(b, 4), gb.get_context(b, 4)
+            assert na_ == nb_ and np.array_equal(xa, xb)
+    assert np.array_equal(ga.table_export(), gb.table_export())
+    ga.close()
+    gb.close()
+
+
 def test_results_do_not_depend_on_the_work_mapping(gpu):
     """Race detection by permutation: the same 14 closed-loop steps under different workgroup -> work mappings of
     the one-launch step (order in which workgroups take rows, rows placed before the tail, tail workgroups per
