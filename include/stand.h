@@ -73,6 +73,8 @@ extern "C" {
                             /* seldom reach below upper_depth: watched while running), else serial             */
 #define STAND_STEP_SERIAL 1 /* dependent launches: with up to 64 trajectories and accepted-path updates two, the  */
                             /* rows and all the rest; else five: rows, exact sums, finish + claims, apply, draft */
+                            /* (five as well where the device's, or the stream's, compute units do not hold eight */
+                            /* times the trajectories' workgroups at once: those wait for each other)           */
 #define STAND_STEP_FUSED 2  /* one launch: the dependent tail runs beside the rows that are still streaming      */
 
 #define STAND_MAX_TOPK 32

@@ -98,6 +98,11 @@ inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int
 // row is summed, which fills the vector ALUs at any batch size: all-nodes steps of 16 x 64 rows 357 / 331, 4 x 64 98 / 94.
 constexpr int exact_loads(bool verify, bool all_nodes, int64_t B) { return verify && !all_nodes && B <= 16 ? 2 : 4; }
 
+// Whether the workgroups of B trajectories may wait in step_tail_kernel, for each other and for workgroups that are started
+// behind them, on compute units that hold `places` such workgroups at once: they take at most an eighth of the places, so
+// that the others have room with launches of seven more such batches beside them.
+constexpr bool plan_tail_places(int64_t B, int64_t places) { return 8 * B <= places; }
+
 // Ranges of vectors of a path row in step_tail_kernel, each summed by one wave; workgroups hold `waves` of them.  One vector
 // per lane for a few trajectories, where the latency of a sum counts; four where so many workgroups would wait to be
 // started.  Steps with 1 / 2 vectors per lane, us: 1 x 32 rows x 152 064 25.6 / 27.6, 8 x 32 x 128 256 41.4 / 42.0; with

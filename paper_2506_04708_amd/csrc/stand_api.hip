@@ -77,6 +77,7 @@ struct stand_handle {
     int row_parts, commit_parts;
     // small batches: what follows the row kernel is one launch (step_tail.hpp)
     bool tail_launch, tail_update;   // of a step or verification; of an update
+    int tail_per_cu, cus;            // workgroups of step_tail_kernel a compute unit holds at once; the device's compute units
     int tail_nsub;                   // ranges of a path row that are summed by a wave each
     unsigned long long *tail_part;   // [B][W][tail_nsub]
     unsigned *tail_bar;              // [2]
@@ -295,7 +296,11 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);
     acc(dmalloc(&h->part_ticket, part_tickets));
     acc(dmalloc(&h->part_head, part_slots)); acc(dmalloc(&h->part_keys, part_slots * kPartKeys));
-    h->tail_launch = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch;
+    const void *tail_fn = cfg->logits_dtype == STAND_BF16 ? (const void *)step_tail_kernel<kDtBf16> : (const void *)step_tail_kernel<kDtF32>;
+    acc(hipOccupancyMaxActiveBlocksPerMultiprocessor(&h->tail_per_cu, tail_fn, kTailThreads, tail_shared_bytes(N)));
+    acc(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, cfg->device));
+    h->tail_launch = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch &&
+                     plan_tail_places(h->B, (int64_t)h->tail_per_cu * h->cus);
     h->tail_update = h->tail_launch && plan_tail_update(h->W, h->NO);
     h->tail_nsub = plan_tail_ranges(h->V, element_bytes(*cfg), h->B, kTailWaves, kSubMax);
     acc(dmalloc(&h->tail_part, h->tail_launch ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, 2));
@@ -435,6 +440,19 @@ static RowPassArgs make_row_args(const stand_handle *h, const VerifyScratch &vs,
     return a;
 }
 
+// Compute units that launches on stream s may use (a stream, or all of a process's, may be masked to some of the device's);
+// 0 if that is not known.
+static int stream_cus(const stand_handle *h, hipStream_t s)
+{
+    uint32_t mask[64] = {};   // 2048 compute units
+    if (hipExtStreamGetCUMask(s, 64, mask) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    int n = 0;
+    for (uint32_t w : mask) n += __builtin_popcount(w);
+    return std::min(n, h->cus);
+}
+// Whether the trajectories' workgroups may wait inside a launch on this stream.
+static bool tail_fits(const stand_handle *h, hipStream_t s) { return plan_tail_places(h->B, (int64_t)h->tail_per_cu * stream_cus(h, s)); }
+
 // the handle's wait limit in ticks of the device's constant clock
 static unsigned long long wait_ticks(const stand_handle *h) { return h->wait_limit_us * (uint64_t)h->wall_khz / 1000ull; }
 
@@ -468,7 +486,8 @@ static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r,
 
 // `own`: the scratch is the handle's own (the parts of a split row meet in the handle's memory, which a caller of the
 // entry point with fixed scratch may not expect to be in use).
-static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, bool own, hipStream_t s)
+// `own`: the handle's scratch; `tail`: a step_tail_kernel follows
+static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, bool own, bool tail, hipStream_t s)
 {
     const int rows = h->B * h->N;
     // (few rows of the entry point with fixed scratch keep sixteen waves each; a grid has at most 65535 trajectories)
@@ -478,7 +497,7 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
     const bool few = unsplit_waves(rows) == kRowWPRFewRows;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * parts : (few ? kRowWPRFewRows : kRowWPR));
-    if (own && h->tail_launch) a.clear = tail_clear(h);
+    if (tail) a.clear = tail_clear(h);
     RowPartsArgs pa = make_parts_args(h, a, split ? parts : 1);
     const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
     const dim3 grid = split ? dim3((unsigned)parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
@@ -678,9 +697,10 @@ extern "C" int stand_update(stand_handle *h, uint64_t step, const void *d_logits
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
     const MergeArgs mg = merge_args(h, d_commit_tok, d_commit_row, d_commit_len);
-    int rc = launch_commit_rows(h, step, d_logits, d_commit_row, d_commit_len, h->tail_update, s);
+    const bool tail = h->tail_update && tail_fits(h, s);
+    int rc = launch_commit_rows(h, step, d_logits, d_commit_row, d_commit_len, tail, s);
     if (rc) return rc;
-    if (h->tail_update)
+    if (tail)
         return launch_step_tail(h, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, d_commit_tok, &mg, nullptr, s);
     rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, s);
     if (rc) return rc;
@@ -712,9 +732,10 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     if (!h || !d_logits || !d_out_tok || !d_out_node || !d_out_len) return STAND_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
-    int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
+    const bool tail = h->tail_launch && tail_fits(h, s);
+    int rc = launch_row_pass(h, h->vs, step, d_logits, true, tail, s);
     if (rc) return rc;
-    if (h->tail_launch)
+    if (tail)
         return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, nullptr, s);
     return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
@@ -753,7 +774,7 @@ extern "C" int stand_verify_static(stand_handle *h, uint64_t step, const void *d
     // Nothing in the scratch has to start at zero: every word a kernel of the verification reads was written
     // by an earlier kernel of the same call (row results and outcomes for all rows; partial sums, stop records
     // and observations for exactly the path rows that are read back).
-    int rc = launch_row_pass(h, vs, step, d_logits, false, s);
+    int rc = launch_row_pass(h, vs, step, d_logits, false, false, s);
     if (rc) return rc;
     return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
@@ -979,10 +1000,11 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     plan_observe(h, s, capturing);
     if (!capturing && step_fused_wanted(h))
         return launch_step_fused(h, step, d_logits, d_out_tok, d_out_node, d_out_len, d_next_draft_tok, commit, s);
-    int rc = launch_row_pass(h, h->vs, step, d_logits, true, s);
+    const bool tail = h->tail_launch && tail_fits(h, s);
+    int rc = launch_row_pass(h, h->vs, step, d_logits, true, tail, s);
     if (rc) return rc;
     const MergeArgs mg = merge_args(h, commit, nullptr, d_out_len);
-    if (h->tail_launch) {
+    if (tail) {
         const DraftArgs da = make_draft_args(h, step + 1, d_next_draft_tok, commit, d_out_len);
         return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, d_force_tok, &mg, &da, s);
     }

@@ -29,8 +29,9 @@ namespace stand {
 //   - Inside a workgroup the waves meet at counters in shared memory until all of them join for the draft.
 //   - Waits are bounded by the handle's wait limit (TailWait).  When all waves of a trajectory have joined, its waits are over:
 //     one of them that ran out is counted there, the trajectory's outputs are void, its context stays and nothing is drafted.
-// The first B workgroups are resident from the start, and two fit a compute unit: even with launches of other handles
-// beside it (four hardware queues) the summing workgroups, which wait for nothing, have room.
+// The first B workgroups are resident from the start and take at most an eighth of what the stream's compute units hold at
+// once (plan_tail_places; asked for every call, a stream may be masked to a few of them): the summing workgroups, which wait
+// for nothing, have room, with launches of other handles beside it as well.
 //
 // Bound by latency: of the 13.5 us of one launch for 1 x 32 rows x 152 064 (clock readings), the path is known at 1.4,
 // the last sum is stored at 3, seen at 4.4 (a word travels about 1 us from one workgroup to another), the token is there
@@ -41,8 +42,8 @@ namespace stand {
 // The arguments are read again in each phase (fresh_args): kept from the start they were 361 spilled scalar registers.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTailThreads = 1024, kTailWaves = kTailThreads / 64;
-// Most trajectories.  (63 x 15 rows x 198 592 130.0 / 128.1 us; beyond, the first workgroups would be more than a share of
-// the device that several launches can have at once, and the launches saved are few per cent of such steps.)
+// Most trajectories.  (63 x 15 rows x 198 592 130.0 / 128.1 us; beyond, the first workgroups would be more than an eighth of
+// the device, and the launches saved are few per cent of such steps.)
 constexpr int kTailBatch = 64;
 constexpr int kSubMax = 512, kSubPerLane = kSubMax / 64;   // most ranges of a row
 constexpr unsigned long long kSumThere = 1ull << 63;   // set in a partial sum (a row's sum is below 2^63)

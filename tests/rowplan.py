@@ -18,6 +18,7 @@ int64_t vectors(int64_t V, int es) { return row_vectors(V, es); }
 int whole(int64_t V, int es, int K) { return plan_row_whole(V, es, K); }
 int ranges(int64_t V, int es, int64_t B) { return plan_tail_ranges(V, es, B, 16, 512); }
 int two_launches(int64_t B, int64_t rows, int64_t V, int es, int K) { return plan_two_launches(B, rows, V, es, K); }
+int tail_places(int64_t B, int64_t places) { return plan_tail_places(B, places); }
 int loads(int verify, int all_nodes, int64_t B) { return exact_loads(verify, all_nodes, B); }
 int threads() { return kPartThreads; }
 int most_vectors() { return kPartVectors; }
@@ -42,6 +43,7 @@ def lib():
         _lib.waves.argtypes = [l]
         _lib.two_launches.argtypes = [l, l, l, i, i]
         _lib.whole.argtypes, _lib.ranges.argtypes = [l, i, i], [l, i, l]
+        _lib.tail_places.argtypes = [l, l]
         _lib.limit.argtypes, _lib.limit.restype = [l], l
         _lib.loads.argtypes = [i, i, l]
         _lib.vectors.argtypes, _lib.vectors.restype = [l, i], l

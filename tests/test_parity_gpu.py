@@ -1003,6 +1003,61 @@ def test_given_tokens_in_the_output_array_are_the_emitted_ones(gpu, plan, B):
     gb.close()
 
 
+def _masked_stream(words):
+    """A stream restricted to the compute units of the mask, or None where the runtime does not give one."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    p = ctypes.c_void_p()
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(p), len(words), (ctypes.c_uint32 * len(words))(*words)) != 0:
+        hip.hipGetLastError()
+        return None, None
+    return torch.cuda.ExternalStream(p.value), lambda: hip.hipStreamDestroy(p)
+
+
+@pytest.mark.parametrize("B", [8, 9, 64])
+def test_stream_of_few_compute_units(gpu, B):
+    """On a stream masked to 32 compute units (64 places for the workgroups that wait for each other) the calls of a batch
+    of 8 still end in one launch after their rows; larger ones take the separate launches.  Outputs, drafts and tables are
+    those of the whole device, and no wait runs out."""
+    binding, lockstep = gpu
+    stream, destroy = _masked_stream([0xFFFFFFFF])
+    if stream is None:
+        pytest.skip("the runtime gives no stream masked to some compute units")
+    assert bool(rowplan.lib().tail_places(B, 64)) == (B == 8)
+    _say("masked stream, %d trajectories" % B)
+    w = synth.Workload("cfg1", run_steps=8, V=3000, B=B, rho=0.7)
+    hs = []
+    for _ in range(2):
+        o, g = lockstep.make_pair(w, 1 << 14)
+        o.close()
+        g.set_step_plan(1, 2, 0, 0)
+        for b in range(w.B):
+            g.set_context(b, w.prompt(b))
+        hs.append((g,) + tuple(g.new_outputs()))
+    (ga, ta, na, la, da), (gb, tb, nb, lb, db) = hs
+    ga.draft(0, da)
+    gb.draft(0, db)
+    for step in range(8):
+        lg = lockstep._logits_to_device(w.logits(step, da.cpu().numpy()), w.dtype)
+        torch.cuda.synchronize()
+        for (g, t, n, l, d), s in ((hs[0], torch.cuda.current_stream()), (hs[1], stream)):
+            with torch.cuda.stream(s):
+                if step % 2:
+                    g.step(step, lg, t, n, l, d)
+                else:
+                    g.verify(step, lg, t, n, l)
+                    g.update(step, lg, t, n, l)
+                    g.draft(step + 1, d)
+            torch.cuda.synchronize()
+        for x, y in ((ta, tb), (na, nb), (la, lb), (da, db)):
+            assert torch.equal(x, y), "step %d" % step
+    assert np.array_equal(ga.table_export(), gb.table_export())
+    assert ga.stats().wait_expired == 0 and gb.stats().wait_expired == 0
+    ga.close()
+    gb.close()
+    destroy()
+
+
 def test_results_do_not_depend_on_the_work_mapping(gpu):
     """Race detection by permutation: the same 14 closed-loop steps under different workgroup -> work mappings of
     the one-launch step (order in which workgroups take rows, rows placed before the tail, tail workgroups per

@@ -87,6 +87,13 @@ def test_ranges_of_a_path_row():
     assert [L.ranges(152064, 2, B) for B in (16, 17, 64)] == [304, 80, 80]
 
 
+def test_waiting_workgroups_leave_room():
+    """At most an eighth of the places of the compute units that may be used: 256 of two places each, 32 of them, one."""
+    assert [rowplan.lib().tail_places(B, 512) for B in (1, 64, 65)] == [1, 1, 0]
+    assert [rowplan.lib().tail_places(B, 64) for B in (8, 9)] == [1, 0]
+    assert [rowplan.lib().tail_places(1, p) for p in (8, 7, 0)] == [1, 0, 0]
+
+
 @pytest.mark.parametrize("B,N,V,dtype,two", [
     (16, 64, 152064, "bf16", True), (16, 65, 152064, "bf16", False), (13, 64, 128256, "f32", False),
     (32, 50, 32000, "bf16", True), (32, 51, 32000, "bf16", False), (32, 64, 152064, "bf16", False), (32, 64, 96, "bf16", False),
