@@ -53,7 +53,7 @@ struct stand_handle {
     int upper_depth;     // rows of nodes up to this depth are dispatched before the tail
     int tail_groups;     // tail workgroups per trajectory (0: chosen from the batch size)
     int rows_first;      // row workgroups dispatched before the tail's (0: as many as the device holds at once)
-    int step_slots;      // workgroups of stand_step_kernel the device holds at once (0: not asked yet)
+    int step_per_cu;     // workgroups of stand_step_kernel a compute unit holds at once
     uint32_t shuffle;    // non-zero: row slots are permuted (a test of independence from the work mapping)
     uint64_t wait_limit_us;
     int wall_khz;        // rate of the device's constant clock (wall_clock64)
@@ -216,7 +216,6 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     h->upper_depth = 2;
     h->tail_groups = 0;
     h->rows_first = 0;
-    h->step_slots = 0;
     h->shuffle = 0;
     h->wait_limit_us = 200000;
     h->stamps = nullptr;
@@ -299,6 +298,8 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     const void *tail_fn = cfg->logits_dtype == STAND_BF16 ? (const void *)step_tail_kernel<kDtBf16> : (const void *)step_tail_kernel<kDtF32>;
     acc(hipOccupancyMaxActiveBlocksPerMultiprocessor(&h->tail_per_cu, tail_fn, kTailThreads, tail_shared_bytes(N)));
     acc(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, cfg->device));
+    const void *step_fn = cfg->logits_dtype == STAND_BF16 ? (const void *)stand_step_kernel<kDtBf16> : (const void *)stand_step_kernel<kDtF32>;
+    acc(hipOccupancyMaxActiveBlocksPerMultiprocessor(&h->step_per_cu, step_fn, kStepThreads, step_shared_bytes(N)));
     h->tail_launch = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch &&
                      plan_tail_places(h->B, (int64_t)h->tail_per_cu * h->cus);
     h->tail_update = h->tail_launch && plan_tail_update(h->W, h->NO);
@@ -850,6 +851,10 @@ static int step_tail_groups(const stand_handle *h)
     return h->tail_groups > 0 ? h->tail_groups : (h->B <= 32 ? 3 : (h->B <= 64 ? 2 : 1));
 }
 
+// Whether the tail of the one launch leaves two thirds of the stream's places to the rows it waits for (on a whole device of
+// 256 compute units: B * groups <= 256, step_fused_possible).
+static bool step_fits(const stand_handle *h, hipStream_t s) { return 3 * (int64_t)h->B * step_tail_groups(h) <= (int64_t)h->step_per_cu * stream_cus(h, s); }
+
 static uint32_t gcd_u32(uint32_t a, uint32_t b) { while (b) { const uint32_t t = a % b; a = b; b = t; } return a; }
 
 static int launch_step_fused(stand_handle *h, uint64_t step, const void *d_logits, int32_t *out_tok, int32_t *out_node,
@@ -886,13 +891,8 @@ static int launch_step_fused(stand_handle *h, uint64_t step, const void *d_logit
     A.upper_nodes = h->level_start[ud + 1];
     const void *fn = bf16 ? (const void *)stand_step_kernel<kDtBf16> : (const void *)stand_step_kernel<kDtF32>;
     const size_t smem = step_shared_bytes(h->N);
-    if (h->step_slots == 0) {
-        // how many of the kernel's workgroups are resident at once: the rows before the tail fill the device once
-        int per_cu = 0, cus = 0;
-        HIP_TRY(h, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kStepThreads, smem));
-        HIP_TRY(h, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->cfg.device));
-        h->step_slots = per_cu * cus > 0 ? per_cu * cus : 1;
-    }
+    // how many of the kernel's workgroups are resident at once: the rows before the tail fill the device once
+    const uint32_t slots = (uint32_t)std::max(h->step_per_cu * h->cus, 1);
     const uint32_t rows = (uint32_t)(h->B * h->N), n_up = (uint32_t)(A.upper_nodes * h->B);
     A.shuffle_mul = 1; A.shuffle_add = 0;
     if (h->shuffle) {
@@ -910,7 +910,7 @@ static int launch_step_fused(stand_handle *h, uint64_t step, const void *d_logit
         // 126.5 against 129.8 us per step at B = 32, 64 nodes); the other tail workgroups take the slots the first
         // rows free.  Never fewer rows than the upper levels have.
         const uint32_t early = (uint32_t)h->B * (uint32_t)(A.G < 2 ? A.G : 2);
-        const uint32_t deflt = (uint32_t)h->step_slots > early ? (uint32_t)h->step_slots - early : 1u;
+        const uint32_t deflt = slots > early ? slots - early : 1u;
         const uint32_t want = h->rows_first > 0 ? (uint32_t)h->rows_first : deflt;
         const uint32_t first = want > n_up ? want : n_up;
         A.rows_first = (int)(first < row_wgs ? first : row_wgs);
@@ -998,7 +998,7 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) { (void)hipGetLastError(); cap = hipStreamCaptureStatusNone; }
     const bool capturing = cap != hipStreamCaptureStatusNone;
     plan_observe(h, s, capturing);
-    if (!capturing && step_fused_wanted(h))
+    if (!capturing && step_fused_wanted(h) && step_fits(h, s))
         return launch_step_fused(h, step, d_logits, d_out_tok, d_out_node, d_out_len, d_next_draft_tok, commit, s);
     const bool tail = h->tail_launch && tail_fits(h, s);
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, tail, s);

@@ -1014,23 +1014,23 @@ def _masked_stream(words):
     return torch.cuda.ExternalStream(p.value), lambda: hip.hipStreamDestroy(p)
 
 
-@pytest.mark.parametrize("B", [8, 9, 64])
-def test_stream_of_few_compute_units(gpu, B):
+@pytest.mark.parametrize("plan,B", [(1, 8), (1, 9), (1, 64), (FUSED, 8), (FUSED, 64), (0, 64)])
+def test_stream_of_few_compute_units(gpu, plan, B):
     """On a stream masked to 32 compute units (64 places for the workgroups that wait for each other) the calls of a batch
-    of 8 still end in one launch after their rows; larger ones take the separate launches.  Outputs, drafts and tables are
-    those of the whole device, and no wait runs out."""
+    of 8 still end in one launch after their rows; larger ones take the separate launches, and so do steps of 64 whose plan
+    is the one launch.  Outputs, drafts and tables are those of the whole device, and no wait runs out."""
     binding, lockstep = gpu
     stream, destroy = _masked_stream([0xFFFFFFFF])
     if stream is None:
         pytest.skip("the runtime gives no stream masked to some compute units")
     assert bool(rowplan.lib().tail_places(B, 64)) == (B == 8)
-    _say("masked stream, %d trajectories" % B)
+    _say("masked stream, plan %d, %d trajectories" % (plan, B))
     w = synth.Workload("cfg1", run_steps=8, V=3000, B=B, rho=0.7)
     hs = []
     for _ in range(2):
         o, g = lockstep.make_pair(w, 1 << 14)
         o.close()
-        g.set_step_plan(1, 2, 0, 0)
+        g.set_step_plan(plan, 2, 0, 0)
         for b in range(w.B):
             g.set_context(b, w.prompt(b))
         hs.append((g,) + tuple(g.new_outputs()))
