@@ -103,14 +103,22 @@ constexpr int exact_loads(bool verify, bool all_nodes, int64_t B) { return verif
 // that the others have room with launches of seven more such batches beside them.
 constexpr bool plan_tail_places(int64_t B, int64_t places) { return 8 * B <= places; }
 
-// Ranges of vectors of a path row in step_tail_kernel, each summed by one wave; workgroups hold `waves` of them.  One vector
-// per lane for a few trajectories, where the latency of a sum counts; four where so many workgroups would wait to be
-// started.  Steps with 1 / 2 vectors per lane, us: 1 x 32 rows x 152 064 25.6 / 27.6, 8 x 32 x 128 256 41.4 / 42.0; with
-// 1 / 2 / 4 / 8: 32 x 64 x 152 064, long paths 158.6 / 152.0 / 148.3 / 149.6.
+// Ranges of vectors of a path row in step_tail_kernel, each summed by one wave; workgroups hold `waves` of them.  Rows are cut
+// as finely as one vector per lane for a few trajectories, where the latency of a sum counts, else four: steps with 1 / 2
+// vectors per lane, us: 1 x 32 rows x 152 064 25.6 / 27.6, 8 x 32 x 128 256 41.4 / 42.0; with 1 / 2 / 4 / 8: 32 x 64 x 152 064,
+// long paths 158.6 / 152.0 / 148.3 / 149.6.  But not into more than 2048 ranges (4096 beyond 16 trajectories) of all
+// trajectories' rows together, unless they were longer than eight vectors per lane: more workgroups only wait to be started and
+// take the trajectories' waves their turn; and never into more than 8192.  Steps of paths of two / five rows, us:
+//   finest / 8192 / 4096 / 2048 ranges in all:  16 x 16 rows x 128 256 46.2, 52.6 / same / 46.1, 52.6 / 44.7, 49.8;
+//     16 x 16 x 300 000 69.9, 83.6 / same / 64.9, 74.7 / 62.7, 70.7;  32 x 16 x 300 000 91.2, 105.3 / same / 91.8, 106.7 / 91.5, 103.1;
+//     32 x 16 x 1 000 003 227.7, 266.5 / 223.4, 256.1 / 221.7, 253.8 / 238.3, 256.3;
+//     64 x 16 x 1 000 003 435.9, 520.9 / 417.1, 479.4 / 421.3, 492.4 / 457.9, 492.4 (separate launches 413.7, 466.9)
 inline int plan_tail_ranges(int64_t V, int element_bytes, int64_t B, int waves, int most)
 {
-    const int64_t per_wave = 64 * (B <= 16 ? 1 : 4);
-    const int64_t n = (row_vectors(V, element_bytes) + per_wave - 1) / per_wave;
+    const bool few = B <= 16;
+    const int64_t vectors = row_vectors(V, element_bytes), finest = 64 * (few ? 1 : 4);
+    const int64_t most_ranges = std::min<int64_t>((vectors + finest - 1) / finest, std::min<int64_t>(8192 / B, most));
+    const int64_t n = std::min<int64_t>(std::max<int64_t>(vectors / 512, (few ? 2048 : 4096) / B), most_ranges);
     return (int)std::min<int64_t>((n + waves - 1) / waves * waves, most);
 }
 

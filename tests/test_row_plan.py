@@ -81,10 +81,19 @@ def test_rows_held_whole():
 
 
 def test_ranges_of_a_path_row():
-    """Whole workgroups of sixteen waves, at most 512 ranges; one vector per lane for few trajectories, four for many."""
+    """Whole workgroups of sixteen waves, at most 512 ranges; one vector per lane for few trajectories, four for many, as
+    long as not too many workgroups are asked for."""
     L = rowplan.lib()
     assert [L.ranges(V, 2, 1) for V in (13, 8192, 8200, 152064, 10 ** 7)] == [16, 16, 32, 304, 512]
-    assert [L.ranges(152064, 2, B) for B in (16, 17, 64)] == [304, 80, 80]
+    assert [L.ranges(152064, 2, B) for B in (4, 8, 16, 17, 32, 64)] == [304, 256, 128, 80, 80, 64]
+    # all trajectories' rows together: not above 2048 or 4096 unless ranges would be longer than 512 vectors, never above 8192
+    assert [L.ranges(300000, 2, B) for B in (1, 16, 32, 64)] == [512, 128, 128, 80]
+    assert [L.ranges(10 ** 6, 2, B) for B in (16, 32, 64)] == [256, 256, 128]
+    for V in (13, 500, 32003, 128256, 300000, 10 ** 6, 4 * 10 ** 6):
+        for B in range(1, 65):
+            n, vec = L.ranges(V, 2, B), L.vectors(V, 2)
+            assert n % 16 == 0 and 16 <= n <= 512 and B * (n - 16) < 8192
+            assert -(-vec // n) <= 64 * 16 or B * n > 4096 or n == 512
 
 
 def test_waiting_workgroups_leave_room():
