@@ -122,6 +122,17 @@ inline int plan_tail_ranges(int64_t V, int element_bytes, int64_t B, int waves, 
     return (int)std::min<int64_t>((n + waves - 1) / waves * waves, most);
 }
 
+// Path rows of a verification that have summing workgroups of their own, `groups` each (the others are taken after them): as
+// many as 512 workgroups serve, at least three.  2 / 3 / 4 / all, steps of 32 x 64 rows x 152 064 (5 groups) with long paths
+// 151.4 / 147.9 / 148.4 / 149.2 us.  Three / as many as 512 workgroups serve, verifications, us (separate launches): 24 x 64 rows
+// x 32 000 (1 group), paths of 2 / 5 / up to 11 rows 36.2 / 36.2 (37.9), 40.0 / 36.3 (38.9), 46.7 / 37.1 (41.3); 32 x 31 x 32 000, up to 16
+// rows, 40.6 / 32.9 (35.0); 8 x 64 x 152 064 (16 groups), 5 rows, 48.5 / 45.3 (47.1).
+constexpr int plan_tail_slots(int64_t B, int W, int groups)
+{
+    const int64_t n = 512 / (B * groups);
+    return (int)(n < 3 ? (W < 3 ? W : 3) : (n < W ? n : W));
+}
+
 // Whether an update with W row slots and NO orders takes step_tail_kernel, where one workgroup finishes a trajectory's rows
 // and applies its records: separate launches / one, us: update and draft of 6 x 14 rows x 4 orders 35.7 / 37.4, of
 // 4 x 32 x 4 50.9 / 66.7 (all slots hold a row); verify, update and draft with 7 x 4 62.3 / 55.0 (paths of one or two rows).

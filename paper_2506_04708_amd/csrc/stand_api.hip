@@ -644,8 +644,7 @@ static int launch_step_tail(stand_handle *h, uint64_t step, const void *d_logits
     A.merge = merge != nullptr; A.drafts = draft != nullptr;
     A.given_tok = given_tok; A.ctx_tail = h->ctx_tail; A.ctx_len = h->ctx_len;
     A.wait_units = (unsigned)((wait_ticks(h) + (1u << kWaitShift) - 1) >> kWaitShift);   // (at most a minute)
-    // path rows with workgroups of their own: 2 / 3 / 4 / all, steps of 32 x 64 rows with long paths 151.4 / 147.9 / 148.4 / 149.2 us
-    A.row_slots = mode == 0 ? std::min(h->W, 3) : h->W;
+    A.row_slots = mode == 0 ? plan_tail_slots(h->B, h->W, A.nsub / kTailWaves) : h->W;
     const dim3 grid((unsigned)(h->B + A.row_slots * h->B * (A.nsub / kTailWaves))), block(kTailThreads);
     const size_t smem = tail_shared_bytes(h->N);
     if (bf16) step_tail_kernel<kDtBf16><<<grid, block, smem, s>>>(A);

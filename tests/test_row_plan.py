@@ -96,6 +96,12 @@ def test_ranges_of_a_path_row():
             assert -(-vec // n) <= 64 * 16 or B * n > 4096 or n == 512
 
 
+def test_path_rows_with_summing_workgroups():
+    """As many as 512 workgroups serve, at least three, no more than a path has."""
+    s = rowplan.lib().tail_slots
+    assert [s(1, 7, 19), s(1, 32, 19), s(1, 32, 32), s(8, 7, 16), s(32, 9, 5), s(24, 32, 1), s(64, 2, 8), s(64, 11, 8)] == [7, 26, 16, 4, 3, 21, 2, 3]
+
+
 def test_waiting_workgroups_leave_room():
     """At most an eighth of the places of the compute units that may be used: 256 of two places each, 32 of them, one."""
     assert [rowplan.lib().tail_places(B, 512) for B in (1, 64, 65)] == [1, 1, 0]
