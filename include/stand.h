@@ -69,10 +69,11 @@ extern "C" {
 
 /* How stand_step issues its work (results are the same; see stand_set_step_plan). */
 #define STAND_STEP_AUTO 0   /* one launch where it pays (769 .. 8192 rows, from about 1024 rows or 320 MB of     */
-                            /* logits with up to 64 trajectories; accepted-path updates, accepted paths that    */
+                            /* logits in small batches; accepted-path updates, accepted paths that              */
                             /* seldom reach below upper_depth: watched while running), else serial             */
-#define STAND_STEP_SERIAL 1 /* dependent launches: with up to 64 trajectories and accepted-path updates two, the  */
-                            /* rows and all the rest; else five: rows, exact sums, finish + claims, apply, draft */
+#define STAND_STEP_SERIAL 1 /* dependent launches: two in small batches (up to 64 trajectories, up to 2048 slots */
+                            /* of trajectories x path tokens x orders, accepted-path updates), the rows and all  */
+                            /* the rest; else five: rows, exact sums, finish + claims, apply, draft             */
                             /* (five as well where the device's, or the stream's, compute units do not hold eight */
                             /* times the trajectories' workgroups at once: those wait for each other)           */
 #define STAND_STEP_FUSED 2  /* one launch: the dependent tail runs beside the rows that are still streaming      */

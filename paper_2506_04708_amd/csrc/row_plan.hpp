@@ -133,10 +133,23 @@ constexpr int plan_tail_slots(int64_t B, int W, int groups)
     return (int)(n < 3 ? (W < 3 ? W : 3) : (n < W ? n : W));
 }
 
-// Whether an update with W row slots and NO orders takes step_tail_kernel, where one workgroup finishes a trajectory's rows
-// and applies its records: separate launches / one, us: update and draft of 6 x 14 rows x 4 orders 35.7 / 37.4, of
-// 4 x 32 x 4 50.9 / 66.7 (all slots hold a row); verify, update and draft with 7 x 4 62.3 / 55.0 (paths of one or two rows).
-constexpr bool plan_tail_update(int W, int NO) { return W * NO <= 40; }
+// Which calls end in step_tail_kernel, where one workgroup finishes a trajectory's rows and applies its records, one wave claims
+// them, and workgroups wait to be started for rows that few paths reach.  W: longest path, NO: orders.  Separate launches / one, us:
+// Verifications: all but those of many trajectories with long rows and long paths (`groups` summing workgroups per row).
+//   64 x 48 rows x 152 064 (5 groups), W = 8, paths of 2 / up to 8 rows: 171.5 / 173, 183 / 189; W = 16: 124.1 / 128.2, 129.7 / 135.8;
+//   W = 32, 5 rows: 127.5 / 139.0;  32 x 31 x 152 064, W = 16: 72.6 / 71.2, 77.2 / 80.9;  64 x 32 x 32 000 (1 group), W = 32: 44.4 / 41.7, 47.7 / 46.3
+inline bool plan_tail_verify(int64_t B, int W, int groups) { return B <= 32 || B * W * groups <= 2560; }
+// Steps: while there are few record slots in all.  Paths of 2 / 4 / up to W rows, 32 000 tokens:
+//   B x W x NO  32 x 8 x 8 = 2048: 58.9 / 57.0, 65.3 / 66.6, 70.5 / 71.6;  48 x 8 x 5 = 1920: 66.5 / 64.2, 73.4 / 72.4, 78.2 / 77.9;
+//   16 x 16 x 8 = 2048: 46.6 / 45.8, 60.5 / 62.0, 69.2 / 70.8;  64 x 8 x 3 = 1536: 73.9 / 70.4, 79.8 / 78.8, 84.2 / 85.7;  32 x 16 x 3: 49.7 / 45.8, 64.8 / 62.3, 73.2 / 72.2
+//   beyond: 64 x 8 x 5 = 2560: 76.4 / 74.6, 84.0 / 85.0, 88.3 / 91.4;  48 x 11 x 5: 76.3 / 75.1, 85.3 / 86.2, 93.0 / 96.2;  32 x 16 x 8 = 4096: 57.9 / 61.1, 74.0 / 75.3, 83.2 / 86.1;
+//   64 x 16 x 5: 72.9 / 71.1, 85.8 / 91.9, 96.1 / 103.1
+//   (the longest paths cost up to 5 % below the line too: 1 x 11 x 8, paths of 2 / 5 / 11: 31.5 / 25.6, 41.1 / 41.1, 43.6 / 48.4)
+inline bool plan_tail_step(int64_t B, int W, int NO) { return B * W * NO <= 2048; }
+// Updates: 50 257 tokens, 2 rows / all W rows: W x NO = 5 x 8 (1 trajectory) 24.2 / 19.1, 23.6 / 22.8; 7 x 4 (6 trajectories) 23.5 / 19.9, 24.4 / 25.4;
+//   10 x 4 (6) 23.4 / 20.2, 26.0 / 28.5, (64) 29.5 / 25.2, 57.9 / 60.6;  not 15 x 2: (6) 22.5 / 19.9, 28.5 / 31.5; 20 x 2: (8) 23.3 / 20.8, 29.7 / 36.1, (64) 35.2 / 31.3, 79.7 / 91.8;
+//   update and draft of 6 x 14 rows x 4 orders 35.7 / 37.4, of 4 x 32 x 4 50.9 / 66.7 (all slots hold a row)
+constexpr bool plan_tail_update(int W, int NO) { return W <= 12 && W * NO <= 40; }
 
 // Whether a step of a small batch (row kernel and step_tail_kernel) keeps these two launches where its rows alone would
 // allow the one launch (more than kRowsFew).  One launch / two launches, bf16, us:

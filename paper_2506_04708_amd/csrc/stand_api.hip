@@ -76,7 +76,7 @@ struct stand_handle {
     // rows split over workgroups (row_parts.hpp): parts per row of a verification and of an update (0: not split)
     int row_parts, commit_parts;
     // small batches: what follows the row kernel is one launch (step_tail.hpp)
-    bool tail_launch, tail_update;   // of a step or verification; of an update
+    bool tail_verify, tail_step, tail_update;
     int tail_per_cu, cus;            // workgroups of step_tail_kernel a compute unit holds at once; the device's compute units
     int tail_nsub;                   // ranges of a path row that are summed by a wave each
     unsigned long long *tail_part;   // [B][W][tail_nsub]
@@ -300,11 +300,13 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, cfg->device));
     const void *step_fn = cfg->logits_dtype == STAND_BF16 ? (const void *)stand_step_kernel<kDtBf16> : (const void *)stand_step_kernel<kDtF32>;
     acc(hipOccupancyMaxActiveBlocksPerMultiprocessor(&h->step_per_cu, step_fn, kStepThreads, step_shared_bytes(N)));
-    h->tail_launch = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch &&
-                     plan_tail_places(h->B, (int64_t)h->tail_per_cu * h->cus);
-    h->tail_update = h->tail_launch && plan_tail_update(h->W, h->NO);
+    const bool small = cfg->update_mode == STAND_UPDATE_ACCEPTED_PATH && h->B <= kTailBatch &&
+                       plan_tail_places(h->B, (int64_t)h->tail_per_cu * h->cus);
     h->tail_nsub = plan_tail_ranges(h->V, element_bytes(*cfg), h->B, kTailWaves, kSubMax);
-    acc(dmalloc(&h->tail_part, h->tail_launch ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, 2));
+    h->tail_verify = small && plan_tail_verify(h->B, h->W, h->tail_nsub / kTailWaves);
+    h->tail_step = small && plan_tail_step(h->B, h->W, h->NO);
+    h->tail_update = small && plan_tail_update(h->W, h->NO);
+    acc(dmalloc(&h->tail_part, small ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, 2));
     acc(dmalloc(&h->stats, (size_t)kStatCount));
     acc(dmalloc(&h->counter, 1));
     if (e != hipSuccess) { free_all(h); return e == hipErrorOutOfMemory ? STAND_ENOMEM : STAND_EHIP; }
@@ -732,7 +734,7 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     if (!h || !d_logits || !d_out_tok || !d_out_node || !d_out_len) return STAND_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(h, hipSetDevice(h->cfg.device));
-    const bool tail = h->tail_launch && tail_fits(h, s);
+    const bool tail = h->tail_verify && tail_fits(h, s);
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, tail, s);
     if (rc) return rc;
     if (tail)
@@ -797,7 +799,7 @@ static bool step_fused_possible(const stand_handle *h)
     // With few rows the pass is latency-bound, and split rows serve it better (see kRowsFew for where).  With very many the
     // dependent launches are a few per cent of the step, which is all one launch could save, and it varied more
     // from run to run than that (B=128 x 128 nodes: 0.84-0.96 ms against 0.85-0.88 ms).
-    if (h->tail_launch && plan_two_launches(h->B, (int64_t)h->B * h->N, h->V, element_bytes(h->cfg), h->K)) return false;
+    if (h->tail_step && plan_two_launches(h->B, (int64_t)h->B * h->N, h->V, element_bytes(h->cfg), h->K)) return false;
     return h->B * h->N > kRowsFew && h->B * h->N <= kRowsMany;
 }
 static bool step_fused_wanted(const stand_handle *h)
@@ -999,7 +1001,7 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
     plan_observe(h, s, capturing);
     if (!capturing && step_fused_wanted(h) && step_fits(h, s))
         return launch_step_fused(h, step, d_logits, d_out_tok, d_out_node, d_out_len, d_next_draft_tok, commit, s);
-    const bool tail = h->tail_launch && tail_fits(h, s);
+    const bool tail = h->tail_step && tail_fits(h, s);
     int rc = launch_row_pass(h, h->vs, step, d_logits, true, tail, s);
     if (rc) return rc;
     const MergeArgs mg = merge_args(h, commit, nullptr, d_out_len);

@@ -20,6 +20,9 @@ int ranges(int64_t V, int es, int64_t B) { return plan_tail_ranges(V, es, B, 16,
 int two_launches(int64_t B, int64_t rows, int64_t V, int es, int K) { return plan_two_launches(B, rows, V, es, K); }
 int tail_places(int64_t B, int64_t places) { return plan_tail_places(B, places); }
 int tail_slots(int64_t B, int W, int groups) { return plan_tail_slots(B, W, groups); }
+int tail_verify(int64_t B, int W, int groups) { return plan_tail_verify(B, W, groups); }
+int tail_step(int64_t B, int W, int NO) { return plan_tail_step(B, W, NO); }
+int tail_update(int W, int NO) { return plan_tail_update(W, NO); }
 int loads(int verify, int all_nodes, int64_t B) { return exact_loads(verify, all_nodes, B); }
 int threads() { return kPartThreads; }
 int most_vectors() { return kPartVectors; }
@@ -45,6 +48,7 @@ def lib():
         _lib.two_launches.argtypes = [l, l, l, i, i]
         _lib.whole.argtypes, _lib.ranges.argtypes = [l, i, i], [l, i, l]
         _lib.tail_places.argtypes = [l, l]
+        _lib.tail_verify.argtypes = _lib.tail_step.argtypes = [l, i, i]
         _lib.tail_slots.argtypes = [l, i, i]
         _lib.limit.argtypes, _lib.limit.restype = [l], l
         _lib.loads.argtypes = [i, i, l]

@@ -102,6 +102,13 @@ def test_path_rows_with_summing_workgroups():
     assert [s(1, 7, 19), s(1, 32, 19), s(1, 32, 32), s(8, 7, 16), s(32, 9, 5), s(24, 32, 1), s(64, 2, 8), s(64, 11, 8)] == [7, 26, 16, 4, 3, 21, 2, 3]
 
 
+def test_calls_that_end_in_one_launch():
+    L = rowplan.lib()
+    assert [L.tail_verify(*a) for a in ((32, 32, 32), (64, 8, 5), (64, 9, 5), (33, 32, 2), (33, 32, 3))] == [1, 1, 0, 1, 0]
+    assert [L.tail_step(*a) for a in ((1, 32, 8), (64, 8, 4), (64, 9, 4), (8, 32, 8), (9, 32, 8), (37, 11, 5), (38, 11, 5))] == [1, 1, 0, 1, 0, 1, 0]
+    assert [L.tail_update(*a) for a in ((5, 8), (10, 4), (6, 7), (12, 3), (13, 1))] == [1, 1, 0, 1, 0]
+
+
 def test_waiting_workgroups_leave_room():
     """At most an eighth of the places of the compute units that may be used: 256 of two places each, 32 of them, one."""
     assert [rowplan.lib().tail_places(B, 512) for B in (1, 64, 65)] == [1, 1, 0]
