@@ -107,11 +107,11 @@ def test_lockstep_draft_candidates_in_rows_of_lanes(gpu, K, omin, omax, mode):
     ("cfg3", dict(V=5000, B=8, rho=0.8, merge_policy=1, step_plan=(FUSED, 2, 0, 0)), 25, True),  # replace policy
     ("cfg3", dict(V=777, B=13, rho=0.8, dtype="f32", step_plan=(FUSED, 2, 0, 9)), 6, False),     # f32 rows, misaligned
     ("cfg3", dict(V=51, B=4, rho=0.5, filter_margin=0.05, step_plan=(FUSED, 2, 0, 0)), 40, False),  # exact second decisions
-    ("cfg3", dict(V=1003, B=13, rho=0.8, step_plan=(1, 2, 0, 0)), 8, True),                # the five-launch step where one launch is the default
+    ("cfg3", dict(V=1003, B=13, rho=0.8, step_plan=(1, 2, 0, 0)), 8, True),                # two launches where one launch is the default
 ])
 def test_lockstep_one_launch_step(gpu, name, over, steps, forced):
     """stand_step as one launch (rows of the upper tree levels, then the dependent tail beside the remaining
-    rows): every output as in the five-launch form, whatever the split, the number of tail workgroups and the
+    rows): every output as in the other forms, whatever the split, the number of tail workgroups and the
     order in which workgroups take rows."""
     binding, lockstep = gpu
     _say("one-launch step %s %s steps=%d forced=%s" % (name, over, steps, forced))
@@ -121,9 +121,28 @@ def test_lockstep_one_launch_step(gpu, name, over, steps, forced):
     assert info["emitted"] >= steps * w.B and info["worst_rel"] < 1e-5
 
 
+@pytest.mark.parametrize("over,steps,forced", [
+    # a chain of 32 nodes and eight orders: long accepted paths (tiny vocabulary), then long rows that start at every alignment
+    (dict(B=9, N=32, D=31, caps=[1], order_max=8, K=10, V=48, dtype="bf16"), 16, False),
+    (dict(B=9, N=32, D=31, caps=[1], order_max=8, K=10, V=50257, dtype="bf16"), 3, True),
+    (dict(B=17, N=31, D=15, caps=[2, 1], order_max=8, K=16, V=32003, dtype="f32"), 3, True),
+    (dict(B=64, N=48, D=7, caps=[6, 3, 2, 1], order_max=5, K=10, V=300, dtype="bf16"), 6, False),
+    (dict(B=65, N=16, D=4, caps=[4, 2, 1, 1], order_max=4, K=10, V=2003, dtype="bf16"), 6, True),
+])
+def test_lockstep_five_launches(gpu, over, steps, forced):
+    """Accepted-path steps that keep the separate launches: rows, exact sums, finish + claims, apply, draft."""
+    binding, lockstep = gpu
+    _say("five launches %s" % over)
+    w = synth.Workload(None, order_min=1, T=0.6, rho=0.7, seed=4711, run_steps=steps, step_plan=(1, 2, 0, 0), **over)
+    assert w.B > 64 or not rowplan.lib().tail_step(w.B, w.W, over["order_max"])
+    info = lockstep.run_lockstep(w, steps, mode="step", capacity=1 << 16, forced=forced, sample_rows=range(0, w.B * w.N, 7))
+    _say("  -> %s" % {k: v for k, v in info.items() if k != "node_counts"})
+    assert info["emitted"] >= steps * w.B and not any(info["one_launch"])
+
+
 def test_step_plan_changes_while_running(gpu):
-    """The launch structure of stand_step is changed every three steps (one launch with different splits, the five
-    launches, the automatic choice): the draft state, the contexts and the table carry over, every output stays
+    """The launch structure of stand_step is changed every three steps (one launch with different splits, the
+    dependent launches, the automatic choice): the draft state, the contexts and the table carry over, every output stays
     equal to the oracle's."""
     binding, lockstep = gpu
     _say("step plan rotation")
@@ -136,7 +155,7 @@ def test_step_plan_changes_while_running(gpu):
 
 def test_automatic_plan_follows_the_acceptance_depth(gpu):
     """STAND_STEP_AUTO starts with the one launch; where most steps have an accepted path that reaches below the
-    rows scheduled first (tiny vocabulary, closed loop) it goes over to the five launches after its first window of
+    rows scheduled first (tiny vocabulary, closed loop) it goes over to the dependent launches after its first window of
     32 steps, and it stays with the one launch where paths are short (random rows).  Outputs equal the oracle's
     under either plan."""
     binding, lockstep = gpu
@@ -925,8 +944,9 @@ def test_vocabularies_above_2_22(gpu, over, steps, rows):
 
 @pytest.mark.parametrize("name,over,one_launch", [
     ("cfg3", dict(V=3000, B=13, rho=0.7), True),
-    ("cfg1", dict(V=70001, B=1, rho=0.7, dtype="bf16"), False),    # split rows, one workgroup for the rest of the step
-    ("cfg1", dict(V=70001, B=3, rho=0.7), False),                  # split rows, separate launches
+    ("cfg3", dict(V=300, B=65, rho=0.7), True),                    # recorded as five launches
+    ("cfg1", dict(V=70001, B=1, rho=0.7, dtype="bf16"), False),    # split rows, one launch for the rest of the step
+    ("cfg1", dict(V=70001, B=3, rho=0.7), False),                  # the same, whose trajectories meet
 ])
 def test_step_recorded_into_a_graph_replays_correctly(gpu, name, over, one_launch):
     """stand_step recorded into a HIP graph (the separate launches are taken while a stream is being captured, whatever the
@@ -1061,15 +1081,17 @@ def test_stream_of_few_compute_units(gpu, plan, B):
 def test_results_do_not_depend_on_the_work_mapping(gpu):
     """Race detection by permutation: the same 14 closed-loop steps under different workgroup -> work mappings of
     the one-launch step (order in which workgroups take rows, rows placed before the tail, tail workgroups per
-    trajectory, tree levels scheduled first) and as five launches.  Every output, the next draft and the exported
-    table are equal bit for bit in all runs; among the one-launch runs (same waves per row) so are the row results
-    with their fast normalisers."""
+    trajectory, tree levels scheduled first), as two launches and (on a stream masked to few compute units, where the
+    runtime gives one) as five.  Every output, the next draft and the exported table are equal bit for bit in all runs;
+    among the one-launch runs (same waves per row) so are the row results with their fast normalisers."""
     binding, lockstep = gpu
+    stream, destroy = _masked_stream([0xFFFFFFFF])
     plans = [(FUSED, 2, 4, 0, 0), (FUSED, 2, 4, 12345, 0), (FUSED, 1, 2, 777, 600), (FUSED, 0, 8, 31, 0), (FUSED, 8, 1, 5, 0),
-             (1, 2, 0, 0, 0)]
+             (1, 2, 0, 0, 0)] + ([(1, 2, 0, 0, 0)] if stream is not None else [])
     runs = []
-    for plan in plans:
-        _say("work mapping %s" % (plan,))
+    for k, plan in enumerate(plans):
+        masked = k == 6
+        _say("work mapping %s%s" % (plan, " on a masked stream" if masked else ""))
         w = synth.Workload("cfg3", run_steps=14, V=600, B=13, rho=0.6)
         o, g = lockstep.make_pair(w, 1 << 14)
         o.close()
@@ -1081,7 +1103,10 @@ def test_results_do_not_depend_on_the_work_mapping(gpu):
         rec = []
         for step in range(14):
             lg = w.logits(step, d.cpu().numpy())
-            g.step(step, lockstep._logits_to_device(lg, w.dtype), out_tok, out_node, out_len, d)
+            dl = lockstep._logits_to_device(lg, w.dtype)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(stream if masked else torch.cuda.current_stream()):
+                g.step(step, dl, out_tok, out_node, out_len, d)
             torch.cuda.synchronize()
             m, sfast, idx, p = g.row_results()
             rec.append([x.cpu().numpy().copy() for x in (out_tok, out_node, out_len, d, m, idx, sfast, p)])
@@ -1097,6 +1122,55 @@ def test_results_do_not_depend_on_the_work_mapping(gpu):
             for a, b in zip(runs[0][0][step][:n_same], runs[k][0][step][:n_same]):
                 assert np.array_equal(a, b), "plan %s differs from plan %s at step %d" % (plans[k], plans[0], step)
         assert np.array_equal(runs[0][1], runs[k][1]) and runs[0][2] == runs[k][2]
+    if stream is not None:
+        destroy()
+
+
+def test_two_handles_on_two_streams(gpu):
+    """Two batches of 64 whose trajectories wait inside their launches, step by step on two streams without
+    synchronisation between them: outputs, drafts and tables are those of the same batches alone."""
+    binding, lockstep = gpu
+    _say("two handles on two streams")
+    steps = 10
+    runs = []
+    for together in (False, True):
+        hs = []
+        for q in range(2):
+            w = synth.Workload("cfg1", run_steps=steps, V=3000, B=64, rho=0.7, seed=99 + q)
+            assert rowplan.lib().tail_step(w.B, w.W, 3)
+            o, g = lockstep.make_pair(w, 1 << 14)
+            o.close()
+            g.set_step_plan(1, 2, 0, 0)
+            for b in range(w.B):
+                g.set_context(b, w.prompt(b))
+            out = g.new_outputs()
+            g.draft(0, out[3])
+            lg = [lockstep._logits_to_device(w.logits(s, out[3].cpu().numpy()), w.dtype) for s in range(2)]
+            kept = [[torch.empty_like(t) for t in out] for _ in range(steps)]
+            hs.append((g, out, lg, kept, torch.cuda.Stream()))
+        torch.cuda.synchronize()
+        for step in range(steps):
+            for g, out, lg, kept, s in hs:
+                with torch.cuda.stream(s):
+                    if step % 3 == 2:
+                        g.verify(step, lg[step % 2], *out[:3])
+                        g.update(step, lg[step % 2], out[0], out[1], out[2])
+                        g.draft(step + 1, out[3])
+                    else:
+                        g.step(step, lg[step % 2], *out)
+                    for t, k in zip(out, kept[step]):
+                        k.copy_(t)
+                if not together:
+                    torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        runs.append([([[t.cpu().numpy() for t in k] for k in kept], g.table_export().copy(), g.stats().wait_expired) for g, _, _, kept, _ in hs])
+        for g, *_ in hs:
+            g.close()
+    for (ka, ta, xa), (kb, tb, xb) in zip(*runs):
+        assert xa == 0 and xb == 0 and np.array_equal(ta, tb)
+        for step in range(steps):
+            for a, b in zip(ka[step], kb[step]):
+                assert np.array_equal(a, b), "step %d" % step
 
 
 def test_reorder_matches_oracle(gpu):

@@ -87,3 +87,26 @@ def test_verify_static_matches_verify_on_calls_that_share_the_scratch():
     assert bool((outs[2] == 1).all())
     for x in (big.g, small.g, g2):
         x.close()
+
+
+@pytest.mark.parametrize("name,over", [
+    ("cfg1", dict(V=32003, B=3, rho=0.7)),                       # fp32, 48 rows: sixteen waves each
+    ("cfg2", dict(V=50257, B=2, rho=0.7)),                       # bf16, rows that start at every alignment
+    ("cfg3", dict(V=70003, B=5, rho=0.7)),                       # 320 rows: four waves each
+    ("cfg3", dict(V=20011, B=5, rho=0.7)),                       # 320 rows, held whole
+])
+def test_verify_static_on_long_rows(name, over):
+    """Rows of many vectors: the token is located over all segments, and head and tail elements lie outside the vectors."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2506_04708_amd import binding
+    from tests import lockstep
+    print("no-alloc verify: %s %s" % (name, over), flush=True)
+    run = _Run(binding, lockstep, name, over, 4)
+    for rep in range(3):
+        ref, got = _both(run.g, run.step, run.logits())
+        for r, x, what in zip(ref, got, ("tokens", "nodes", "lengths")):
+            assert np.array_equal(r, x), "%s differ: %s vs %s" % (what, x, r)
+        run.advance()
+    assert run.g.stats().filter_mismatch == 0
+    run.g.close()
