@@ -88,15 +88,15 @@ def host_description():
         return "%d CPUs usable by this process" % len(os.sched_getaffinity(0))
 
 
-def launch_names(fused, B, rows, update_mode, small_batch=False):
-    """(kernel that reads the logits, how the step is issued).  The one workload here of at most 512 rows has its rows
-    split over workgroups; what follows the rows of a small batch (up to 64 trajectories, accepted-path updates) is one launch."""
+def launch_names(fused, B, N, V, K, W, orders, update_mode):
+    """(kernel that reads the logits, how the step is issued) of bf16 steps on a whole device: the library's rules in short
+    (csrc/row_plan.hpp).  The workloads of at most 512 rows here have them split over workgroups; rows of up to 4096
+    vectors of 16 bytes are held whole.  What follows the rows of a small batch is one launch."""
     if fused:
         return "stand_step_kernel", "one launch"
-    if small_batch:
-        return "row_parts_kernel" if rows <= 512 else "row_pass_kernel", "two launches"
-    return ("row_parts_kernel" if rows <= 512 else "row_pass_kernel",
-            "three launches" if B == 1 and update_mode == 0 else "five launches")
+    whole = 10 * K <= -(-V // 8) <= 4096
+    small_batch = update_mode == 0 and B <= 64 and B * W * orders <= 2048
+    return ("row_parts_kernel" if B * N <= 512 or whole else "row_pass_kernel", "two launches" if small_batch else "five launches")
 
 
 def measure(args, np, torch, binding, synth, peak, max_peaks, K_steps, W_steps, T_warm, cpu_steps, label):
@@ -382,7 +382,7 @@ def measure(args, np, torch, binding, synth, peak, max_peaks, K_steps, W_steps, 
     step_bytes = logits_bytes + w.B * w.V * 2 + rows * (8 + 12 * w.K) + 1_200_000 + 500_000
     row_bytes = logits_bytes + rows * (8 + 12 * w.K)
     fused = h2.step_is_one_launch()
-    kernel, issue = launch_names(fused, w.B, rows, args.update_mode, w.B <= 64 and args.update_mode == 0)
+    kernel, issue = launch_names(fused, w.B, w.N, w.V, w.K, w.W, cfg["order_max"] - cfg["order_min"] + 1, args.update_mode)
     kbytes = step_bytes if fused else row_bytes
     # HBM bytes per launch of that kernel from profiler counters, if the committed summary holds them
     traffic = traffic_commit = None
@@ -460,7 +460,7 @@ def main():
                     help="each row peaks on 1..max-peaks tokens (workload recipe: 1-4); 1 with a high --peak models a confident "
                          "target, where acceptance follows the quality of the drafts")
     ap.add_argument("--step-mode", type=int, default=0,
-                    help="how stand_step is issued: 0 the library's choice, 1 five dependent launches, 2 one launch")
+                    help="how stand_step is issued: 0 the library's choice, 1 dependent launches, 2 one launch")
     ap.add_argument("--upper-depth", type=int, default=2, help="one-launch step: tree levels whose rows go first")
     ap.add_argument("--tail-groups", type=int, default=0, help="one-launch step: tail workgroups per trajectory (0: library's choice)")
     ap.add_argument("--rows-first", type=int, default=0,
