@@ -4,7 +4,7 @@
 //   row_pass.hpp     row_pass_kernel     softmax statistics + top-K of every logits row in one streaming
 //                                        pass, and the accept/reject outcome of the row's tree node
 //                                                                              (paper Sec. 4.1, 3.2)
-//   row_plan.hpp     (host) which rows are split, and by how much
+//   row_plan.hpp     (host) which launch forms a call takes: rows split, held whole or streamed; what follows them
 //   row_parts.hpp    row_parts_kernel    the same for few rows, for short rows and for the rows of an update: every row split
 //                                        over workgroups that hold their part (or all of it) in registers
 //   path_pass.hpp    path_exact_kernel   exact integer partial sums of the rows on the accepted path;

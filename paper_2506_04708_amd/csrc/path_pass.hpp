@@ -212,27 +212,21 @@ struct FinishShared {
     int32_t top0;                       // the row's best token
 };
 
-// integer masses of the EPV elements of a vector; those in `without` count nothing
-template <int DT>
-__device__ __forceinline__ void vector_masses(const uint4 &w, uint32_t without, float m, float c, int shift, unsigned long long *f)
-{
-    constexpr int EPV = VecTraits<DT>::EPV;
-    float x[EPV];
-    unpack<DT>(w, x);
-#pragma unroll
-    for (int q = 0; q < EPV; ++q) f[q] = ((without >> q) & 1u) ? 0ull : fixed_mass(exact_exp2(scaled_offset(x[q], m, c)), shift);
-}
-// the same for elements e0 .. e0 + EPV - 1 of the row without the stored ids
+// integer masses of the EPV elements of a vector, elements e0 .. e0 + EPV - 1 of the row; the stored ids count nothing
 template <int DT>
 __device__ __forceinline__ void vector_masses(const uint4 &w, int e0, float m, float c, int shift, const FinishShared &sh,
                                               unsigned long long *f)
 {
+    constexpr int EPV = VecTraits<DT>::EPV;
+    float x[EPV];
+    unpack<DT>(w, x);
     uint32_t bits = 0u;
     for (int q = 0; q < sh.nsup; ++q) {
         const uint32_t d = (uint32_t)(sh.sup_id[q] - e0);
-        if (d < (uint32_t)VecTraits<DT>::EPV) bits |= 1u << d;
+        if (d < (uint32_t)EPV) bits |= 1u << d;
     }
-    vector_masses<DT>(w, bits, m, c, shift, f);
+#pragma unroll
+    for (int q = 0; q < EPV; ++q) f[q] = ((bits >> q) & 1u) ? 0ull : fixed_mass(exact_exp2(scaled_offset(x[q], m, c)), shift);
 }
 // Update mode: maximum and top-K of the given commit rows (one workgroup of 4 waves per row).
 struct CommitScanArgs {

@@ -1,5 +1,5 @@
-// row_parts.hpp -- row_parts_kernel: the row pass for few rows (paper Sec. 4.1, 3.2).  Every row is split over
-// workgroups that hold their part in registers.
+// row_parts.hpp -- row_parts_kernel: the row pass for few rows, and for short rows however many (paper Sec. 4.1, 3.2).  Every
+// row is split over workgroups that hold their part in registers; a row that fits one is its only part.
 #pragma once
 #include "row_pass.hpp"
 

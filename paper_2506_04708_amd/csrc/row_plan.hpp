@@ -6,10 +6,11 @@
 
 namespace stand {
 
-// Row pass.  Thousands of rows: one row per workgroup of four waves.  Few rows: every row is split over workgroups
-// (row_parts.hpp), or, where that does not pay (plan_row_parts) or does not apply (the entry point with fixed scratch),
-// held whole by one (plan_row_whole), or spread over the sixteen waves of one as long as each compute unit has at most one of them: verifications, sixteen / four
-// waves, us: 256 rows of 522 KB (bf16) 49.2 / 54.3, 288 rows 63.7 / 59.6.
+// Row pass.  Few rows: every row is split over workgroups that hold their parts in registers (row_parts.hpp), where that pays
+// (plan_row_parts) and applies (not at the entry point with fixed scratch).  Else rows that fit a workgroup's registers are
+// held whole, however many they are (plan_row_whole).  Others stream through the four waves of a workgroup, or through
+// sixteen as long as each compute unit has at most one such workgroup: verifications, sixteen / four waves, us: 256 rows of
+// 522 KB (bf16) 49.2 / 54.3, 288 rows 63.7 / 59.6.
 #ifndef STAND_ROW_WPR
 #define STAND_ROW_WPR 4
 #endif
@@ -93,9 +94,11 @@ inline int plan_commit_parts(int64_t V, int element_bytes, int64_t B, int W, int
     return usual * p <= (all ? split_limit(usual) : kCommitWorkgroups) ? p : 0;
 }
 
-// 16-byte loads per thread and segment of the exact sums: one round of four, or of two for the few path rows of a small
-// batch (steps with 2 / 4, us: 1 x 32 rows 33.3 / 34.2, 8 x 32 50.4 / 51.2, 32 x 64 158.0 / 156.4).  Not where every drafted
-// row is summed, which fills the vector ALUs at any batch size: all-nodes steps of 16 x 64 rows 357 / 331, 4 x 64 98 / 94.
+// 16-byte loads per thread and segment of the exact sums in a launch of their own: one round of four, or of two for the few
+// path rows of a small batch (the entry point with fixed scratch; steps of deep trees).  That entry point with 2 / 4, us:
+// 1 x 32 rows x 152 064 30.4 / 31.2, 8 x 32 x 128 256 31.1 / 32.2, 16 x 48 x 32 003 fp32 32.7 / 32.9, x 32 000 24.5 / 26.0;
+// steps of 32 x 64 158.0 / 156.4.  Not where every drafted row is summed, which fills the vector ALUs at any batch size:
+// all-nodes steps of 16 x 64 rows 357 / 331, 4 x 64 98 / 94.
 constexpr int exact_loads(bool verify, bool all_nodes, int64_t B) { return verify && !all_nodes && B <= 16 ? 2 : 4; }
 
 // Whether the workgroups of B trajectories may wait in step_tail_kernel, for each other and for workgroups that are started

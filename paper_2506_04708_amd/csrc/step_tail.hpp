@@ -74,7 +74,7 @@ struct SmallTail {
     unsigned long long P[kSubMax];
     alignas(16) unsigned long long scratch[kTailWaves][2 * kMaxK];
 };
-// Per node: outcome + 1, drafted children << 6, children << 12, first child + 1 << 18 (a node has at most kMaxK children).
+// Per node: outcome + 1, drafted children << 6, first child + 1 << 12 (a node has at most kMaxK children).
 struct TailStage { int32_t *word; float *m; int32_t *tok; };
 constexpr size_t kTailFixed = (sizeof(SmallTail) + 15) & ~(size_t)15;
 constexpr size_t tail_shared_bytes(int N) { return kTailFixed + (size_t)(3 * N + 3) / 4 * 16 + draft_shared_bytes(N, kTailWaves); }
@@ -86,8 +86,7 @@ __device__ __forceinline__ TailStage tail_stage(char *smem, int N)
 }
 __device__ __forceinline__ int stage_outcome(int32_t w) { return (w & 63) - 1; }
 __device__ __forceinline__ int stage_drafted(int32_t w) { return (w >> 6) & 63; }
-__device__ __forceinline__ int stage_children(int32_t w) { return (w >> 12) & 63; }
-__device__ __forceinline__ int stage_first(int32_t w) { return (w >> 18) - 1; }
+__device__ __forceinline__ int stage_first(int32_t w) { return (w >> 12) - 1; }
 
 // follows the accepted path (one thread, after the staging)
 __device__ __forceinline__ int tail_walk(const TailStage &st, int D, int *path)
@@ -136,7 +135,7 @@ __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
         } else {
             if (len < 0) {
                 for (int u = tid; u < a.N; u += kTailThreads) {
-                    st.word[u] = (a.outcome[(size_t)b * a.N + u] + 1) | ((a.tree.first_child[u] + 1) << 18);
+                    st.word[u] = (a.outcome[(size_t)b * a.N + u] + 1) | ((a.tree.first_child[u] + 1) << 12);
                     st.m[u] = a.src_m[(size_t)b * a.N + u];
                 }
                 __syncthreads();
@@ -458,12 +457,12 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
             if (A.drafts) level_reg = lane < a.tree.D + 2 ? a.tree.level_start[lane] : 0;
             for (int u = tid; u < N; u += kTailThreads) {
                 const size_t at = (size_t)b * N + u;
-                const int fc = a.tree.first_child[u], nch = a.tree.nchild[u];
-                stage.word[u] = (a.outcome[at] + 1) | (a.draft_has[at] << 6) | (nch << 12) | ((fc + 1) << 18);
+                const int fc = a.tree.first_child[u];
+                stage.word[u] = (a.outcome[at] + 1) | (a.draft_has[at] << 6) | ((fc + 1) << 12);
                 stage.m[u] = a.src_m[at];
                 stage.tok[u] = a.draft_tok[at];
                 if (A.drafts) {
-                    dsm.info[u] = (fc << 8) | nch;
+                    dsm.info[u] = (fc << 8) | a.tree.nchild[u];
                     if (u > 0) dsm.tok[u] = -1;
                     dsm.has[u] = 0;
                 }
