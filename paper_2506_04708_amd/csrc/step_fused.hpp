@@ -373,7 +373,11 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
     int level_reg = 0;
     tail_barrier(sy, 1, (unsigned)a.B, ts, [&] { level_reg = draft_prepare<kStepThreads>(A.draft, b, dsm); });
     if (tid == 0) stamp(sy, b, 6);
-    if (tid == 0 && !ts->ok) atomicAdd(&a.stats[kStatWaitExpired], 1ull);
+    if (__builtin_expect(!ts->ok, 0)) {
+        // (a wait of this trajectory has run out: its outputs, some of which are written already, are void)
+        if (tid < W) { a.out_tok[(size_t)b * W + tid] = -1; a.out_node[(size_t)b * W + tid] = -1; }
+        if (tid == 0) { a.out_len[b] = 0; atomicAdd(&a.stats[kStatWaitExpired], 1ull); }
+    }
     draft_run<kStepThreads>(A.draft, b, dsm, level_reg);
     if (tid == 0) stamp(sy, b, 7);
 }

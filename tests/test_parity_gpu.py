@@ -204,8 +204,10 @@ def test_one_launch_step_waits_are_bounded(gpu):
     st = g.stats()
     _say("wait limit 0: %d waits expired, lengths %s" % (st.wait_expired, out_len.cpu().numpy().tolist()))
     assert st.wait_expired > 0
-    ln = out_len.cpu().numpy()
-    assert ((ln >= 0) & (ln <= w.W)).all()
+    ln, tok, node = out_len.cpu().numpy(), out_tok.cpu().numpy(), out_node.cpu().numpy()
+    assert ((ln >= 0) & (ln <= w.W)).all() and (ln == 0).any()
+    for b in range(w.B):
+        assert (ln[b] == 0) == bool((tok[b] == -1).all()) == bool((node[b] == -1).all())
     g.close()
     # the default limit: the same calls complete without an expiry
     g = binding.Stand(w.V, w.B, 1, 4, w.K, w.parent, w.T, 1 << 14, 64, 5, binding.STAND_BF16)
