@@ -263,14 +263,16 @@ def test_small_batch_waits_are_bounded(gpu, call):
         return int(rec["count"].sum()) if len(rec) else 0
 
     for step in range(3):
-        before = [g.get_context(b, 1)[1] for b in range(w.B)]
+        before = [g.get_context(b, 4) for b in range(w.B)]
         expired = g.stats().wait_expired
         g.set_wait_limit(0)
         run(step)
         void = g.stats().wait_expired - expired
         _say("  -> %d waits expired" % void)
         assert void > 0
-        moved = [g.get_context(b, 1)[1] - before[b] for b in range(w.B)]
+        after = [g.get_context(b, 4) for b in range(w.B)]
+        moved = [y[1] - x[1] for x, y in zip(before, after)]
+        assert all(m or np.array_equal(x[0], y[0]) for m, x, y in zip(moved, before, after)), "a context was not put back"
         if call == "verify":
             assert moved == [0] * w.B
         elif call == "update":
