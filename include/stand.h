@@ -242,8 +242,8 @@ int stand_step_is_one_launch(const stand_handle *h);
  * launch that follows the rows of a small batch (stand_step in two launches, stand_verify, stand_update).  A
  * wait that runs out is counted in stand_stats.wait_expired; every kernel still ends normally, but the call's
  * outputs for the affected trajectories are void (out_len 0, tokens -1) and the table must be considered invalid.
- * In the launch after the rows of a small batch the context of such a trajectory does not move on, none of its
- * records is merged and nothing is drafted for it.  With a healthy device no wait comes near the default.
+ * After a step or update whose wait ran out in the launch that follows the rows of a small batch the trajectory's
+ * context is as before and nothing is drafted for it.  With a healthy device no wait comes near the default.
  * 0 makes every wait that is not satisfied at once expire (for tests of this path). */
 int stand_set_wait_limit(stand_handle *h, uint64_t microseconds);
 
