@@ -13,8 +13,16 @@ namespace stand {
 //   - the part's maximum is known before its first exponential (no running reference);
 //   - no candidate list is kept while streaming: the K-th largest of the 64 maxima of 8-lane groups is a lower bound
 //     of the part's K-th largest element, and it is tight: 64 ln(64 / (64 - K)) elements reach it on average (11 for
-//     K = 10, 44 for K = 32); those are collected straight from the registers;
+//     K = 10, 44 for K = 32); the vectors that hold them go to shared memory, where every thread takes an element;
 //   - nothing is read twice.
+// Where a launch fills the device, what bounds it after its last byte are the vector instructions of all its waves (eight to a
+// SIMD: 100 more in each are 1.6 us), so what is not done per element is kept short: the arguments are read again in the later
+// phases instead of spilled from the start (up to 90 scalar registers), streamed and plain loads are two kernels instead of
+// two branches that meet in moves, and candidates are not taken apart in the registers that happen to hold them (200 of 800
+// instructions).  Steps, with all this before / as it is, us: 8 x 32 rows x 128 256 bf16 41.4 / 39.8, 24 x 20 x 50 000 42.9 / 40.8,
+// verify of 2 x 40 x 150 000 fp32, K = 32 39.0 / 37.4, update and draft of 4 x 32 x 152 064 47.8 / 44.8 (its rows without the fast
+// normaliser, which an update does not use).  Vectors taken one by one as they arrive, relative to a reference that is
+// raised on the way, were slower (40.3 / 40.8): the phases of a unit's four workgroups overlap as it is.
 // The last workgroup of a row to finish (a counter that its last user sets back to zero, so a recorded launch can be
 // replayed) merges the parts: the largest of the parts' bounds cuts the candidates again, one wave ranks them exactly
 // while another runs the node's accept tests.
@@ -28,6 +36,7 @@ namespace stand {
 constexpr int kTicketStride = 32;                    // words between two rows' counters: a cache line each
 constexpr int kPartKeys = 64;                        // candidate keys a part hands over
 constexpr int kPartList = kPartsMax * kPartKeys;     // candidates collected in shared memory
+constexpr int kPartVecs = 384;                       // vectors collected in shared memory
 constexpr int kPartTies = 32;                        // more lanes of a wave than this at or above the bound: most elements there equal it
 constexpr int kPartTied = 1 << 20;                   // added to the count of candidates by such a wave
 
@@ -35,7 +44,6 @@ struct PartHead { float m, s, theta; int cnt; };     // maximum, fast sum relati
 
 struct RowPartsArgs {
     RowPassArgs r;
-    bool streamed;                 // non-temporal loads
     int P, per;                    // parts per row, vectors per part (<= kPartThreads * R)
     unsigned *ticket;              // [rows or row slots][kTicketStride] parts that have finished; back at zero after the launch
     PartHead *head;                // [slots * P]
@@ -53,8 +61,11 @@ struct PartShared {
     float bins[64];                // maxima of groups of 8 lanes
     int above[64];                 // number of bins above each
     float wmax[kPartWaves], wsum[kPartWaves];
-    int n, n_row, last;            // candidates of the part, then of the row
-    int rank[kPartList];
+    int n_vec, n, n_row, last;     // vectors that reach the bound, candidates of the part, then of the row
+    union {
+        int rank[kPartList];
+        struct { uint4 vec[kPartVecs]; int vec_at[kPartVecs]; };   // those vectors and their places in the row
+    };
     union {
         unsigned long long list[kPartList + 8];
         RowShared<kPartWaves> scan;  // the streaming scan's own memory (ties)
@@ -122,7 +133,7 @@ __device__ __forceinline__ void load_part(uint4 (&w)[R], __amdgpu_buffer_rsrc_t 
 
 // (64 registers leave room for four workgroups per compute unit, so that their phases overlap: 256 rows of 257 KB
 // take 19.7 us; with 116 registers and two workgroups 21.2)
-template <int DT, int R>
+template <int DT, int R, bool STREAMED>
 __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void row_parts_kernel(RowPartsArgs a)
 {
     constexpr int ES = VecTraits<DT>::ES, EPV = VecTraits<DT>::EPV;
@@ -130,9 +141,14 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     const RowPassArgs &r = a.r;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // grid (parts, trajectories, nodes or commit positions): all trajectories' rows of node 0 first
-    const int part = blockIdx.x, b = blockIdx.y, j = blockIdx.z, slot = j * r.B + b;
+    const int part = blockIdx.x, b = blockIdx.y, j = blockIdx.z;
+    const int V = r.V, K = r.K, P = a.P;
+    const bool commit = a.commit;
+    const float c = r.c;
+    // (the later phases read the arguments again: kept from the start they were up to 90 spilled scalar registers, a tenth of
+    // the vector instructions of a wave)
+    auto late = []() -> const RowPartsArgs & { return fresh_args<RowPartsArgs>(); };
     int node = j;
-    if (part == 0) r.clear.row(b, j);
     if (a.commit) {
         if (a.all_nodes) node = r.draft_tok[(size_t)b * r.N + j] >= 0 ? j : -1;
         else {
@@ -140,7 +156,10 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
             cl = cl < 0 ? 0 : (cl > a.W ? a.W : cl);
             node = j < cl ? a.commit_row[(size_t)b * a.W + j] : -1;
         }
-        if (node < 0 || node >= r.N) return;  // (the same for all parts of the row)
+        if (node < 0 || node >= r.N) {  // (the same for all parts of the row)
+            if (part == 0) late().r.clear.row(b, j);
+            return;
+        }
     }
     node = __builtin_amdgcn_readfirstlane(node);
     const int row = b * r.N + node;
@@ -154,24 +173,20 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     {
         const __amdgpu_buffer_rsrc_t rsrc =
             __builtin_amdgcn_make_buffer_rsrc((void *)(g.vp + v0), (short)0, (v1 - v0) * 16, 0x00020000);
-        if (a.streamed) load_part<2>(w, rsrc, tid);
-        else load_part<0>(w, rsrc, tid);
+        load_part<STREAMED ? 2 : 0>(w, rsrc, tid);
+        if (part == 0) late().r.clear.row(b, j);
     }
     // elements of the row before its first and after its last aligned vector: one per lane of the first wave
     auto edge_of_lane = [&]() {
         int id = -1;
         if (wave == 0) {
             if (part == 0 && lane < g.head) id = lane;
-            if (part == a.P - 1 && lane >= 32 && lane - 32 < g.ntail) id = g.tail0 + lane - 32;
+            if (part == P - 1 && lane >= 32 && lane - 32 < g.ntail) id = g.tail0 + lane - 32;
         }
         return id;
     };
     const int edge_id = edge_of_lane();
     const float edge_val = edge_id >= 0 ? load_scalar<DT>(rowp, edge_id) : -__builtin_inff();
-    // the node's proposal, for the wave that runs the accept tests if this workgroup is the row's last
-    NodeProposal prop;
-    if (!a.commit && wave == 1) prop.request(r, row, node, lane);
-
     // ---- maxima
     float cm[R], lm = edge_val;
 #pragma unroll
@@ -195,8 +210,9 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     const bool none = wm == -__builtin_inff();         // (no vector, or masked throughout: adds nothing)
     const float m_ref = none ? 0.0f : wm;
     float dlt;
-    const float nb = fast_offset(m_ref, r.c, dlt);
-    float s_t = edge_id >= 0 ? fast_exp2(__builtin_fmaf(edge_val, r.c, nb)) : 0.0f;
+    const float nb = fast_offset(m_ref, c, dlt);
+    float s_t = edge_id >= 0 ? fast_exp2(__builtin_fmaf(edge_val, c, nb)) : 0.0f;
+    if (!commit)   // (an update takes its rows' exact sums only)
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         float x[EPV];
@@ -205,13 +221,13 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         unpack<DT>(w[q], x);
         float e = 0.0f;
 #pragma unroll
-        for (int k = 0; k < EPV; ++k) e += fast_exp2(__builtin_fmaf(x[k], r.c, nb));
+        for (int k = 0; k < EPV; ++k) e += fast_exp2(__builtin_fmaf(x[k], c, nb));
         s_t += v0 + q * kPartThreads + tid < v1 ? e : 0.0f;
     }
     s_t = wave_sum_f32(s_t);
     if ((lane & 7) == 0) sm.bins[wave * 8 + (lane >> 3)] = x8;
     if (lane == 0) { sm.wmax[wave] = none ? -3.402823466e38f : wm; sm.wsum[wave] = s_t * fast_exp2(dlt); }
-    if (wave == 0) { sm.above[lane] = 0; if (lane == 0) { sm.n = 0; sm.n_row = 0; } }
+    if (wave == 0) { sm.above[lane] = 0; if (lane == 0) { sm.n_vec = 0; sm.n = 0; sm.n_row = 0; } }
     __syncthreads();
 
     // ---- K-th largest of the 64 bins: every wave compares all bins with eight of them
@@ -223,62 +239,57 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         atomicAdd(&sm.above[lane], c);
     }
     __syncthreads();
-    const float theta = -wave_max_f32(sm.above[lane] < r.K ? -my_bin : -__builtin_inff());
+    const float theta = -wave_max_f32(sm.above[lane] < K ? -my_bin : -__builtin_inff());
 
     float pm, ps;   // the part's maximum and sum (in the waves that use them)
-    if (wave < 2 || a.P == 1) {
+    if (wave < 2 || P == 1) {
         const float wm_l = lane < kPartWaves ? sm.wmax[lane] : -3.402823466e38f;
         pm = wave_max_f32(wm_l);
-        ps = wave_sum_f32(lane < kPartWaves ? sm.wsum[lane] * fast_exp2((wm_l - pm) * r.c) : 0.0f);
+        ps = wave_sum_f32(lane < kPartWaves ? sm.wsum[lane] * fast_exp2((wm_l - pm) * c) : 0.0f);
     }
 
-    // ---- the elements that reach the bound.  A lane takes its vectors that hold one in turn (nearly always one or
-    // none, so the code for it stands here once and not for every register).
-    unsigned mask = 0u;
+    // ---- the vectors that reach the bound go to shared memory, then every thread takes an element of them
+    {
+        unsigned long long reach[R], any = 0ull;
 #pragma unroll
-    for (int q = 0; q < R; ++q) mask |= (v0 + q * kPartThreads + tid < v1 && cm[q] >= theta) ? 1u << q : 0u;
-    // `which` elements of the lane's vector q, ws, join the list
-    auto collect = [&](const uint4 &ws, int q, unsigned which) {
-        float x[EPV];
-        unpack<DT>(ws, x);
-        int at = atomicAdd(&sm.n, __popc(which));
-        const int id0 = g.head + (v0 + q * kPartThreads + tid) * EPV;
-        while (which) {
-            const int k = __ffs((int)which) - 1;
-            which &= which - 1u;
-            float xv = x[0];
-#pragma unroll
-            for (int e = 1; e < EPV; ++e) xv = k == e ? x[e] : xv;
-            if (at < kPartList) sm.list[at] = rank_key(xv, (uint32_t)(id0 + k));
-            ++at;
+        for (int q = 0; q < R; ++q) {
+            reach[q] = __ballot(v0 + q * kPartThreads + tid < v1 && cm[q] >= theta);
+            any |= reach[q];
         }
-    };
-    if (__popcll(__ballot(mask != 0u)) > kPartTies) {
-        if (lane == 0) atomicAdd(&sm.n, kPartTied);
-        mask = 0u;
-    }
-    while (__ballot(mask != 0u)) {
-        uint4 ws = w[0];
-        int q = 0;
+        if (__popcll(any) > kPartTies) {
+            if (lane == 0) atomicAdd(&sm.n_vec, kPartTied);
+        } else if (any) {
 #pragma unroll
-        for (int k = 1; k < R; ++k)
-            if (!(mask & ((1u << k) - 1u))) { ws = w[k]; q = k; }   // the lowest set bit is at least k
-        if (mask) {
-            float x[EPV];
-            unpack<DT>(ws, x);
-            unsigned in = 0u;
-#pragma unroll
-            for (int k = 0; k < EPV; ++k) in |= x[k] >= theta ? 1u << k : 0u;
-            collect(ws, q, in);
-            mask &= mask - 1u;
+            for (int q = 0; q < R; ++q) {
+                if (!reach[q]) continue;
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&sm.n_vec, __popcll(reach[q]));
+                const int at = __builtin_amdgcn_readfirstlane(base) + lane_prefix_count(reach[q]);
+                if (((reach[q] >> lane) & 1ull) && at < kPartVecs) { sm.vec[at] = w[q]; sm.vec_at[at] = v0 + q * kPartThreads + tid; }
+            }
         }
     }
     if (edge_id >= 0 && edge_val >= theta) {
         const int at = atomicAdd(&sm.n, 1);
-        if (at < kPartList) sm.list[at] = rank_key(edge_val, (uint32_t)edge_id);
+        sm.list[at] = rank_key(edge_val, (uint32_t)edge_id);
     }
     __syncthreads();
-    int n = sm.n;
+    // the node's proposal, for the wave that runs the accept tests if this workgroup is the row's last (asked for here, where
+    // the part's registers are free)
+    NodeProposal prop;
+    if (!commit && wave == 1) prop.request(late().r, row, node, lane);
+    int n = sm.n_vec;
+    if (__builtin_expect(n <= kPartVecs, 1)) {
+        for (int i = tid; i < n * EPV; i += kPartThreads) {
+            const float x = load_scalar<DT>(sm.vec, i);
+            if (x >= theta) {
+                const int at = atomicAdd(&sm.n, 1);   // (at most kPartVecs * EPV)
+                if (at < kPartList) sm.list[at] = rank_key(x, (uint32_t)(g.head + sm.vec_at[i / EPV] * EPV + i % EPV));
+            }
+        }
+        __syncthreads();
+        n = sm.n;
+    } else n = kPartTied;
     if (__builtin_expect(n >= kPartTied, 0)) {
         // again, without most of what equals the bound (the part is fetched a second time: kept until here it would cost
         // the registers of a fourth workgroup per compute unit)
@@ -289,7 +300,22 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
             __builtin_amdgcn_make_buffer_rsrc((void *)(g.vp + v0), (short)0, (v1 - v0) * 16, 0x00020000);
         uint4 next[1];
         load_part<0>(next, rsrc, tid);
-        int left = r.K;   // elements equal to the bound that the wave may still take
+        auto collect = [&](const uint4 &ws, int q, unsigned which) {   // `which` elements of the lane's vector q, ws, join the list
+            float x[EPV];
+            unpack<DT>(ws, x);
+            int at = atomicAdd(&sm.n, __popc(which));
+            const int id0 = g.head + (v0 + q * kPartThreads + tid) * EPV;
+            while (which) {
+                const int k = __ffs((int)which) - 1;
+                which &= which - 1u;
+                float xv = x[0];
+#pragma unroll
+                for (int e = 1; e < EPV; ++e) xv = k == e ? x[e] : xv;
+                if (at < kPartList) sm.list[at] = rank_key(xv, (uint32_t)(id0 + k));
+                ++at;
+            }
+        };
+        int left = K;   // elements equal to the bound that the wave may still take
 #pragma unroll 1
         for (int q = 0; q < R; ++q) {
             const uint4 ws = next[0];
@@ -321,7 +347,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
                 const int keep = left - (upto - c);   // what the lower lanes leave
                 for (int d = c; d > keep && d > 0; --d) equal &= ~(0x80000000u >> __clz((int)equal));
                 in |= equal;
-                left = (q == 0 ? r.K : left) - all;
+                left = (q == 0 ? K : left) - all;
             }
             if (in) collect(ws, q, in);
         }
@@ -338,29 +364,30 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         // too many above the bound: the streaming scan over this part (edges included) finds its K best
         __syncthreads();  // every wave has seen n
         const int base = part == 0 ? 0 : g.head + v0 * EPV;
-        const int end = part == a.P - 1 ? r.V : g.head + v1 * EPV;
+        const int end = part == P - 1 ? V : g.head + v1 * EPV;
         const void *sub = rowp + (size_t)base * ES;
         WaveScan *wsc = &sm.scan.wsh[wave];
-        const WavePartial wp = wave_row_stream<DT>(sub, end - base, r.c, r.K, wsc, lane, wave, kPartWaves);
+        const WavePartial wp = wave_row_stream<DT>(sub, end - base, c, K, wsc, lane, wave, kPartWaves);
         if (lane == 0) sm.scan.part_cnt[wave] = wp.cnt;
         __syncthreads();
         if (wave == 0) {
-            const int cnt = gather_wave_records<DT, kPartWaves>(&sm.scan, lane, r.K);
-            wave_row_finish<DT>(sub, end - base, r.K, wsc, sm.scan.ebuf, lane, cnt);
-            const unsigned long long key = lane < r.K ? wsc->top[lane] - (unsigned long long)base : 0ull;  // (the low word counts ids down)
+            const int cnt = gather_wave_records<DT, kPartWaves>(&sm.scan, lane, K);
+            wave_row_finish<DT>(sub, end - base, K, wsc, sm.scan.ebuf, lane, cnt);
+            const unsigned long long key = lane < K ? wsc->top[lane] - (unsigned long long)base : 0ull;  // (the low word counts ids down)
             __builtin_amdgcn_wave_barrier();
-            if (lane < r.K) sm.list[lane] = key;
+            if (lane < K) sm.list[lane] = key;
         }
-        n = r.K;   // more than kPartList elements: the part has K
+        n = K;   // more than kPartList elements: the part has K
         __syncthreads();
     }
-    if (__builtin_expect(n > kPartCut, 0)) n = cut_list(sm.list, n, r.K, lane, wave);
+    if (__builtin_expect(n > kPartCut, 0)) n = cut_list(sm.list, n, K, lane, wave);
     // (here and not where their data arrive: the part's registers are free, and the other waves are handing over)
-    if (wave == 1 && !a.commit) {
+    if (wave == 1 && !commit) {
+        const RowPassArgs &r = late().r;
         prop.template request_logits<DT>(r, b, rowp, lane);
         prop.prepare(r, b, lane);
     }
-    if (a.P > 1) {
+    if (P > 1) {
         if (n > kPartKeys) {
             // more than a part hands over: its K best
             for (int i = tid; i < n; i += kPartThreads) sm.rank[i] = 0;
@@ -368,13 +395,15 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
             rank_against(sm.list, sm.rank, n, n * wave / kPartWaves, n * (wave + 1) / kPartWaves, lane);
             __syncthreads();
             for (int i = tid; i < n; i += kPartThreads)
-                if (sm.rank[i] < r.K) sm.top[sm.rank[i]] = sm.list[i];
+                if (sm.rank[i] < K) sm.top[sm.rank[i]] = sm.list[i];
             __syncthreads();
-            if (tid < r.K) sm.list[tid] = sm.top[tid];
-            n = r.K;
+            if (tid < K) sm.list[tid] = sm.top[tid];
+            n = K;
         }
         // ---- hand over; the row's last workgroup goes on
-        const size_t first = (size_t)slot * a.P, at = first + part;
+        const RowPartsArgs &a = late();
+        const int slot = j * a.r.B + b;
+        const size_t first = (size_t)slot * P, at = first + part;
         if (wave == 0) {
             __builtin_amdgcn_wave_barrier();
             if (lane < n) st_agent(&a.keys[at * kPartKeys + lane], sm.list[lane]);
@@ -386,7 +415,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
             if (lane == 0) {
                 unsigned *tk = &a.ticket[(size_t)slot * kTicketStride];
                 const unsigned before = atomicAdd(tk, 1u);
-                sm.last = before == (unsigned)a.P - 1u;
+                sm.last = before == (unsigned)P - 1u;
                 if (sm.last) st_agent(tk, 0u);
             }
         }
@@ -397,7 +426,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         // lengths arrive with the same round trip)
         PartHead h;
         h.m = -3.402823466e38f; h.s = 0.0f; h.theta = -__builtin_inff(); h.cnt = 0;
-        if (lane < a.P) {
+        if (lane < P) {
             const uint32_t *p = (const uint32_t *)&a.head[first + lane];
             h.m = u2f(ld_agent(p)); h.s = u2f(ld_agent(p + 1)); h.theta = u2f(ld_agent(p + 2)); h.cnt = (int)ld_agent(p + 3);
         }
@@ -406,15 +435,15 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
 #pragma unroll
         for (int q = 0; q < kRounds; ++q) {
             const int p = q * kPartWaves + wave;
-            k[q] = p < a.P ? ld_agent(&a.keys[(first + p) * kPartKeys + lane]) : 0ull;
+            k[q] = p < P ? ld_agent(&a.keys[(first + p) * kPartKeys + lane]) : 0ull;
         }
         pm = wave_max_f32(h.m);
         const float bound = wave_max_f32(h.theta);
-        ps = wave_sum_f32(h.s * fast_exp2((h.m - pm) * r.c));
+        ps = wave_sum_f32(h.s * fast_exp2((h.m - pm) * c));
 #pragma unroll
         for (int q = 0; q < kRounds; ++q) {
             const int p = q * kPartWaves + wave;
-            if (p < a.P) {
+            if (p < P) {
                 const int c = __builtin_amdgcn_readlane(h.cnt, p);
                 const bool in = lane < c && rank_key_value(k[q]) >= bound;
                 const unsigned long long bal = __ballot(in);
@@ -426,7 +455,7 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
         }
         __syncthreads();
         n = sm.n_row;
-        if (__builtin_expect(n > kPartCut, 0)) n = cut_list(sm.list, n, r.K, lane, wave);
+        if (__builtin_expect(n > kPartCut, 0)) n = cut_list(sm.list, n, K, lane, wave);
     } else {
         for (int i = tid; i < n; i += kPartThreads) sm.rank[i] = 0;
         __syncthreads();
@@ -434,31 +463,32 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     // ---- one wave runs the accept tests, the others rank the candidates
     const float m = pm + 0.0f;  // (no negative zero)
     if (wave == 1) {
-        if (!a.commit) prop.template outcome<DT>(r, b, row, rowp, lane, m, ps);
+        if (!commit) prop.template outcome<DT>(late().r, b, row, rowp, lane, m, ps);
     } else {
         const int who = wave == 0 ? 0 : wave - 1;
         rank_against(sm.list, sm.rank, n, n * who / (kPartWaves - 1), n * (who + 1) / (kPartWaves - 1), lane);
     }
     __syncthreads();
-    if (!a.commit && fast_sum_void(m, r.c)) ps = wave_row_plain_sum<DT>(rowp, r.V, m, r.c, lane);
-    const size_t o = (size_t)(a.commit ? b * a.R + j : row) * r.K;
+    if (!commit && __builtin_expect(fast_sum_void(m, c), 0)) ps = wave_row_plain_sum<DT>(rowp, V, m, c, lane);
+    const RowPartsArgs &e = late();
+    const size_t o = (size_t)(commit ? b * e.R + j : row) * K;
     for (int i = tid; i < n; i += kPartThreads) {
         const int at = sm.rank[i];
-        if (at >= r.K) continue;
+        if (at >= K) continue;
         const unsigned long long key = sm.list[i];
         const float l = rank_key_value(key);
-        if (a.commit) {
-            a.pr_top_idx[o + at] = (int32_t)rank_key_id(key);
-            a.pr_top_l[o + at] = l;
+        if (commit) {
+            e.pr_top_idx[o + at] = (int32_t)rank_key_id(key);
+            e.pr_top_l[o + at] = l;
         } else {
-            r.top_idx[o + at] = (int32_t)rank_key_id(key);
-            r.top_l[o + at] = l;
-            r.top_p[o + at] = exact_exp2(scaled_offset(l, m, r.c)) / ps;
+            e.r.top_idx[o + at] = (int32_t)rank_key_id(key);
+            e.r.top_l[o + at] = l;
+            e.r.top_p[o + at] = exact_exp2(scaled_offset(l, m, c)) / ps;
         }
     }
     if (tid == 0) {
-        if (a.commit) a.pr_m[b * a.R + j] = m;
-        else { r.row_m[row] = m; r.row_s[row] = ps; }
+        if (commit) e.pr_m[b * e.R + j] = m;
+        else { e.r.row_m[row] = m; e.r.row_s[row] = ps; }
     }
 }
 

@@ -462,16 +462,24 @@ static unsigned long long wait_ticks(const stand_handle *h) { return h->wait_lim
 // what the row kernel before a step_tail_kernel clears
 static SumClear tail_clear(const stand_handle *h) { return SumClear{h->tail_part, h->tail_bar, h->W, h->tail_nsub}; }
 
-template <int DT>
+template <int DT, bool STREAMED>
 static const void *row_parts_fn(int vectors)
 {
-    return vectors <= 1 ? (const void *)row_parts_kernel<DT, 1>
-         : vectors <= 2 ? (const void *)row_parts_kernel<DT, 2>
-         : vectors <= 3 ? (const void *)row_parts_kernel<DT, 3>
-         : vectors <= 4 ? (const void *)row_parts_kernel<DT, 4>
-         : vectors <= 6 ? (const void *)row_parts_kernel<DT, 6>
-                        : (const void *)row_parts_kernel<DT, kPartVectors>;
+    return vectors <= 1 ? (const void *)row_parts_kernel<DT, 1, STREAMED>
+         : vectors <= 2 ? (const void *)row_parts_kernel<DT, 2, STREAMED>
+         : vectors <= 3 ? (const void *)row_parts_kernel<DT, 3, STREAMED>
+         : vectors <= 4 ? (const void *)row_parts_kernel<DT, 4, STREAMED>
+         : vectors <= 6 ? (const void *)row_parts_kernel<DT, 6, STREAMED>
+                        : (const void *)row_parts_kernel<DT, kPartVectors, STREAMED>;
 }
+static const void *row_parts_fn(bool bf16, int vectors, bool streamed)
+{
+    return bf16 ? (streamed ? row_parts_fn<kDtBf16, true>(vectors) : row_parts_fn<kDtBf16, false>(vectors))
+                : (streamed ? row_parts_fn<kDtF32, true>(vectors) : row_parts_fn<kDtF32, false>(vectors));
+}
+// Logits beyond what the eight L2 caches hold together (32 MB) are read past them: step of 256 rows of 257 KB 51.1
+// against 54.6 us; below, the path rows' second read finds them there (16 rows of 128 KB: 29.3 against 30.0 us)
+static bool rows_streamed(const stand_handle *h) { return (int64_t)h->B * h->N * h->V * element_bytes(h->cfg) > ((int64_t)32 << 20); }
 // Launch parameters of row_parts_kernel for `parts` parts per row.
 static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r, int parts)
 {
@@ -479,9 +487,6 @@ static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r,
     memset(&a, 0, sizeof(a));
     a.r = r;
     a.P = parts;
-    // logits beyond what the eight L2 caches hold together (32 MB) are read past them: step of 256 rows of 257 KB 51.1
-    // against 54.6 us; below, the path rows' second read finds them there (16 rows of 128 KB: 29.3 against 30.0 us)
-    a.streamed = (int64_t)h->B * h->N * h->V * element_bytes(h->cfg) > ((int64_t)32 << 20);
     a.per = (int)((row_vectors(h->V, element_bytes(h->cfg)) + parts - 1) / parts);
     a.ticket = h->part_ticket; a.head = h->part_head; a.keys = h->part_keys;
     return a;
@@ -505,7 +510,7 @@ static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t st
     const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
     const dim3 grid = split ? dim3((unsigned)parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
     const dim3 block(split ? (unsigned)kPartThreads : 64u * (unsigned)(few ? kRowWPRFewRows : kRowWPR));
-    const void *fn = split ? (bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors))
+    const void *fn = split ? row_parts_fn(bf16, vectors, rows_streamed(h))
                    : bf16 ? (few ? (const void *)row_pass_kernel<kDtBf16, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtBf16, kRowWPR>)
                           : (few ? (const void *)row_pass_kernel<kDtF32, kRowWPRFewRows> : (const void *)row_pass_kernel<kDtF32, kRowWPR>);
     void *args[] = {split ? (void *)&pa : (void *)&a};
@@ -575,13 +580,13 @@ static int launch_commit_rows(stand_handle *h, uint64_t step, const void *d_logi
     if (h->commit_parts > 0) {
         RowPartsArgs pa = make_parts_args(h, make_row_args(h, h->vs, step, d_logits, kPartWaves * h->commit_parts), h->commit_parts);
         pa.r.clear = clear;
-        pa.streamed = false;  // (every row of an update is read again for its exact sum: 63.6 against 64.9 us, 128 rows of 304 KB)
         pa.commit = true; pa.all_nodes = h->cfg.update_mode == STAND_UPDATE_ALL_NODES; pa.W = h->W; pa.R = h->R;
         pa.commit_row = commit_row; pa.commit_len = commit_len;
         pa.pr_m = h->pr_m; pa.pr_top_idx = h->pr_top_idx; pa.pr_top_l = h->pr_top_l;
         const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
         void *args[] = {&pa};
-        HIP_TRY(h, hipLaunchKernel(bf16 ? row_parts_fn<kDtBf16>(vectors) : row_parts_fn<kDtF32>(vectors),
+        // (not streamed: every row of an update is read again for its exact sum: 63.6 against 64.9 us, 128 rows of 304 KB)
+        HIP_TRY(h, hipLaunchKernel(row_parts_fn(bf16, vectors, false),
                                    dim3((unsigned)h->commit_parts, (unsigned)h->B, (unsigned)h->R), dim3(kPartThreads), args, 0, s));
         return STAND_OK;
     }

@@ -517,6 +517,22 @@ def test_rows_of_equal_logits_split_over_workgroups(gpu, dtype, V, K):
     _row_case(gpu, rows, dtype, K, parent=parent, check=range(8))
 
 
+@pytest.mark.parametrize("dtype,V,K", [("bf16", 32768, 25), ("bf16", 30001, 32), ("f32", 16384, 25), ("f32", 3 * 16384 - 7, 32)])
+def test_rows_with_more_vectors_at_the_bound_than_are_collected(gpu, dtype, V, K):
+    """Of every 64 vectors (a wave's lanes) 6 to 24 lie above the others, i.e. fewer lane groups than K, so that the part's bound is
+    among the lower ones and from 384 to 1536 vectors reach it, though few lanes of a wave: at the memory's limit, above it, below."""
+    r = np.random.default_rng(V + K)
+    epv = 8 if dtype == "bf16" else 4
+    rows = []
+    for high in (5, 6, 7, 16, 24):
+        x = r.uniform(-1.0, 0.0, V).astype(np.float32)
+        up = (np.arange(V) // epv) % 64 < high
+        x[up] = r.uniform(5.0, 6.0, int(up.sum())).astype(np.float32)
+        rows.append(x)
+    _say("rows with many vectors at the bound %s V=%d K=%d" % (dtype, V, K))
+    _row_case(gpu, np.stack(rows * 60), dtype, K, parent=np.array([-1] + [(u - 1) // 20 for u in range(1, 300)], np.int32), check=range(10))
+
+
 @pytest.mark.parametrize("mask", ["half", "few", "lowest"])
 def test_masked_rows_cost_what_others_cost(gpu, mask):
     """The row pass over masked vocabularies takes about the time of the unmasked one (with every tie ordered by the
