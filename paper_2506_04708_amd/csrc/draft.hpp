@@ -117,9 +117,10 @@ __device__ __forceinline__ float uniform_by_halves(uint64_t seed, uint32_t b, ui
     return word_to_uniform(want_upper == upper ? mine : other);
 }
 
-// Levels of the draft of trajectory b (see draft_trajectory): tree levels in sequence, one wave per node.
-template <int NT, int G>
-__device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const DraftShared &sm, int level_reg, long long clen)
+// Levels of the draft of trajectory b (see draft_trajectory): tree levels in sequence, one wave per node.  join(): called by all
+// threads once what does not need the root's token is formed; that token is in `sm` when it returns.
+template <int NT, int G, typename Join>
+__device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const DraftShared &sm, int level_reg, const Join &join)
 {
     using L = CandLayout<G>;
     constexpr int kMaxRounds = kMaxOrder / G;
@@ -144,12 +145,17 @@ __device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const Dr
     unsigned my_hits = 0u;   // lane n <= kMaxOrder: lookups of this wave answered by order n; lane 0: misses
     int32_t *qid_out = a.draft_qid + (size_t)b * N * K;
     float *qmu_out = a.draft_qmu + (size_t)b * N * K;
-    for (int d = 0; d < a.tree.D; ++d) {
+    // the first node of a level falls to the second wave: the first one may have just found the root's token
+    const int turn = (wave + NT / 64 - 1) & (NT / 64 - 1);
+    const int D = a.tree.D;
+    join();
+    const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
+    for (int d = 0; d < D; ++d) {
         // values read from shared memory that are the same in every lane go to scalar registers
         const int lo = __builtin_amdgcn_readlane(level_reg, d), hi = __builtin_amdgcn_readlane(level_reg, d + 1);
         // the wave's first node of the level is read together with the flag that ends the tree
         int live = sm.live[d];
-        int u = lo + wave;
+        int u = lo + turn;
         int4 r_lo, r_hi;
         int32_t my_recent;
         int info, my_tok;
@@ -162,7 +168,7 @@ __device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const Dr
         asm volatile("" : "+v"(live), "+v"(info), "+v"(my_tok), "+v"(my_recent));  // (one round trip, not one after the branch)
         if (!__builtin_amdgcn_readfirstlane(live)) break;  // a level without a drafted node ends the tree (the same in every wave)
         for (; u < hi; u += NT / 64) {
-            if (u != lo + wave) read_node(u);
+            if (u != lo + turn) read_node(u);
             info = __builtin_amdgcn_readfirstlane(info);
             const int nch = info & 0xFF, first = info >> 8;
             if (nch == 0 || __builtin_amdgcn_readfirstlane(my_tok) < 0) continue;
@@ -334,7 +340,8 @@ __device__ __forceinline__ void draft_levels(const DraftArgs &a, int b, const Dr
 // round run side by side (53 cycles a round instead of 107), ln mu is taken beside ln U, header and payload of every
 // order are requested without a branch between them (which had made two round trips of them), a node's outputs are stored
 // before its ranking, and nothing in the level loop waits for a store.  With clock readings between the parts a level of a
-// warm 64-node tree went from about 4 700 to 2 900 cycles; draft of 32 such trees 19.7 -> 15.0 us, steps of 32 x 64 rows
+// warm 64-node tree went from about 4 700 to 2 900 cycles (and with the constants formed before the first level is waited for:
+// draft and packing of 32 such trees 18.3 -> 17.3 us); draft of 32 such trees 19.7 -> 15.0 us, steps of 32 x 64 rows
 // x 152 064 154.3 -> 149.9 us (separate launches) and 116.9 -> 114.3 us (one launch), of 8 x 32 49.3 -> 47.1 us.
 // (Table entries are read past the XCD's own caches in every launch form: in the one-launch step other workgroups
 // have just written them, and as ordinary loads they made no repeated call faster and the first call after other work
@@ -387,16 +394,15 @@ __device__ __forceinline__ int draft_prepare(const DraftArgs &a, int b, const Dr
     return level_reg;
 }
 
-// (called after a barrier that follows draft_prepare, or whatever else has filled `sm`)
-template <int NT>
-__device__ __forceinline__ void draft_run(const DraftArgs &a, int b, const DraftShared &sm, int level_reg)
+// (`sm` as draft_prepare, or whatever else has filled it, leaves it; join() ends with a barrier)
+template <int NT, typename Join>
+__device__ __forceinline__ void draft_run(const DraftArgs &a, int b, const DraftShared &sm, int level_reg, const Join &join)
 {
     const int tid = threadIdx.x, N = a.tree.N;
     const int32_t *tok = sm.tok;
     const int32_t(*recent)[kMaxOrder] = sm.recent;
-    const long long clen = (long long)readlane_u64((unsigned long long)*sm.clen, 0);
-    if (a.K <= 16) draft_levels<NT, 4>(a, b, sm, level_reg, clen);
-    else draft_levels<NT, 2>(a, b, sm, level_reg, clen);
+    if (a.K <= 16) draft_levels<NT, 4>(a, b, sm, level_reg, join);
+    else draft_levels<NT, 2>(a, b, sm, level_reg, join);
     if (tid <= a.omax) {
         const unsigned c = sm.n_hit[tid];
         if (c) atomicAdd(&a.stats[tid == 0 ? (int)kStatMisses : (int)kStatHits + tid], (unsigned long long)c);
@@ -415,8 +421,7 @@ template <int NT>
 __device__ __forceinline__ void draft_trajectory(const DraftArgs &a, int b, const DraftShared &sm)
 {
     const int level_reg = draft_prepare<NT>(a, b, sm);
-    __syncthreads();
-    draft_run<NT>(a, b, sm, level_reg);
+    draft_run<NT>(a, b, sm, level_reg, [] { __syncthreads(); });
 }
 
 __global__ __launch_bounds__(kDraftThreads) void draft_kernel(DraftArgs a)

@@ -463,7 +463,10 @@ __global__ __launch_bounds__(kPartThreads) __attribute__((amdgpu_waves_per_eu(8,
     // ---- one wave runs the accept tests, the others rank the candidates
     const float m = pm + 0.0f;  // (no negative zero)
     if (wave == 1) {
-        if (!commit) prop.template outcome<DT>(late().r, b, row, rowp, lane, m, ps);
+        if (!commit) {
+            prop.stage(late().r, row, lane);
+            prop.template outcome<DT>(late().r, b, row, rowp, lane, m, ps);
+        }
     } else {
         const int who = wave == 0 ? 0 : wave - 1;
         rank_against(sm.list, sm.rank, n, n * who / (kPartWaves - 1), n * (who + 1) / (kPartWaves - 1), lane);

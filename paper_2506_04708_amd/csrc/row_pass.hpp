@@ -571,11 +571,12 @@ __device__ __forceinline__ float wave_row_plain_sum(const void *rowp, int V, flo
     return (float)s;
 }
 
-// The words in which a step_tail_kernel meets (partial sums of the path rows, two counters), set to zero by the row kernel
+constexpr unsigned kTailCounters = 3;
+// The words in which a step_tail_kernel meets (partial sums of the path rows, counters), set to zero by the row kernel
 // that is launched before it.
 struct SumClear {
     unsigned long long *part;   // [B][R][words], or NULL: nothing to clear
-    unsigned *bar;              // [2]
+    unsigned *bar;              // [kTailCounters]
     int R, words;
     // called by all threads of the workgroup that holds (the first part of) row slot j of trajectory b
     __device__ __forceinline__ void row(int b, int j) const
@@ -583,9 +584,15 @@ struct SumClear {
         if (!part) return;
         if (j < R)
             for (int i = threadIdx.x; i < words; i += blockDim.x) part[((size_t)b * R + j) * words + i] = 0ull;
-        if (b == 0 && j == 0 && threadIdx.x < 2) bar[threadIdx.x] = 0u;
+        if (b == 0 && j == 0 && threadIdx.x < kTailCounters) bar[threadIdx.x] = 0u;
     }
 };
+
+// Lane i of a node's accept tests: the row's logit at its i-th stored id, that id's weight in the proposal; uniform and place of
+// the i-th child's test.  Left by row_parts_kernel for the replay of path rows with exact probabilities: formed again there,
+// these were 1.5 us of the path of one trajectory's step.  (Not by the streaming row pass: 2048 rows of 304 KB took 108.5
+// instead of 103 us with these stores.)
+struct alignas(16) StagedTest { float l, w, om; int pos; };
 
 struct RowPassArgs {
     const void *logits;
@@ -606,6 +613,7 @@ struct RowPassArgs {
     float eps;                  // relative error assumed for the fast normaliser from its additions (>= kFastEps)
     int fx_shift;               // the exact normaliser counts in units of 2^-(40 - fx_shift) (0 up to V = 2^22)
     SumClear clear;             // what the step_tail_kernel that follows needs at zero
+    StagedTest *staged;         // [B*N][K] for it, or NULL: the nodes' proposals as they enter the tests
 };
 
 // The proposal of a node and its accept tests, by one wave.
@@ -643,6 +651,10 @@ struct NodeProposal {
     __device__ __forceinline__ void prepare(const RowPassArgs &a, int b, int lane)
     {
         if (nch > 0) tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+    }
+    __device__ __forceinline__ void stage(const RowPassArgs &a, int row, int lane) const
+    {
+        if (a.staged && nch > 0 && lane < a.K) a.staged[(size_t)row * a.K + lane] = StagedTest{my_l, tests.w, tests.om, tests.pos};
     }
     // accept / reject outcome of the node's children (paper Sec. 3.2, applied recursively)
     template <int DT>

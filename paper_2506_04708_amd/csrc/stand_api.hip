@@ -80,7 +80,8 @@ struct stand_handle {
     int tail_per_cu, cus;            // workgroups of step_tail_kernel a compute unit holds at once; the device's compute units
     int tail_nsub;                   // ranges of a path row that are summed by a wave each
     unsigned long long *tail_part;   // [B][W][tail_nsub]
-    unsigned *tail_bar;              // [2]
+    unsigned *tail_bar;              // [kTailCounters]
+    StagedTest *staged;              // [B*N][K]
     unsigned *part_ticket;           // [rows or commit slots], zero between launches
     PartHead *part_head;
     unsigned long long *part_keys;
@@ -150,7 +151,7 @@ static void free_all(stand_handle *h)
     if (!h) return;
     void *ptrs[] = {h->d_tree, h->table, h->ctx_tail, h->ctx_len, h->ctx_tail2, h->ctx_len2, h->reorder_map, h->export_buf, h->draft_tok, h->draft_has, h->draft_qid, h->draft_qmu,
                     h->vs.row_m, h->vs.row_s, h->vs.top_l, h->vs.top_p, h->vs.top_idx, h->vs.outcome, h->vs.obs_idx, h->vs.obs_p, h->rec_slot,
-                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->tail_part, h->tail_bar, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
+                    h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->tail_part, h->tail_bar, h->staged, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
     for (void *p : ptrs) (void)hipFree(p);
     for (hipEvent_t e : h->ev_begin) (void)hipEventDestroy(e);
     for (hipEvent_t e : h->ev_end) (void)hipEventDestroy(e);
@@ -306,7 +307,8 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     h->tail_verify = small && plan_tail_verify(h->B, h->W, h->tail_nsub / kTailWaves);
     h->tail_step = small && plan_tail_step(h->B, h->W, h->NO);
     h->tail_update = small && plan_tail_update(h->W, h->NO);
-    acc(dmalloc(&h->tail_part, small ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, 2));
+    acc(dmalloc(&h->tail_part, small ? B * h->W * h->tail_nsub : 0)); acc(dmalloc(&h->tail_bar, (size_t)kTailCounters));
+    acc(dmalloc(&h->staged, small ? rows * K : 0));
     acc(dmalloc(&h->stats, (size_t)kStatCount));
     acc(dmalloc(&h->counter, 1));
     if (e != hipSuccess) { free_all(h); return e == hipErrorOutOfMemory ? STAND_ENOMEM : STAND_EHIP; }
@@ -440,6 +442,7 @@ static RowPassArgs make_row_args(const stand_handle *h, const VerifyScratch &vs,
     a.eps = fast_eps(h, wpr);
     a.fx_shift = h->fx_shift;
     a.clear = SumClear{nullptr, nullptr, 0, 0};
+    a.staged = nullptr;
     return a;
 }
 
@@ -492,20 +495,27 @@ static RowPartsArgs make_parts_args(const stand_handle *h, const RowPassArgs &r,
     return a;
 }
 
-// `own`: the scratch is the handle's own (the parts of a split row meet in the handle's memory, which a caller of the
-// entry point with fixed scratch may not expect to be in use).
+// Parts of every row of a verification, 0: the rows stream.  `own`: the scratch is the handle's own (the parts of a split row
+// meet in the handle's memory, which a caller of the entry point with fixed scratch may not expect to be in use; few rows keep
+// sixteen waves each there).
+static int row_pass_parts(const stand_handle *h, bool own)
+{
+    if (own && h->row_parts > 0) return h->row_parts;
+    // (a grid has at most 65535 trajectories)
+    return plan_row_whole(h->V, element_bytes(h->cfg), h->K) && (own || h->B * h->N > kRowsSixteenWaves) && h->B <= 65535 ? 1 : 0;
+}
+
 // `own`: the handle's scratch; `tail`: a step_tail_kernel follows
 static int launch_row_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, bool own, bool tail, hipStream_t s)
 {
     const int rows = h->B * h->N;
-    // (few rows of the entry point with fixed scratch keep sixteen waves each; a grid has at most 65535 trajectories)
-    const bool whole = plan_row_whole(h->V, element_bytes(h->cfg), h->K) && (own || rows > kRowsSixteenWaves) && h->B <= 65535;
-    const int parts = own && h->row_parts > 0 ? h->row_parts : (whole ? 1 : 0);
+    const int parts = row_pass_parts(h, own);
     const bool split = parts > 0;
     const bool few = unsplit_waves(rows) == kRowWPRFewRows;  // one workgroup per row; more waves per row when rows are few
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
     RowPassArgs a = make_row_args(h, vs, step, d_logits, split ? kPartWaves * parts : (few ? kRowWPRFewRows : kRowWPR));
     if (tail) a.clear = tail_clear(h);
+    if (tail && split) a.staged = h->staged;
     RowPartsArgs pa = make_parts_args(h, a, split ? parts : 1);
     const int vectors = (pa.per + kPartThreads - 1) / kPartThreads;
     const dim3 grid = split ? dim3((unsigned)parts, (unsigned)h->B, (unsigned)h->N) : dim3((unsigned)rows);
@@ -647,7 +657,7 @@ static int launch_step_tail(stand_handle *h, uint64_t step, const void *d_logits
     A.mg = merge ? *merge : merge_args(h, nullptr, nullptr, nullptr);
     if (draft) A.draft = *draft;
     else A.draft.tree = A.path.tree;
-    A.part = h->tail_part; A.bar = h->tail_bar; A.nsub = h->tail_nsub;
+    A.part = h->tail_part; A.bar = h->tail_bar; A.staged = row_pass_parts(h, true) > 0 ? h->staged : nullptr; A.nsub = h->tail_nsub;
     A.merge = merge != nullptr; A.drafts = draft != nullptr;
     A.given_tok = given_tok; A.ctx_tail = h->ctx_tail; A.ctx_len = h->ctx_len;
     A.wait_units = (unsigned)((wait_ticks(h) + (1u << kWaitShift) - 1) >> kWaitShift);   // (at most a minute)

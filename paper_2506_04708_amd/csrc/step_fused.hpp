@@ -378,7 +378,7 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
         if (tid < W) { a.out_tok[(size_t)b * W + tid] = -1; a.out_node[(size_t)b * W + tid] = -1; }
         if (tid == 0) { a.out_len[b] = 0; atomicAdd(&a.stats[kStatWaitExpired], 1ull); }
     }
-    draft_run<kStepThreads>(A.draft, b, dsm, level_reg);
+    draft_run<kStepThreads>(A.draft, b, dsm, level_reg, [] {});
     if (tid == 0) stamp(sy, b, 7);
 }
 

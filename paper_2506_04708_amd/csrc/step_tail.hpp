@@ -21,11 +21,13 @@ namespace stand {
 //   last wave           claims of the table slots (they need the path's tokens only)
 //   the others          observations of the path rows, then the merge records
 //
-// so that the longest chain is path, sums, token, draft, with claims and applies beside it.
+// so that the longest chain is path, sums, token, draft, with claims and applies beside it.  The other path nodes are replayed by
+// the summing workgroups, when their sums are done.
 //   - A partial sum is one self-validating word (top bit set; the row kernel before has cleared the words).  The ranges
 //     are so small that the wave which draws the token finds it by itself, with one more look at one range.
 //   - Between claims and applies, and between applies and the draft's lookups, the trajectories meet at a counter
-//     (cleared by the row kernel as well, so that a recorded launch can be replayed).
+//     (cleared by the row kernel as well, so that a recorded launch can be replayed).  A third one counts observations: only
+//     a slot that several records have claimed needs those of others.
 //   - Inside a workgroup the waves meet at counters in shared memory until all of them join for the draft.
 //   - Waits are bounded by the handle's wait limit (TailWait).  When all waves of a trajectory have joined, its waits are over:
 //     one of them that ran out is counted there, the trajectory's outputs are void, its context stays and nothing is drafted.
@@ -33,12 +35,17 @@ namespace stand {
 // once (plan_tail_places; asked for every call, a stream may be masked to a few of them): the summing workgroups, which wait
 // for nothing, have room, with launches of other handles beside it as well.
 //
-// Bound by latency: of the 13.5 us of one launch for 1 x 32 rows x 152 064 (clock readings), the path is known at 1.4,
-// the last sum is stored at 3, seen at 4.4 (a word travels about 1 us from one workgroup to another), the token is there
-// at 8 and the draft takes the last 4.7; claims end at 3.8, applies at 7.5.  Steps, separate launches / one launch, us:
+// Bound by latency: of the 13 us of one launch for 1 x 32 rows x 152 064 (clock readings), the path is known at 1.6, the last
+// sum is stored at 1.9, seen at 3 (a word travels about 1 us from one workgroup to another), the token is there at 8.6 and the
+// draft takes the last 4.5; claims end at 4.1, applies at 7.
+// Steps, separate launches / one launch, us:
 // 1 x 16 rows x 32 000 fp32 27.9 / 22.5, 1 x 32 x 152 064 bf16 32.4 / 25.5, 8 x 32 x 128 256 47.1 / 41.4,
 // 6 x 40 x 50 257 by verify, update and draft 62.3 / 55.0, 32 x 64 x 152 064 with long paths 149.9 / 148.0; verify of
 // 12 x 48 x 32 003 fp32 37.6 / 33.7.
+// Then, with what waits for nothing moved off the chains (the stop node's tests left by the row kernel, a range looked at once,
+// the draft's constants formed before the waves join and its root taken by an idle wave, claims met without observations, upper
+// nodes replayed by summing workgroups, a wave's next record requested while one is folded): 1 x 16 22.8 / 22.05, 1 x 32 25.2 /
+// 24.2, 8 x 32 39.9 / 38.55, 24 x 20 x 50 000 40.8 / 37.9, 16 x 30 x 100 000 50.3 / 48.4, 32 x 64 with long paths 146.7 / 144.0.
 // The arguments are read again in each phase (fresh_args): kept from the start they were 361 spilled scalar registers.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTailThreads = 1024, kTailWaves = kTailThreads / 64;
@@ -53,7 +60,8 @@ struct StepTailArgs {
     MergeArgs mg;
     DraftArgs draft;
     unsigned long long *part;   // [B][W][nsub]
-    unsigned *bar;              // [2]
+    unsigned *bar;              // [kTailCounters] trajectories whose claims are made, records applied, observations written
+    const StagedTest *staged;   // [B*N][K] what the row kernel has left of the nodes' tests, or NULL
     int nsub;                   // ranges of a row: a multiple of kTailWaves
     int row_slots;              // path rows that have summing workgroups of their own (longer paths loop)
     unsigned wait_units;        // bound of every wait in units of wait_clock
@@ -67,11 +75,11 @@ struct StepTailArgs {
 struct SmallTail {
     int path[kMaxDepth + 2];
     int len, ok;                // ok: 0 once a wait of the trajectory has run out (TailWait)
-    int arrived[2], met;        // waves that are done with their part before a meeting; the first meeting is over
+    int arrived[2], met;        // waves that have written their observations / applied their records; all claims are made
     int32_t seq[kMaxOrder + kMaxDepth + 2];   // context tail (oldest first), then the committed tokens
     long long had;                            // length of the context before
     long long slot[kMaxOrder * (kMaxDepth + 1)];   // table slot of each record of the trajectory
-    unsigned long long P[kSubMax];
+    alignas(16) unsigned long long P[kSubMax];   // masses of the ranges; then, while the token is located, the vectors of one
     alignas(16) unsigned long long scratch[kTailWaves][2 * kMaxK];
 };
 // Per node: outcome + 1, drafted children << 6, first child + 1 << 12 (a node has at most kMaxK children).
@@ -108,56 +116,6 @@ __device__ __forceinline__ SubRange sub_range(const RowGeom &g, int per, int sub
 {
     const int v0 = sub * per < g.nvec ? sub * per : g.nvec;
     return SubRange{v0, v0 + per < g.nvec ? v0 + per : g.nvec};
-}
-
-template <int DT>
-__device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
-{
-    constexpr int ES = VecTraits<DT>::ES;
-    const StepTailArgs &A = fresh_args<StepTailArgs>();
-    const PathArgs &a = A.path;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int groups = A.nsub / kTailWaves;
-    // row slots are the slowest: the workgroups of the root rows, which every path has, are first
-    const int j = i / (groups * a.B), b = i / groups % a.B, sub = i % groups * kTailWaves + wave;
-    const TailStage st = tail_stage(smem, a.N);
-    int len = -1;
-    for (int jj = j; jj < a.R; jj += A.row_slots) {
-        int node;
-        float m;
-        if (a.mode != 0) {
-            node = commit_row_of(a, b, jj);
-            if (node < 0) continue;   // (the same in the whole workgroup)
-            m = a.src_m[b * a.R + jj];
-        } else if (jj == 0) {
-            node = 0;
-            m = a.src_m[b * a.N];
-        } else {
-            if (len < 0) {
-                for (int u = tid; u < a.N; u += kTailThreads) {
-                    st.word[u] = (a.outcome[(size_t)b * a.N + u] + 1) | ((a.tree.first_child[u] + 1) << 12);
-                    st.m[u] = a.src_m[(size_t)b * a.N + u];
-                }
-                __syncthreads();
-                if (tid == 0) ts->len = tail_walk(st, a.tree.D, ts->path);
-                __syncthreads();
-                len = ts->len;
-            }
-            if (jj >= len) return;
-            node = ts->path[jj];
-            m = st.m[node];
-        }
-        node = __builtin_amdgcn_readfirstlane(node);
-        const char *rowp = (const char *)a.logits + (size_t)(b * a.N + node) * (size_t)a.V * ES;
-        const RowGeom g = row_geom<DT>(rowp, a.V);
-        const int per = sub_vectors(g, A.nsub);
-        const SubRange r = sub_range(g, per, sub);
-        unsigned long long S;
-        if (per <= 64) S = thread_exact_partial<DT, 1>(rowp, g, r.v0, r.v1, sub == 0, m, a.c, lane, 64, a.fx_shift);
-        else S = thread_exact_partial<DT, 4>(rowp, g, r.v0, r.v1, sub == 0, m, a.c, lane, 64, a.fx_shift);
-        S = wave_sum_u64(S);
-        if (lane == 0) st_agent(&A.part[((size_t)b * a.R + jj) * A.nsub + sub], S | kSumThere);
-    }
 }
 
 __device__ __forceinline__ bool still_ok(const SmallTail *ts)
@@ -232,6 +190,108 @@ __device__ __forceinline__ unsigned long long lane_total(const SubSums &s)
     return t;
 }
 
+// A node's proposal as it enters its accept tests (lane i: stored id i, -1 if there is none, and what StagedTest says).
+template <int DT>
+__device__ __forceinline__ StagedTest tail_node_tests(const StepTailArgs &A, int b, size_t row, int nch, int fc, int lane, int32_t &my_id)
+{
+    const PathArgs &a = A.path;
+    StagedTest t{0.0f, 0.0f, 0.0f, -1};
+    my_id = -1;
+    if (A.staged) {
+        if (lane < a.K) { my_id = a.draft_qid[row * a.K + lane]; t = A.staged[row * a.K + lane]; }
+        if ((uint32_t)my_id >= (uint32_t)a.V) my_id = -1;
+        return t;
+    }
+    float mu = 0.0f;
+    int32_t ch = -1;
+    if (lane < a.K) { my_id = a.draft_qid[row * a.K + lane]; mu = a.draft_qmu[row * a.K + lane]; }
+    if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
+    if ((uint32_t)my_id >= (uint32_t)a.V) { my_id = -1; mu = 0.0f; }  // never index outside the row
+    else t.l = load_scalar<DT>((const char *)a.logits + row * (size_t)a.V * VecTraits<DT>::ES, my_id);
+    const NodeTests n = node_tests_prepare(lane, a.K, my_id, mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+    t.w = n.w; t.om = n.om; t.pos = n.pos;
+    return t;
+}
+
+// A node of the accepted path above the stop node, by one wave: its accept tests again with exact probabilities.  They must name
+// the child that the row pass (with the fast normaliser and its error bound) has named.
+template <int DT>
+__device__ __forceinline__ void replay_upper_row(const StepTailArgs &A, SmallTail *ts, int b, int j, int node, int lane)
+{
+    const PathArgs &a = A.path;
+    const size_t row = (size_t)b * a.N + node;
+    const int walked = a.outcome[row];
+    if (walked < 0) return;   // (the stop node: the trajectory's first wave)
+    SubSums part;
+    part.request(A, b, j, (A.nsub + 63) / 64, lane);
+    const int nch = a.draft_has[row];
+    const float m = a.src_m[row];
+    int32_t id;
+    const StagedTest t = tail_node_tests<DT>(A, b, row, nch, a.tree.first_child[node], lane, id);
+    part.wait(ts, A.wait_units);
+    if (!still_ok(ts)) return;
+    const float s = normaliser_from_fixed(wave_sum_u64(lane_total(part)), a.fx_shift);
+    const float e = id >= 0 ? exact_exp2(scaled_offset(t.l, m, a.c)) : 0.0f;
+    const NodeResult nr = wave_node_outcome(lane, a.K, NodeTests{t.w, t.om, t.pos}, e / s, nch, false, 0.0f, a.onehot);
+    if (lane == 0 && nr.accepted != walked) atomicAdd(&a.stats[kStatMismatch], 1ull);
+}
+
+template <int DT>
+__device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
+{
+    constexpr int ES = VecTraits<DT>::ES;
+    const StepTailArgs &A = fresh_args<StepTailArgs>();
+    const PathArgs &a = A.path;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int groups = A.nsub / kTailWaves;
+    // row slots are the slowest: the workgroups of the root rows, which every path has, are first
+    const int j = i / (groups * a.B), b = i / groups % a.B, sub = i % groups * kTailWaves + wave;
+    const TailStage st = tail_stage(smem, a.N);
+    int len = a.mode != 0 ? -1 : 0;   // (0: not followed yet)
+    for (int jj = j; jj < a.R; jj += A.row_slots) {
+        int node;
+        float m;
+        if (a.mode != 0) {
+            node = commit_row_of(a, b, jj);
+            if (node < 0) continue;   // (the same in the whole workgroup)
+            m = a.src_m[b * a.R + jj];
+        } else if (jj == 0) {
+            node = 0;
+            m = a.src_m[b * a.N];
+        } else {
+            if (len == 0) {
+                for (int u = tid; u < a.N; u += kTailThreads) {
+                    st.word[u] = (a.outcome[(size_t)b * a.N + u] + 1) | ((a.tree.first_child[u] + 1) << 12);
+                    st.m[u] = a.src_m[(size_t)b * a.N + u];
+                }
+                __syncthreads();
+                if (tid == 0) ts->len = tail_walk(st, a.tree.D, ts->path);
+                __syncthreads();
+                len = ts->len;
+            }
+            if (jj >= len) break;
+            node = ts->path[jj];
+            m = st.m[node];
+        }
+        node = __builtin_amdgcn_readfirstlane(node);
+        const char *rowp = (const char *)a.logits + (size_t)(b * a.N + node) * (size_t)a.V * ES;
+        const RowGeom g = row_geom<DT>(rowp, a.V);
+        const int per = sub_vectors(g, A.nsub);
+        const SubRange r = sub_range(g, per, sub);
+        unsigned long long S;
+        if (per <= 64) S = thread_exact_partial<DT, 1>(rowp, g, r.v0, r.v1, sub == 0, m, a.c, lane, 64, a.fx_shift);
+        else S = thread_exact_partial<DT, 4>(rowp, g, r.v0, r.v1, sub == 0, m, a.c, lane, 64, a.fx_shift);
+        S = wave_sum_u64(S);
+        if (lane == 0) st_agent(&A.part[((size_t)b * a.R + jj) * A.nsub + sub], S | kSumThere);
+    }
+    // (by the last workgroup of the row: it waits for none that is started behind it)
+    if (a.mode == 0 && i % groups == groups - 1 && wave == 0) {
+        if (lane == 0) ts->ok = 1;
+        __builtin_amdgcn_wave_barrier();
+        for (int jj = j; jj < a.R && (jj == 0 || jj < len); jj += A.row_slots) replay_upper_row<DT>(A, ts, b, jj, jj == 0 ? 0 : ts->path[jj], lane);
+    }
+}
+
 // The stop row of trajectory b by its first wave: replay of the node's accept tests with exact probabilities and the
 // resampled token, which is returned.  The same arithmetic as finish_stop_row, in ranges instead of segments.
 template <int DT>
@@ -241,35 +301,31 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     const PathArgs &a = A.path;
     const int node = __builtin_amdgcn_readfirstlane(ts->path[len - 1]);
     const int32_t word = __builtin_amdgcn_readfirstlane(stage.word[node]);
-    const int nch = stage_drafted(word), fc = stage_first(word);
+    const int nch = stage_drafted(word);
     const float m = uniform_f32(stage.m[node]);
     const size_t row = (size_t)b * a.N + node;
     const char *rowp = (const char *)a.logits + row * (size_t)a.V * ES;
     const RowGeom g = row_geom<DT>(rowp, a.V);
     const int per = sub_vectors(g, A.nsub);
     // ---- before the sums are needed: the node's proposal, the row's edges, the tests and the position's random bits
-    int32_t my_id = -1, ch = -1;
-    float my_mu = 0.0f, my_l = 0.0f;
-    if (nch > 0 && lane < a.K) { my_id = a.draft_qid[row * a.K + lane]; my_mu = a.draft_qmu[row * a.K + lane]; }
+    int32_t my_id = -1;
+    StagedTest mine_t{0.0f, 0.0f, 0.0f, -1};
+    if (nch > 0) mine_t = tail_node_tests<DT>(A, b, row, nch, stage_first(word), lane, my_id);
     const int32_t top0 = a.src_top_idx[row * a.K];
-    if (lane < nch && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = stage.tok[fc + lane];
     int edge_id = -1;
     if (lane < g.head) edge_id = lane;
     else if (lane < g.head + g.ntail) edge_id = g.tail0 + (lane - g.head);
     const unsigned long long edge_f =
         edge_id >= 0 ? fixed_mass(exact_exp2(scaled_offset(load_scalar<DT>(rowp, edge_id), m, a.c)), a.fx_shift) : 0ull;
-    if ((uint32_t)my_id >= (uint32_t)a.V) { my_id = -1; my_mu = 0.0f; }  // never index outside the row
-    else my_l = load_scalar<DT>(rowp, my_id);
     SubSums part;
     part.request(A, b, len - 1, q, lane);
     const Philox4 ph = philox_group(a.seed, (uint32_t)b, a.step, (uint32_t)node, 0u, kStreamBonus);
     unsigned long long u = ((unsigned long long)ph.x << 32) | ph.y;
     asm volatile("" : "+v"(u));   // (here: these instructions cost nothing while the sums are on their way)
-    const float my_e = my_id >= 0 ? exact_exp2(scaled_offset(my_l, m, a.c)) : 0.0f;
+    const float my_e = my_id >= 0 ? exact_exp2(scaled_offset(mine_t.l, m, a.c)) : 0.0f;
     const bool has_edge = g.head + g.ntail > 0;  // rows that start on a 16-byte boundary have none
     const unsigned long long edge_all = has_edge ? wave_sum_u64(edge_f) : 0ull;
-    NodeTests tests;
-    if (nch > 0) tests = node_tests_prepare(lane, a.K, my_id, my_mu, nch, ch, a.seed, (uint32_t)b, a.step, fc);
+    const NodeTests tests{mine_t.w, mine_t.om, mine_t.pos};
     const bool in_sub = my_id >= g.head && my_id < g.tail0;
     const int my_sub = in_sub ? ((my_id - g.head) / EPV) / per : -1;
 
@@ -357,6 +413,8 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     const int r0 = r.v0 + lane * cpt < r.v1 ? r.v0 + lane * cpt : r.v1, r1 = r0 + cpt < r.v1 ? r0 + cpt : r.v1;
     const unsigned long long within = __ballot(support && lane < a.K && in_sub && my_sub == sub);   // stored ids in this range
     constexpr int kBatch = 4;
+    uint4 *run = (uint4 *)ts->P;   // a range of up to kBatch vectors per lane is looked at twice: the second time here
+    static_assert(sizeof(ts->P) >= 64 * kBatch * sizeof(uint4), "a range in shared memory");
     unsigned long long sum = 0ull;
     const int last = r1 > r0 ? r1 - 1 : (r.v1 > 0 ? r.v1 - 1 : 0);
     for (int k0 = 0; k0 < cpt; k0 += kBatch) {
@@ -375,6 +433,7 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
                 const uint32_t d = (uint32_t)(__builtin_amdgcn_readlane(my_id, __ffsll((long long)left) - 1) - e0);
                 if (d < (uint32_t)EPV) without |= 1u << d;
             }
+            if (k0 == 0) run[lane * kBatch + k] = w[k];
             add_exact_terms<DT>(w[k], r0 + k0 + k < r1 ? without : ~0u, m, a.c, (uint32_t)a.fx_shift << 23, acc);
         }
         whole_end();
@@ -385,10 +444,12 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     if (who >= 0) {
         rem -= readlane_u64(finc, who) - readlane_u64(sum, who);
         const int first = g.head + __builtin_amdgcn_readlane(r0, who) * EPV, n = (__builtin_amdgcn_readlane(r1, who) - __builtin_amdgcn_readlane(r0, who)) * EPV;
+        __builtin_amdgcn_wave_barrier();
         for (int base = 0; base < n; base += 64) {
             const int id = first + base + lane;
             const bool in = base + lane < n;
-            unsigned long long f = in ? fixed_mass(exact_exp2(scaled_offset(load_scalar<DT>(rowp, in ? id : first), m, a.c)), a.fx_shift) : 0ull;
+            const float x = cpt <= kBatch ? load_scalar<DT>(run + who * kBatch, in ? base + lane : 0) : load_scalar<DT>(rowp, in ? id : first);
+            unsigned long long f = in ? fixed_mass(exact_exp2(scaled_offset(x, m, a.c)), a.fx_shift) : 0ull;
             for (unsigned long long left = within; left; left &= left - 1)
                 if (__builtin_amdgcn_readlane(my_id, __ffsll((long long)left) - 1) == id) f = 0ull;
             const unsigned long long einc = wave_inclusive_scan_u64(f);
@@ -403,10 +464,11 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
 }
 
 // A counter in shared memory at which the waves of a workgroup meet without the first one.
-__device__ __forceinline__ void wave_arrive(int *counter, int lane)
+// Returns (in lane 0) how many had arrived before.
+__device__ __forceinline__ int wave_arrive(int *counter, int lane)
 {
     publish_fence();   // what this wave stored is complete
-    if (lane == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return lane == 0 ? __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
 }
 __device__ __forceinline__ void wave_await(const int *counter, int target)
 {
@@ -425,6 +487,16 @@ __device__ __forceinline__ void tail_meet(const StepTailArgs &A, int which, Smal
         while (ld_agent(&A.bar[which]) < B && w.goes_on(ts, A.wait_units)) __builtin_amdgcn_s_sleep(1);
     }
     consume_fence();
+}
+// Waits until every trajectory's observations are there.
+__device__ __forceinline__ bool tail_observed(const StepTailArgs &A, SmallTail *ts, int lane)
+{
+    if (lane == 0) {
+        TailWait w;
+        while (ld_agent(&A.bar[2]) < (unsigned)A.path.B && w.goes_on(ts, A.wait_units)) __builtin_amdgcn_s_sleep(1);
+    }
+    consume_fence();
+    return still_ok(ts);
 }
 
 template <int DT>
@@ -543,55 +615,52 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
                 if (len > a.late_len) atomicAdd(&a.stats[kStatLatePaths], 1ull);
             }
         }
-        for (int j = wave - first; j < len; j += kControl - first) {
+        // observations (a verification leaves none)
+        for (int j = wave - first; A.merge && j < len; j += kControl - first) {
             const int node = __builtin_amdgcn_readfirstlane(ts->path[j]);
             if (node < 0) continue;
-            if (mode == 0 && j == len - 1) {
-                // the stop row's observation; the rest of that row is the first wave's
-                if (!A.merge) continue;
-                const size_t row = (size_t)b * a.N + node;
-                int32_t id = 0;
-                float l = 0.0f;
-                if (lane < a.K) { id = a.src_top_idx[row * a.K + lane]; l = a.src_top_l[row * a.K + lane]; }
-                SubSums part;
-                part.request(A, b, j, q, lane);
-                part.wait(ts, A.wait_units);
-                const unsigned long long S = wave_sum_u64(lane_total(part));
-                write_observation(a, b, j, id, l, stage.m[node], normaliser_from_fixed(S, a.fx_shift), lane);
-                continue;
-            }
-            const float m = mode == 0 ? stage.m[node] : a.src_m[b * a.R + j];
-            finish_upper_row<DT>(a, b, j, node, m, [&] {
-                SubSums part;
-                part.request(A, b, j, q, lane);
-                part.wait(ts, A.wait_units);
-                return lane_total(part);
-            }, lane, -2, [&] { return still_ok(ts); });
+            const size_t src = mode == 0 ? (size_t)b * a.N + node : (size_t)b * a.R + j;
+            int32_t id = 0;
+            float l = 0.0f;
+            if (lane < a.K) { id = a.src_top_idx[src * a.K + lane]; l = a.src_top_l[src * a.K + lane]; }
+            const float m = mode == 0 ? stage.m[node] : a.src_m[src];
+            SubSums part;
+            part.request(A, b, j, q, lane);
+            part.wait(ts, A.wait_units);
+            const unsigned long long S = wave_sum_u64(lane_total(part));
+            write_observation(a, b, j, id, l, m, normaliser_from_fixed(S, a.fx_shift), lane);
         }
     }
     if (fresh_args<StepTailArgs>().merge && wave >= first) {
-        // ---- the trajectory's claims and observations, then every trajectory's; then its records
+        // ---- every trajectory's claims, this one's observations; then its records
         const StepTailArgs &A = fresh_args<StepTailArgs>();
         const MergeArgs &mg = A.mg;
         const int NO = mg.omax - mg.omin + 1, rec0 = b * mg.R * NO;
-        wave_arrive(&ts->arrived[0], lane);
-        wave_await(&ts->arrived[0], kTailWaves - first);
+        if (wave == kControl) {
+            publish_fence();   // the claims are complete
+            tail_meet(A, 0, ts, lane);
+            if (lane == 0) __hip_atomic_store(&ts->met, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        } else if (wave_arrive(&ts->arrived[0], lane) == kControl - first - 1 && lane == 0) {
+            atomicAdd(&A.bar[2], 1u);   // the last of them: the trajectory's observations are complete
+        }
+        wave_await(&ts->met, 1);
         const int n_rec = len * NO;
         int i = wave - first;
         long long slot = i < n_rec ? ts->slot[i] : -1;
-        StoredEntry e{-1, 0.0f};
-        if (slot >= 0) e = request_entry(mg, slot, lane);   // (on its way while the trajectories meet)
-        if (wave == kControl) {
-            tail_meet(A, 0, ts, lane);
-            if (lane == 0) __hip_atomic_store(&ts->met, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        wave_await(&ts->met, 1);
+        ClaimedRecord r;
+        if (slot >= 0) r.request_slot(mg, rec0 + i, slot, lane);
+        wave_await(&ts->arrived[0], kControl - first);
         if (still_ok(ts)) {
+            if (slot >= 0) r.request_observation(mg, lane);
             while (i < n_rec) {
-                if (slot >= 0) apply_claimed(mg, rec0 + i, slot, e, lane, ts->scratch[wave]);
+                // (the next record is on its way while this one is folded)
                 i += kTailWaves - first;
-                slot = i < n_rec ? ts->slot[i] : -1;
-                if (slot >= 0) e = request_entry(mg, slot, lane);
+                const long long next_slot = i < n_rec ? ts->slot[i] : -1;
+                ClaimedRecord next;
+                if (next_slot >= 0) { next.request_slot(mg, rec0 + i, next_slot, lane); next.request_observation(mg, lane); }
+                if (slot >= 0) apply_claimed(mg, r, lane, ts->scratch[wave], [&] { return tail_observed(A, ts, lane); });
+                slot = next_slot;
+                r = next;
             }
         } else {
             for (; i < n_rec; i += kTailWaves - first) {
@@ -628,8 +697,9 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
         }
     }
     const bool drafts = fresh_args<StepTailArgs>().drafts != 0;
-    __syncthreads();   // (every wave has joined: no wait of this trajectory is left)
-    if (drafts) draft_run<kTailThreads>(fresh_args<StepTailArgs>().draft, b, dsm, level_reg);
+    // (after this barrier every wave has joined: no wait of this trajectory is left)
+    if (drafts) draft_run<kTailThreads>(fresh_args<StepTailArgs>().draft, b, dsm, level_reg, [] { __syncthreads(); });
+    else __syncthreads();
     if (__builtin_expect(!still_ok(ts), 0)) {
         // (not reachable while the other workgroups run)
         const StepTailArgs &A = fresh_args<StepTailArgs>();

@@ -136,34 +136,75 @@ __device__ __forceinline__ StoredEntry request_entry(const MergeArgs &a, long lo
     return e;
 }
 
-// Record `rec`, which claimed `slot`, by one wave (all 64 lanes call this; scratch: 2 * kMaxK words of shared memory, 16-byte aligned, owned by
-// the wave); `stored`: the slot's entry.  Does nothing unless the record leads its slot.
+// Takes back what the claim of a record that will not be applied left in its slot's header (one lane): no later merge or
+// lookup sees it.
+__device__ __forceinline__ void release_claimed(const MergeArgs &a, long long slot)
+{
+    SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
+    atomicAnd(&h->order, (1u << kTagShift) - 1u);
+    atomicAnd(&h->count, ~kMultiBit);
+}
+
+// A record that has claimed a slot, as a wave asks for what it needs: the slot (header and stored entry, once every claim is made)
+// and its observation (lanes 32 .. 32 + K - 1).
+struct ClaimedRecord {
+    int rec;
+    long long slot;
+    StoredEntry e;
+    uint32_t order_word, count;
+    int32_t o_id;
+    float o_p;
+    __device__ __forceinline__ void request_slot(const MergeArgs &a, int record, long long claimed, int lane)
+    {
+        rec = record; slot = claimed;
+        const SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
+        order_word = ld_agent(&h->order);
+        count = ld_agent(&h->count);
+        e = request_entry(a, slot, lane);
+    }
+    __device__ __forceinline__ void request_observation(const MergeArgs &a, int lane)
+    {
+        o_id = -1; o_p = 0.0f;
+        if (lane >= 32 && lane < 32 + a.K) {
+            const size_t at = (size_t)(rec / (a.omax - a.omin + 1)) * a.K + (lane - 32);
+            o_id = ld_agent(&a.obs_idx[at]);
+            o_p = ld_agent(&a.obs_p[at]);
+        }
+    }
+};
+
+// Applies a record by one wave (all 64 lanes call this; scratch: 2 * kMaxK words of shared memory, 16-byte aligned, owned by
+// the wave).  Does nothing unless the record leads its slot.  others_there(): whether the observations of other
+// trajectories' records are there (a caller may wait for them; without them the claim is released).
 // Folding one observation into an entry was 2 600 (K = 10) to 6 700 cycles (K = 32) of readlanes; with ids and keys read
 // from shared memory, four and two per access, K compares and 2 K 64-bit compares remain.
-__device__ __forceinline__ void apply_claimed(const MergeArgs &a, int rec, long long slot, const StoredEntry &stored, int lane,
-                                              unsigned long long *scratch)
+struct AlwaysThere { __device__ __forceinline__ bool operator()() const { return true; } };
+template <typename OthersThere = AlwaysThere>
+__device__ __forceinline__ void apply_claimed(const MergeArgs &a, const ClaimedRecord &r, int lane, unsigned long long *scratch,
+                                              const OthersThere &others_there = OthersThere())
 {
+    const int rec = r.rec;
+    const long long slot = r.slot;
     const int NO = a.omax - a.omin + 1;
     const int nrec = a.B * a.R * NO;
     const int K = a.K;
     SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
     int32_t *ids = slot_ids(a.table, (uint64_t)slot, a.slot_bytes);
     float *mus = slot_mu(a.table, (uint64_t)slot, a.slot_bytes, K);
-    // header, stored entry and this record's observation are requested together
-    const uint32_t order_word = ld_agent(&h->order);
-    uint32_t count = ld_agent(&h->count);
-    int32_t e_id = stored.id;
-    float e_mu = stored.mu;
+    const uint32_t order_word = r.order_word;
+    uint32_t count = r.count;
+    int32_t e_id = r.e.id;
+    float e_mu = r.e.mu;
     // lanes 0..K-1: stored entry; lanes 32..32+K-1: observation
-    int32_t o_id = -1;
-    float o_p = 0.0f;
-    if (lane >= 32 && lane < 32 + K) {
-        o_id = ld_agent(&a.obs_idx[(size_t)(rec / NO) * K + (lane - 32)]);
-        o_p = ld_agent(&a.obs_p[(size_t)(rec / NO) * K + (lane - 32)]);
-    }
+    const int32_t o_id = r.o_id;
+    const float o_p = r.o_p;
     if (kTagMax - (order_word >> kTagShift) != (uint32_t)rec) return;  // another record leads this slot
     const bool multi = (count & kMultiBit) != 0u;
     count &= ~kMultiBit;
+    if (multi && !others_there()) {
+        if (lane == 0) release_claimed(a, slot);
+        return;
+    }
     if (count == 0) { e_id = -1; e_mu = 0.0f; }
 
     auto apply = [&](int32_t o_id, float o_p) {
@@ -243,21 +284,15 @@ __device__ __forceinline__ void apply_claimed(const MergeArgs &a, int rec, long 
     if (lane == 0) { st_agent(&h->count, count); st_agent(&h->order, order_word & ((1u << kTagShift) - 1u)); }
 }
 
-// Takes back what the claim of a record that will not be applied left in its slot's header (one lane): no later merge or
-// lookup sees it.
-__device__ __forceinline__ void release_claimed(const MergeArgs &a, long long slot)
-{
-    SlotHeader *h = slot_header(a.table, (uint64_t)slot, a.slot_bytes);
-    atomicAnd(&h->order, (1u << kTagShift) - 1u);
-    atomicAnd(&h->count, ~kMultiBit);
-}
-
 // apply_claimed for a record whose slot is still to be looked up; does nothing unless it exists.
 __device__ __forceinline__ void apply_record(const MergeArgs &a, int rec, int lane, unsigned long long *scratch)
 {
     const long long slot = ld_agent(&a.rec_slot[rec]);
     if (slot < 0) return;
-    apply_claimed(a, rec, slot, request_entry(a, slot, lane), lane, scratch);
+    ClaimedRecord r;
+    r.request_slot(a, rec, slot, lane);
+    r.request_observation(a, lane);
+    apply_claimed(a, r, lane, scratch);
 }
 
 // Appends the committed tokens of trajectory b to its context tail (one thread).
