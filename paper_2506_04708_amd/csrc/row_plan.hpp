@@ -73,10 +73,20 @@ inline int plan_row_parts(int64_t V, int element_bytes, int64_t rows, int K)
 // pass's.  (Rows of one part use none of the memory in which parts meet.)  Streaming with four waves / whole, us:
 //   verify 1036 x 2096 vectors (bf16) 32.2 / 29.9, 1440 x 3804 44.3 / 41.4, 2784 x 3800 55.7 / 54.6, 882 x 2064 (fp32) 28.4 / 25.8,
 //   16384 x 4000 193.1 / 192.7, fp32 199.9 / 185.2, 16384 x 500 101.0 / 99.5;  step 540 x 1079 37.3 / 34.6, 720 x 1024 33.3 / 29.2
-// (Two parts of rows that do not fit: 553 x 4288 41.3 / 42.2, 759 x 5280 43.3 / 47.1.)
 constexpr bool plan_row_whole(int64_t V, int element_bytes, int K)
 {
     return row_vectors(V, element_bytes) <= kPartThreads * kPartVectors && bound_holds(row_vectors(V, element_bytes), K);
+}
+
+// More rows than plan_row_parts splits, too long for one workgroup, short enough for two: two parts as long as the launch has
+// little more than a device-full of workgroups (1024 are resident).  Verifications, streaming with four waves / two parts, us:
+//   520 rows x 33 000 bf16 27.8 / 26.9, x 65 000, K = 32 36.2 / 31.9;  576 x 32 003 fp32 33.1 / 31.1;  640 x 50 001 bf16 33.0 / 32.3,
+//   x 20 000 fp32 29.3 / 28.4;  not 720 x 65 000 bf16 34.9 / 35.3, 768 x 50 000 31.8 / 34.6;  steps of 640 x 50 001 41.6 / 41.6, x 32 003 fp32 42.8 / 42.7
+constexpr int kRowsTwoParts = 640;
+constexpr bool plan_row_two_parts(int64_t V, int element_bytes, int64_t rows, int K)
+{
+    return rows > kRowsSplit && rows <= kRowsTwoParts && row_vectors(V, element_bytes) <= 2 * kPartThreads * kPartVectors &&
+           row_vectors(V, element_bytes) > kPartThreads * kPartVectors && bound_holds(row_vectors(V, element_bytes), K);
 }
 
 // Parts per row of an update with R row slots per trajectory, W = longest path, N = nodes; 0: not split.

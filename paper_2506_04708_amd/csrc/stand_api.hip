@@ -291,6 +291,7 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(dmalloc(&h->vs.stop_qmu, B * kMaxK)); acc(dmalloc(&h->vs.stop_ql, B * kMaxK)); acc(dmalloc(&h->vs.stop_child, B * kMaxK));
     acc(dmalloc(&h->pr_m, B * h->R)); acc(dmalloc(&h->pr_top_l, B * h->R * K)); acc(dmalloc(&h->pr_top_idx, B * h->R * K));
     h->row_parts = plan_row_parts(h->V, element_bytes(*cfg), (int64_t)rows, K);
+    if (h->row_parts == 0 && plan_row_two_parts(h->V, element_bytes(*cfg), (int64_t)rows, K)) h->row_parts = 2;
     h->commit_parts = plan_commit_parts(h->V, element_bytes(*cfg), h->B, h->W, N, h->R, K);
     const size_t part_tickets = std::max(h->row_parts ? rows : 0, h->commit_parts ? B * h->R : 0) * kTicketStride;
     const size_t part_slots = std::max(rows * h->row_parts, B * h->R * h->commit_parts);

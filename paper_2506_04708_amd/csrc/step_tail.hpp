@@ -317,8 +317,6 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     else if (lane < g.head + g.ntail) edge_id = g.tail0 + (lane - g.head);
     const unsigned long long edge_f =
         edge_id >= 0 ? fixed_mass(exact_exp2(scaled_offset(load_scalar<DT>(rowp, edge_id), m, a.c)), a.fx_shift) : 0ull;
-    SubSums part;
-    part.request(A, b, len - 1, q, lane);
     const Philox4 ph = philox_group(a.seed, (uint32_t)b, a.step, (uint32_t)node, 0u, kStreamBonus);
     unsigned long long u = ((unsigned long long)ph.x << 32) | ph.y;
     asm volatile("" : "+v"(u));   // (here: these instructions cost nothing while the sums are on their way)
@@ -329,6 +327,9 @@ __device__ __forceinline__ int32_t tail_token(const StepTailArgs &A, SmallTail *
     const bool in_sub = my_id >= g.head && my_id < g.tail0;
     const int my_sub = in_sub ? ((my_id - g.head) / EPV) / per : -1;
 
+    // (asked for not before they are needed: they are there by now, and an answer that came too early would be a second question)
+    SubSums part;
+    part.request(A, b, len - 1, q, lane);
     part.wait(ts, A.wait_units);
     const unsigned long long S = wave_sum_u64(lane_total(part));
     const float s = normaliser_from_fixed(S, a.fx_shift);

@@ -16,6 +16,7 @@ int waves(int64_t rows) { return unsplit_waves(rows); }
 int64_t limit(int64_t rows) { return split_limit(rows); }
 int64_t vectors(int64_t V, int es) { return row_vectors(V, es); }
 int whole(int64_t V, int es, int K) { return plan_row_whole(V, es, K); }
+int two_parts(int64_t V, int es, int64_t rows, int K) { return plan_row_two_parts(V, es, rows, K); }
 int ranges(int64_t V, int es, int64_t B) { return plan_tail_ranges(V, es, B, 16, 512); }
 int two_launches(int64_t B, int64_t rows, int64_t V, int es, int K) { return plan_two_launches(B, rows, V, es, K); }
 int tail_places(int64_t B, int64_t places) { return plan_tail_places(B, places); }
@@ -46,6 +47,7 @@ def lib():
         _lib.commit_parts.argtypes = [l, i, l, i, i, i, i]
         _lib.waves.argtypes = [l]
         _lib.two_launches.argtypes = [l, l, l, i, i]
+        _lib.two_parts.argtypes = [l, i, l, i]
         _lib.whole.argtypes, _lib.ranges.argtypes = [l, i, i], [l, i, l]
         _lib.tail_places.argtypes = [l, l]
         _lib.tail_verify.argtypes = _lib.tail_step.argtypes = [l, i, i]

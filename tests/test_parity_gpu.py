@@ -632,6 +632,23 @@ def test_lockstep_rows_held_whole(gpu, name, over, mode):
     assert info["worst_rel"] < 1e-5
 
 
+@pytest.mark.parametrize("over,mode", [
+    (dict(V=32776, B=33, dtype="bf16"), "step"),             # 528 rows: 4097 vectors, one more than a workgroup holds
+    (dict(V=65536, B=33, dtype="bf16", K=32), "separate"),   # two workgroups full
+    (dict(V=32003, B=40), "separate"),                       # fp32, misaligned; the most rows
+    (dict(V=32003, B=41), "step"),                           # streamed again
+])
+def test_lockstep_rows_in_two_parts(gpu, over, mode):
+    """More rows than are split otherwise, each held by two workgroups."""
+    binding, lockstep = gpu
+    _say("lockstep rows in two parts %s" % over)
+    w = synth.Workload("cfg1", run_steps=3, rho=0.7, **over)
+    assert rowplan.lib().two_parts(w.V, rowplan.element_bytes(w.dtype), w.B * w.N, w.K) == (w.B <= 40)
+    info = lockstep.run_lockstep(w, 3, mode=mode, capacity=1 << 14, table_every=3, sample_rows=range(0, w.B * w.N, 7))
+    _say("  -> %s" % info)
+    assert info["worst_rel"] < 1e-5
+
+
 @pytest.mark.parametrize("name,over,steps,mode,forced", [
     ("cfg1", dict(V=13, B=2, rho=0.5, K=10, dtype="bf16"), 40, "step", False),        # one vector or none, the rest are edges
     ("cfg1", dict(V=600_011, B=1, rho=0.7), 8, "step", False),                        # the most ranges, several vectors per lane

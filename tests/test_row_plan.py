@@ -80,6 +80,14 @@ def test_rows_held_whole():
     assert [L.whole(V, 4, 32) for V in (1276, 1280, 16384, 16385)] == [0, 1, 1, 0]
 
 
+def test_rows_in_two_parts():
+    """More rows than are split otherwise, of more vectors than one workgroup holds and no more than two."""
+    L = rowplan.lib()
+    assert [L.two_parts(V, 2, 576, 16) for V in (32768, 32769, 65536, 65537)] == [0, 1, 1, 0]
+    assert [L.two_parts(32003, 4, r, 20) for r in (512, 513, 640, 641)] == [0, 1, 1, 0]
+    assert all(L.row_parts(V, 2, r, 16) == 0 for V in (32769, 65536) for r in (513, 640))
+
+
 def test_ranges_of_a_path_row():
     """Whole workgroups of sixteen waves, at most 512 ranges; one vector per lane for few trajectories, four for many, as
     long as not too many workgroups are asked for."""
