@@ -307,42 +307,48 @@ __device__ __forceinline__ void write_observation(const PathArgs &a, int b, int 
     }
 }
 
+// Replay of the row pass's decision at a node of a verification's path above the stop node, by ONE wave: the accept tests again with
+// exact probabilities must name the child the row pass (with the fast normaliser and its error bound) has named.
+struct UpperReplay {
+    int n = 0, fc = -1;
+    int32_t id = -1, ch = -1;
+    float mu = 0.0f, l = 0.0f;
+    template <int DT>
+    __device__ __forceinline__ void request(const PathArgs &a, int b, int node, int lane)
+    {
+        const int row = b * a.N + node;
+        n = a.draft_has[row]; fc = a.tree.first_child[node];
+        if (n <= 0) return;
+        if (lane < a.K) { id = a.draft_qid[(size_t)row * a.K + lane]; mu = a.draft_qmu[(size_t)row * a.K + lane]; }
+        if (lane < n && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
+        if ((uint32_t)id >= (uint32_t)a.V) { id = -1; mu = 0.0f; }  // never index outside the row
+        else l = load_scalar<DT>((const char *)a.logits + (size_t)row * (size_t)a.V * VecTraits<DT>::ES, id);
+    }
+    // m, s: the row's maximum and exact normaliser; walked: the node's outcome
+    __device__ __forceinline__ void run(const PathArgs &a, int b, float m, float s, int walked, int lane) const
+    {
+        if (n <= 0) return;
+        const float e = id >= 0 ? exact_exp2(scaled_offset(l, m, a.c)) : 0.0f;
+        const NodeTests t = node_tests_prepare(lane, a.K, id, mu, n, ch, a.seed, (uint32_t)b, a.step, fc);
+        const NodeResult nr = wave_node_outcome(lane, a.K, t, e / s, n, false, 0.0f, a.onehot);
+        if (lane == 0 && nr.accepted != walked) atomicAdd(&a.stats[kStatMismatch], 1ull);
+    }
+};
+
 // Finishes row slot j of trajectory b, whose row is tree node `node` and not the stop row of a verification, by ONE wave:
-// its observation and, on the path of a verification, a replay of the row pass's decision.  m: the row's maximum.
-// get_part() gives the lane its share of the row's exact sum; it is called where the sum is needed (a caller may wait for
-// it there).  `walked`: the node's outcome as the caller followed it, or -2: read it from the row pass's results.
-// sum_valid(), asked where the replay differs: whether that share was the whole one (a wait for it may have run out).
-struct AlwaysValid { __device__ __forceinline__ bool operator()() const { return true; } };
-template <int DT, typename GetPart, typename SumValid = AlwaysValid>
-__device__ __forceinline__ void finish_upper_row(const PathArgs &a, int b, int j, int node, float m, const GetPart &get_part, int lane,
-                                                 int walked = -2, const SumValid &sum_valid = SumValid())
+// its observation and, on the path of a verification, the replay.  m: the row's maximum; part: the lane's share of its exact sum.
+template <int DT>
+__device__ __forceinline__ void finish_upper_row(const PathArgs &a, int b, int j, int node, float m, unsigned long long part, int lane)
 {
     const int row = b * a.N + node;
-    const int src = a.mode == 0 ? row : b * a.R + j;
-    const char *rowp = (const char *)a.logits + (size_t)row * (size_t)a.V * VecTraits<DT>::ES;
     int32_t o_idx = 0;
     float o_l = 0.0f;
-    load_top(a, src, lane, o_idx, o_l);
-    // the self-check's inputs: the accept tests again with exact probabilities must name the child the row pass (with the
-    // fast normaliser and its error bound) has named
-    int c_n = 0, c_fc = -1;
-    int32_t c_id = -1, c_ch = -1;
-    float c_mu = 0.0f, c_l = 0.0f;
-    if (a.mode == 0) { c_n = a.draft_has[row]; c_fc = a.tree.first_child[node]; }
-    if (c_n > 0) {
-        if (lane < a.K) { c_id = a.draft_qid[(size_t)row * a.K + lane]; c_mu = a.draft_qmu[(size_t)row * a.K + lane]; }
-        if (lane < c_n && lane < kMaxK && c_fc >= 0 && c_fc + lane < a.N) c_ch = a.draft_tok[(size_t)b * a.N + c_fc + lane];
-        if ((uint32_t)c_id >= (uint32_t)a.V) { c_id = -1; c_mu = 0.0f; }  // never index outside the row
-        else c_l = load_scalar<DT>(rowp, c_id);
-    }
-    const float s = normaliser_from_fixed(wave_sum_u64(get_part()), a.fx_shift);
+    load_top(a, a.mode == 0 ? row : b * a.R + j, lane, o_idx, o_l);
+    UpperReplay replay;
+    if (a.mode == 0) replay.request<DT>(a, b, node, lane);
+    const float s = normaliser_from_fixed(wave_sum_u64(part), a.fx_shift);
     write_observation(a, b, j, o_idx, o_l, m, s, lane);
-    if (c_n > 0) {
-        const float c_e = c_id >= 0 ? exact_exp2(scaled_offset(c_l, m, a.c)) : 0.0f;
-        const NodeTests ct = node_tests_prepare(lane, a.K, c_id, c_mu, c_n, c_ch, a.seed, (uint32_t)b, a.step, c_fc);
-        const NodeResult nr = wave_node_outcome(lane, a.K, ct, c_e / s, c_n, false, 0.0f, a.onehot);
-        if (lane == 0 && nr.accepted != (walked != -2 ? walked : a.outcome[row]) && sum_valid()) atomicAdd(&a.stats[kStatMismatch], 1ull);
-    }
+    if (replay.n > 0) replay.run(a, b, m, s, a.outcome[row], lane);
 }
 
 // Finishes the stop row of a verification, row slot j of trajectory b and tree node `node`: its observation, the replay of
@@ -630,7 +636,7 @@ __global__ __launch_bounds__(kFinishThreads) void path_finish_kernel(PathArgs a,
     }
     if (node < 0) return;
     const float m = a.src_m[a.mode == 0 ? b * a.N + node : b * a.R + j];
-    finish_upper_row<DT>(a, b, j, node, m, [&] { return part; }, lane);
+    finish_upper_row<DT>(a, b, j, node, m, part, lane);
 }
 
 }  // namespace stand

@@ -122,14 +122,15 @@ struct TailShared {
     alignas(16) unsigned long long scratch[kStepWPR][2 * kMaxK];
 };
 
-// All workgroups of one count arrive, then wait for the rest (`meanwhile` runs in between).  Called by the whole workgroup.
-template <typename Meanwhile>
-__device__ __forceinline__ void tail_barrier(const StepSync &sy, int which, unsigned arrivals, TailShared *ts, const Meanwhile &meanwhile)
+// All workgroups of one count arrive, then wait for the rest.  Both called by the whole workgroup.
+__device__ __forceinline__ void tail_arrive(const StepSync &sy, int which)
 {
     publish_fence();  // this workgroup's stores (table, records, observations) are complete before its arrival
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(&sy.bar[which], 1u);
-    meanwhile();
+}
+__device__ __forceinline__ void tail_await(const StepSync &sy, int which, unsigned arrivals, TailShared *ts)
+{
     if (threadIdx.x == 0) {
         if (!wait_reached(&sy.bar[which], arrivals * sy.epoch, sy.wait_ticks)) ts->ok = 0;
     }
@@ -348,7 +349,10 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
         for (int j = wave; j + 1 < len; j += kStepWPR) {  // rows above the stop row: one wave each
             const int node = ts->path[j];
             const unsigned long long part = wait_parts(j);
-            finish_upper_row<DT>(a, b, j, node, ts->pm[j], [&] { return part; }, lane, ts->acc[j]);
+            int32_t o_idx = 0;
+            float o_l = 0.0f;
+            load_top(a, b * N + node, lane, o_idx, o_l);
+            write_observation(a, b, j, o_idx, o_l, ts->pm[j], normaliser_from_fixed(wave_sum_u64(part), a.fx_shift), lane);
         }
         __syncthreads();
         if (ts->ok) {
@@ -362,7 +366,15 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
 
     // ---- every trajectory's claims and observations, then this trajectory's records
     if (tid == 0) stamp(sy, b, 4);
-    tail_barrier(sy, 0, (unsigned)a.B, ts, [] {});
+    tail_arrive(sy, 0);
+    // (the replay of the rows above the stop row is a check, which nothing waits for)
+    for (int j = wave; j + 1 < len && ts->ok; j += kStepWPR) {
+        UpperReplay replay;
+        replay.request<DT>(a, b, ts->path[j], lane);
+        const unsigned long long part = lane < nseg ? ld_agent(&a.seg_part[((size_t)b * a.R + j) * kSegMax + lane]) & ~kPartThere : 0ull;
+        replay.run(a, b, ts->pm[j], normaliser_from_fixed(wave_sum_u64(part), a.fx_shift), ts->acc[j], lane);
+    }
+    tail_await(sy, 0, (unsigned)a.B, ts);
     if (tid == 0) stamp(sy, b, 5);
     {
         const int NO = A.mg.omax - A.mg.omin + 1;
@@ -370,15 +382,14 @@ __device__ __forceinline__ void tail_role(const StepArgs &A, int b, int g, char 
     }
     // ---- every trajectory's records applied, then the next draft
     const DraftShared dsm = draft_shared_carve(smem + ((sizeof(TailShared) + 15) & ~(size_t)15), A.draft.tree.N, kStepWPR);
-    int level_reg = 0;
-    tail_barrier(sy, 1, (unsigned)a.B, ts, [&] { level_reg = draft_prepare<kStepThreads>(A.draft, b, dsm); });
-    if (tid == 0) stamp(sy, b, 6);
+    tail_arrive(sy, 1);
+    const int level_reg = draft_prepare<kStepThreads>(A.draft, b, dsm);
+    draft_run<kStepThreads>(A.draft, b, dsm, level_reg, [&] { tail_await(sy, 1, (unsigned)a.B, ts); if (tid == 0) stamp(sy, b, 6); });
     if (__builtin_expect(!ts->ok, 0)) {
         // (a wait of this trajectory has run out: its outputs, some of which are written already, are void)
         if (tid < W) { a.out_tok[(size_t)b * W + tid] = -1; a.out_node[(size_t)b * W + tid] = -1; }
         if (tid == 0) { a.out_len[b] = 0; atomicAdd(&a.stats[kStatWaitExpired], 1ull); }
     }
-    draft_run<kStepThreads>(A.draft, b, dsm, level_reg, [] {});
     if (tid == 0) stamp(sy, b, 7);
 }
 
