@@ -321,8 +321,13 @@ struct UpperReplay {
         if (n <= 0) return;
         if (lane < a.K) { id = a.draft_qid[(size_t)row * a.K + lane]; mu = a.draft_qmu[(size_t)row * a.K + lane]; }
         if (lane < n && lane < kMaxK && fc >= 0 && fc + lane < a.N) ch = a.draft_tok[(size_t)b * a.N + fc + lane];
-        if ((uint32_t)id >= (uint32_t)a.V) { id = -1; mu = 0.0f; }  // never index outside the row
-        else l = load_scalar<DT>((const char *)a.logits + (size_t)row * (size_t)a.V * VecTraits<DT>::ES, id);
+        // (members are written on one path each: see NodeProposal)
+        const bool inside = (uint32_t)id < (uint32_t)a.V;  // never index outside the row
+        float at_id = 0.0f;
+        if (inside) at_id = load_scalar<DT>((const char *)a.logits + (size_t)row * (size_t)a.V * VecTraits<DT>::ES, id);
+        l = at_id;
+        id = inside ? id : -1;
+        mu = inside ? mu : 0.0f;
     }
     // m, s: the row's maximum and exact normaliser; walked: the node's outcome
     __device__ __forceinline__ void run(const PathArgs &a, int b, float m, float s, int walked, int lane) const
