@@ -67,6 +67,7 @@ struct stand_handle {
     unsigned long long *stamps;  // [2 + 8 * B] clock readings of the last one-launch step, or NULL (stand_step_timeline)
     VerifyScratch vs;  // row results, partial sums, stop records, observations (hipMalloc'ed at create)
     long long *rec_slot;
+    unsigned *exact_ticket;   // [B*R], zero between launches
     int R;            // row / record slots per trajectory: W, or N with STAND_UPDATE_ALL_NODES
     int32_t *recent;  // [B][N][kMaxOrder], all-nodes mode only
     unsigned long long *node_count, *anc;  // anc: [N][anc_words] ancestor-or-self bit sets
@@ -150,7 +151,7 @@ static void free_all(stand_handle *h)
 {
     if (!h) return;
     void *ptrs[] = {h->d_tree, h->table, h->ctx_tail, h->ctx_len, h->ctx_tail2, h->ctx_len2, h->reorder_map, h->export_buf, h->draft_tok, h->draft_has, h->draft_qid, h->draft_qmu,
-                    h->vs.row_m, h->vs.row_s, h->vs.top_l, h->vs.top_p, h->vs.top_idx, h->vs.outcome, h->vs.obs_idx, h->vs.obs_p, h->rec_slot,
+                    h->vs.row_m, h->vs.row_s, h->vs.top_l, h->vs.top_p, h->vs.top_idx, h->vs.outcome, h->vs.obs_idx, h->vs.obs_p, h->rec_slot, h->exact_ticket,
                     h->recent, h->draft_tok2, h->draft_has2, h->draft_qid2, h->draft_qmu2, h->row_pub, h->top_pub, h->bar, h->item_next, h->path_flag, h->path_pub, h->stamps, h->vs.seg_part, h->node_count, h->anc, h->vs.stop_i, h->vs.stop_qid, h->vs.stop_child, h->vs.stop_m, h->vs.stop_qmu, h->vs.stop_ql, h->pr_m, h->pr_top_l, h->pr_top_idx, h->tail_part, h->tail_bar, h->staged, h->part_ticket, h->part_head, h->part_keys, h->stats, h->counter};
     for (void *p : ptrs) (void)hipFree(p);
     for (hipEvent_t e : h->ev_begin) (void)hipEventDestroy(e);
@@ -282,6 +283,7 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(dmalloc(&h->vs.outcome, rows));
     acc(dmalloc(&h->vs.obs_idx, B * h->R * K)); acc(dmalloc(&h->vs.obs_p, B * h->R * K));
     acc(dmalloc(&h->rec_slot, nrec));
+    acc(dmalloc(&h->exact_ticket, B * h->R));
     acc(dmalloc(&h->vs.seg_part, B * h->R * kSegMax));
     acc(dmalloc(&h->recent, rows * kMaxOrder));
     acc(dmalloc(&h->node_count, (size_t)N));
@@ -352,6 +354,7 @@ extern "C" int stand_create(const stand_config *cfg, stand_handle **out)
     acc(hipMemset(h->vs.row_m, 0, rows * sizeof(float))); acc(hipMemset(h->vs.row_s, 0, rows * sizeof(float)));
     acc(hipMemset(h->vs.top_l, 0, rows * K * sizeof(float))); acc(hipMemset(h->vs.top_p, 0, rows * K * sizeof(float)));
     acc(hipMemset(h->vs.top_idx, 0, rows * K * sizeof(int32_t)));
+    acc(hipMemset(h->exact_ticket, 0, B * h->R * sizeof(unsigned)));
     acc(hipMemset(h->part_ticket, 0, part_tickets * sizeof(unsigned)));
     acc(hipMemset(h->stats, 0, kStatCount * sizeof(unsigned long long)));
     acc(hipHostMalloc((void **)&h->probe_host, sizeof(unsigned long long), hipHostMallocDefault));
@@ -576,6 +579,7 @@ static PathArgs make_path_args(const stand_handle *h, const VerifyScratch &vs, u
     a.late_len = (h->upper_depth < h->D ? h->upper_depth : h->D) + 1;
     a.fx_shift = h->fx_shift;
     a.top_pub = nullptr;
+    a.ticket = h->exact_ticket;
     // segments of seg_vectors 16-byte vectors where kSegMax allows it
     const int row_vectors = (int)(((size_t)h->V * (bf16 ? 2 : 4) + 15) / 16);
     a.nseg = clampi((row_vectors + seg_vectors - 1) / seg_vectors, 1, kSegMax);
@@ -615,8 +619,8 @@ static int launch_commit_rows(stand_handle *h, uint64_t step, const void *d_logi
 }
 
 // What follows the row kernel, in separate launches: exact sums, then the rows' ends.  mode 0 (verify): path from the row
-// pass's outcomes; mode 1 (update): rows given by the caller.  With `claim` the launch that finishes the path rows also
-// claims the table slots of that merge.
+// pass's outcomes; mode 1 (update): rows given by the caller, whose ends are in the launch of the sums.  With `claim` (always for an
+// update) the last launch also claims the table slots of that merge.
 static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row,
                             const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len,
                             const MergeArgs *claim, hipStream_t s)
@@ -630,16 +634,22 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
     // mostly short; the kernel loops over longer ones)
     const int row_slots = (mode == 0 && !a.all_nodes) ? std::min(h->R, 4) : h->R;
     const dim3 g1((unsigned)a.nseg + 1, (unsigned)h->B, (unsigned)row_slots), block(kPathThreads);
-    const bool single = mode == 0 && h->R == 1;   // (paths of one node: every row is a stop row)
+    const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
+    if (mode != 0) {
+        if (bf16) path_exact_kernel<kDtBf16, true><<<g1, block, 0, s>>>(a, mg);
+        else path_exact_kernel<kDtF32, true><<<g1, block, 0, s>>>(a, mg);
+        HIP_TRY(h, hipGetLastError());
+        return STAND_OK;
+    }
+    const bool single = h->R == 1;   // (paths of one node: every row is a stop row)
     const int row_blocks = single ? 0 : (h->B * h->R + kFinishThreads / 64 - 1) / (kFinishThreads / 64);
     const int claim_blocks = claim ? (h->B * h->R * h->NO + kFinishThreads - 1) / kFinishThreads : 0;
-    const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
-    const dim3 g2((unsigned)((mode == 0 ? h->B : 0) + row_blocks + claim_blocks));
+    const dim3 g2((unsigned)(h->B + row_blocks + claim_blocks));
     if (bf16) {
-        path_exact_kernel<kDtBf16><<<g1, block, 0, s>>>(a);
+        path_exact_kernel<kDtBf16, false><<<g1, block, 0, s>>>(a, mg);
         path_finish_kernel<kDtBf16><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     } else {
-        path_exact_kernel<kDtF32><<<g1, block, 0, s>>>(a);
+        path_exact_kernel<kDtF32, false><<<g1, block, 0, s>>>(a, mg);
         path_finish_kernel<kDtF32><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     }
     HIP_TRY(h, hipGetLastError());
