@@ -28,7 +28,7 @@
 // every probability that is stored in the table or used for resampling, is recomputed with
 // the exact integer normaliser of numeric.hpp, so all decisions are those of exact arithmetic.
 // The kernels after the row pass are chains of dependent instructions and round trips over little data;
-// their workgroups exchange data only across kernel boundaries (row_parts_kernel: through a counter per row).  step_tail_kernel
+// their workgroups exchange data only across kernel boundaries (row_parts_kernel and the sums of an update: through a counter per row).  step_tail_kernel
 // runs them as one launch for small batches, stand_step_kernel the same
 // device functions in one launch and orders them with counters instead.
 #pragma once

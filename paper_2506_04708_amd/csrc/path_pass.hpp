@@ -17,7 +17,7 @@ namespace stand {
 //                       replays the node with exact probabilities and draws the resampled token by inverting
 //                       the residual's cumulative integer mass), a wave per other row.  Further blocks of the
 //                       same launch claim the table slots of the merge, which depends on the path's tokens only.
-// Kernel boundaries are the only synchronisation between blocks.
+// Kernel boundaries are the only synchronisation between blocks, but for the counter at which an update's segments of a row meet.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSegMax = 32;  // most segments per path row
 constexpr int kFinishThreads = 1024;  // path_finish_kernel: many waves, so that locating a token is one short round

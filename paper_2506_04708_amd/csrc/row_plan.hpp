@@ -22,7 +22,7 @@ constexpr int kPartWaves = 8, kPartThreads = 64 * kPartWaves;
 constexpr int kPartVectors = 8;                      // most vectors per lane
 constexpr int kPartsMax = 32;                        // most parts of a row
 constexpr int kPartsTarget = 256;                    // workgroups that few rows are split into
-constexpr int kRowsSplit = 512;                      // more rows are never split (but may be held whole, plan_row_whole)
+constexpr int kRowsSplit = 512;                      // more rows are held whole (plan_row_whole), in two parts (plan_row_two_parts), or they stream
 constexpr int kCommitSlotsSplit = 4096;              // row slots of an update that may be split (most hold no row)
 constexpr int kCommitWorkgroups = 2560;              // workgroups that find a row in a split update of short paths
 
