@@ -19,10 +19,12 @@ namespace stand {
 //
 //   first wave          the token: replay of the stop node, resampled token, the new context
 //   last wave           claims of the table slots (they need the path's tokens only)
-//   the others          observations of the path rows, then the merge records
+//   the others          observations of the path rows, then the merge records, then the replay of the other path nodes
 //
-// so that the longest chain is path, sums, token, draft, with claims and applies beside it.  The other path nodes are replayed by
-// the summing workgroups, when their sums are done.
+// so that the longest chain is path, sums, token, draft, with claims and applies beside it.  The replay of the other path nodes
+// is a check that no result waits for, but it reads the pending draft, which the same workgroup overwrites when all its waves have
+// joined: it comes before that and in this workgroup, the waves without records first.  The summing workgroups read nothing that
+// this launch overwrites, and wait for nothing.
 //   - A partial sum is one self-validating word (top bit set; the row kernel before has cleared the words).  The ranges
 //     are so small that the wave which draws the token finds it by itself, with one more look at one range.
 //   - Between claims and applies, and between applies and the draft's lookups, the trajectories meet at a counter
@@ -44,7 +46,7 @@ namespace stand {
 // 12 x 48 x 32 003 fp32 37.6 / 33.7.
 // Then, with what waits for nothing moved off the chains (the stop node's tests left by the row kernel, a range looked at once,
 // the draft's constants formed before the waves join and its root taken by an idle wave, claims met without observations, upper
-// nodes replayed by summing workgroups, a wave's next record requested while one is folded): 1 x 16 22.8 / 22.05, 1 x 32 25.2 /
+// nodes replayed by waves that are done, a wave's next record requested while one is folded): 1 x 16 22.8 / 22.05, 1 x 32 25.2 /
 // 24.2, 8 x 32 39.9 / 38.55, 24 x 20 x 50 000 40.8 / 37.9, 16 x 30 x 100 000 50.3 / 48.4, 32 x 64 with long paths 146.7 / 144.0.
 // The arguments are read again in each phase (fresh_args): kept from the start they were 361 spilled scalar registers.
 // ---------------------------------------------------------------------------------------------
@@ -213,29 +215,6 @@ __device__ __forceinline__ StagedTest tail_node_tests(const StepTailArgs &A, int
     return t;
 }
 
-// A node of the accepted path above the stop node, by one wave: its accept tests again with exact probabilities.  They must name
-// the child that the row pass (with the fast normaliser and its error bound) has named.
-template <int DT>
-__device__ __forceinline__ void replay_upper_row(const StepTailArgs &A, SmallTail *ts, int b, int j, int node, int lane)
-{
-    const PathArgs &a = A.path;
-    const size_t row = (size_t)b * a.N + node;
-    const int walked = a.outcome[row];
-    if (walked < 0) return;   // (the stop node: the trajectory's first wave)
-    SubSums part;
-    part.request(A, b, j, (A.nsub + 63) / 64, lane);
-    const int nch = a.draft_has[row];
-    const float m = a.src_m[row];
-    int32_t id;
-    const StagedTest t = tail_node_tests<DT>(A, b, row, nch, a.tree.first_child[node], lane, id);
-    part.wait(ts, A.wait_units);
-    if (!still_ok(ts)) return;
-    const float s = normaliser_from_fixed(wave_sum_u64(lane_total(part)), a.fx_shift);
-    const float e = id >= 0 ? exact_exp2(scaled_offset(t.l, m, a.c)) : 0.0f;
-    const NodeResult nr = wave_node_outcome(lane, a.K, NodeTests{t.w, t.om, t.pos}, e / s, nch, false, 0.0f, a.onehot);
-    if (lane == 0 && nr.accepted != walked) atomicAdd(&a.stats[kStatMismatch], 1ull);
-}
-
 template <int DT>
 __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
 {
@@ -247,7 +226,7 @@ __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
     // row slots are the slowest: the workgroups of the root rows, which every path has, are first
     const int j = i / (groups * a.B), b = i / groups % a.B, sub = i % groups * kTailWaves + wave;
     const TailStage st = tail_stage(smem, a.N);
-    int len = a.mode != 0 ? -1 : 0;   // (0: not followed yet)
+    int len = 0;   // (not followed yet)
     for (int jj = j; jj < a.R; jj += A.row_slots) {
         int node;
         float m;
@@ -269,7 +248,7 @@ __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
                 __syncthreads();
                 len = ts->len;
             }
-            if (jj >= len) break;
+            if (jj >= len) return;
             node = ts->path[jj];
             m = st.m[node];
         }
@@ -283,12 +262,6 @@ __device__ __forceinline__ void tail_sums(int i, SmallTail *ts, char *smem)
         else S = thread_exact_partial<DT, 4>(rowp, g, r.v0, r.v1, sub == 0, m, a.c, lane, 64, a.fx_shift);
         S = wave_sum_u64(S);
         if (lane == 0) st_agent(&A.part[((size_t)b * a.R + jj) * A.nsub + sub], S | kSumThere);
-    }
-    // (by the last workgroup of the row: it waits for none that is started behind it)
-    if (a.mode == 0 && i % groups == groups - 1 && wave == 0) {
-        if (lane == 0) ts->ok = 1;
-        __builtin_amdgcn_wave_barrier();
-        for (int jj = j; jj < a.R && (jj == 0 || jj < len); jj += A.row_slots) replay_upper_row<DT>(A, ts, b, jj, jj == 0 ? 0 : ts->path[jj], lane);
     }
 }
 
@@ -633,7 +606,7 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
         }
     }
     if (fresh_args<StepTailArgs>().merge && wave >= first) {
-        // ---- every trajectory's claims, this one's observations; then its records
+        // ---- every trajectory's claims, this one's observations; then its records (a wave without one waits for neither)
         const StepTailArgs &A = fresh_args<StepTailArgs>();
         const MergeArgs &mg = A.mg;
         const int NO = mg.omax - mg.omin + 1, rec0 = b * mg.R * NO;
@@ -644,29 +617,31 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
         } else if (wave_arrive(&ts->arrived[0], lane) == kControl - first - 1 && lane == 0) {
             atomicAdd(&A.bar[2], 1u);   // the last of them: the trajectory's observations are complete
         }
-        wave_await(&ts->met, 1);
         const int n_rec = len * NO;
         int i = wave - first;
-        long long slot = i < n_rec ? ts->slot[i] : -1;
-        ClaimedRecord r;
-        if (slot >= 0) r.request_slot(mg, rec0 + i, slot, lane);
-        wave_await(&ts->arrived[0], kControl - first);
-        if (still_ok(ts)) {
-            if (slot >= 0) r.request_observation(mg, lane);
-            while (i < n_rec) {
-                // (the next record is on its way while this one is folded)
-                i += kTailWaves - first;
-                const long long next_slot = i < n_rec ? ts->slot[i] : -1;
-                ClaimedRecord next;
-                if (next_slot >= 0) { next.request_slot(mg, rec0 + i, next_slot, lane); next.request_observation(mg, lane); }
-                if (slot >= 0) apply_claimed(mg, r, lane, ts->scratch[wave], [&] { return tail_observed(A, ts, lane); });
-                slot = next_slot;
-                r = next;
-            }
-        } else {
-            for (; i < n_rec; i += kTailWaves - first) {
-                slot = ts->slot[i];
-                if (slot >= 0 && lane == 0) release_claimed(mg, slot);
+        if (i < n_rec) {
+            wave_await(&ts->met, 1);
+            long long slot = ts->slot[i];
+            ClaimedRecord r;
+            if (slot >= 0) r.request_slot(mg, rec0 + i, slot, lane);
+            wave_await(&ts->arrived[0], kControl - first);
+            if (still_ok(ts)) {
+                if (slot >= 0) r.request_observation(mg, lane);
+                while (i < n_rec) {
+                    // (the next record is on its way while this one is folded)
+                    i += kTailWaves - first;
+                    const long long next_slot = i < n_rec ? ts->slot[i] : -1;
+                    ClaimedRecord next;
+                    if (next_slot >= 0) { next.request_slot(mg, rec0 + i, next_slot, lane); next.request_observation(mg, lane); }
+                    if (slot >= 0) apply_claimed(mg, r, lane, ts->scratch[wave], [&] { return tail_observed(A, ts, lane); });
+                    slot = next_slot;
+                    r = next;
+                }
+            } else {
+                for (; i < n_rec; i += kTailWaves - first) {
+                    slot = ts->slot[i];
+                    if (slot >= 0 && lane == 0) release_claimed(mg, slot);
+                }
             }
         }
         if (A.drafts) {
@@ -675,6 +650,28 @@ __device__ __forceinline__ void tail_trajectory(int b, SmallTail *ts, char *smem
                 wave_await(&ts->arrived[1], kTailWaves - first);
                 tail_meet(A, 1, ts, lane);   // every record is applied before the first lookup
             }
+        }
+    }
+    if (mode == 0 && wave >= first && wave < kControl) {
+        // ---- replay of the path nodes above the stop node, the first ones by the waves with the fewest records.  What it reads of
+        // the pending draft is overwritten behind the barrier below.  (Sum before node: together they need more registers
+        // than there are.)  Where waves without records waited for the claims as well / as it is: 1 x 16 rows 23.1 / 22.7 us,
+        // 1 x 32 24.6 / 24.4, 8 x 32 39.2 / 39.2.
+        const StepTailArgs &A = fresh_args<StepTailArgs>();
+        const PathArgs &a = A.path;
+        for (int j = kControl - 1 - wave; j + 1 < len; j += kControl - first) {
+            const int node = __builtin_amdgcn_readfirstlane(ts->path[j]);
+            float s;
+            {
+                SubSums part;
+                part.request(A, b, j, q, lane);
+                part.wait(ts, A.wait_units);
+                s = normaliser_from_fixed(wave_sum_u64(lane_total(part)), a.fx_shift);
+            }
+            if (!still_ok(ts)) break;   // (the sum may not be the whole one; the trajectory is void)
+            UpperReplay replay;
+            replay.request<DT>(a, b, node, lane);
+            replay.run(a, b, stage.m[node], s, stage_outcome(stage.word[node]), lane);
         }
     }
     if (wave == 0 && mode == 0) {

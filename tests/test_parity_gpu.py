@@ -668,6 +668,78 @@ def test_lockstep_rest_of_the_step_in_one_launch(gpu, name, over, steps, mode, f
     _say("  -> %s" % info)
 
 
+@pytest.mark.parametrize("B,V,K,dtype,orders", [
+    (64, 600, 2, "bf16", (1, 1)),     # rows held in registers
+    (64, 600, 2, "f32", (1, 1)),
+    (64, 600, 16, "bf16", (1, 1)),    # rows that stream
+    (16, 600, 16, "f32", (1, 4)),
+])
+def test_long_paths_before_drafts_that_end_at_once(gpu, B, V, K, dtype, orders):
+    """Every node of an accepted path is replayed from the pending draft before the same launch overwrites it: whole chains of 31
+    nodes are accepted (longer than the path rows that have summing workgroups of their own, for 64 trajectories), in every other
+    trajectory the context then ends in a token that no entry knows, so that its next tree is empty at once, and all trajectories
+    claim the same slots."""
+    binding, lockstep = gpu
+    L, N, M, es = rowplan.lib(), 32, 24, rowplan.element_bytes(dtype)
+    D, W = N - 1, N
+    assert L.tail_step(B, W, orders[1] - orders[0] + 1) and bool(L.whole(V, es, K)) == (K == 2)
+    assert B < 64 or L.tail_slots(B, W, 1) < W
+    parent = np.arange(-1, D, dtype=np.int32)
+    o = oracle.Oracle(V, B, orders[0], orders[1], K, parent, 0.6, 1 << 12, 64, 3, oracle.DT_F32 if dtype == "f32" else oracle.DT_BF16)
+    g = binding.Stand(V, B, orders[0], orders[1], K, parent, 0.6, 1 << 12, 64, 3,
+                      binding.STAND_F32 if dtype == "f32" else binding.STAND_BF16)
+    g.set_step_plan(1, 2, 0, 0)
+    r = np.random.default_rng(B + K)
+
+    def follows(t):   # the language: a cycle of M tokens; the tokens beyond are in no entry
+        return (np.where(t < 0, 0, t) + 1) % M
+
+    def logits(tokens):   # [B, N] -> every row peaked on what follows its node's token
+        x = r.standard_normal((B, N, V)).astype(np.float32)
+        np.put_along_axis(x, follows(tokens)[:, :, None], 25.0, axis=2)
+        return x if dtype == "f32" else synth.f32_to_bf16_bits(x)
+
+    for b in range(B):
+        o.set_context(b, np.array([5, 6, 7, 8, b % 2], np.int32))
+        g.set_context(b, np.array([5, 6, 7, 8, b % 2], np.int32))
+    # a transcript of 32 tokens each goes into the table
+    seq = (np.arange(W + 1)[None, :] + (np.arange(B) % 2)[:, None]).astype(np.int32) % M
+    lg, rows = logits(seq[:, :N]), np.tile(np.arange(W, dtype=np.int32), (B, 1))
+    lens = np.full(B, W, np.int32)
+    o.update(0, lg, np.ascontiguousarray(seq[:, 1:]), rows, lens)
+    g.update(0, lockstep._logits_to_device(lg, dtype), *(torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (seq[:, 1:], rows, lens)))
+    out_tok, out_node, out_len, d = g.new_outputs()
+    od = o.draft(1)
+    g.draft(1, d)
+    last, long_paths, empty, unknown = seq[:, -1].copy(), 0, 0, M
+    for step in range(1, 9):
+        _say("  B=%d K=%d %s step %d" % (B, K, dtype, step))
+        lg = logits(np.concatenate([last[:, None], od[:, 1:]], axis=1))
+        otok, onode, olen = o.verify(step, lg)
+        force = otok.copy()
+        for b in range(B):
+            if olen[b] > 1 and (b + step) % 2:
+                force[b, olen[b] - 1] = unknown
+                unknown += 1
+        last = force[np.arange(B), olen - 1]
+        o.update(step, lg, force, onode, olen)
+        od = o.draft(step + 1)
+        g.step(step, lockstep._logits_to_device(lg, dtype), out_tok, out_node, out_len, d, torch.from_numpy(force).cuda())
+        torch.cuda.synchronize()
+        assert not g.step_is_one_launch()
+        for got, want in ((out_tok, otok), (out_node, onode), (out_len, olen), (d, od)):
+            assert np.array_equal(got.cpu().numpy(), want)
+        long_paths += int((olen == W).sum())
+        empty += int(((olen == W) & (od[:, 1] < 0)).sum())
+    lockstep.compare_tables(o, g, K)
+    st = g.stats()
+    _say("  -> %d whole chains accepted, %d of them before an empty tree" % (long_paths, empty))
+    assert long_paths > 4 * B and empty > B and unknown <= V
+    assert st.filter_mismatch == 0 and st.wait_expired == 0
+    o.close()
+    g.close()
+
+
 @pytest.mark.parametrize("over,mode", [
     (dict(V=70001, B=2, rho=0.7), "separate"), (dict(V=70001, B=2, rho=0.7, dtype="bf16"), "separate"),
     (dict(V=70003, B=3, rho=0.7, dtype="bf16", update_mode=1), "separate"), (dict(V=66000, B=47, rho=0.7, dtype="bf16"), "step"),
