@@ -130,9 +130,10 @@ __device__ __forceinline__ void write_observation(const PathArgs &a, int b, int 
     }
 }
 
-// UPDATE: the rows are given (mode 1).  Then nothing depends on the sums but the observations, which the last segment of a row
-// writes (a counter that its last user sets back to zero), and the claims are made by the extra blocks: what path_finish_kernel does for a verification, one launch less.  Update and draft
-// of 4 x 32 rows x 152 064 43.7 -> 41.0 us, of 16 x 20 x 30 000 42.4 -> 35.3.
+// UPDATE: the rows are given (mode 1), `mg` is the merge of their records.  Then nothing depends on the sums but the observations,
+// which the last segment of a row writes (a counter that its last user sets back to zero), and the claims are made by the extra
+// blocks: what path_finish_kernel does for a verification, one launch less.  Update and draft of 4 x 32 rows x 152 064 43.7 -> 41.0 us,
+// of 16 x 20 x 30 000 42.4 -> 35.3.
 template <int DT, bool UPDATE>
 __global__ __launch_bounds__(kPathThreads) void path_exact_kernel(PathArgs a, MergeArgs mg)
 {
@@ -204,8 +205,8 @@ __global__ __launch_bounds__(kPathThreads) void path_exact_kernel(PathArgs a, Me
         bool staged = false;
         // (in verify mode the root row is always on the path, also when the trajectory has no context yet
         // and its root carries no token)
-        if (a.all_nodes) node = (a.draft_tok[(size_t)b * a.N + jj] >= 0 || (a.mode == 0 && jj == 0)) ? jj : -1;
-        else if (a.mode != 0) node = commit_row_of(a, b, jj);
+        if (a.all_nodes) node = (a.draft_tok[(size_t)b * a.N + jj] >= 0 || (!UPDATE && jj == 0)) ? jj : -1;
+        else if constexpr (UPDATE) node = commit_row_of(a, b, jj);
         else if (jj == 0) node = 0;
         else {
             if (len < 0) {
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kPathThreads) void path_exact_kernel(PathArgs a, Me
         if (node < 0) continue;  // block-uniform: no such row
         const int row = b * a.N + node;
         const char *rowp = (const char *)a.logits + (size_t)row * (size_t)a.V * ES;
-        const float m = staged ? stage.m[node] : a.src_m[a.mode == 0 ? row : b * a.R + jj];
+        const float m = staged ? stage.m[node] : a.src_m[UPDATE ? b * a.R + jj : row];
         const RowGeom g = row_geom<DT>(rowp, a.V);
         const int per = (g.nvec + nseg - 1) / nseg;
         const int v0 = seg * per < g.nvec ? seg * per : g.nvec;

@@ -618,29 +618,26 @@ static int launch_commit_rows(stand_handle *h, uint64_t step, const void *d_logi
     return STAND_OK;
 }
 
-// What follows the row kernel, in separate launches: exact sums, then the rows' ends.  mode 0 (verify): path from the row
-// pass's outcomes; mode 1 (update): rows given by the caller, whose ends are in the launch of the sums.  With `claim` (always for an
-// update) the last launch also claims the table slots of that merge.
-static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode, const int32_t *commit_row,
-                            const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len,
-                            const MergeArgs *claim, hipStream_t s)
+// Path arguments of the separate launches.  Segments: one round of loads per thread where kSegMax allows it.
+static PathArgs separate_path_args(const stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int mode,
+                                   const int32_t *commit_row, const int32_t *commit_len, int32_t *out_tok, int32_t *out_node, int32_t *out_len)
+{
+    const int per_thread = exact_loads(mode == 0, h->cfg.update_mode == STAND_UPDATE_ALL_NODES, h->B);
+    return make_path_args(h, vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, per_thread * kPathThreads);
+}
+
+// What follows the row kernel of a verification, in separate launches: exact sums, then the rows' ends.  With `claim` the second
+// launch also claims the table slots of that merge.
+static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t step, const void *d_logits, int32_t *out_tok,
+                            int32_t *out_node, int32_t *out_len, const MergeArgs *claim, hipStream_t s)
 {
     const bool bf16 = h->cfg.logits_dtype == STAND_BF16;
-    // segments: one round of loads per thread where kSegMax allows it; one more block per (row, trajectory) slot for the
-    // outputs and the stop record
-    const int per_thread = exact_loads(mode == 0, h->cfg.update_mode == STAND_UPDATE_ALL_NODES, h->B);
-    PathArgs a = make_path_args(h, vs, step, d_logits, mode, commit_row, commit_len, out_tok, out_node, out_len, per_thread * kPathThreads);
-    // row slots of the grid: every slot in update / all-nodes mode; in verify mode four (paths are
-    // mostly short; the kernel loops over longer ones)
-    const int row_slots = (mode == 0 && !a.all_nodes) ? std::min(h->R, 4) : h->R;
+    const PathArgs a = separate_path_args(h, vs, step, d_logits, 0, nullptr, nullptr, out_tok, out_node, out_len);
+    // one more block per (row, trajectory) slot for the outputs and the stop record; row slots: every one in all-nodes mode,
+    // else four (paths are mostly short; the kernel loops over longer ones)
+    const int row_slots = !a.all_nodes ? std::min(h->R, 4) : h->R;
     const dim3 g1((unsigned)a.nseg + 1, (unsigned)h->B, (unsigned)row_slots), block(kPathThreads);
-    const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);
-    if (mode != 0) {
-        if (bf16) path_exact_kernel<kDtBf16, true><<<g1, block, 0, s>>>(a, mg);
-        else path_exact_kernel<kDtF32, true><<<g1, block, 0, s>>>(a, mg);
-        HIP_TRY(h, hipGetLastError());
-        return STAND_OK;
-    }
+    const MergeArgs mg = claim ? *claim : merge_args(h, nullptr, nullptr, nullptr);   // (not looked at without `claim`)
     const bool single = h->R == 1;   // (paths of one node: every row is a stop row)
     const int row_blocks = single ? 0 : (h->B * h->R + kFinishThreads / 64 - 1) / (kFinishThreads / 64);
     const int claim_blocks = claim ? (h->B * h->R * h->NO + kFinishThreads - 1) / kFinishThreads : 0;
@@ -652,6 +649,18 @@ static int launch_path_pass(stand_handle *h, const VerifyScratch &vs, uint64_t s
         path_exact_kernel<kDtF32, false><<<g1, block, 0, s>>>(a, mg);
         path_finish_kernel<kDtF32><<<g2, dim3(kFinishThreads), 0, s>>>(a, mg, row_blocks);
     }
+    HIP_TRY(h, hipGetLastError());
+    return STAND_OK;
+}
+
+// The same for an update, whose rows are given: sums, observations and the merge's claims in one launch.
+static int launch_update_pass(stand_handle *h, uint64_t step, const void *d_logits, const int32_t *commit_row, const int32_t *commit_len,
+                              const MergeArgs &claim, hipStream_t s)
+{
+    const PathArgs a = separate_path_args(h, h->vs, step, d_logits, 1, commit_row, commit_len, nullptr, nullptr, nullptr);
+    const dim3 grid((unsigned)a.nseg + 1, (unsigned)h->B, (unsigned)h->R), block(kPathThreads);   // one more block per slot: claims
+    if (h->cfg.logits_dtype == STAND_BF16) path_exact_kernel<kDtBf16, true><<<grid, block, 0, s>>>(a, claim);
+    else path_exact_kernel<kDtF32, true><<<grid, block, 0, s>>>(a, claim);
     HIP_TRY(h, hipGetLastError());
     return STAND_OK;
 }
@@ -730,7 +739,7 @@ extern "C" int stand_update(stand_handle *h, uint64_t step, const void *d_logits
     if (rc) return rc;
     if (tail)
         return launch_step_tail(h, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, d_commit_tok, &mg, nullptr, s);
-    rc = launch_path_pass(h, h->vs, step, d_logits, 1, d_commit_row, d_commit_len, nullptr, nullptr, nullptr, &mg, s);
+    rc = launch_update_pass(h, step, d_logits, d_commit_row, d_commit_len, mg, s);
     if (rc) return rc;
     return launch_merge_apply(h, mg, true, s);
 }
@@ -765,7 +774,7 @@ extern "C" int stand_verify(stand_handle *h, uint64_t step, const void *d_logits
     if (rc) return rc;
     if (tail)
         return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, nullptr, nullptr, s);
-    return launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
+    return launch_path_pass(h, h->vs, step, d_logits, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
 
 // Bytes of scratch a verification of this handle's shape needs, laid out as carve_scratch does.
@@ -804,7 +813,7 @@ extern "C" int stand_verify_static(stand_handle *h, uint64_t step, const void *d
     // and observations for exactly the path rows that are read back).
     int rc = launch_row_pass(h, vs, step, d_logits, false, false, s);
     if (rc) return rc;
-    return launch_path_pass(h, vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, nullptr, s);
+    return launch_path_pass(h, vs, step, d_logits, d_out_tok, d_out_node, d_out_len, nullptr, s);
 }
 
 extern "C" uint64_t stand_static_scratch_need(const stand_handle *h)
@@ -1035,7 +1044,7 @@ extern "C" int stand_step(stand_handle *h, uint64_t step, const void *d_logits, 
         const DraftArgs da = make_draft_args(h, step + 1, d_next_draft_tok, commit, d_out_len);
         return launch_step_tail(h, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, d_force_tok, &mg, &da, s);
     }
-    rc = launch_path_pass(h, h->vs, step, d_logits, 0, nullptr, nullptr, d_out_tok, d_out_node, d_out_len, &mg, s);
+    rc = launch_path_pass(h, h->vs, step, d_logits, d_out_tok, d_out_node, d_out_len, &mg, s);
     if (rc) return rc;
     rc = launch_merge_apply(h, mg, false, s);
     if (rc) return rc;
