@@ -91,11 +91,11 @@ def host_description():
 def launch_names(fused, B, N, V, K, W, orders, update_mode):
     """(kernel that reads the logits, how the step is issued) of bf16 steps on a whole device: the library's rules in short
     (csrc/row_plan.hpp).  The workloads of at most 512 rows here have them split over workgroups; rows of up to 4096
-    vectors of 16 bytes are held whole, up to 640 rows of up to 8192 in two parts.  What follows the rows of a small batch is one
+    vectors of 16 bytes are held whole, up to 584 rows of up to 8192 in two parts.  What follows the rows of a small batch is one
     launch."""
     if fused:
         return "stand_step_kernel", "one launch"
-    whole = 10 * K <= -(-V // 8) <= (8192 if B * N <= 640 else 4096)
+    whole = 10 * K <= -(-V // 8) <= (8192 if B * N <= 584 else 4096)
     small_batch = update_mode == 0 and B <= 64 and B * W * orders <= 2048
     return ("row_parts_kernel" if B * N <= 512 or whole else "row_pass_kernel", "two launches" if small_batch else "five launches")
 

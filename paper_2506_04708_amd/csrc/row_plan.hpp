@@ -79,14 +79,21 @@ constexpr bool plan_row_whole(int64_t V, int element_bytes, int K)
 }
 
 // More rows than plan_row_parts splits, too long for one workgroup, short enough for two: two parts as long as the launch has
-// little more than a device-full of workgroups (1024 are resident).  Verifications, streaming with four waves / two parts, us:
-//   520 rows x 33 000 bf16 27.8 / 26.9, x 65 000, K = 32 36.2 / 31.9;  576 x 32 003 fp32 33.1 / 31.1;  640 x 50 001 bf16 33.0 / 32.3,
-//   x 20 000 fp32 29.3 / 28.4;  not 720 x 65 000 bf16 34.9 / 35.3, 768 x 50 000 31.8 / 34.6;  steps of 640 x 50 001 41.6 / 41.6, x 32 003 fp32 42.8 / 42.7
-constexpr int kRowsTwoParts = 640;
+// little more than a device-full of workgroups (1024 are resident), beyond 584 rows only if the parts are nearly full.
+// Streaming with four waves / two parts, bf16, K = 10 (rows on cache lines), us; verifications:
+//   520 rows x 4104 vectors 27.0 / 26.4, x 5000 29.0 / 26.6, x 8192 33.7 / 29.9;  553 x 4288 29.0 / 28.0, x 6248 31.7 / 30.0;
+//   584 x 4104 28.4 / 28.3, x 5000 30.2 / 28.8, x 6248 31.5 / 30.6, x 7936 34.8 / 31.8;  not 600 x 4104 29.7 / 30.2, x 6248 33.4 / 33.3,
+//   640 x 4288 27.7 / 28.4, x 6248 30.7 / 30.8;  600 x 7936 36.5 / 34.7, 640 x 7936 33.2 / 32.6, x 8192 35.9 / 33.4;
+//   misaligned 576 x 4100 fp32 29.3 / 27.3, 640 x 7696, K = 16 35.2 / 33.4;  not 720 x 8125 34.9 / 35.3, 768 x 6250 31.8 / 34.6
+// and steps:  520 x 4104 38.2 / 37.3;  553 x 4288 37.9 / 37.5;  584 x 4104 40.9 / 40.9, x 5000 40.3 / 39.5, x 6248 43.1 / 43.0, x 7936 46.8 / 45.9;
+//   not 640 x 4288 39.0 / 40.2, x 6248 42.3 / 43.2, x 7176 42.6 / 43.3;  600 x 7936 46.1 / 45.7, 640 x 7696 44.9 / 45.2, K = 16 45.7 / 45.3,
+//   x 8192 45.5 / 44.8, 620 x 7800 fp32 44.8 / 44.1
+constexpr int kRowsTwoParts = 584, kRowsTwoFullParts = 640;
 constexpr bool plan_row_two_parts(int64_t V, int element_bytes, int64_t rows, int K)
 {
-    return rows > kRowsSplit && rows <= kRowsTwoParts && row_vectors(V, element_bytes) <= 2 * kPartThreads * kPartVectors &&
-           row_vectors(V, element_bytes) > kPartThreads * kPartVectors && bound_holds(row_vectors(V, element_bytes), K);
+    const int64_t vectors = row_vectors(V, element_bytes), full = kPartThreads * kPartVectors;
+    return rows > kRowsSplit && rows <= (vectors > 15 * full / 8 ? kRowsTwoFullParts : kRowsTwoParts) &&
+           vectors > full && vectors <= 2 * full && bound_holds(vectors, K);
 }
 
 // Parts per row of an update with R row slots per trajectory, W = longest path, N = nodes; 0: not split.

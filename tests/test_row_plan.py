@@ -86,6 +86,8 @@ def test_rows_in_two_parts():
     assert [L.two_parts(V, 2, 576, 16) for V in (32768, 32769, 65536, 65537)] == [0, 1, 1, 0]
     assert [L.two_parts(32003, 4, r, 20) for r in (512, 513, 640, 641)] == [0, 1, 1, 0]
     assert all(L.row_parts(V, 2, r, 16) == 0 for V in (32769, 65536) for r in (513, 640))
+    # beyond 584 rows only parts of more than 7.5 vectors per lane
+    assert [L.two_parts(V, 2, r, 16) for V in (34304, 61440, 61441) for r in (584, 585, 640, 641)] == [1, 0, 0, 0, 1, 0, 0, 0, 1, 1, 1, 0]
 
 
 def test_ranges_of_a_path_row():
