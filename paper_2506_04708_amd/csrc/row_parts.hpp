@@ -18,7 +18,8 @@ namespace stand {
 // Where a launch fills the device, what bounds it after its last byte are the vector instructions of all its waves (eight to a
 // SIMD: 100 more in each are 1.6 us), so what is not done per element is kept short: the arguments are read again in the later
 // phases instead of spilled from the start (up to 90 scalar registers), streamed and plain loads are two kernels instead of
-// two branches that meet in moves, and candidates are not taken apart in the registers that happen to hold them (200 of 800
+// two branches that meet in moves (of all this the least: 8 x 32 x 128 256 40.0 / 39.6, 1 x 32 x 152 064 25.9 / 25.7, verify of
+// 12 x 48 x 32 003 fp32 31.7 / 31.4), and candidates are not taken apart in the registers that happen to hold them (200 of 800
 // instructions).  Steps, with all this before / as it is, us: 8 x 32 rows x 128 256 bf16 41.4 / 39.8, 24 x 20 x 50 000 42.9 / 40.8,
 // verify of 2 x 40 x 150 000 fp32, K = 32 39.0 / 37.4, update and draft of 4 x 32 x 152 064 47.8 / 44.8 (its rows without the fast
 // normaliser, which an update does not use).  Vectors taken one by one as they arrive, relative to a reference that is
@@ -36,7 +37,11 @@ namespace stand {
 constexpr int kTicketStride = 32;                    // words between two rows' counters: a cache line each
 constexpr int kPartKeys = 64;                        // candidate keys a part hands over
 constexpr int kPartList = kPartsMax * kPartKeys;     // candidates collected in shared memory
-constexpr int kPartVecs = 384;                       // vectors collected in shared memory
+// Vectors collected in shared memory.  Where more hold an element at the bound, though few lanes of a wave (rows of which 6 to 24 of
+// every 64 vectors lie above the others), the part is fetched again; candidates taken out of the registers / as it is, verifications,
+// us: 300 rows x 32 768 bf16, K = 25, ordinary rows 17.6 / 16.8, 2 of 64 46.0 / 29.7, 5 48.1 / 34.3, 6 48.4 / 49.5, 24 56.6 / 57.3;
+// 256 x 128 256, K = 32, 29.4 / 27.3, 77.8 / 49.4, 73.9 / 50.0, 74.8 / 77.1, 86.9 / 89.6
+constexpr int kPartVecs = 384;
 constexpr int kPartTies = 32;                        // more lanes of a wave than this at or above the bound: most elements there equal it
 constexpr int kPartTied = 1 << 20;                   // added to the count of candidates by such a wave
 

@@ -589,8 +589,9 @@ struct SumClear {
 };
 
 // Lane i of a node's accept tests: the row's logit at its i-th stored id, that id's weight in the proposal; uniform and place of
-// the i-th child's test.  Left by row_parts_kernel for the replay of path rows with exact probabilities: formed again there,
-// these were 1.5 us of the path of one trajectory's step.  (Not by the streaming row pass: 2048 rows of 304 KB took 108.5
+// the i-th child's test.  Left by row_parts_kernel for the stop node's replay with exact probabilities in step_tail_kernel: formed
+// again there, these were 1.5 us of the path of one trajectory's step.  (None of them depends on the normaliser, which is what that
+// replay checks; the other path nodes' replays form their own.)  (Not by the streaming row pass: 2048 rows of 304 KB took 108.5
 // instead of 103 us with these stores.)
 struct alignas(16) StagedTest { float l, w, om; int pos; };
 

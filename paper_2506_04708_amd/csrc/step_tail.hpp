@@ -46,8 +46,9 @@ namespace stand {
 // 12 x 48 x 32 003 fp32 37.6 / 33.7.
 // Then, with what waits for nothing moved off the chains (the stop node's tests left by the row kernel, a range looked at once,
 // the draft's constants formed before the waves join and its root taken by an idle wave, claims met without observations, upper
-// nodes replayed by waves that are done, a wave's next record requested while one is folded): 1 x 16 22.8 / 22.05, 1 x 32 25.2 /
-// 24.2, 8 x 32 39.9 / 38.55, 24 x 20 x 50 000 40.8 / 37.9, 16 x 30 x 100 000 50.3 / 48.4, 32 x 64 with long paths 146.7 / 144.0.
+// nodes replayed by waves that are done, a wave's next record requested while one is folded; with what the row kernel gained at the
+// same time): 1 x 16 22.9 / 22.3, 1 x 32 25.0 / 23.4, 8 x 32 42.0 / 39.2, with long paths 47.9 / 44.7, 24 x 20 x 50 000 42.7 / 38.1,
+// 32 x 64 with long paths 147.3 / 144.9, chains of 32 nodes all accepted, x 32 000, 1 trajectory 54.4 / 54.6, 12 76.5 / 73.3.
 // The arguments are read again in each phase (fresh_args): kept from the start they were 361 spilled scalar registers.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTailThreads = 1024, kTailWaves = kTailThreads / 64;

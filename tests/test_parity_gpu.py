@@ -519,8 +519,9 @@ def test_rows_of_equal_logits_split_over_workgroups(gpu, dtype, V, K):
 
 @pytest.mark.parametrize("dtype,V,K", [("bf16", 32768, 25), ("bf16", 30001, 32), ("f32", 16384, 25), ("f32", 3 * 16384 - 7, 32)])
 def test_rows_with_more_vectors_at_the_bound_than_are_collected(gpu, dtype, V, K):
-    """Of every 64 vectors (a wave's lanes) 6 to 24 lie above the others, i.e. fewer lane groups than K, so that the part's bound is
-    among the lower ones and from 384 to 1536 vectors reach it, though few lanes of a wave: at the memory's limit, above it, below."""
+    """Of every 64 vectors (a wave's lanes) 5 to 24 lie above the others, i.e. fewer lane groups than K, so that the part's bound is
+    among the lower ones and from 320 to 1536 vectors reach it, though few lanes of a wave: below the memory's limit (384), at it,
+    above."""
     r = np.random.default_rng(V + K)
     epv = 8 if dtype == "bf16" else 4
     rows = []
